@@ -1,22 +1,34 @@
-"""Builds libbbo_mlp.so (HIP, gfx950) in-tree with hipcc."""
+"""Builds libbbo_mlp.so (HIP, gfx950) in-tree with hipcc, the kernel families side by side."""
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbbo_mlp.so")
-SOURCES = ["bbo_mlp.hip"]
-FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
+SOURCES = ["kernels_tiled.hip", "kernels_small.hip", "kernels_mid.hip", "kernels_linear.hip", "bbo_mlp.hip"]
+FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
 
 
-def build_lib(verbose=False):
-    cmd = ["hipcc"] + FLAGS + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB]
+def _run(cmd):
     res = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + err)
-    if verbose and err.strip():
+    return err
+
+
+def build_lib(verbose=False):
+    jobs = int(os.environ.get("MAX_JOBS", 0)) or min(8, os.cpu_count() or 1)
+    with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(jobs) as pool:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        errs = list(pool.map(lambda so: _run(["hipcc"] + FLAGS + ["-c", os.path.join(CSRC, so[0]), "-o", so[1]]),
+                             zip(SOURCES, objs)))
+        errs.append(_run(["hipcc", "--offload-arch=gfx950", "-shared"] + objs + ["-o", LIB]))
+    err = "\n".join(e for e in errs if e.strip())
+    if verbose and err:
         print(err)
     return LIB
 

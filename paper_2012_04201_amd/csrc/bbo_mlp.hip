@@ -46,6 +46,7 @@
 #include "../../include/bbo_mlp.h"
 
 #include "common.h"
+#include "kernels.h"
 #include "train_tiled_bf16.h"
 #include "train_small_f32.h"
 #include "train_mid_f32.h"
@@ -1230,46 +1231,28 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
     P.queue = queues + k;
     P.slot_bytes = sp.slot_bytes;
     P.n_items = (int)sp.items.size();
+    const int c_out = n_classes >= 2 ? n_classes : 1;
+    const void* fn;
+    int threads = NTHREADS;
     if (k == KC_TILED) {
-      if ((rc = ensure_dynamic_lds((const void*)k_train_tiled, sp.lds_bytes))) return rc;
-      hipLaunchKernelGGL(k_train_tiled, dim3(sp.n_slots), dim3(TB_THREADS), sp.lds_bytes, s, P);
+      fn = tiled_kernel();
+      threads = TB_THREADS;
     } else if (k == KC_SMALL) {
-      const int kt = d + 1 <= 16 ? 1 : (d + 1 <= 32 ? 2 : 4);
-      const int c_out = n_classes >= 2 ? n_classes : 1, co = c_out <= 2 ? c_out : 4;
-      typedef void (*small_fn)(const TrainParams);
-      static const small_fn fns[3][3] = {
-          {k_train_small<1, 1>, k_train_small<1, 2>, k_train_small<1, 4>},
-          {k_train_small<2, 1>, k_train_small<2, 2>, k_train_small<2, 4>},
-          {k_train_small<4, 1>, k_train_small<4, 2>, k_train_small<4, 4>}};
-      const small_fn fn = fns[kt == 1 ? 0 : (kt == 2 ? 1 : 2)][co == 1 ? 0 : (co == 2 ? 1 : 2)];
-      if ((rc = ensure_dynamic_lds((const void*)fn, sp.lds_bytes))) return rc;
-      hipLaunchKernelGGL(fn, dim3(sp.n_slots), dim3(SM_THREADS), sp.lds_bytes, s, P);
+      fn = small_kernel(d + 1 <= 16 ? 1 : (d + 1 <= 32 ? 2 : 4), c_out <= 2 ? c_out : 4);
+      threads = SM_THREADS;
     } else if (k == KC_MID) {
-      typedef void (*mid_fn)(const TrainParams);
-      const int kt = md_kt(d);
-      const mid_fn fn = kt == 2 ? k_train_mid<2> : (kt == 4 ? k_train_mid<4> : (kt == 5 ? k_train_mid<5> : (kt == 6 ? k_train_mid<6> : k_train_mid<8>)));
-      if ((rc = ensure_dynamic_lds((const void*)fn, sp.lds_bytes))) return rc;
-      hipLaunchKernelGGL(fn, dim3(sp.n_slots), dim3(MD_THREADS), sp.lds_bytes, s, P);
+      fn = mid_kernel(md_kt(d));
+      threads = MD_THREADS;
     } else if (k == KC_LINEAR) {
-      const int c_out = n_classes >= 2 ? n_classes : 1, co = ln_co(c_out), ki = ln_ki(d);
-      typedef void (*linear_fn)(const TrainParams);
-      // [padded outputs 1, 2, 4, 8, 16][rows of W per lane 1, 2, 4], at most 32 parameters per lane
-      static const linear_fn fns[5][3] = {
-          {k_train_linear<1, 1>, k_train_linear<1, 2>, k_train_linear<1, 4>},
-          {k_train_linear<2, 1>, k_train_linear<2, 2>, k_train_linear<2, 4>},
-          {k_train_linear<4, 1>, k_train_linear<4, 2>, k_train_linear<4, 4>},
-          {k_train_linear<8, 1>, k_train_linear<8, 2>, k_train_linear<8, 4>},
-          {k_train_linear<16, 1>, k_train_linear<16, 2>, nullptr}};
-      const linear_fn fn =
-          fns[co == 1 ? 0 : (co == 2 ? 1 : (co == 4 ? 2 : (co == 8 ? 3 : 4)))][ki == 1 ? 0 : (ki == 2 ? 1 : 2)];
-      if (!fn) return fail(BBO_DEVICE_ERROR, "no kernel for this linear shape");  // ruled out by linear_eligible()
-      if ((rc = ensure_dynamic_lds((const void*)fn, sp.lds_bytes))) return rc;
-      hipLaunchKernelGGL(fn, dim3(sp.n_slots), dim3(64 * sp.waves), sp.lds_bytes, s, P);
-    } else if (dtype == BBO_F32) {
-      hipLaunchKernelGGL(k_train<float>, dim3(sp.n_slots), dim3(NTHREADS), 0, s, P);
+      fn = linear_kernel(ln_co(c_out), ln_ki(d));
+      threads = 64 * sp.waves;
     } else {
-      hipLaunchKernelGGL(k_train<__bf16>, dim3(sp.n_slots), dim3(NTHREADS), 0, s, P);
+      fn = dtype == BBO_F32 ? (const void*)k_train<float> : (const void*)k_train<__bf16>;
     }
+    if (!fn) return fail(BBO_DEVICE_ERROR, "no kernel for this shape");  // ruled out by kernel_class()
+    if (sp.lds_bytes && (rc = ensure_dynamic_lds(fn, sp.lds_bytes))) return rc;
+    void* args[] = {&P};
+    HIP_TRY(hipLaunchKernel(fn, dim3(sp.n_slots), dim3(threads), args, sp.lds_bytes, s));
     HIP_TRY(hipGetLastError());
   }
   hipLaunchKernelGGL(k_reduce, dim3((B + 255) / 256), dim3(256), 0, s, P.item_out, B, n_folds, scores, status,

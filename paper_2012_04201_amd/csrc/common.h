@@ -237,4 +237,29 @@ struct Plateau {
   }
 };
 
+// One optimizer step of one element, with the step's constants.
+struct OptC {
+  bool adam, nest;
+  float b1, b2, omb1, omb2, eps, lr_t, mu, lr, am;
+};
+
+__device__ inline void opt_update(const OptC& c, float g, float& w, float& m, float& v) {
+  if (c.adam) {
+    m = c.b1 * m + c.omb1 * g;
+    v = c.b2 * v + c.omb2 * (g * g);
+    // hardware reciprocal and square root (1 ulp each): far inside the per-step tolerance
+    w = w - (c.lr_t * m) * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(v) + c.eps);
+  } else {
+    const float u = c.mu * m - c.lr * g;
+    m = u;
+    w = w + (c.nest ? c.mu * u - c.lr * g : u);
+  }
+}
+
+// Position in the training schedule: epoch, step of the epoch, first row of
+// the chunk within the step's minibatch.
+struct ChunkPos {
+  int e, st, c0;
+};
+
 }  // namespace

@@ -37,7 +37,6 @@
 // network evaluation costs four LDS reads instead of twelve 64-bit multiplies.
 #pragma once
 #include "common.h"
-#include "train_tiled_bf16.h"  // OptC, opt_update
 
 namespace {
 

@@ -24,7 +24,6 @@
 // current one is processed.
 #pragma once
 #include "common.h"
-#include "train_tiled_bf16.h"  // OptC, opt_update
 
 namespace {
 

@@ -33,7 +33,6 @@
 //   zp[wave][row][4], d2[wave][row][4], ys[2][row], row ids, the epoch's row order
 #pragma once
 #include "common.h"
-#include "train_tiled_bf16.h"  // OptC, opt_update
 
 namespace {
 
@@ -103,12 +102,6 @@ __device__ inline float row16_sum(float v) {
   v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, false));
   return v;
 }
-
-// Position in the training schedule: epoch, step of the epoch, first row of
-// the chunk within the step's minibatch.
-struct ChunkPos {
-  int e, st, c0;
-};
 
 // KT: 16-wide k tiles of the input layer (inputs + bias).  CO: output slots in use (1, 2 or 4); 1 and 2 are
 // exact output counts, 4 serves 3 or 4 outputs.

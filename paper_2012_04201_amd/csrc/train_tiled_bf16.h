@@ -159,24 +159,6 @@ struct TItem {
 typedef const __attribute__((address_space(4))) ItemDesc ConstItemDesc;
 typedef const __attribute__((address_space(4))) TLay ConstTLay;
 
-struct OptC {
-  bool adam, nest;
-  float b1, b2, omb1, omb2, eps, lr_t, mu, lr, am;
-};
-
-__device__ inline void opt_update(const OptC& c, float g, float& w, float& m, float& v) {
-  if (c.adam) {
-    m = c.b1 * m + c.omb1 * g;
-    v = c.b2 * v + c.omb2 * (g * g);
-    // hardware reciprocal and square root (1 ulp each): far inside the per-step tolerance
-    w = w - (c.lr_t * m) * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(v) + c.eps);
-  } else {
-    const float u = c.mu * m - c.lr * g;
-    m = u;
-    w = w + (c.nest ? c.mu * u - c.lr * g : u);
-  }
-}
-
 // Transposing LDS read: within each group of 16 lanes the 16 x 4 values that
 // the lanes address (lane t: 4 consecutive units of row t/4, unit offset
 // 4*(t%4)) come back transposed, lane t holding unit t of the 4 rows.
@@ -1491,22 +1473,5 @@ struct Tiled {
     }
   }
 };
-
-__global__ __launch_bounds__(TB_THREADS) void k_train_tiled(const TrainParams P) {
-  extern __shared__ __align__(16) char smem[];
-  __shared__ int s_item;
-  __shared__ double red[TB_THREADS / 64];
-  char* slot = P.slots + (uint64_t)blockIdx.x * P.slot_bytes;
-  for (;;) {
-    __syncthreads();
-    if (threadIdx.x == 0) s_item = atomicAdd(P.queue, 1);
-    __syncthreads();
-    const int item = __builtin_amdgcn_readfirstlane(s_item);
-    if (item >= P.n_items) break;
-    const __attribute__((address_space(4))) TItem* ti = (const __attribute__((address_space(4))) TItem*)P.items + item;
-    Tiled T{P, ti->d, ti->y, slot, smem, red};
-    T.run();
-  }
-}
 
 }  // namespace
