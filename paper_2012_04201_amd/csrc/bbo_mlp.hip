@@ -189,7 +189,7 @@ __device__ inline float row_loss(const float* z, int c, int n_classes, const voi
 
 // The training kernels.  Every suggestion of a call goes to the fastest kernel that takes its shape, so
 // a suggestion's scores do not depend on which other suggestions share its call.
-enum { KC_TILED = 0, KC_SMALL = 1, KC_LINEAR = 2, KC_GENERIC = 3, KC_MID = 4, KC_N = 5 };
+enum { KC_TILED = 0, KC_SMALL = 1, KC_LINEAR = 2, KC_GENERIC = 3, KC_MID = 4 };
 
 // ---------------------------------------------------------------------------
 // Fold lists (ascending), one workgroup per list; also resets the work queues.
@@ -200,11 +200,11 @@ __global__ __launch_bounds__(NTHREADS) void k_fold_lists(const int32_t* __restri
                                                          int32_t* __restrict__ train_idx,
                                                          int32_t* __restrict__ val_idx,
                                                          int32_t* __restrict__ counts, int32_t* queue,
-                                                         int fold_base) {
+                                                         int n_queues, int fold_base) {
   __shared__ int wtr[NTHREADS / 64], wva[NTHREADS / 64];
   __shared__ int base_tr, base_va;
   const int f = blockIdx.x, fold = (int)blockIdx.x + fold_base, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (f == 0 && tid < KC_N && queue) queue[tid] = 0;  // one work-queue counter per training kernel
+  if (f == 0 && tid < n_queues) queue[tid] = 0;  // the work-queue counters of the launches that follow
   if (tid == 0) base_tr = base_va = 0;
   __syncthreads();
   for (int64_t c0 = 0; c0 < n; c0 += NTHREADS) {
@@ -795,22 +795,29 @@ void fill_dims(const bbo_mlp_hparams& h, int d, int n_classes, int32_t* dims, in
   dims[*L] = n_classes >= 2 ? n_classes : 1;
 }
 
+// One launch: the items of a call that run on one variant of one kernel.
 struct SubPlan {
-  std::vector<ItemDesc> items;  // this kernel's items, most expensive first
+  int kc = KC_GENERIC;          // kernel
+  SmallCut cut = {0, 0, 0, 0};  // register-resident kernel: how its models are cut (all alike in one launch)
+  std::vector<ItemDesc> items;  // most expensive first
+  std::vector<double> cost;     // estimated, by item (before sorting)
   uint64_t slot_bytes = 0;      // global memory per resident workgroup
   int n_slots = 0;              // workgroups to launch
   uint32_t lds_bytes = 0;       // dynamic LDS per workgroup
   int waves = 0;                // linear kernel: wavefronts per workgroup
   size_t item_bytes = 0;        // size of its item record
   uint64_t o_items = 0;         // workspace byte offset of its item array
+  uint64_t o_slots = 0;         // ... and of its workgroups' slots
+  double longest = 0;           // estimated cost of its most expensive item
 };
 
+constexpr int MAX_LAUNCHES = 64;  // queue counters in the workspace
+
 struct Plan {
-  SubPlan sub[KC_N];
+  std::vector<SubPlan> sub;
   size_t n_items = 0;
-  // workspace byte offsets; the kernels run one after the other and share the slot region
-  uint64_t o_items = 0, items_bytes = 0, o_queue = 0, o_out = 0, o_train = 0, o_val = 0, o_counts = 0, o_slots = 0,
-           total = 0;
+  // workspace byte offsets; the launches run side by side, each with slots of its own
+  uint64_t o_items = 0, items_bytes = 0, o_queue = 0, o_out = 0, o_train = 0, o_val = 0, o_counts = 0, total = 0;
 };
 
 // Resident workgroups of the generic kernel / compute units, of the current device (looked up once per
@@ -893,11 +900,7 @@ int kernel_class(const int32_t* dims, int L, int64_t n, int dtype) {
     return n * (int64_t)d < 0x7fffffff && linear_eligible(dims, L) ? KC_LINEAR : KC_GENERIC;
   }
   if (n * (int64_t)d >= 0x7fffffff) return KC_GENERIC;
-  if (small_eligible(dims, L)) {
-    SLay sy;
-    make_slay(sy, dims, n);
-    if (sy.lds_total <= SM_LDS_LIMIT) return KC_SMALL;
-  }
+  if (small_eligible(dims, L)) return KC_SMALL;
   if (mid_eligible(dims, L)) {
     MLay my;
     make_mlay(my, dims, n);
@@ -910,18 +913,17 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
               int dtype) {
   const int kstep = dtype == BBO_F32 ? 16 : 32, opsz = dtype == BBO_F32 ? 4 : 2;
   const double n_tr_est = n_folds > 1 && fold_base >= 0 ? (double)n * (n_folds - 1) / n_folds : (double)n;
-  std::vector<double> cost[KC_N];
-  for (int k = 0; k < KC_N; k++) {
-    pl.sub[k] = SubPlan();
-    pl.sub[k].items.reserve((size_t)B * n_folds);
-    cost[k].reserve((size_t)B * n_folds);
-  }
-  pl.sub[KC_TILED].item_bytes = sizeof(TItem);
-  pl.sub[KC_SMALL].item_bytes = sizeof(SItem);
-  pl.sub[KC_LINEAR].item_bytes = sizeof(ItemDesc);
-  pl.sub[KC_GENERIC].item_bytes = sizeof(ItemDesc);
-  pl.sub[KC_MID].item_bytes = sizeof(MItem);
-  pl.sub[KC_SMALL].slot_bytes = 256;
+  pl.sub.clear();
+  auto launch_of = [&](int kc, const SmallCut& cut) -> SubPlan& {
+    for (SubPlan& sp : pl.sub)
+      if (sp.kc == kc && sp.cut.nt == cut.nt && sp.cut.waves == cut.waves) return sp;
+    SubPlan sp;
+    sp.kc = kc;
+    sp.cut = cut;
+    sp.item_bytes = kc == KC_TILED ? sizeof(TItem) : (kc == KC_SMALL ? sizeof(SItem) : (kc == KC_MID ? sizeof(MItem) : sizeof(ItemDesc)));
+    pl.sub.push_back(std::move(sp));
+    return pl.sub.back();
+  };
   for (int b = 0; b < B; b++) {
     const bbo_mlp_hparams& h = hp[b];
     ItemDesc it;
@@ -952,43 +954,47 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
       params += (double)it.dims[l] * it.dims[l + 1];
     }
     const int k = kernel_class(it.dims, it.L, n, dtype);
+    const SmallCut cut = k == KC_SMALL ? small_cut(it.dims) : SmallCut{0, 0, 0, 0};
+    SubPlan& sp = launch_of(k, cut);
+    uint64_t slot_bytes = 0;
+    uint32_t lds_bytes = 0;
     if (k == KC_TILED) {
       TLay ty;
       make_tlay(ty, it.dims, it.L);
-      pl.sub[k].slot_bytes = std::max<uint64_t>(pl.sub[k].slot_bytes, ty.total);
-      pl.sub[k].lds_bytes = std::max<uint32_t>(pl.sub[k].lds_bytes, ty.lds_total);
+      slot_bytes = ty.total;
+      lds_bytes = ty.lds_total;
     } else if (k == KC_SMALL) {
       SLay sy;
-      make_slay(sy, it.dims, n);  // only the hidden layer's moments live in global memory
-      // the hidden layer's moments, and room for the best epoch's weights (early stopping on held-out rows)
-      pl.sub[k].slot_bytes = std::max<uint64_t>(pl.sub[k].slot_bytes, (3ull * sy.HP * sy.ldw + (sy.HP + 1) * 4ull) * 4);
-      pl.sub[k].lds_bytes = std::max<uint32_t>(pl.sub[k].lds_bytes, sy.lds_total);
+      make_slay(sy, it.dims, n, cut);
+      slot_bytes = 4ull * sy.slot_floats;
+      lds_bytes = sy.lds_total;
     } else if (k == KC_MID) {
       MLay my;
       make_mlay(my, it.dims, n);  // the moments of both layers live in global memory
-      pl.sub[k].slot_bytes = std::max<uint64_t>(pl.sub[k].slot_bytes, my.g_total);
-      pl.sub[k].lds_bytes = std::max<uint32_t>(pl.sub[k].lds_bytes, my.lds_total);
+      slot_bytes = my.g_total;
+      lds_bytes = my.lds_total;
     } else if (k == KC_GENERIC) {
       Layout y;
       make_layout(y, it.dims, it.L, it.rows_cap, kstep, opsz);
-      pl.sub[k].slot_bytes = std::max<uint64_t>(pl.sub[k].slot_bytes, y.total);
+      slot_bytes = y.total;
     }  // KC_LINEAR: a model per wavefront, nothing kept in global memory
+    sp.slot_bytes = std::max(sp.slot_bytes, slot_bytes);
+    sp.lds_bytes = std::max(sp.lds_bytes, lds_bytes);
     const double steps = std::ceil(n_tr_est / (double)std::max<int64_t>(bs, 1));
     const double c = (double)h.epochs * (n_tr_est * fps + steps * (params * 24.0 + 2.0e4));
     for (int f = 0; f < n_folds; f++) {
       it.fold = f + fold_base;
-      pl.sub[k].items.push_back(it);
-      cost[k].push_back(c);
+      sp.items.push_back(it);
+      sp.cost.push_back(c);
     }
   }
   pl.n_items = (size_t)B * n_folds;
-  uint64_t slots_region = 0;
-  for (int k = 0; k < KC_N; k++) {
-    SubPlan& sp = pl.sub[k];
-    if (sp.items.empty()) continue;
+  if (pl.sub.size() > (size_t)MAX_LAUNCHES) return fail(BBO_UNSUPPORTED, "too many kernel variants in one call");
+  for (SubPlan& sp : pl.sub) {
+    const int k = sp.kc;
     std::vector<int> order(sp.items.size());
     for (size_t i = 0; i < order.size(); i++) order[i] = (int)i;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b2) { return cost[k][a] > cost[k][b2]; });
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b2) { return sp.cost[a] > sp.cost[b2]; });
     std::vector<ItemDesc> sorted(sp.items.size());
     for (size_t i = 0; i < order.size(); i++) sorted[i] = sp.items[order[i]];
     sp.items.swap(sorted);
@@ -996,7 +1002,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     int rc = k == KC_GENERIC ? device_slots(dtype, &max_slots) : device_cus(&max_slots);
     if (rc) return rc;
     size_t units = sp.items.size();
-    if (k == KC_SMALL) max_slots *= 2;  // the kernel's LDS footprint is capped at half a CU's LDS
+    if (k == KC_SMALL) max_slots *= small_per_cu(sp.cut, sp.lds_bytes);
     if (k == KC_LINEAR) {
       // as many workgroups as the LDS lets a CU hold, each of `waves` wavefronts with a model apiece
       const int c_out = n_classes >= 2 ? n_classes : 1;
@@ -1008,8 +1014,10 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     sp.slot_bytes = (sp.slot_bytes + 255) & ~(uint64_t)255;
     if (k == KC_LINEAR) sp.slot_bytes = 0;
     sp.n_slots = (int)std::min<size_t>(units, (size_t)max_slots);
-    slots_region = std::max<uint64_t>(slots_region, sp.slot_bytes * (uint64_t)sp.n_slots);
+    sp.longest = sp.cost[order[0]];
   }
+  // the launch with the longest single model is enqueued first: nothing can make up for starting that one late
+  std::stable_sort(pl.sub.begin(), pl.sub.end(), [](const SubPlan& a, const SubPlan& b2) { return a.longest > b2.longest; });
   uint64_t off = 0;
   auto take = [&](uint64_t bytes) {
     uint64_t o = off;
@@ -1018,14 +1026,14 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
   };
   const uint64_t nn = (uint64_t)std::max<int64_t>(n, 1);
   pl.o_items = off;
-  for (int k = 0; k < KC_N; k++) pl.sub[k].o_items = take(pl.sub[k].item_bytes * pl.sub[k].items.size());
+  for (SubPlan& sp : pl.sub) sp.o_items = take(sp.item_bytes * sp.items.size());
   pl.items_bytes = off - pl.o_items;
-  pl.o_queue = take(256);  // one counter per kernel
+  pl.o_queue = take(4 * MAX_LAUNCHES);
   pl.o_out = take(8ull * std::max<size_t>(pl.n_items, 1));
   pl.o_train = take(4ull * nn * n_folds);
   pl.o_val = take(4ull * nn * n_folds);
   pl.o_counts = take(8ull * n_folds);
-  pl.o_slots = take(std::max<uint64_t>(slots_region, 256));
+  for (SubPlan& sp : pl.sub) sp.o_slots = take(std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256));
   pl.total = off;
   return BBO_OK;
 }
@@ -1069,6 +1077,50 @@ int stage_items(const void* src, size_t bytes, void* dst, hipStream_t s) {
   HIP_TRY(hipMemcpyAsync(dst, st->ptr, bytes, hipMemcpyHostToDevice, s));
   HIP_TRY(hipEventRecord(st->ev, s));
   st->pending = true;
+  return BBO_OK;
+}
+
+// Side streams for the launches of a call: its kernel variants run side by side, so that the tail of one (a few long
+// models) is filled by the next, and a call with few models takes as long as its longest model, not as the sum of
+// each variant's longest.  Kept per host thread and device, at most SIDE_STREAMS of them, given back when the
+// thread ends.  Within a call they start behind everything enqueued on the caller's stream, and the caller's stream
+// goes on behind them; two calls of one thread on different streams merely queue up on them.
+constexpr int SIDE_STREAMS = 3;  // with the caller's stream, the hardware queues a process has by default
+struct SideStreams {
+  int dev = -1;
+  hipStream_t s[SIDE_STREAMS] = {};
+  hipEvent_t fork = nullptr, join[SIDE_STREAMS] = {};
+};
+struct SidePool {
+  std::vector<SideStreams> all;
+  ~SidePool() {
+    for (SideStreams& e : all) {
+      for (int i = 0; i < SIDE_STREAMS; i++) {
+        if (e.s[i]) (void)hipStreamDestroy(e.s[i]);
+        if (e.join[i]) (void)hipEventDestroy(e.join[i]);
+      }
+      if (e.fork) (void)hipEventDestroy(e.fork);
+    }
+  }
+};
+int side_streams(int n, SideStreams** out) {
+  static thread_local SidePool pool;
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  SideStreams* st = nullptr;
+  for (SideStreams& e : pool.all)
+    if (e.dev == dev) st = &e;
+  if (!st) {
+    pool.all.push_back(SideStreams());
+    st = &pool.all.back();
+    st->dev = dev;
+  }
+  if (!st->fork) HIP_TRY(hipEventCreateWithFlags(&st->fork, hipEventDisableTiming));
+  for (int i = 0; i < n; i++) {
+    if (!st->s[i]) HIP_TRY(hipStreamCreateWithFlags(&st->s[i], hipStreamNonBlocking));
+    if (!st->join[i]) HIP_TRY(hipEventCreateWithFlags(&st->join[i], hipEventDisableTiming));
+  }
+  *out = st;
   return BBO_OK;
 }
 
@@ -1166,8 +1218,8 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
     // the item arrays of all kernels, laid out as in the workspace, in one staged copy
     static thread_local std::vector<char> blob;  // kept between calls
     blob.assign(pl.items_bytes, 0);
-    for (int k = 0; k < KC_N; k++) {
-      const SubPlan& sp = pl.sub[k];
+    for (const SubPlan& sp : pl.sub) {
+      const int k = sp.kc;
       char* at = blob.data() + (sp.o_items - pl.o_items);
       for (size_t i = 0; i < sp.items.size(); i++) {
         if (k == KC_TILED) {
@@ -1180,7 +1232,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
           SItem si;
           memset(&si, 0, sizeof(si));
           si.d = sp.items[i];
-          make_slay(si.y, sp.items[i].dims, n);
+          make_slay(si.y, sp.items[i].dims, n, sp.cut);
           memcpy(at + i * sizeof(SItem), &si, sizeof(SItem));
         } else if (k == KC_MID) {
           MItem mi;
@@ -1206,7 +1258,6 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
   P.val_idx = (const int32_t*)(ws + pl.o_val);
   P.counts = (const int32_t*)(ws + pl.o_counts);
   P.item_out = (float*)(ws + pl.o_out);
-  P.slots = ws + pl.o_slots;
   P.n = n;
   P.d = d;
   P.n_classes = n_classes;
@@ -1219,16 +1270,24 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
   P.state_in = traced ? state_in : nullptr;
   P.x_bf16 = dtype == BBO_BF16;
 
-  int32_t* queues = (int32_t*)(ws + pl.o_queue);  // one work-queue counter per kernel, reset by k_fold_lists
+  int32_t* queues = (int32_t*)(ws + pl.o_queue);  // one work-queue counter per launch, reset by k_fold_lists
   hipLaunchKernelGGL(k_fold_lists, dim3(n_folds), dim3(NTHREADS), 0, s, fold_idx, n, (int32_t*)(ws + pl.o_train),
-                     (int32_t*)(ws + pl.o_val), (int32_t*)(ws + pl.o_counts), queues, fold_base);
+                     (int32_t*)(ws + pl.o_val), (int32_t*)(ws + pl.o_counts), queues, MAX_LAUNCHES, fold_base);
   HIP_TRY(hipGetLastError());
-  // one launch per kernel that has items, one after the other on the caller's stream
-  for (int k = 0; k < KC_N; k++) {
-    const SubPlan& sp = pl.sub[k];
-    if (sp.items.empty()) continue;
+  // one launch per kernel variant that has items, side by side: the first on the caller's stream
+  const int n_side = std::min<int>((int)pl.sub.size() - 1, SIDE_STREAMS);
+  SideStreams* side = nullptr;
+  if (n_side > 0) {
+    if ((rc = side_streams(n_side, &side))) return rc;
+    HIP_TRY(hipEventRecord(side->fork, s));
+    for (int i = 0; i < n_side; i++) HIP_TRY(hipStreamWaitEvent(side->s[i], side->fork, 0));
+  }
+  for (size_t li = 0; li < pl.sub.size(); li++) {
+    const SubPlan& sp = pl.sub[li];
+    const int k = sp.kc;
     P.items = ws + sp.o_items;
-    P.queue = queues + k;
+    P.slots = ws + sp.o_slots;
+    P.queue = queues + li;
     P.slot_bytes = sp.slot_bytes;
     P.n_items = (int)sp.items.size();
     const int c_out = n_classes >= 2 ? n_classes : 1;
@@ -1238,8 +1297,10 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
       fn = tiled_kernel();
       threads = TB_THREADS;
     } else if (k == KC_SMALL) {
-      fn = small_kernel(d + 1 <= 16 ? 1 : (d + 1 <= 32 ? 2 : 4), c_out <= 2 ? c_out : 4);
-      threads = SM_THREADS;
+      const SmallCut& t = sp.cut;
+      fn = t.kt == 1 ? small_kernel1(t.nt, t.waves, t.co) : (t.kt == 2 ? small_kernel2(t.nt, t.waves, t.co)
+         : (t.kt == 3 ? small_kernel3(t.nt, t.waves, t.co) : small_kernel4(t.nt, t.waves, t.co)));
+      threads = 64 * t.waves;
     } else if (k == KC_MID) {
       fn = mid_kernel(md_kt(d));
       threads = MD_THREADS;
@@ -1252,8 +1313,13 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
     if (!fn) return fail(BBO_DEVICE_ERROR, "no kernel for this shape");  // ruled out by kernel_class()
     if (sp.lds_bytes && (rc = ensure_dynamic_lds(fn, sp.lds_bytes))) return rc;
     void* args[] = {&P};
-    HIP_TRY(hipLaunchKernel(fn, dim3(sp.n_slots), dim3(threads), args, sp.lds_bytes, s));
+    const int lane = (int)(li % (size_t)(n_side + 1));
+    HIP_TRY(hipLaunchKernel(fn, dim3(sp.n_slots), dim3(threads), args, sp.lds_bytes, lane ? side->s[lane - 1] : s));
     HIP_TRY(hipGetLastError());
+  }
+  for (int i = 0; i < n_side; i++) {
+    HIP_TRY(hipEventRecord(side->join[i], side->s[i]));
+    HIP_TRY(hipStreamWaitEvent(s, side->join[i], 0));
   }
   hipLaunchKernelGGL(k_reduce, dim3((B + 255) / 256), dim3(256), 0, s, P.item_out, B, n_folds, scores, status,
                      per_fold);
@@ -1312,7 +1378,7 @@ int bbo_mlp_fold_lists(const int32_t* fold_idx, int64_t n, int32_t n_folds, int3
   if (n < 0 || n > 0x3fffffff || n_folds < 1 || n_folds > 1024) return fail(BBO_INVALID_ARG, "bad n or n_folds");
   if (!counts || (n > 0 && (!fold_idx || !train_idx || !val_idx))) return fail(BBO_INVALID_ARG, "null pointer");
   hipLaunchKernelGGL(k_fold_lists, dim3(n_folds), dim3(NTHREADS), 0, (hipStream_t)stream, fold_idx, n, train_idx,
-                     val_idx, counts, (int32_t*)nullptr, 0);
+                     val_idx, counts, (int32_t*)nullptr, 0, 0);
   HIP_TRY(hipGetLastError());
   return BBO_OK;
 }
@@ -1330,7 +1396,7 @@ int bbo_mlp_holdout_lists(const int32_t* fold_idx, int64_t n, int32_t* train_idx
   if (n < 0 || n > 0x3fffffff) return fail(BBO_INVALID_ARG, "bad n");
   if (!counts || (n > 0 && (!fold_idx || !train_idx || !val_idx))) return fail(BBO_INVALID_ARG, "null pointer");
   hipLaunchKernelGGL(k_fold_lists, dim3(1), dim3(NTHREADS), 0, (hipStream_t)stream, fold_idx, n, train_idx, val_idx,
-                     counts, (int32_t*)nullptr, -1);
+                     counts, (int32_t*)nullptr, 0, -1);
   HIP_TRY(hipGetLastError());
   return BBO_OK;
 }

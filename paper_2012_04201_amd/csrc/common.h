@@ -118,6 +118,39 @@ struct ItemDesc {
   float bound[MAXL];
 };
 
+// The staged items are written by the host before the launch and never by a kernel: reading them through the
+// constant address space lets the compiler use scalar loads and keep them in scalar registers.
+typedef const __attribute__((address_space(4))) ItemDesc ConstItemDesc;
+
+// A wave-uniform value that the compiler holds in vector registers (anything read from memory the kernel also
+// writes), moved to scalar registers.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// The same for a value the compiler knows to be uniform but computes on the vector unit (any float arithmetic): the
+// empty asm hides that knowledge, or the move would be dropped again.  The move itself must stay the builtin: the
+// hardware wants wait states between a vector write, this move and the use of its scalar result, and the compiler
+// places them for instructions that it knows, not inside an asm.
+__device__ __forceinline__ float uniform(float v) {
+  asm volatile("" : "+v"(v));
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+// Global memory by name: a pointer that has been through an asm is a generic one otherwise, and generic accesses
+// count as LDS accesses too, so that every later LDS access waits for them.
+typedef __attribute__((address_space(1))) float GlobalF32;
+typedef __attribute__((address_space(1))) int32_t GlobalI32;
+
+// A scalar value that is to stay in scalar registers instead of being loaded again where it is used.
+template <class T>
+__device__ __forceinline__ T pin(T v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+template <class T>
+__device__ __forceinline__ T* uniform(T* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (T*)(((uint64_t)hi << 32) | lo);
+}
+
 __host__ __device__ inline int rup(int x, int m) { return (x + m - 1) / m * m; }
 
 struct Layout {

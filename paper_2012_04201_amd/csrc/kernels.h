@@ -5,6 +5,10 @@
 #define BBO_HIDDEN __attribute__((visibility("hidden")))
 
 BBO_HIDDEN const void* tiled_kernel();
-BBO_HIDDEN const void* small_kernel(int kt, int co);   // 16-wide k tiles of the input layer, output slots
+// unit tiles per wave, waves, output slots; one function per number of 16-wide k tiles of the input layer
+BBO_HIDDEN const void* small_kernel1(int nt, int waves, int co);
+BBO_HIDDEN const void* small_kernel2(int nt, int waves, int co);
+BBO_HIDDEN const void* small_kernel3(int nt, int waves, int co);
+BBO_HIDDEN const void* small_kernel4(int nt, int waves, int co);
 BBO_HIDDEN const void* mid_kernel(int kt);             // 16-wide k tiles of the input layer
 BBO_HIDDEN const void* linear_kernel(int co, int ki);  // padded outputs, rows of W per lane

@@ -1,50 +1,58 @@
-// LDS-resident training / scoring kernel for small fp32 models with one hidden
-// layer (the "many concurrent studies" shape: up to 63 inputs, hidden width up
-// to 224, up to 4 outputs).
+// Register-resident training / scoring kernel for small fp32 models with one hidden layer (the "many concurrent
+// studies" shape: up to 63 inputs, hidden width up to 224, up to 4 outputs).
 //
-// One workgroup (4 waves) trains one model, and the model never leaves the
-// chip: the weights of both layers stay in LDS for all epochs and the
-// minibatch is processed in chunks of 64 rows.  The hidden layer's optimizer
-// moments are the one thing kept in global memory (a per-workgroup slot that
-// stays L2-resident, read and written once per step in the update); HBM is
-// otherwise touched only for the gathered input rows, fetched one chunk ahead
-// into registers.  The LDS footprint stays under half a CU's LDS so that two
-// workgroups share a CU and cover each other's barriers.
+// One workgroup of W waves trains one model.  Wave w owns the hidden-unit tiles (16 units) w, w + W, .. for the
+// whole run, and everything that belongs to them stays in its registers from the first draw to the score: the
+// hidden layer's weights, both moments and the step's gradient, and the units' rows of the output layer with
+// theirs.  That works because the MFMA (16x16x4 fp32) wants a weight in the same lane as operand of the forward
+// product as it leaves its gradient in: lane (unit li, columns 4q..4q+3 of a k tile).  The output bias is kept by
+// every wave, and every wave computes the loss and the output delta of all rows of a chunk (lane = row), so the
+// waves exchange nothing but their partial outputs: ONE barrier per chunk of 64 rows.
 //
-// Each wave owns the same hidden-unit tiles in every phase, so the hidden
-// activations never leave its registers:
-//   phase 1  forward MFMA (16x16x4 fp32): D[row][unit] = xs[row][k] . w1[unit][k]
-//            (bias rides in column d of xs/w1), ReLU in the accumulators; the
-//            wave's share of the output layer is reduced over its 16 unit lanes
-//            with DPP adds and parked in LDS (4 KB);
-//   phase 2  every wave sums the four shares for all 64 rows (lane = row),
-//            takes softmax / loss / output delta, then turns its accumulators
-//            into hidden deltas in place and feeds them straight back to the
-//            MFMA as the B operand of the weight gradient, D[k][unit] += xt[k][row]
-//            . delta[unit][row], accumulated over the chunks of the step in
-//            registers; the optimizer update reads the gradient from those
-//            registers and the weights from LDS.
-// Two block-wide barriers per chunk (the input-major tile is double-buffered).
+//   forward   D[row][unit] = xs[row][k] . w1[unit][k], accumulators started at the unit's bias; ReLU; the wave's
+//             share of the outputs is summed over the 16 unit lanes by a folding tree that leaves the total of row
+//             (rt, 4q + e) in lane (q, li = 4 rt + e): one value per lane and output, parked in LDS
+//   outputs   sum of the waves' shares, softmax / logistic / squared loss, output delta (lane = row)
+//   backward  hidden deltas in the accumulators, which feed the MFMA again as the B operand of the weight gradient
+//             D[k][unit] += xs[row][k] . delta[row][unit]
+//   update    Adam / SGD, registers only
 //
-// LDS (floats; rows padded by 4 against bank conflicts):
-//   xs[row][k], xt[2][k][row]     gathered inputs, both orders; column d = 1 on real rows
-//   w1[unit][k]                   hidden layer, bias in column d
-//   w2, m2, v2 [unit][4]          output layer and its moments, bias in row HP
-//   zp[wave][row][4], d2[wave][row][4], ys[2][row], row ids, the epoch's row order
+// Inputs are fetched two chunks ahead: requested into registers right after a chunk's barrier, put into LDS before
+// the next one (three input tiles in rotation, so that neither needs a barrier of its own).  The rows of an epoch
+// are tabled in LDS (16-bit row ids, two tables in turn); the rows set aside for early stopping are scored by the
+// same loop as chunks of their own between two epochs, and so are the held fold's rows at the end.
+//
+// What bounds it: with the chip full, the matrix pipe shares its SIMD with the vector work around it (ReLU, output
+// layer, softmax, update), and two to four waves per SIMD have to cover each other's latencies; with few models,
+// the chain of a step's dependent phases.  The form before this one kept the weights in LDS and the moments in L2, at
+// two workgroups per CU whatever the width and two barriers per chunk.  Before and after, per call: 10,240 models
+// 569 x 30, 50..200 units, 20 epochs 45.3 -> 32.4 ms; 40 models 506 x 13, SGD, 30 epochs 3.41 -> 1.74 ms; 40 models of
+// 10,000 x 45 rows, 3 epochs 10.9 -> 4.45 ms; 40 models 150 x 4, 20 epochs 0.39 -> 0.25 ms.
+//
+// LDS: xs[3][64][16 KT + 4] inputs (the stride spreads the 16 rows of an operand over all banks and the four row
+// groups of a gradient operand over its quarters), zp[2][W][CO][64], d2[CO][64], ys[3][64], row lists.
 #pragma once
 #include "common.h"
 
 namespace {
 
-constexpr int SM_THREADS = 256;
-constexpr int SM_RC = 64;                          // rows per chunk
-constexpr uint32_t SM_LDS_LIMIT = 80 * 1024 - 64;  // per workgroup: two workgroups per CU
+constexpr int SM_RC = 64;                   // rows per chunk
+constexpr int SM_MAX_WAVES = 8;
+constexpr uint32_t SM_LDS_LIMIT = 156 * 1024;  // of a workgroup, row tables included
+constexpr int SM_NET = 4096;                 // rows up to which an epoch's permutation network is tabled whole
+
+// How a model is cut: waves per workgroup and unit tiles per wave.
+struct SmallCut {
+  int kt, nt, co, waves;
+};
 
 struct SLay {
-  int32_t d, h, c, K0, HP, ldw, lda;
+  int32_t d, h, c, nut, waves;
   int32_t cw[2], cb[2], P;
-  uint32_t o_w1, o_w2, o_m2, o_v2, o_xs, o_xt, o_zp, o_d2, o_rows, o_ys, o_epoch, lds_total;
-  int32_t epoch_cap;  // entries of the per-epoch row table in LDS (0: rows are permuted on the fly)
+  uint32_t o_ft, o_net, o_sl, o_ep, lds_total;  // LDS offsets of the row tables; what precedes them is fixed by the variant
+  int32_t netted;  // the permutation network is tabled whole
+  int32_t tabled;  // the epoch's rows are tabled in LDS; otherwise they are permuted chunk by chunk
+  uint32_t slot_floats;  // best epoch's parameters (early stopping on held-out rows)
 };
 
 struct SItem {
@@ -55,94 +63,168 @@ struct SItem {
 __host__ __device__ inline bool small_eligible(const int32_t* dims, int L) {
   return L == 2 && dims[0] <= 63 && dims[1] <= 224 && dims[2] <= 4;
 }
+__host__ __device__ constexpr int sm_ldw(int kt) { return 16 * kt + 4; }
+// LDS of a variant ahead of the row tables
+__host__ __device__ constexpr uint32_t sm_fixed_lds(int kt, int nt, int co, int waves) {
+  return (3 * SM_RC * sm_ldw(kt) + 2 * waves * co * SM_RC + co * SM_RC + 5 * SM_RC + waves * (nt * (1 + co) + co) * 32) * 4;
+}
+// registers a wave needs to park its share of the parameters
+__host__ __device__ constexpr int sm_regs(int kt, int nt, int co) { return nt * (4 * kt + 1 + co) + co; }
 
-__host__ __device__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n) {
+// The cut depends on the shape alone, never on the call: the order in which the waves' partial outputs are added
+// is part of a suggestion's result, and that must not depend on its companions.
+__host__ inline SmallCut small_cut(const int32_t* dims) {
+  SmallCut s;
+  const int nut = rup(dims[1], 16) / 16;
+  s.kt = rup(dims[0], 16) / 16;
+  s.co = dims[2] <= 2 ? dims[2] : 4;
+  const int ntmax = s.kt == 4 ? 1 : (s.kt == 3 || s.co == 4 ? 2 : 3);
+  s.waves = s.kt == 1 && nut <= 2 ? 2 : 4;  // two waves could not hold the inputs of a wider chunk in flight
+  if (nut > s.waves * ntmax) s.waves = 8;
+  s.nt = (nut + s.waves - 1) / s.waves;
+  return s;
+}
+
+__host__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n, const SmallCut& s) {
   y.d = dims[0];
   y.h = dims[1];
   y.c = dims[2];
-  y.K0 = dims[0] + 1 <= 16 ? 16 : (dims[0] + 1 <= 32 ? 32 : 64);
-  y.HP = rup(dims[1], 16);
-  y.ldw = y.K0 + 4;
-  y.lda = SM_RC + 4;
+  y.nut = rup(dims[1], 16) / 16;
+  y.waves = s.waves;
   y.cw[0] = 0;
   y.cb[0] = y.d * y.h;
   y.cw[1] = y.cb[0] + y.h;
   y.cb[1] = y.cw[1] + y.h * y.c;
   y.P = y.cb[1] + y.c;
+  y.slot_floats = (uint32_t)(s.waves * sm_regs(s.kt, s.nt, s.co) * 64);
   uint32_t o = 0;
-  auto take = [&](uint32_t floats) {
+  auto take = [&](uint32_t bytes) {
     uint32_t r = o;
-    o += ((floats * 4) + 15) & ~15u;
+    o += (bytes + 15) & ~15u;
     return r;
   };
-  y.o_w1 = take(y.HP * y.ldw);
-  y.o_w2 = take((y.HP + 1) * 4);
-  y.o_m2 = take((y.HP + 1) * 4);
-  y.o_v2 = take((y.HP + 1) * 4);
-  y.o_xs = take(SM_RC * y.ldw);
-  y.o_xt = take(2 * y.K0 * y.lda);
-  y.o_zp = take(4 * SM_RC * 4);
-  y.o_d2 = take(4 * SM_RC * 4);
-  y.o_rows = take(2 * SM_RC);
-  y.o_ys = take(2 * SM_RC);
-  y.o_epoch = o;
-  y.epoch_cap = 0;
-  if (n <= 4096 && o + 4 * (uint32_t)n + 16 <= SM_LDS_LIMIT) {
-    y.epoch_cap = (int32_t)n;
-    o += (4 * (uint32_t)n + 15) & ~15u;
+  take(sm_fixed_lds(s.kt, s.nt, s.co, s.waves));
+  // 16-bit tables: the fold's row list in the order of the early-stopping cut, the epoch's row order, the round
+  // function of the permutation network (a copy per wave) and, up to SM_NET rows, the whole network
+  int hb = 1;
+  while ((1 << (2 * hb)) < n) hb++;
+  const uint32_t ft = (uint32_t)(s.waves * (4 << hb) * 2), net = n <= SM_NET ? 2u << (2 * hb) : 0u;
+  const uint32_t tab = (uint32_t)((2 * n + 15) & ~(int64_t)15);
+  y.tabled = n >= 1 && n <= 0xffff && o + ft + net + 2 * tab <= SM_LDS_LIMIT;
+  y.netted = net > 0;  // (sized for n rows; the fold's own network is never wider)
+  y.o_ft = y.o_net = y.o_sl = y.o_ep = o;
+  if (y.tabled) {
+    y.o_ft = take(ft);
+    y.o_net = take(net);
+    y.o_sl = take(tab);
+    y.o_ep = take(tab);
   }
   y.lds_total = o;
 }
 
-// Sum over the 16 lanes of a DPP row; every lane gets the total.
-__device__ inline float row16_sum(float v) {
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xf, 0xf, false));
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x124, 0xf, 0xf, false));
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xf, 0xf, false));
-  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, false));
-  return v;
+// Waves per SIMD the registers of a variant are budgeted for (512 registers per lane and SIMD).
+__host__ __device__ constexpr int sm_occupancy(int kt, int nt, int co) {
+#ifdef SM_OCC2
+  return nt == 1 && kt <= 2 ? 4 : (nt == 2 && kt <= 2 ? SM_OCC2 : 2);
+#endif
+  return nt == 1 && kt <= 2 ? 4 : 2;
+}
+// workgroups a CU holds
+__host__ inline int small_per_cu(const SmallCut& s, uint32_t lds_bytes) {
+  const int by_regs = 4 * sm_occupancy(s.kt, s.nt, s.co) / s.waves, by_lds = (int)(160u * 1024u / (lds_bytes + 512));
+  const int n = by_regs < by_lds ? by_regs : by_lds;
+  return n < 1 ? 1 : n;
 }
 
-// KT: 16-wide k tiles of the input layer (inputs + bias).  CO: output slots in use (1, 2 or 4); 1 and 2 are
-// exact output counts, 4 serves 3 or 4 outputs.
-template <int KT, int CO>
+template <int CTRL>
+__device__ __forceinline__ float sm_dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+// Sum over the four 16-lane rows of a wave, the same bits in every lane.
+__device__ __forceinline__ float sm_rowsum(float v) {
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
+}
+// Sum over the 16 lanes of a row, the same bits in every lane.
+__device__ __forceinline__ float sm_row16sum(float v) {
+  v += sm_dpp<0x128>(v);  // row rotation by 8
+  v += sm_dpp<0x141>(v);  // mirror within 8 lanes
+  v += sm_dpp<0x4E>(v);   // quad permutations
+  return v + sm_dpp<0xB1>(v);
+}
+__device__ __forceinline__ double sm_wavesum_d(double v) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+// Folding sums over the 16 lanes of a row.  sm_fold_quad: four values p[e]; lane e of each quad is left with the
+// quad's sum of p[e].  sm_fold_row: four values v[rt]; quad rt of each row is left with the sum over the four
+// quads of v[rt], lane by lane.  A lane hands on the half it does not keep: three instructions per halving.
+__device__ __forceinline__ float sm_fold_quad(const float (&p)[4], bool b0, bool b1) {
+  const float A = (b0 ? p[1] : p[0]) + sm_dpp<0xB1>(b0 ? p[0] : p[1]);
+  const float B = (b0 ? p[3] : p[2]) + sm_dpp<0xB1>(b0 ? p[2] : p[3]);
+  return (b1 ? B : A) + sm_dpp<0x4E>(b1 ? A : B);
+}
+__device__ __forceinline__ float sm_fold_row(const float (&v)[4], bool b2, bool b3) {
+  const float A = (b3 ? v[2] : v[0]) + sm_dpp<0x128>(b3 ? v[0] : v[2]);
+  const float B = (b3 ? v[3] : v[1]) + sm_dpp<0x128>(b3 ? v[1] : v[3]);
+  const float x = sm_dpp<0x141>(b2 ? A : B);       // lane i gets 7 - i of its eight,
+  return (b2 ? B : A) + sm_dpp<0x1B>(x);           // and the reversal of the quad makes that i ^ 4
+}
+
+// What the phases of a chunk need to know about it, packed into one scalar (two chunks are in the pipeline behind
+// the position that is being advanced): its rows (0..64), its mode, and flags.
+enum {
+  SC_ROWS = 0x7f,
+  SC_MODE = 0x380,       // RowMode << 7, or one of the next two
+  SC_END = 3 << 7,       // past the last chunk
+  SC_NONE = 4 << 7,      // the pipeline is filling
+  SC_FIRST = 1 << 10,    // first chunk of a step, or of a scoring pass
+  SC_LAST = 1 << 11,     // last chunk of a step
+  SC_RAGGED = 1 << 12,   // the epoch's last step
+  SC_EPOCH = 1 << 13,    // the epoch's first step
+  SC_DECIDE = 1 << 14,   // the stopping rule is applied after it
+};
+__device__ __forceinline__ int sc_mode(int ch) { return (ch & SC_MODE) >> 7; }
+
+// KT: 16-wide k tiles of the input layer.  NT: unit tiles per wave (every wave has NT, or NT - 1, of them).
+// CO: output slots in use (1 and 2 are exact output counts, 4 serves 3 or 4 outputs).  W: waves.
+template <int KT, int NT, int CO, int W>
 struct Small {
-  static constexpr int K0 = 16 * KT, RSTEP = SM_THREADS / K0, NX = SM_RC / RSTEP;
+  static constexpr int K0 = 16 * KT, LDW = sm_ldw(KT);
+  static constexpr int KS = KT == 3 ? 64 : K0;             // lanes per row when inputs are fetched
+  static constexpr int NTHR = 64 * W, RSTEP = NTHR / KS, NX = SM_RC / RSTEP;  // rows per pass, passes
   const TrainParams& P;
-  const ItemDesc& it;
-  const SLay& y;
+  const ConstItemDesc& it;
+  const __attribute__((address_space(4))) SLay& y;
   char* lds;
-  char* slot;  // global: m1[unit][k], v1[unit][k]
+  float* slot;
   double* red;
+  double* trace_stash;  // thread 0's own
+  // What every chunk needs of the item and the call, held in scalar registers: left to itself the compiler reloads
+  // each field where it is used, a few hundred cycles every time.
+  const GlobalF32* X;
+  const GlobalI32* Y;
+  int d, n_fit, n_classes, o_sl, o_ep, tabled, nut;
 
-  __device__ float* f(uint32_t off) const { return (float*)(lds + off); }
-  __device__ float* m1g() const { return (float*)slot; }
-  __device__ float* v1g() const { return (float*)slot + y.HP * y.ldw; }
-  // weights of the best epoch so far (early stopping on held-out rows): both layers, as they lie in LDS
-  __device__ float* bestg() const { return (float*)slot + 2 * y.HP * y.ldw; }
-  // Keep the current weights aside / put the kept ones back.  Block-wide; the caller orders it against updates.
-  __device__ __forceinline__ void copy_best(bool keep) const {
-    float* w1 = f(y.o_w1);
-    float* w2 = f(y.o_w2);
-    float* b = bestg();
-    const int n1 = y.HP * y.ldw, n2 = (y.HP + 1) * 4;
-    for (int i = threadIdx.x; i < n1 + n2; i += blockDim.x) {
-      float* l = i < n1 ? w1 + i : w2 + (i - n1);
-      if (keep)
-        b[i] = *l;
-      else
-        *l = b[i];
-    }
-  }
-  __device__ int32_t* rowlist(int par) const { return (int32_t*)(lds + y.o_rows) + par * SM_RC; }
-  __device__ float* xt(int par) const { return f(y.o_xt) + par * K0 * y.lda; }
-  __device__ float* ys(int par) const { return f(y.o_ys) + par * SM_RC; }
+  struct Regs {
+    f32x4 w[NT][KT], m[NT][KT], v[NT][KT], g[NT][KT];  // hidden layer: lane (unit li, columns 16 kk + 4q + e)
+    float bw[NT], bg[NT];                              // its bias
+    float w2[NT][CO], g2[NT][CO];                      // the unit's row of the output layer, alike in the four q
+    float ow[CO], og[CO];                              // output bias, alike in every lane (og: the lane's share)
+  };
+  // The moments of the last three, which are needed once per step and are alike in the four q, wait in LDS:
+  // [wave][bias, outputs of each tile, then the output bias][first, second][li].
+  static constexpr int NMOM = NT * (1 + CO) + CO;
 
-  // packed index (W1[in][out], b1, W2[in][out], b2) of hidden-layer element (unit j, column k); -1 for pads
-  __device__ __forceinline__ int ci_hidden(int j, int k) const {
-    if (j >= y.h || k > y.d) return -1;
-    return k < y.d ? y.cw[0] + k * y.h + j : y.cb[0] + j;
-  }
+  // offsets in floats
+  static constexpr int O_ZP = 3 * SM_RC * LDW, O_D2 = O_ZP + 2 * W * CO * SM_RC, O_YS = O_D2 + CO * SM_RC, O_ROWS = O_YS + 3 * SM_RC,
+                       O_MOM = O_ROWS + 2 * SM_RC;
+  static_assert((O_MOM + W * NMOM * 32) * 4 == sm_fixed_lds(KT, NT, CO, W), "LDS layout");
+  __device__ __forceinline__ float* f(int off) const { return (float*)lds + off; }
+  __device__ __forceinline__ float* xs(int b) const { return f(b * (SM_RC * LDW)); }
+  __device__ __forceinline__ float* ys(int b) const { return f(O_YS + b * SM_RC); }
+  __device__ __forceinline__ int32_t* rowlist(int par) const { return (int32_t*)lds + O_ROWS + par * SM_RC; }
+  __device__ __forceinline__ uint16_t* u16(uint32_t off) const { return (uint16_t*)(lds + off); }
   // The thread index as a value the compiler cannot see through: lane coordinates and the addresses derived
   // from them are recomputed in each phase instead of being kept in registers for the whole run.
   __device__ __forceinline__ static int tid() {
@@ -150,258 +232,335 @@ struct Small {
     asm volatile("" : "+v"(t));
     return t;
   }
+  __device__ __forceinline__ static int wave() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+  // does the wave's i-th tile exist?  Only the last one can be missing.
+  __device__ __forceinline__ bool has(int i, int w) const { return i + 1 < NT || w + i * W < nut; }
+
+  // ---- parameters ----------------------------------------------------------
   __device__ __forceinline__ float init_value(int l, int e, bool isb) const {
     const uint64_t kt = key_fold(key_model(it.seed, it.fold), 16 + 2 * l + (isb ? 1 : 0));
     const uint32_t k24 = (uint32_t)(key_fold(kt, (uint64_t)e) >> 40);
     return it.bound[l] * ((float)((int32_t)k24 - 8388608) * 0x1p-23f);
   }
-
-  // Weights (and the output layer's moments) into LDS, from the initial draw or from a packed state.
-  __device__ __forceinline__ void put_weights(const float* st) const {
-    const int d = y.d, h = y.h, c = y.c;
-    float* w1 = f(y.o_w1);
-    float* w2 = f(y.o_w2);
-    for (int ci = threadIdx.x; ci < y.P; ci += blockDim.x) {
-      if (ci < y.cw[1]) {
-        const bool isb = ci >= y.cb[0];
-        const int o = isb ? (ci - y.cb[0]) * y.ldw + d : (ci % h) * y.ldw + ci / h;
-        w1[o] = st ? st[ci] : init_value(0, isb ? ci - y.cb[0] : ci, isb);
-        if (st) {
-          m1g()[o] = st[y.P + ci];
-          v1g()[o] = st[2 * y.P + ci];
-        }
-      } else {
-        const bool isb = ci >= y.cb[1];
-        const int e = isb ? ci - y.cb[1] : ci - y.cw[1];
-        const int o = isb ? y.HP * 4 + e : (e / c) * 4 + e % c;
-        w2[o] = st ? st[ci] : init_value(1, e, isb);
-        if (st) {
-          f(y.o_m2)[o] = st[y.P + ci];
-          f(y.o_v2)[o] = st[2 * y.P + ci];
-        }
-      }
-    }
-  }
-
-  // ---- input staging, one chunk ahead ---------------------------------------
-  // (1) row ids of a chunk: the load is issued here, the value parked in LDS later
-  __device__ __forceinline__ int fetch_row_id(const int32_t* list, const RowSplit& sp, int mode, uint64_t key, int lo,
-                                              int rows) const {
-    const int p = threadIdx.x;
-    if (p >= SM_RC || p >= rows) return -1;
-    if (mode == ROWS_EPOCH && y.epoch_cap) return ((const int32_t*)(lds + y.o_epoch))[lo + p];
-    return list[row_index(sp, mode, key, (uint32_t)(lo + p))];
-  }
-  // Row ids of a whole epoch, in minibatch order, into the LDS table.
-  __device__ __forceinline__ void build_epoch_table(const int32_t* list, const RowSplit& sp, uint64_t key) const {
-    int32_t* tab = (int32_t*)(lds + y.o_epoch);
-    for (int p = threadIdx.x; p < sp.n_fit; p += blockDim.x) tab[p] = list[fit_index(sp, key, (uint32_t)p)];
-  }
-  __device__ __forceinline__ void park_row_id(int par, int row) const {
-    if ((int)threadIdx.x < SM_RC) rowlist(par)[threadIdx.x] = row;
-  }
-  // (2) the chunk's input values (and label) into registers
-  __device__ __forceinline__ void fetch_inputs(int par, float (&xr)[NX], float& yv) const {
-    const int32_t* rl = rowlist(par);
-    const float* X = (const float*)P.X;
-    const int t_ = tid(), k = t_ % K0, r0 = t_ / K0, d = y.d;
+  // The wave's share of the parameters as it lies in its part of the slot: [register][lane], the registers in the
+  // order each_param() visits them.
+  static constexpr int NREG = sm_regs(KT, NT, CO);
+  __device__ __forceinline__ float* park() const { return slot + wave() * (NREG * 64) + (threadIdx.x & 63); }
+  // fn(index, reference) for the hidden weights of `w`, fs(index, position in NMOM) for everything else
+  template <class F, class S>
+  __device__ __forceinline__ static void each_param(f32x4 (&w)[NT][KT], F fn, S fs) {
+    int n = 0, k = 0;
 #pragma unroll
-    for (int i = 0; i < NX; i++) {
-      const int row = rl[r0 + i * RSTEP];
-      xr[i] = 0.f;
-      if (row >= 0) xr[i] = k < d ? X[row * d + k] : (k == d ? 1.f : 0.f);  // n*d < 2^31 (checked by the host)
-    }
-    yv = 0.f;
-    if ((int)threadIdx.x < SM_RC) {
-      const int row = rl[threadIdx.x];
-      if (row >= 0) yv = P.n_classes >= 1 ? __int_as_float(((const int32_t*)P.y)[row]) : ((const float*)P.y)[row];
-    }
-  }
-  // (3) registers -> the LDS tiles (the input-major tile and the labels of parity par)
-  __device__ __forceinline__ void commit_inputs(int par, const float (&xr)[NX], float yv) const {
-    float* s = f(y.o_xs);
-    float* t = xt(par);
-    const int t_ = tid(), k = t_ % K0, r0 = t_ / K0;
+    for (int i = 0; i < NT; i++) {
 #pragma unroll
-    for (int i = 0; i < NX; i++) {
-      const int r = r0 + i * RSTEP;
-      s[r * y.ldw + k] = xr[i];
-      t[k * y.lda + r] = xr[i];
-    }
-    if ((int)threadIdx.x < SM_RC) ys(par)[threadIdx.x] = yv;
-  }
-
-  // ---- phase 1: hidden layer forward; the wave's share of the outputs -> zp ----
-  // A full chunk (all four row tiles): one straight-line block per unit tile of the wave, with the input
-  // operands of all row tiles in registers, so that the ReLU and output-layer arithmetic of one row tile can
-  // be issued while the MFMAs of the next are in flight.  Same order of every accumulation as forward().
-  __device__ __forceinline__ void forward_full(f32x4 (&acc)[4][4]) const {
-    const int t_ = tid(), lane = t_ & 63, w = t_ >> 6, li = lane & 15, q = lane >> 4;
-    const int nut = y.HP / 16, ldw = y.ldw;
-    const float* s = f(y.o_xs);
-    const float* w1 = f(y.o_w1);
-    constexpr bool c2 = CO >= 2, c4 = CO >= 4;
-    f32x4 a[4][KT];
-#pragma unroll
-    for (int r = 0; r < 4; r++)
-#pragma unroll
-      for (int kk = 0; kk < KT; kk++) a[r][kk] = *(const f32x4*)(s + (r * 16 + li) * ldw + kk * 16 + 4 * q);
-    float pz[4][4][CO];  // [row tile][row 4q+e][output]
-#pragma unroll
-    for (int r = 0; r < 4; r++)
-#pragma unroll
-      for (int e = 0; e < 4; e++)
-#pragma unroll
-        for (int cc = 0; cc < CO; cc++) pz[r][e][cc] = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-#pragma unroll
-      for (int r = 0; r < 4; r++) acc[i][r] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (w + 4 * i < nut) {
-        f32x4 b[KT];
-#pragma unroll
-        for (int kk = 0; kk < KT; kk++) b[kk] = *(const f32x4*)(w1 + ((w + 4 * i) * 16 + li) * ldw + kk * 16 + 4 * q);
-        const f32x4 w2 = *(const f32x4*)(f(y.o_w2) + ((w + 4 * i) * 16 + li) * 4);
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-#pragma unroll
-          for (int kk = 0; kk < KT; kk++)
-#pragma unroll
-            for (int e = 0; e < 4; e++)
-              acc[i][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r][kk][e], b[kk][e], acc[i][r], 0, 0, 0);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; r++)
-#pragma unroll
-          for (int e = 0; e < 4; e++) {
-            const float av = fmaxf(acc[i][r][e], 0.f);
-            acc[i][r][e] = av;
-            pz[r][e][0] += av * w2[0];
-            if (c2) pz[r][e][1] += av * w2[1];
-            if (c4) {
-              pz[r][e][2] += av * w2[2];
-              pz[r][e][3] += av * w2[3];
-            }
-          }
-      }
-    }
-    float* zp = f(y.o_zp) + w * SM_RC * 4;
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-      f32x4 o[4];
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int cc = 0; cc < CO; cc++) o[e][cc] = row16_sum(pz[r][e][cc]);
-      }
-      if (li == 0) {
-#pragma unroll
-        for (int e = 0; e < 4; e++) *(f32x4*)(zp + (r * 16 + 4 * q + e) * 4) = o[e];
-      }
-    }
-  }
-
-  __device__ __forceinline__ void forward(int nrt, f32x4 (&acc)[4][4]) const {
-    if (KT <= 2 && CO <= 2 && nrt == 4) {
-      forward_full(acc);
-      return;
-    }
-    const int t_ = tid(), lane = t_ & 63, w = t_ >> 6, li = lane & 15, q = lane >> 4;
-    const int nut = y.HP / 16, ldw = y.ldw;
-    const float* s = f(y.o_xs);
-    const float* w1 = f(y.o_w1);
-    constexpr bool c2 = CO >= 2, c4 = CO >= 4;
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) acc[i][r] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kk = 0; kk < KT; kk++) {
-      f32x4 a[4], b[4];
-#pragma unroll
-      for (int r = 0; r < 4; r++)
-        if (r < nrt) a[r] = *(const f32x4*)(s + (r * 16 + li) * ldw + kk * 16 + 4 * q);
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-        if (w + 4 * i < nut) b[i] = *(const f32x4*)(w1 + ((w + 4 * i) * 16 + li) * ldw + kk * 16 + 4 * q);
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-        if (w + 4 * i < nut) {
-#pragma unroll
-          for (int r = 0; r < 4; r++)
-            if (r < nrt) {
-#pragma unroll
-              for (int e = 0; e < 4; e++)
-                acc[i][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r][e], b[i][e], acc[i][r], 0, 0, 0);
-            }
-        }
-    }
-    // ReLU, and the output layer restricted to this wave's units: lane (unit li, rows 4q..4q+3)
-    f32x4 w2r[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-      w2r[i] = w + 4 * i < nut ? *(const f32x4*)(f(y.o_w2) + ((w + 4 * i) * 16 + li) * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
-    float* zp = f(y.o_zp) + w * SM_RC * 4;
-#pragma unroll
-    for (int r = 0; r < 4; r++)
-      if (r < nrt) {
-        f32x4 pz[4];  // [row 4q+e][output]
-#pragma unroll
-        for (int e = 0; e < 4; e++) pz[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-          if (w + 4 * i < nut) {
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-              const float av = fmaxf(acc[i][r][e], 0.f);
-              acc[i][r][e] = av;
-              pz[e][0] += av * w2r[i][0];
-              if (c2) pz[e][1] += av * w2r[i][1];
-              if (c4) {
-                pz[e][2] += av * w2r[i][2];
-                pz[e][3] += av * w2r[i][3];
-              }
-            }
-          }
+      for (int kk = 0; kk < KT; kk++)
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-          pz[e][0] = row16_sum(pz[e][0]);
-          if (c2) pz[e][1] = row16_sum(pz[e][1]);
-          if (c4) {
-            pz[e][2] = row16_sum(pz[e][2]);
-            pz[e][3] = row16_sum(pz[e][3]);
-          }
+          float x = w[i][kk][e];
+          fn(n++, x);
+          w[i][kk][e] = x;
         }
-        if (li == 0) {
 #pragma unroll
-          for (int e = 0; e < 4; e++) *(f32x4*)(zp + (r * 16 + 4 * q + e) * 4) = pz[e];
-        }
+      for (int cc = 0; cc <= CO; cc++) fs(n++, k++);
+    }
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++) fs(n++, k++);
+  }
+  // the register of position k of NMOM
+  __device__ __forceinline__ static float& small_param(Regs& R, int k) {
+    if (k >= NT * (1 + CO)) return R.ow[k - NT * (1 + CO)];
+    const int i = k / (1 + CO), r = k - i * (1 + CO);
+    return r == 0 ? R.bw[i] : R.w2[i][r - 1];
+  }
+  // the lane's share of its gradient, summed over the row of 16 lanes where those hold different rows
+  __device__ __forceinline__ static float small_grad(const Regs& R, int k) {
+    if (k >= NT * (1 + CO)) return sm_row16sum(R.og[k - NT * (1 + CO)]);
+    const int i = k / (1 + CO), r = k - i * (1 + CO);
+    return r == 0 ? R.bg[i] : R.g2[i][r - 1];
+  }
+  __device__ __forceinline__ float* mom(int k, int which) const {
+    return f(O_MOM) + ((wave() * NMOM + k) * 2 + which) * 16 + (threadIdx.x & 15);
+  }
+  // Packed parameters (or one of their moments) `st`, or the initial draw where st is null, into the wave's part of
+  // the slot.  A rolled loop: the registers are filled from the slot afterwards.
+  __device__ __forceinline__ void unpack(const float* st) const {
+    const int lane = threadIdx.x & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
+    const int d = y.d, h = y.h, c = y.c;
+    float* b = park();
+    constexpr int PER = 4 * KT + 1 + CO;
+#pragma unroll 1
+    for (int n = 0; n < NREG; n++) {
+      const int i = n / PER, r = n - i * PER, j = (w_ + i * W) * 16 + li;
+      int l = 0, ci = -1, e = 0;
+      bool isb = false;
+      if (i == NT) {  // output bias
+        l = 1;
+        isb = true;
+        e = n - NT * PER;
+        if (e < c) ci = y.cb[1] + e;
+      } else if (r < 4 * KT) {
+        const int k = (r >> 2) * 16 + 4 * q + (r & 3);
+        e = k * h + j;
+        if (j < h && k < d) ci = y.cw[0] + e;
+      } else if (r == 4 * KT) {
+        isb = true;
+        e = j;
+        if (j < h) ci = y.cb[0] + j;
+      } else {
+        l = 1;
+        const int cc = r - 4 * KT - 1;
+        e = j * c + cc;
+        if (j < h && cc < c) ci = y.cw[1] + e;
       }
+      float val = 0.f;
+      if (ci >= 0) val = st ? st[ci] : init_value(l, e, isb);
+      b[64 * n] = val;
+    }
+  }
+  __device__ __forceinline__ void load(Regs& R, const float* st) const {
+    const float* b = park();
+    auto take = [&](int n, float& x) { x = b[64 * n]; };
+    auto zero = [&](int, float& x) { x = 0.f; };
+    if (st) {
+      unpack(st + y.P);
+      each_param(R.m, take, [&](int n, int k) { *mom(k, 0) = b[64 * n]; });
+      unpack(st + 2 * y.P);
+      each_param(R.v, take, [&](int n, int k) { *mom(k, 1) = b[64 * n]; });
+    } else {
+      each_param(R.m, zero, [&](int, int k) { *mom(k, 0) = 0.f; });
+      each_param(R.v, zero, [&](int, int k) { *mom(k, 1) = 0.f; });
+    }
+    unpack(st);
+    restore_best(R);
+  }
+  // Keep the current parameters aside / take the kept ones back: every wave its own, no barrier.
+  __device__ __forceinline__ void keep_best(Regs& R) const {
+    float* b = park();
+    each_param(R.w, [&](int n, float& x) { b[64 * n] = x; }, [&](int n, int k) { b[64 * n] = small_param(R, k); });
+  }
+  __device__ __forceinline__ void restore_best(Regs& R) const {
+    const float* b = park();
+    each_param(R.w, [&](int n, float& x) { x = b[64 * n]; }, [&](int n, int k) { small_param(R, k) = b[64 * n]; });
+    // waited for here: the loop's own waits would otherwise have to allow for these loads, at the price of the input
+    // values that are meant to stay in flight
+    __builtin_amdgcn_s_waitcnt(0);
+  }
+  __device__ __forceinline__ static void zero_grad(Regs& R) {
+#pragma unroll
+    for (int i = 0; i < NT; i++) {
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++) R.g[i][kk] = f32x4{0.f, 0.f, 0.f, 0.f};
+      R.bg[i] = 0.f;
+#pragma unroll
+      for (int cc = 0; cc < CO; cc++) R.g2[i][cc] = 0.f;
+    }
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++) R.og[cc] = 0.f;
   }
 
-  // ---- phase 2a: outputs, loss and output delta of all 64 rows (lane = row), per wave ----
-  template <bool TRAIN>
-  __device__ __forceinline__ void outputs(int par, int rows, float inv_mb, double& lsum, double& hits, f32x4& gb2) const {
-    const int t_ = tid(), lane = t_ & 63, w = t_ >> 6, c = CO <= 2 ? CO : y.c;
-    const float* zp = f(y.o_zp);
-    const f32x4 b2 = *(const f32x4*)(f(y.o_w2) + y.HP * 4);
-    float z0 = b2[0], z1 = b2[1], z2 = b2[2], z3 = b2[3];
-#pragma unroll
-    for (int ww = 0; ww < 4; ww++) {
-      const f32x4 pv = *(const f32x4*)(zp + (ww * SM_RC + lane) * 4);
-      z0 += pv[0];
-      z1 += pv[1];
-      z2 += pv[2];
-      z3 += pv[3];
+  // ---- rows and inputs ------------------------------------------------------
+  // The epoch's rows in visiting order -> ep.  The permutation network's round function sees the round and one half
+  // of the position only, so its 4 x 2^hb values are tabled first (each wave its own copy): a network evaluation is
+  // four LDS reads instead of twelve 64-bit multiplies.  Small data sets table the whole network from it, so that
+  // the walk back into the list is one read per hop; a lane whose position has landed starts its next one.
+  __device__ __forceinline__ void build_epoch(uint64_t ke) const {
+    const int t_ = tid(), lane = t_ & 63;
+    uint16_t* ep = u16(o_ep);
+    const uint16_t* sl = u16(o_sl);
+    if (n_fit <= 1) {
+      __syncthreads();
+      if (t_ < n_fit) ep[t_] = sl[0];
+      return;
     }
-    const float z[4] = {z0, z1, z2, z3};
-    const float yv = ys(par)[lane];
-    f32x4 dl = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (lane < rows) {
-      double l = 0.0;
-      double hit = 0.0;  // a correct prediction, or the absolute error
-      if (P.n_classes >= 2) {
+    const PermDomain dm = perm_domain((uint32_t)n_fit);
+    const int half = 1 << dm.hb;
+    uint16_t* ft = u16(y.o_ft) + wave() * (4 * half);
+    for (int i = lane; i < 4 * half; i += 64)
+      ft[i] = (uint16_t)((uint32_t)key_fold(ke, ((uint64_t)(i >> dm.hb) << 32) | ((uint32_t)i & dm.mask)) & dm.mask);
+    __syncthreads();  // nobody reads the last epoch's order, or the network, any more
+    auto network = [&](uint32_t x) {
+      uint32_t Lh = x >> dm.hb, Rh = x & dm.mask;
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const uint32_t t = Lh ^ ft[(r << dm.hb) + Rh];
+        Lh = Rh;
+        Rh = t;
+      }
+      return (Lh << dm.hb) | Rh;
+    };
+    int p = t_;
+    if (y.netted) {
+      uint16_t* net = u16(y.o_net);
+      for (int x = t_; x < half * half; x += 4 * NTHR) {  // four evaluations in flight
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) v[u] = network((uint32_t)(x + u * NTHR) & (uint32_t)(half * half - 1));
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+          if (x + u * NTHR < half * half) net[x + u * NTHR] = (uint16_t)v[u];
+      }
+      __syncthreads();
+      // two positions of a lane walk side by side
+      for (; p < n_fit; p += 2 * NTHR) {
+        const int p2 = p + NTHR < n_fit ? p + NTHR : p;
+        uint32_t x = net[p], z = net[p2];
+        while (x >= (uint32_t)n_fit || z >= (uint32_t)n_fit) {
+          const uint32_t nx = net[x], nz = net[z];
+          x = x >= (uint32_t)n_fit ? nx : x;
+          z = z >= (uint32_t)n_fit ? nz : z;
+        }
+        const uint16_t rx = sl[x], rz = sl[z];
+        ep[p] = rx;
+        ep[p2] = rz;
+      }
+    } else {
+      uint32_t x = (uint32_t)p;
+      while (p < n_fit) {
+        x = network(x);
+        if (x < (uint32_t)n_fit) {
+          ep[p] = sl[x];
+          p += NTHR;
+          x = (uint32_t)p;
+        }
+      }
+    }
+  }
+  // Row ids of a chunk that is not tabled, into rowlist(par) by the first 64 threads.
+  __device__ __forceinline__ void park_rows(int chunk, int at, int e, int par, const int32_t* tr, const int32_t* va,
+                                            const RowSplit& sp, uint64_t km) const {
+    const int r = threadIdx.x;
+    if (r >= SM_RC) return;
+    int row = -1;
+    if (r < (chunk & SC_ROWS)) {
+      if (sc_mode(chunk) == ROWS_PLAIN)
+        row = va[at + r];
+      else
+        row = tr[row_index(sp, sc_mode(chunk), key_epoch(km, e), (uint32_t)(at + r))];
+    }
+    rowlist(par)[r] = row;
+  }
+  // The chunk's input values (and label) requested into registers; `at`: its first row's position in the epoch's
+  // order, or in the list being scored.  Straight-line code: past the chunk's rows and the input's columns the last
+  // valid element is requested again, and commit() puts zeros there.
+  __device__ __forceinline__ void fetch(int chunk, int at, int par, float (&xr)[NX], float& yv) const {
+    const int t_ = tid(), k = min(t_ % KS, d - 1), r0 = t_ / KS;
+    const int last = (chunk & SC_ROWS) - 1, mode = sc_mode(chunk);
+    int row[NX], yrow;
+    if (tabled && mode != ROWS_PLAIN) {
+      const uint16_t* t16 = (mode == ROWS_EPOCH ? u16(o_ep) : u16(o_sl) + n_fit) + at;
+#pragma unroll
+      for (int i = 0; i < NX; i++) row[i] = t16[min(r0 + i * RSTEP, last)];
+      yrow = t16[min(t_ & 63, last)];
+    } else {
+      const int32_t* t32 = rowlist(par);
+#pragma unroll
+      for (int i = 0; i < NX; i++) row[i] = t32[min(r0 + i * RSTEP, last)];
+      yrow = t32[min(t_ & 63, last)];
+    }
+#pragma unroll
+    for (int i = 0; i < NX; i++) xr[i] = X[row[i] * d + k];  // n*d < 2^31 (checked by the host)
+    yv = __int_as_float(Y[yrow]);  // class id or target: 32 bits either way
+  }
+  // registers -> input tile and labels of buffer b
+  __device__ __forceinline__ void commit(int chunk, int b, const float (&xr)[NX], float yv) const {
+    float* s = xs(b);
+    const int t_ = tid(), k = t_ % KS, r0 = t_ / KS, rows = chunk & SC_ROWS;
+    if (KS == K0 || k < K0) {
+#pragma unroll
+      for (int i = 0; i < NX; i++) s[(r0 + i * RSTEP) * LDW + k] = r0 + i * RSTEP < rows && k < d ? xr[i] : 0.f;
+    }
+    if (t_ < SM_RC) ys(b)[t_] = yv;
+  }
+
+  // ---- hidden layer forward; the wave's share of the outputs -> zp ----------------
+  // One row tile: products of all the wave's tiles in turn (independent accumulators), ReLU, output-layer share.
+  // ALL: the wave's last tile exists.
+  template <bool ALL>
+  __device__ __forceinline__ void forward_tile(const Regs& R, const float* s, int r, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
+    const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
+    const float* a_ = s + (r * 16 + li) * LDW + 4 * q;
+    f32x4 a[KT];
+#pragma unroll
+    for (int kk = 0; kk < KT; kk++) a[kk] = *(const f32x4*)(a_ + kk * 16);
+#pragma unroll
+    for (int i = 0; i < NT; i++) acc[i][r] = f32x4{R.bw[i], R.bw[i], R.bw[i], R.bw[i]};
+#pragma unroll
+    for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+#pragma unroll
+        for (int i = 0; i < NT; i++)
+          if (i + 1 < NT || ALL) acc[i][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], R.w[i][kk][e], acc[i][r], 0, 0, 0);
+      }
+    float p[CO][4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+#pragma unroll
+      for (int i = 0; i < NT; i++) {
+        const float av = fmaxf(acc[i][r][e], 0.f);
+        acc[i][r][e] = av;
+#pragma unroll
+        for (int cc = 0; cc < CO; cc++) p[cc][e] = i == 0 ? av * R.w2[0][cc] : p[cc][e] + av * R.w2[i][cc];
+      }
+    }
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++) v[cc][r] = sm_fold_quad(p[cc], li & 1, li & 2);
+  }
+  template <bool ALL, int N>
+  __device__ __forceinline__ void forward_tiles(const Regs& R, const float* s, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      if (r < N) {
+        forward_tile<ALL>(R, s, r, acc, v);
+      } else {
+#pragma unroll
+        for (int cc = 0; cc < CO; cc++) v[cc][r] = 0.f;
+      }
+    }
+  }
+  template <bool ALL>
+  __device__ __forceinline__ void forward_chunk(const Regs& R, const float* s, int nrt, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
+    if (nrt == 4)
+      forward_tiles<ALL, 4>(R, s, acc, v);
+    else if (nrt == 3)
+      forward_tiles<ALL, 3>(R, s, acc, v);
+    else if (nrt == 2)
+      forward_tiles<ALL, 2>(R, s, acc, v);
+    else
+      forward_tiles<ALL, 1>(R, s, acc, v);
+  }
+  __device__ __forceinline__ void forward(const Regs& R, int b, int par, int nrt, f32x4 (&acc)[NT][4]) const {
+    const int w_ = wave();
+    float v[CO][4];
+    if (has(NT - 1, w_))
+      forward_chunk<true>(R, xs(b), nrt, acc, v);
+    else
+      forward_chunk<false>(R, xs(b), nrt, acc, v);
+    const int lane = tid() & 63, li = lane & 15;
+    float* zp = f(O_ZP) + (par * W + w_) * (CO * SM_RC) + lane;
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++) zp[cc * SM_RC] = sm_fold_row(v[cc], li & 4, li & 8);
+  }
+
+  // ---- outputs, loss and output delta of the chunk's rows; the same in every wave ----
+  __device__ __forceinline__ void outputs(Regs& R, int b, int par, int rows, bool train, float inv_mb, double& lsum, double& hits) const {
+    const int lane = tid() & 63, li = lane & 15, q = lane >> 4, c = CO <= 2 ? CO : y.c;
+    const int row = (li >> 2) * 16 + 4 * q + (li & 3);  // the row the folding tree left in this lane
+    const float* zp = f(O_ZP) + par * W * (CO * SM_RC) + lane;
+    float z[CO];
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++) z[cc] = R.ow[cc];
+#pragma unroll
+    for (int ww = 0; ww < W; ww++) {
+#pragma unroll
+      for (int cc = 0; cc < CO; cc++) z[cc] += zp[(ww * CO + cc) * SM_RC];
+    }
+    const float yv = ys(b)[row];
+    float dl[CO];
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++) dl[cc] = 0.f;
+    if (row < rows) {
+      if (n_classes >= 2) {
         const int yr = __float_as_int(yv);
         float mx = z[0], zy = z[0];
         int best = 0;
@@ -414,441 +573,462 @@ struct Small {
             }
             zy = cc == yr ? z[cc] : zy;
           }
-        float se = 0.f;
-#pragma unroll
-        for (int cc = 0; cc < CO; cc++)
-          if (cc < c) se += expf(z[cc] - mx);
-        const float lse = mx + logf(se);
-        l = (double)(lse - zy);
-        hit = best == yr ? 1.0 : 0.0;
-        if (TRAIN) {
-#pragma unroll
-          for (int cc = 0; cc < CO; cc++)
-            if (cc < c) dl[cc] = (expf(z[cc] - lse) - (cc == yr ? 1.f : 0.f)) * inv_mb;
-        }
-      } else if (P.n_classes == 1) {
-        // one logit, labels 0/1: log(1 + e^z) - y z, delta (sigmoid(z) - y)/m
-        const int yr = __float_as_int(yv);
-        const float zz = z[0];
-        l = (double)(fmaxf(zz, 0.f) + log1pf(expf(-fabsf(zz))) - (yr ? zz : 0.f));
-        hit = (zz > 0.f) == (yr != 0) ? 1.0 : 0.0;
-        if (TRAIN) dl[0] = (1.f / (1.f + expf(-zz)) - (float)yr) * inv_mb;
-      } else {
-        const float e0 = z[0] - yv;
-        l = TRAIN ? 0.5 * (double)e0 * (double)e0 : (double)e0 * (double)e0;
-        hit = (double)fabsf(e0);
-        if (TRAIN) dl[0] = e0 * inv_mb;
-      }
-      if (w == 0) {  // every wave computes the same values; one of them keeps the statistics
-        lsum += l;
-        hits += hit;
-      }
-    }
-    if (TRAIN) {
-      *(f32x4*)(f(y.o_d2) + (w * SM_RC + lane) * 4) = dl;
-      if (w == 0) {
-#pragma unroll
-        for (int cc = 0; cc < CO; cc++) gb2[cc] += dl[cc];
-      }
-      // the wave reads back what its other lanes wrote: LDS executes a wave's accesses in order
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    }
-  }
-
-  // ---- phase 2b: hidden deltas in the accumulators, output-layer gradient, hidden weight gradient ----
-  __device__ __forceinline__ void backward(int par, int nrt, f32x4 (&acc)[4][4], f32x4 (&accg)[4][KT], f32x4 (&g2p)[4]) const {
-    const int t_ = tid(), lane = t_ & 63, w = t_ >> 6, li = lane & 15, q = lane >> 4;
-    const int nut = y.HP / 16, lda = y.lda;
-    const float* t = xt(par);
-    const float* d2 = f(y.o_d2) + w * SM_RC * 4;
-    constexpr bool c2 = CO >= 2, c4 = CO >= 4;
-    f32x4 w2r[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-      w2r[i] = w + 4 * i < nut ? *(const f32x4*)(f(y.o_w2) + ((w + 4 * i) * 16 + li) * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int r = 0; r < 4; r++)
-      if (r < nrt) {
-        f32x4 dv[4], a[KT];
-#pragma unroll
-        for (int e = 0; e < 4; e++) dv[e] = *(const f32x4*)(d2 + (r * 16 + 4 * q + e) * 4);
-#pragma unroll
-        for (int m = 0; m < KT; m++) a[m] = *(const f32x4*)(t + (m * 16 + li) * lda + r * 16 + 4 * q);
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-          if (w + 4 * i < nut) {
-            f32x4 dh;
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-              const float av = acc[i][r][e];
-              float s = dv[e][0] * w2r[i][0];
-              g2p[i][0] += av * dv[e][0];
-              if (c2) {
-                s += dv[e][1] * w2r[i][1];
-                g2p[i][1] += av * dv[e][1];
-              }
-              if (c4) {
-                s += dv[e][2] * w2r[i][2] + dv[e][3] * w2r[i][3];
-                g2p[i][2] += av * dv[e][2];
-                g2p[i][3] += av * dv[e][3];
-              }
-              dh[e] = av > 0.f ? s : 0.f;
-            }
-#pragma unroll
-            for (int m = 0; m < KT; m++) {
-#pragma unroll
-              for (int e = 0; e < 4; e++)
-                accg[i][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m][e], dh[e], accg[i][m], 0, 0, 0);
-            }
-          }
-      }
-  }
-
-  // ---- optimizer step: gradients (and hidden moments) in registers, weights in LDS ----
-  // Hidden-layer update of the wave's tiles.  ADAM and TRACED are compile-time so that the element loop is
-  // straight-line code: the L2 term and the pad columns are handled by selects, not branches.
-  template <bool ADAM, bool TRACED>
-  __device__ __forceinline__ void update_hidden(const OptC& oc, const f32x4 (&accg)[4][KT], float* rec) const {
-    const int t_ = tid(), lane = t_ & 63, w = t_ >> 6, li = lane & 15, q = lane >> 4;
-    const int nut = y.HP / 16, ldw = y.ldw, d = y.d, h = y.h;
-    float* w1 = f(y.o_w1);
-    float* m1 = m1g();
-    float* v1 = v1g();
-    OptC c = oc;
-    c.adam = ADAM;
-    // all moment loads of the wave first, so that their latency overlaps
-    f32x4 m1r[4][KT], v1r[4][KT];
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-      for (int m = 0; m < KT; m++) {
-        const int j = (w + 4 * i) * 16 + li, k0 = m * 16 + 4 * q;
-        m1r[i][m] = v1r[i][m] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (w + 4 * i < nut && j < h && k0 <= d) {
-          m1r[i][m] = *(const f32x4*)(m1 + j * ldw + k0);
-          if (ADAM) v1r[i][m] = *(const f32x4*)(v1 + j * ldw + k0);
-        }
-      }
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-      if (w + 4 * i < nut) {
-        const int j = (w + 4 * i) * 16 + li;
-#pragma unroll
-        for (int m = 0; m < KT; m++) {
-          const int k0 = m * 16 + 4 * q;
-          if (j < h && k0 <= d) {
-            const int o = j * ldw + k0;
-            f32x4 wv = *(const f32x4*)(w1 + o);
-            f32x4 mv = m1r[i][m], vv = v1r[i][m], gv;
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-              const int k = k0 + e;
-              float wr = wv[e], mr = mv[e], vr = vv[e];
-              gv[e] = accg[i][m][e] + (k < d ? c.am * wr : 0.f);  // column d is the bias: no penalty
-              opt_update(c, gv[e], wr, mr, vr);
-              const bool real = k <= d;
-              wv[e] = real ? wr : wv[e];
-              mv[e] = real ? mr : mv[e];
-              vv[e] = real ? vr : vv[e];
-            }
-            *(f32x4*)(w1 + o) = wv;
-            *(f32x4*)(m1 + o) = mv;
-            if (ADAM) *(f32x4*)(v1 + o) = vv;
-            if (TRACED) {
-#pragma unroll
-              for (int e = 0; e < 4; e++)
-                if (k0 + e <= d) {
-                  const int ci = ci_hidden(j, k0 + e);
-                  rec[1 + ci] = gv[e];
-                  rec[1 + y.P + ci] = wv[e];
-                }
-            }
-          }
-        }
-      }
-  }
-
-  __device__ __forceinline__ void update(const OptC& oc, const f32x4 (&accg)[4][KT], f32x4 (&g2p)[4], f32x4 gb2, float* rec) const {
-    const int t_ = tid(), lane = t_ & 63, w = t_ >> 6, li = lane & 15, q = lane >> 4;
-    const int h = y.h, c = CO <= 2 ? CO : y.c;
-    if (rec) {
-      if (oc.adam)
-        update_hidden<true, true>(oc, accg, rec);
-      else
-        update_hidden<false, true>(oc, accg, rec);
-    } else {
-      if (oc.adam)
-        update_hidden<true, false>(oc, accg, rec);
-      else
-        update_hidden<false, false>(oc, accg, rec);
-    }
-    // output layer: finish the sums over the rows held by the four lane groups, lane group 0 updates
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-      for (int cc = 0; cc < CO; cc++) {
-        float v = g2p[i][cc];
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
-        g2p[i][cc] = v;
-      }
-    if (w == 0) {
-#pragma unroll
-      for (int cc = 0; cc < CO; cc++) {
-        float v = gb2[cc];
-#pragma unroll
-        for (int s = 1; s < 64; s <<= 1) v += __shfl_xor(v, s);
-        gb2[cc] = v;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 5; i++) {
-      // i < 4: unit (w+4i)*16+li by lane group 0; i == 4: the bias row by lane 0 of wave 0
-      const bool isb = i == 4;
-      const int u = isb ? y.HP : (w + 4 * (i & 3)) * 16 + li;
-      const bool mine = isb ? (w == 0 && lane == 0) : (q == 0 && u < h);
-      if (mine) {
-        const f32x4 g = isb ? gb2 : g2p[i & 3];
-        float* w2 = f(y.o_w2) + u * 4;
-        float* m2 = f(y.o_m2) + u * 4;
-        float* v2 = f(y.o_v2) + u * 4;
-        f32x4 wv = *(const f32x4*)w2, mv = *(const f32x4*)m2, vv = *(const f32x4*)v2;
+        float ex[CO], se = 0.f;
 #pragma unroll
         for (int cc = 0; cc < CO; cc++)
           if (cc < c) {
-            float wr = wv[cc], mr = mv[cc], vr = vv[cc];
-            const float gg = isb ? g[cc] : g[cc] + oc.am * wr;
-            opt_update(oc, gg, wr, mr, vr);
-            if (rec) {
-              const int ci = isb ? y.cb[1] + cc : y.cw[1] + u * c + cc;
-              rec[1 + ci] = gg;
-              rec[1 + y.P + ci] = wr;
-            }
-            wv[cc] = wr;
-            mv[cc] = mr;
-            vv[cc] = vr;
+            ex[cc] = expf(z[cc] - mx);
+            se += ex[cc];
           }
-        *(f32x4*)w2 = wv;
-        *(f32x4*)m2 = mv;
-        *(f32x4*)v2 = vv;
+        lsum += (double)(mx + logf(se) - zy);
+        hits += best == yr ? 1.0 : 0.0;
+        const float inv = 1.f / se;
+#pragma unroll
+        for (int cc = 0; cc < CO; cc++)
+          if (cc < c) dl[cc] = (ex[cc] * inv - (cc == yr ? 1.f : 0.f)) * inv_mb;
+      } else if (n_classes == 1) {
+        // one logit, labels 0/1: log(1 + e^z) - y z, delta (sigmoid(z) - y)/m
+        const int yr = __float_as_int(yv);
+        const float zz = z[0];
+        lsum += (double)(fmaxf(zz, 0.f) + log1pf(expf(-fabsf(zz))) - (yr ? zz : 0.f));
+        hits += (zz > 0.f) == (yr != 0) ? 1.0 : 0.0;
+        dl[0] = (1.f / (1.f + expf(-zz)) - (float)yr) * inv_mb;
+      } else {
+        const float e0 = z[0] - yv;
+        lsum += train ? 0.5 * (double)e0 * (double)e0 : (double)e0 * (double)e0;
+        hits += (double)fabsf(e0);
+        dl[0] = e0 * inv_mb;
       }
+    }
+    if (train) {
+      float* d2 = f(O_D2) + lane;  // every wave writes the same values, and reads back only what it wrote itself
+#pragma unroll
+      for (int cc = 0; cc < CO; cc++) {
+        d2[cc * SM_RC] = dl[cc];
+        R.og[cc] += dl[cc];
+      }
+      __builtin_amdgcn_wave_barrier();
     }
   }
 
-  __device__ __forceinline__ double penalty_sum() const {
-    double s = 0.0;
-    const float* w1 = f(y.o_w1);
-    const float* w2 = f(y.o_w2);
-    for (int i = threadIdx.x; i < y.d * y.h; i += blockDim.x) {
-      const float w = w1[(i / y.d) * y.ldw + i % y.d];
-      s += (double)w * (double)w;
+  // ---- backward: hidden deltas, output-layer gradient, hidden weight gradient -------
+  template <bool ALL>
+  __device__ __forceinline__ void backward_tile(Regs& R, const float* s, int r, const f32x4 (&acc)[NT][4]) const {
+    const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
+    const float* d2 = f(O_D2) + q * 16 + r * 4;
+    const float* a_ = s + (r * 16 + 4 * q) * LDW + li;
+    f32x4 dv[CO];
+    float a[KT][4];
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++) dv[cc] = *(const f32x4*)(d2 + cc * SM_RC);
+#pragma unroll
+    for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) a[kk][e] = a_[e * LDW + kk * 16];
+    f32x4 dh[NT];
+#pragma unroll
+    for (int i = 0; i < NT; i++)
+      if (i + 1 < NT || ALL) {
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const float av = acc[i][r][e];
+          float sum = dv[0][e] * R.w2[i][0];
+          R.g2[i][0] += av * dv[0][e];
+#pragma unroll
+          for (int cc = 1; cc < CO; cc++) {
+            sum += dv[cc][e] * R.w2[i][cc];
+            R.g2[i][cc] += av * dv[cc][e];
+          }
+          const float x = av > 0.f ? sum : 0.f;
+          dh[i][e] = x;
+          R.bg[i] += x;
+        }
+      }
+#pragma unroll
+    for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+#pragma unroll
+        for (int i = 0; i < NT; i++)
+          if (i + 1 < NT || ALL) R.g[i][kk] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], dh[i][e], R.g[i][kk], 0, 0, 0);
+      }
+  }
+  template <bool ALL, int N>
+  __device__ __forceinline__ void backward_tiles(Regs& R, const float* s, const f32x4 (&acc)[NT][4]) const {
+#pragma unroll
+    for (int r = 0; r < N; r++) backward_tile<ALL>(R, s, r, acc);
+  }
+  template <bool ALL>
+  __device__ __forceinline__ void backward_chunk(Regs& R, const float* s, int nrt, const f32x4 (&acc)[NT][4]) const {
+    if (nrt == 4)
+      backward_tiles<ALL, 4>(R, s, acc);
+    else if (nrt == 3)
+      backward_tiles<ALL, 3>(R, s, acc);
+    else if (nrt == 2)
+      backward_tiles<ALL, 2>(R, s, acc);
+    else
+      backward_tiles<ALL, 1>(R, s, acc);
+  }
+  __device__ __forceinline__ void backward(Regs& R, int b, int nrt, const f32x4 (&acc)[NT][4]) const {
+    if (has(NT - 1, wave()))
+      backward_chunk<true>(R, xs(b), nrt, acc);
+    else
+      backward_chunk<false>(R, xs(b), nrt, acc);
+  }
+
+  // ---- optimizer step -------------------------------------------------------------
+  // Pad elements need no mask: their inputs, deltas and weights are zero, and so is their step (0 / eps).  Only an
+  // eps of zero would make it 0 / 0; that case clears them afterwards.
+  template <bool ADAM>
+  __device__ __forceinline__ void update(Regs& R, const OptC& oc) const {
+    const int w_ = wave();
+    OptC o = oc;
+    o.adam = ADAM;
+#pragma unroll
+    for (int i = 0; i < NT; i++)
+      if (has(i, w_)) {
+#pragma unroll
+        for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            float wr = R.w[i][kk][e], mr = R.m[i][kk][e], vr = R.v[i][kk][e];
+            opt_update(o, R.g[i][kk][e] + o.am * wr, wr, mr, vr);
+            R.w[i][kk][e] = wr;
+            R.m[i][kk][e] = mr;
+            R.v[i][kk][e] = vr;
+          }
+      }
+    // everything else: sums over the row groups, the moments from LDS, all requested before the first is needed
+    float g[NMOM], m[NMOM], v[NMOM];
+#pragma unroll
+    for (int k = 0; k < NMOM; k++) {
+      m[k] = *mom(k, 0);
+      v[k] = ADAM ? *mom(k, 1) : 0.f;
+      g[k] = small_grad(R, k);
     }
-    for (int i = threadIdx.x; i < y.h * y.c; i += blockDim.x) {
-      const float w = w2[(i / y.c) * 4 + i % y.c];
-      s += (double)w * (double)w;
+#pragma unroll
+    for (int k = 0; k < NMOM; k++) g[k] += __shfl_xor(g[k], 16);
+#pragma unroll
+    for (int k = 0; k < NMOM; k++) g[k] += __shfl_xor(g[k], 32);
+#pragma unroll
+    for (int k = 0; k < NMOM; k++) {
+      float& w = small_param(R, k);
+      const bool weight = k < NT * (1 + CO) && k % (1 + CO) != 0;  // no penalty on the biases
+      opt_update(o, weight ? g[k] + o.am * w : g[k], w, m[k], v[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < NMOM; k++) {
+      *mom(k, 0) = m[k];
+      if (ADAM) *mom(k, 1) = v[k];
+    }
+    if (ADAM && o.eps == 0.f) clear_pads(R);
+  }
+  // A traced step's gradient (before the update: GRAD) or new parameters into out[P].
+  template <bool GRAD>
+  __device__ __forceinline__ void record(const Regs& R, float am, float* out) const {
+    const int t_ = tid(), lane = t_ & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
+    const int d = y.d, h = y.h, c = CO <= 2 ? CO : y.c;
+#pragma unroll
+    for (int i = 0; i < NT; i++) {
+      const int j = (w_ + i * W) * 16 + li;
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const int k = kk * 16 + 4 * q + e;
+          if (j < h && k < d) out[y.cw[0] + k * h + j] = GRAD ? R.g[i][kk][e] + am * R.w[i][kk][e] : R.w[i][kk][e];
+        }
+      const float b = GRAD ? sm_rowsum(R.bg[i]) : R.bw[i];
+      if (j < h && q == 0) out[y.cb[0] + j] = b;
+#pragma unroll
+      for (int cc = 0; cc < CO; cc++) {
+        const float x = GRAD ? sm_rowsum(R.g2[i][cc]) + am * R.w2[i][cc] : R.w2[i][cc];
+        if (j < h && q == 0 && cc < c) out[y.cw[1] + j * c + cc] = x;
+      }
+    }
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++) {
+      const float x = GRAD ? sm_rowsum(sm_row16sum(R.og[cc])) : R.ow[cc];
+      if (t_ == 0 && cc < c) out[y.cb[1] + cc] = x;
+    }
+  }
+  __device__ __forceinline__ void clear_pads(Regs& R) const {
+    const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4, c = CO <= 2 ? CO : y.c;
+#pragma unroll
+    for (int i = 0; i < NT; i++) {
+      const bool unit = (w_ + i * W) * 16 + li < y.h;
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+          if (!unit || kk * 16 + 4 * q + e >= y.d) R.w[i][kk][e] = R.m[i][kk][e] = R.v[i][kk][e] = 0.f;
+#pragma unroll
+      for (int r = 0; r <= CO; r++)
+        if (!unit || r > c) {
+          const int k = i * (1 + CO) + r;
+          small_param(R, k) = 0.f;
+          *mom(k, 0) = *mom(k, 1) = 0.f;
+        }
+    }
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++)
+      if (cc >= c) {
+        const int k = NT * (1 + CO) + cc;
+        R.ow[cc] = 0.f;
+        *mom(k, 0) = *mom(k, 1) = 0.f;
+      }
+  }
+
+  // squared weights, for a traced step's loss
+  __device__ __forceinline__ double penalty_sum(const Regs& R) const {
+    const int lane = threadIdx.x & 63, q = lane >> 4;
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < NT; i++) {
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) s += (double)R.w[i][kk][e] * (double)R.w[i][kk][e];
+      if (q == 0) {
+#pragma unroll
+        for (int cc = 0; cc < CO; cc++) s += (double)R.w2[i][cc] * (double)R.w2[i][cc];
+      }
     }
     return block_sum(s, red);
   }
 
-  __device__ __forceinline__ void run() const {
+  __device__ __forceinline__ void run() {
     const int f_ = it.fold, fl = it.fold - P.fold_base;  // fl: which row list
-    const int n_tr = P.counts[2 * fl], n_va = P.counts[2 * fl + 1];
+    const int n_tr = uniform(P.counts[2 * fl]), n_va = uniform(P.counts[2 * fl + 1]);
     const int32_t* tr = P.train_idx + (int64_t)fl * P.n;
     const int32_t* va = P.val_idx + (int64_t)fl * P.n;
     const uint64_t km = key_model(it.seed, f_);
     const RowSplit sp = row_split(km, it.patience, it.val_frac, n_tr);
-    const int n_fit = sp.n_fit;
-    const int bs = eff_batch(it.batch_size, n_fit);
-    const int steps = n_fit > 0 ? (n_fit + bs - 1) / bs : 0;
+    X = pin((const GlobalF32*)P.X);
+    Y = pin((const GlobalI32*)P.y);
+    d = pin(y.d);
+    n_fit = pin(uniform(sp.n_fit));
+    n_classes = pin(P.n_classes);
+    o_sl = pin((int)y.o_sl);
+    o_ep = pin((int)y.o_ep);
+    tabled = pin(y.tabled);
+    nut = pin(y.nut);
+    const int bs = pin(uniform(eff_batch(it.batch_size, n_fit)));
+    const int steps = pin(uniform(n_fit > 0 ? (n_fit + bs - 1) / bs : 0));
+    const int epochs = pin(it.epochs);
     const bool traced = P.trace_item == it.b * P.n_folds + fl;
-
-    // zero the weights and output-layer moments (pads must be zero), then the initial or given parameters
-    {
-      uint4* z = (uint4*)lds;
-      const uint32_t n16 = y.o_xs / 16;
-      for (uint32_t i = threadIdx.x; i < n16; i += blockDim.x) z[i] = uint4{0, 0, 0, 0};
-    }
-    __syncthreads();
-    {
-      uint4* z = (uint4*)slot;
-      const uint32_t n16 = 2 * y.HP * y.ldw * 4 / 16;
-      for (uint32_t i = threadIdx.x; i < n16; i += blockDim.x) z[i] = uint4{0, 0, 0, 0};
-    }
-    double b1t = 1.0, b2t = 1.0;
-    int64_t gstep = 0;
-    ChunkPos pos = {0, 0, 0};
     const bool resume = traced && P.state_in && steps > 0;
+    const bool watch = it.patience > 0 && steps > 0 && !resume;
+    const int n_hold = pin(uniform(watch ? sp.n_hold : 0));
+    const float mb_last = uniform((float)(n_fit - (steps - 1) * bs));
+    const float inv_full = uniform(1.f / (float)bs), inv_last = uniform(1.f / mb_last);
+    const float am_full = uniform(it.alpha / (float)bs), am_last = uniform(it.alpha / mb_last);
+
+    // ---- the schedule: training chunks, after each epoch the rows set aside, at the end the held fold ----
+    // Position of the chunk whose inputs are requested next: first row `at` in its order, step st of epoch e.
+    int e = 0, st = 0, at = 0;
+    auto step_rows = [&](int s) { return min(bs, n_fit - s * bs); };
+    auto training = [&]() {  // the chunk at (e, st, at)
+      const int in_step = at - st * bs, left = step_rows(st) - in_step;
+      int ch = (ROWS_EPOCH << 7) | min(SM_RC, left);
+      if (in_step == 0) ch |= SC_FIRST;
+      if (left <= SM_RC) ch |= SC_LAST;
+      if (st == 0) ch |= SC_EPOCH;
+      if (st + 1 == steps) ch |= SC_RAGGED;
+      if (st + 1 == steps && left <= SM_RC && watch && !n_hold) ch |= SC_DECIDE;
+      return ch;
+    };
+    auto list_chunk = [&](int mode, int count) {
+      int ch = (mode << 7) | min(SM_RC, count - at);
+      if (at == 0) ch |= SC_FIRST;
+      if (mode == ROWS_HELD && count - at <= SM_RC) ch |= SC_DECIDE;
+      return ch;
+    };
+    auto score_start = [&]() -> int {
+      at = 0;
+      return n_va > 0 ? list_chunk(ROWS_PLAIN, n_va) : (int)SC_END;
+    };
+    auto epoch_start = [&]() -> int {
+      at = st = 0;
+      return steps > 0 && e < epochs ? training() : score_start();
+    };
+    auto next = [&](int ch) -> int {
+      const int mode = sc_mode(ch);
+      at += ch & SC_ROWS;
+      if (mode == ROWS_EPOCH) {
+        if (ch & SC_LAST) st++;
+        if (st < steps) return training();
+        if (n_hold) {
+          at = 0;
+          return list_chunk(ROWS_HELD, n_hold);
+        }
+        e++;
+        return epoch_start();
+      }
+      if (mode == ROWS_HELD) {
+        if (at < n_hold) return list_chunk(ROWS_HELD, n_hold);
+        e++;
+        return epoch_start();
+      }
+      return mode == ROWS_PLAIN && at < n_va ? list_chunk(ROWS_PLAIN, n_va) : (int)SC_END;
+    };
+
+    Regs R;
+    int64_t gstep = 0;
+    int c2 = epoch_start();  // the chunk at the position above
     if (resume) {
       gstep = P.step_begin;
-      pos.e = (int)(gstep / steps);
-      pos.st = (int)(gstep % steps);
-      for (int64_t i = 0; i < gstep; i++) {  // beta^gstep by repeated products, as the free run builds it
-        b1t *= (double)it.beta1;
-        b2t *= (double)it.beta2;
-      }
+      e = (int)(gstep / steps);
+      st = (int)(gstep % steps);
+      at = st * bs;
+      c2 = e < epochs ? training() : score_start();
     }
-    __syncthreads();  // zeroed moments before a resumed state overwrites them
-    put_weights(resume ? P.state_in : nullptr);
-    __syncthreads();
+    load(R, resume ? P.state_in : nullptr);
 
     OptC oc;
-    oc.adam = it.solver == BBO_ADAM;
+    const int solver = pin(it.solver);
+    oc.adam = solver == BBO_ADAM;
     oc.nest = it.nesterov != 0;
-    oc.b1 = it.beta1;
-    oc.b2 = it.beta2;
-    oc.omb1 = 1.f - it.beta1;
-    oc.omb2 = 1.f - it.beta2;
-    oc.eps = it.eps;
-    oc.mu = it.momentum;
+    oc.b1 = pin(it.beta1);
+    oc.b2 = pin(it.beta2);
+    oc.omb1 = uniform(1.f - it.beta1);
+    oc.omb2 = uniform(1.f - it.beta2);
+    oc.eps = pin(it.eps);
+    oc.mu = pin(it.momentum);
     oc.lr = it.lr;
     oc.lr_t = it.lr;
+    oc.am = 0.f;
+    float lr_tab = 0.f;      // Adam: the step sizes of 64 steps, one per lane
+    int64_t lr_base = -64;   // ... the first of them
 
-    // ---- training: the chunks of all steps of all epochs, inputs fetched one chunk ahead ----
-    int epochs_lim = it.epochs;  // lowered when the plateau rule ends training
-    auto chunk_valid = [&](const ChunkPos& p) { return steps > 0 && p.e < epochs_lim; };
-    auto chunk_rows = [&](const ChunkPos& p) { return min(SM_RC, min(bs, n_fit - p.st * bs) - p.c0); };
-    auto chunk_next = [&](ChunkPos p) {
-      const int mb = min(bs, n_fit - p.st * bs);
-      p.c0 += SM_RC;
-      if (p.c0 >= mb) {
-        p.c0 = 0;
-        if (++p.st >= steps) {
-          p.st = 0;
-          p.e++;
-        }
-      }
-      return p;
-    };
-    auto chunk_row_id = [&](const ChunkPos& p) {
-      return fetch_row_id(tr, sp, ROWS_EPOCH, key_epoch(km, p.e), p.st * bs + p.c0, chunk_rows(p));
-    };
-    float xr[NX], yv = 0.f;
-    int par = 0;
-    if (chunk_valid(pos)) {
-      if (y.epoch_cap) {
-        build_epoch_table(tr, sp, key_epoch(km, pos.e));
-        __syncthreads();
-      }
-      park_row_id(0, chunk_row_id(pos));
+    if (tabled) {  // rows of the training list in the order of the early-stopping cut
+      uint16_t* sl = u16(y.o_sl);
+      for (int p = threadIdx.x; p < n_tr; p += blockDim.x)
+        sl[p] = (uint16_t)tr[sp.n_hold ? (int)perm_index(sp.ksplit, (uint32_t)n_tr, (uint32_t)p) : p];
       __syncthreads();
-      fetch_inputs(0, xr, yv);
     }
-    f32x4 acc[4][4], accg[4][KT], g2p[4];
-    f32x4 gb2 = f32x4{0.f, 0.f, 0.f, 0.f};
-    double lsum = 0.0, hits = 0.0, pen = 0.0, esum = 0.0;  // esum: the lane's share of the epoch's summed data loss
+    float xr[NX], yv = 0.f;
+#pragma unroll
+    for (int i = 0; i < NX; i++) xr[i] = 0.f;
+    int b = 0, par = 0;  // input buffer and exchange parity of the current chunk
+    int built = -1;      // the last epoch whose rows have been tabled
+    int c0 = SC_NONE, c1 = SC_NONE;  // the chunk being worked on; the one whose inputs are on their way in registers
+    int e_lr = e - 1;                // epoch of the step being worked on (set when one opens)
+    if (resume && st > 0) e_lr = e;
+    double lsum = 0.0, hits = 0.0;  // the lane's share of the summed data loss: of the epoch, or of a scoring pass
     float* rec = nullptr;
     Plateau plateau;
     bool have_best = false;
-    const bool watch = it.patience > 0 && !resume;
-    // Loss and second score (the thread's share) of `count` rows of a list under the current weights; uses
-    // the input tiles of parity 0 and the forward accumulators.
-    auto score_rows = [&](const int32_t* list, int mode, int count, double& ls, double& hs) {
-      for (int off = 0; off < count; off += SM_RC) {
-        const int rows = min(SM_RC, count - off);
-        park_row_id(0, fetch_row_id(list, sp, mode, 0, off, rows));
-        __syncthreads();
-        fetch_inputs(0, xr, yv);
-        commit_inputs(0, xr, yv);
-        __syncthreads();
-        forward((rows + 15) / 16, acc);
-        __syncthreads();
-        outputs<false>(0, rows, 0.f, ls, hs, gb2);
-        __syncthreads();
+    float inv_mb = inv_full;
+    for (int phase = 0; phase < 2; phase++) {  // training with its stopping rule; the score
+    if (phase == 1 && have_best) restore_best(R);  // the best epoch's model is the one scored
+    while ((c0 & SC_MODE) != SC_END && (phase == 1 || sc_mode(c0) != ROWS_PLAIN)) {
+      const bool train = sc_mode(c0) == ROWS_EPOCH, live = (c0 & SC_MODE) != SC_NONE;
+      const int bn = b == 2 ? 0 : b + 1, rows = c0 & SC_ROWS, nrt = (rows + 15) / 16;
+      if (sc_mode(c1) <= ROWS_PLAIN) commit(c1, bn, xr, yv);
+      // the rows of the chunk whose inputs are requested next: its epoch's table if it opens one, or a row list
+      if ((c2 & SC_MODE) != SC_END) {
+        if (!tabled || sc_mode(c2) == ROWS_PLAIN) {
+          park_rows(c2, at, e, par, tr, va, sp, km);
+        } else if (sc_mode(c2) == ROWS_EPOCH && e != built) {
+          build_epoch(key_epoch(km, e));
+          built = e;
+        }
       }
-    };
-    while (chunk_valid(pos)) {
-      const int mb = min(bs, n_fit - pos.st * bs);
-      const int rows = chunk_rows(pos), nrt = (rows + 15) / 16;
-      if (pos.c0 == 0) {  // first chunk of a step
-        oc.am = it.alpha / (float)mb;
-        if (!oc.adam) oc.lr = epoch_lr(it.lr, it.power_t, pos.e, n_fit);
-        if (oc.adam) {
-          b1t *= (double)it.beta1;
-          b2t *= (double)it.beta2;
-          oc.lr_t = (float)((double)it.lr * sqrt(1.0 - b2t) / (1.0 - b1t));
-        }
-        rec = nullptr;
-        if (traced && gstep >= P.step_begin && gstep < P.step_end)
-          rec = P.trace_out + (gstep - P.step_begin) * (1 + 2 * (int64_t)y.P);
-        if (rec) {
-          __syncthreads();  // the previous step's update, by every wave
-          pen = penalty_sum();
-        }
-        lsum = 0.0;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          g2p[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int m = 0; m < KT; m++) accg[i][m] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        gb2 = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-      commit_inputs(par, xr, yv);
-      const ChunkPos nxt = chunk_next(pos);
-      const bool more = chunk_valid(nxt);
-      if (more && nxt.e != pos.e && y.epoch_cap) {
-        // the next chunk opens an epoch: its row order replaces the table (this epoch's last rows are already read)
-        build_epoch_table(tr, sp, key_epoch(km, nxt.e));
-        __syncthreads();
-      }
-      int nrow = -1;
-      if (more) nrow = chunk_row_id(nxt);  // load in flight across the forward phase
-      __syncthreads();                     // inputs of this chunk (and last step's weights) visible
-      forward(nrt, acc);
-      if (more) park_row_id(par ^ 1, nrow);
-      __syncthreads();  // all four shares of the outputs, and the next chunk's row ids, visible
-      if (more) fetch_inputs(par ^ 1, xr, yv);  // in flight across the backward phase
-      outputs<true>(par, rows, 1.f / (float)mb, lsum, hits, gb2);
-      backward(par, nrt, acc, accg, g2p);
-      if (nxt.c0 == 0) {  // that was the last chunk of the step
-        __syncthreads();  // every wave is past its reads of the output bias
-        update(oc, accg, g2p, gb2, rec);
-        if (rec) {
-          const double data = block_sum(lsum, red) / (double)mb;
-          if (threadIdx.x == 0) rec[0] = (float)(data + 0.5 * (double)it.alpha * pen / (double)mb);
-        }
-        gstep++;
-        esum += lsum;
-        if (watch && nxt.e != pos.e) {  // that was the last step of the epoch
-          float watched;
-          if (sp.n_hold) {
-            // the loss of the rows set aside for early stopping, under the weights the epoch ends with; the
-            // pass takes over the input tiles, so the next chunk's rows and inputs are fetched again after it
-            __syncthreads();  // the update, by every wave
-            double hl = 0.0, hh = 0.0;
-            score_rows(tr, ROWS_HELD, sp.n_hold, hl, hh);
-            watched = (float)(block_sum(hl, red) / (double)sp.n_hold);
-            if (more) {
-              park_row_id(par ^ 1, chunk_row_id(nxt));
-              __syncthreads();
-              fetch_inputs(par ^ 1, xr, yv);
-            }
-          } else {
-            watched = (float)(block_sum(esum, red) / (double)n_fit);
+      if (c0 & SC_FIRST) {
+        if (train) {  // first chunk of a step
+          const bool last = c0 & SC_RAGGED;
+          oc.am = last ? am_last : am_full;
+          inv_mb = last ? inv_last : inv_full;
+          if (c0 & SC_EPOCH) {
+            e_lr++;
+            lsum = 0.0;
           }
-          if (plateau.stop_after(watched, it.tol, it.patience)) epochs_lim = pos.e + 1;
-          if (sp.n_hold && plateau.improved) {  // (the scoring pass ended with a barrier: the weights are at rest)
-            copy_best(true);
+          if (oc.adam) {
+            if (gstep >= lr_base + 64) {
+              // beta^t of the next 64 steps, a step per lane, by repeated squaring in double
+              lr_base = gstep;
+              float f1 = it.beta1, f2 = it.beta2;
+              asm volatile("" : "+s"(f1), "+s"(f2));  // converted here, not ahead of the loop
+              double q1 = (double)f1, q2 = (double)f2, b1t = 1.0, b2t = 1.0;
+#pragma unroll 1
+              for (uint64_t t = (uint64_t)(gstep + 1) + (threadIdx.x & 63); __any(t != 0); t >>= 1) {
+                b1t *= t & 1 ? q1 : 1.0;
+                b2t *= t & 1 ? q2 : 1.0;
+                q1 *= q1;
+                q2 *= q2;
+              }
+              lr_tab = (float)((double)it.lr * sqrt(1.0 - b2t) / (1.0 - b1t));
+            }
+            oc.lr_t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lr_tab), (int)(gstep - lr_base)));
+          } else {
+            oc.lr = uniform(epoch_lr(it.lr, it.power_t, e_lr, n_fit));
+          }
+          rec = nullptr;
+          if (traced && gstep >= P.step_begin && gstep < P.step_end) {
+            rec = P.trace_out + (gstep - P.step_begin) * (1 + 2 * (int64_t)y.P);
+            const double pen = penalty_sum(R);
+            // the step's loss is the difference this step makes to the epoch's sum; both starting points wait in LDS
+            const double before = sm_wavesum_d(lsum);
+            if (threadIdx.x == 0) {
+              trace_stash[0] = pen;
+              trace_stash[1] = before;
+            }
+          }
+          zero_grad(R);
+        } else {
+          lsum = hits = 0.0;
+        }
+      }
+      f32x4 acc[NT][4];
+      if (live) forward(R, b, par, nrt, acc);
+      __syncthreads();  // the outputs' shares, the next chunk's inputs and the rows of the one after it
+      if ((c2 & SC_MODE) != SC_END) fetch(c2, at, par, xr, yv);  // in flight until the next chunk is under way
+      bool stop = false;
+      if (live) {
+        outputs(R, b, par, rows, train, inv_mb, lsum, hits);
+        if (train) {
+          backward(R, b, nrt, acc);
+          if (c0 & SC_LAST) {  // last chunk of the step
+            if (rec) record<true>(R, oc.am, rec + 1);
+            if (oc.adam)
+              update<true>(R, oc);
+            else
+              update<false>(R, oc);
+            if (rec) {
+              record<false>(R, oc.am, rec + 1 + y.P);
+              const double after = sm_wavesum_d(lsum);
+              const float mb = c0 & SC_RAGGED ? mb_last : (float)bs;
+              if (threadIdx.x == 0) rec[0] = (float)((after - trace_stash[1] + 0.5 * (double)it.alpha * trace_stash[0]) / (double)mb);
+            }
+            gstep++;
+          }
+        }
+        // the end of an epoch (with the rows set aside, if any): the stopping rule, decided alike in every wave
+        if (c0 & SC_DECIDE) {
+          const float watched = (float)(sm_wavesum_d(lsum) / (double)(float)(n_hold ? n_hold : n_fit));
+          stop = plateau.stop_after(watched, it.tol, it.patience);
+          if (n_hold && plateau.improved) {
+            keep_best(R);
             have_best = true;
           }
-          esum = 0.0;
         }
       }
-      pos = nxt;
+      if (uniform(stop ? 1 : 0) && sc_mode(c1) == ROWS_EPOCH) {  // what is already on its way is dropped, and the pipeline starts over
+        __syncthreads();
+        c2 = score_start();
+        c0 = c1 = SC_NONE;
+      } else {
+        c0 = c1;
+        c1 = c2;
+        c2 = next(c2);
+        b = bn;
+      }
       par ^= 1;
     }
-    __syncthreads();
-    if (have_best) {  // early stopping on held-out rows scores the best epoch's model
-      copy_best(false);
-      __syncthreads();
     }
-
-    // ---- validation score on the held rows ----
-    lsum = 0.0;
-    hits = 0.0;
-    score_rows(va, ROWS_PLAIN, n_va, lsum, hits);
-    lsum = block_sum(lsum, red);
-    hits = block_sum(hits, red);
+    lsum = sm_wavesum_d(lsum);
+    hits = sm_wavesum_d(hits);
     if (threadIdx.x == 0) {
       float* out = P.item_out + 2 * ((int64_t)it.b * P.n_folds + fl);
       out[0] = n_va > 0 ? (float)(lsum / (double)n_va) : __builtin_nanf("");
@@ -857,19 +1037,21 @@ struct Small {
   }
 };
 
-template <int KT, int CO>
-__global__ __launch_bounds__(SM_THREADS, 2) void k_train_small(const TrainParams P) {
+template <int KT, int NT, int CO, int W>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_waves_per_eu(sm_occupancy(KT, NT, CO), sm_occupancy(KT, NT, CO))))
+void k_train_small(const TrainParams P) {
   extern __shared__ __align__(16) char smem[];
   __shared__ int s_item;
-  __shared__ double red[SM_THREADS / 64];
+  __shared__ double red[W], trace_stash[2];
   for (;;) {
     __syncthreads();
     if (threadIdx.x == 0) s_item = atomicAdd(P.queue, 1);
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item);
     if (item >= P.n_items) break;
-    const SItem* __restrict__ si = (const SItem*)P.items + item;
-    Small<KT, CO> T{P, si->d, si->y, smem, P.slots + (uint64_t)blockIdx.x * P.slot_bytes, red};
+    const __attribute__((address_space(4))) SItem* si = (const __attribute__((address_space(4))) SItem*)P.items + item;
+    Small<KT, NT, CO, W> T{P, si->d, si->y, smem, (float*)(P.slots + (uint64_t)blockIdx.x * P.slot_bytes), red, trace_stash,
+                           nullptr, nullptr, 0, 0, 0, 0, 0, 0, 0};
     T.run();
   }
 }

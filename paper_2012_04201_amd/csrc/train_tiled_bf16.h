@@ -154,9 +154,6 @@ struct TItem {
   TLay y;
 };
 
-// The staged items are written by the host before the launch and never by a kernel: reading them through the
-// constant address space lets the compiler use scalar loads and keep the layout in scalar registers.
-typedef const __attribute__((address_space(4))) ItemDesc ConstItemDesc;
 typedef const __attribute__((address_space(4))) TLay ConstTLay;
 
 // Transposing LDS read: within each group of 16 lanes the 16 x 4 values that
@@ -180,16 +177,6 @@ __device__ inline bf16x8 lds_operand_tr(const char* base, int ld, int r0, int u0
   u.s.lo = lds_read_tr(p);
   u.s.hi = lds_read_tr(p + (size_t)4 * ld * 2);
   return u.v;
-}
-
-// A wave-uniform value that the compiler holds in vector registers (anything read from memory the kernel also
-// writes), moved to scalar registers.
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-template <class T>
-__device__ __forceinline__ T* uniform(T* p) {
-  const uint64_t v = (uint64_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (T*)(((uint64_t)hi << 32) | lo);
 }
 
 struct Tiled {
