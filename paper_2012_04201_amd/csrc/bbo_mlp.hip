@@ -900,7 +900,7 @@ int kernel_class(const int32_t* dims, int L, int64_t n, int dtype) {
     return n * (int64_t)d < 0x7fffffff && linear_eligible(dims, L) ? KC_LINEAR : KC_GENERIC;
   }
   if (n * (int64_t)d >= 0x7fffffff) return KC_GENERIC;
-  if (small_eligible(dims, L)) return KC_SMALL;
+  if ((uint64_t)n * (uint64_t)d < (1ull << 30) && small_eligible(dims, L)) return KC_SMALL;  // 32-bit byte offsets into X
   if (mid_eligible(dims, L)) {
     MLay my;
     make_mlay(my, dims, n);

@@ -133,10 +133,18 @@ __device__ __forceinline__ float uniform(float v) {
   asm volatile("" : "+v"(v));
   return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
+// A pointer the compiler cannot see through: what is read from it stays where it is read.
+template <class T>
+__device__ __forceinline__ T* launder(T* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 // Global memory by name: a pointer that has been through an asm is a generic one otherwise, and generic accesses
 // count as LDS accesses too, so that every later LDS access waits for them.
 typedef __attribute__((address_space(1))) float GlobalF32;
 typedef __attribute__((address_space(1))) int32_t GlobalI32;
+typedef __attribute__((address_space(1))) char GlobalChar;
 
 // A scalar value that is to stay in scalar registers instead of being loaded again where it is used.
 template <class T>
@@ -235,6 +243,8 @@ struct TrainParams {
   const float* state_in;  // optional [3P]: parameters, m, v of the traced item before step_begin
   int32_t x_bf16;         // wavefront-per-model kernel: X holds bfloat16 and the products take bfloat16 operands
 };
+
+typedef const __attribute__((address_space(4))) TrainParams ConstParams;  // the kernel argument, read through its pointer
 
 __device__ inline double block_sum(double v, double* red) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);

@@ -46,13 +46,19 @@ struct SmallCut {
   int kt, nt, co, waves;
 };
 
-struct SLay {
-  int32_t d, h, c, nut, waves;
-  int32_t cw[2], cb[2], P;
-  uint32_t o_ft, o_net, o_sl, o_ep, lds_total;  // LDS offsets of the row tables; what precedes them is fixed by the variant
+// Row pipeline part of a model's LDS layout: where the row tables lie (what precedes them is fixed by the variant).
+struct PipeLay {
+  int32_t d, P;    // inputs; parameters of the model
   int32_t netted;  // the permutation network is tabled whole
   int32_t tabled;  // the epoch's rows are tabled in LDS; otherwise they are permuted chunk by chunk
-  uint32_t slot_floats;  // best epoch's parameters (early stopping on held-out rows)
+  uint32_t o_ft, o_net, o_sl, o_ep, total;
+};
+
+struct SLay {
+  PipeLay p;
+  int32_t h, c, nut;
+  int32_t cw[2], cb[2];
+  uint32_t lds_total, slot_floats;  // slot: the wave's parameters as they are drawn, and the best epoch's
 };
 
 struct SItem {
@@ -64,10 +70,6 @@ __host__ __device__ inline bool small_eligible(const int32_t* dims, int L) {
   return L == 2 && dims[0] <= 63 && dims[1] <= 224 && dims[2] <= 4;
 }
 __host__ __device__ constexpr int sm_ldw(int kt) { return 16 * kt + 4; }
-// LDS of a variant ahead of the row tables
-__host__ __device__ constexpr uint32_t sm_fixed_lds(int kt, int nt, int co, int waves) {
-  return (3 * SM_RC * sm_ldw(kt) + 2 * waves * co * SM_RC + co * SM_RC + 5 * SM_RC + waves * (nt * (1 + co) + co) * 32) * 4;
-}
 // registers a wave needs to park its share of the parameters
 __host__ __device__ constexpr int sm_regs(int kt, int nt, int co) { return nt * (4 * kt + 1 + co) + co; }
 
@@ -85,31 +87,32 @@ __host__ inline SmallCut small_cut(const int32_t* dims) {
   return s;
 }
 
-__host__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n, const SmallCut& s) {
-  y.d = dims[0];
-  y.h = dims[1];
-  y.c = dims[2];
-  y.nut = rup(dims[1], 16) / 16;
-  y.waves = s.waves;
-  y.cw[0] = 0;
-  y.cb[0] = y.d * y.h;
-  y.cw[1] = y.cb[0] + y.h;
-  y.cb[1] = y.cw[1] + y.h * y.c;
-  y.P = y.cb[1] + y.c;
-  y.slot_floats = (uint32_t)(s.waves * sm_regs(s.kt, s.nt, s.co) * 64);
+// LDS of the row pipeline: input tiles, labels, row lists
+__host__ __device__ constexpr uint32_t pipe_lds(int kt, int buffers) {
+  return (buffers * SM_RC * sm_ldw(kt) + buffers * SM_RC + 2 * SM_RC) * 4;
+}
+// LDS of a variant of k_train_small ahead of the row tables
+__host__ __device__ constexpr uint32_t sm_fixed_lds(int kt, int nt, int co, int waves) {
+  return pipe_lds(kt, 3) + (2 * waves * co * SM_RC + co * SM_RC + waves * (nt * (1 + co) + co) * 32) * 4;
+}
+
+// ... and the row tables behind `fixed` bytes of everything else
+__host__ inline void make_pipelay(PipeLay& y, int d, int P, int64_t n, int waves, uint32_t fixed) {
+  y.d = d;
+  y.P = P;
   uint32_t o = 0;
   auto take = [&](uint32_t bytes) {
     uint32_t r = o;
     o += (bytes + 15) & ~15u;
     return r;
   };
-  take(sm_fixed_lds(s.kt, s.nt, s.co, s.waves));
+  take(fixed);
   // 16-bit tables: the fold's row list in the order of the early-stopping cut, the epoch's row order, the round
   // function of the permutation network (a copy per wave) and, up to SM_NET rows, the whole network
   int hb = 1;
   while ((1 << (2 * hb)) < n) hb++;
-  const uint32_t ft = (uint32_t)(s.waves * (4 << hb) * 2), net = n <= SM_NET ? 2u << (2 * hb) : 0u;
-  const uint32_t tab = (uint32_t)((2 * n + 15) & ~(int64_t)15);
+  const uint32_t ft = (uint32_t)(waves * (4 << hb) * 2), net = n <= SM_NET ? 2u << (2 * hb) : 0u;
+  const uint32_t tab = (uint32_t)(2 * (n + SM_RC));  // (a chunk may read its row ids past the end: spare entries)
   y.tabled = n >= 1 && n <= 0xffff && o + ft + net + 2 * tab <= SM_LDS_LIMIT;
   y.netted = net > 0;  // (sized for n rows; the fold's own network is never wider)
   y.o_ft = y.o_net = y.o_sl = y.o_ep = o;
@@ -119,14 +122,25 @@ __host__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n, const Sm
     y.o_sl = take(tab);
     y.o_ep = take(tab);
   }
-  y.lds_total = o;
+  y.total = o;
+}
+
+__host__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n, const SmallCut& s) {
+  const int d = dims[0];
+  y.h = dims[1];
+  y.c = dims[2];
+  y.nut = rup(dims[1], 16) / 16;
+  y.cw[0] = 0;
+  y.cb[0] = d * y.h;
+  y.cw[1] = y.cb[0] + y.h;
+  y.cb[1] = y.cw[1] + y.h * y.c;
+  make_pipelay(y.p, d, y.cb[1] + y.c, n, s.waves, sm_fixed_lds(s.kt, s.nt, s.co, s.waves));
+  y.slot_floats = (uint32_t)(s.waves * sm_regs(s.kt, s.nt, s.co) * 64);
+  y.lds_total = y.p.total;
 }
 
 // Waves per SIMD the registers of a variant are budgeted for (512 registers per lane and SIMD).
 __host__ __device__ constexpr int sm_occupancy(int kt, int nt, int co) {
-#ifdef SM_OCC2
-  return nt == 1 && kt <= 2 ? 4 : (nt == 2 && kt <= 2 ? SM_OCC2 : 2);
-#endif
   return nt == 1 && kt <= 2 ? 4 : 2;
 }
 // workgroups a CU holds
@@ -186,40 +200,42 @@ enum {
 };
 __device__ __forceinline__ int sc_mode(int ch) { return (ch & SC_MODE) >> 7; }
 
-// KT: 16-wide k tiles of the input layer.  NT: unit tiles per wave (every wave has NT, or NT - 1, of them).
-// CO: output slots in use (1 and 2 are exact output counts, 4 serves 3 or 4 outputs).  W: waves.
-template <int KT, int NT, int CO, int W>
-struct Small {
-  static constexpr int K0 = 16 * KT, LDW = sm_ldw(KT);
-  static constexpr int KS = KT == 3 ? 64 : K0;             // lanes per row when inputs are fetched
-  static constexpr int NTHR = 64 * W, RSTEP = NTHR / KS, NX = SM_RC / RSTEP;  // rows per pass, passes
+// The row pipeline of a training run, shared by the kernels that take their inputs through LDS in chunks of 64 rows:
+// the schedule, the rows of an epoch, the inputs two chunks ahead, the stopping rules, tracing and the scores.  `Self`
+// has the model: its state (State, what stays in registers for the run; Acts, what a chunk's forward pass leaves for
+// its backward pass), forward(), outputs(), backward(), update(), record(), penalty_sum(), load(), keep_best(),
+// restore_best(), zero_grad() and total() (a sum over the block of what outputs() accumulates per thread).
+//   KT        16-wide k tiles of the input layer
+//   W         waves
+//   BARRIERS  1: a chunk has one barrier, between forward() and outputs(); its inputs were put into LDS before the
+//             barrier of the chunk before, so three input tiles rotate.  2: one more between outputs() and
+//             backward(), and two input tiles are enough.
+template <class Self, class Lay, int KT, int W, int BARRIERS>
+struct RowPipe {
+  static constexpr int K0 = 16 * KT, LDW = sm_ldw(KT), NB = BARRIERS == 1 ? 3 : 2;
+  static constexpr int KS = K0 <= 16 ? 16 : (K0 <= 32 ? 32 : (K0 <= 64 ? 64 : 128));  // lanes per row when inputs are fetched
+  static constexpr int NTHR = 64 * W, RSTEP = NTHR / KS, NX = SM_RC / RSTEP;          // rows per pass, passes
+  typedef const __attribute__((address_space(4))) Lay ConstLay;
   const TrainParams& P;
   const ConstItemDesc& it;
-  const __attribute__((address_space(4))) SLay& y;
+  ConstLay& y;
   char* lds;
   float* slot;
   double* red;
   double* trace_stash;  // thread 0's own
   // What every chunk needs of the item and the call, held in scalar registers: left to itself the compiler reloads
   // each field where it is used, a few hundred cycles every time.
-  const GlobalF32* X;
-  const GlobalI32* Y;
-  int d, n_fit, n_classes, o_sl, o_ep, tabled, nut;
+  const GlobalF32* X = nullptr;
+  const GlobalI32* Y = nullptr;
+  int d = 0, n_fit = 0, n_classes = 0, o_sl = 0, o_ep = 0, tabled = 0;
 
-  struct Regs {
-    f32x4 w[NT][KT], m[NT][KT], v[NT][KT], g[NT][KT];  // hidden layer: lane (unit li, columns 16 kk + 4q + e)
-    float bw[NT], bg[NT];                              // its bias
-    float w2[NT][CO], g2[NT][CO];                      // the unit's row of the output layer, alike in the four q
-    float ow[CO], og[CO];                              // output bias, alike in every lane (og: the lane's share)
-  };
-  // The moments of the last three, which are needed once per step and are alike in the four q, wait in LDS:
-  // [wave][bias, outputs of each tile, then the output bias][first, second][li].
-  static constexpr int NMOM = NT * (1 + CO) + CO;
+  __device__ __forceinline__ RowPipe(const TrainParams& P_, const ConstItemDesc& it_, ConstLay& y_, char* lds_, float* slot_,
+                                     double* red_, double* stash_)
+      : P(P_), it(it_), y(y_), lds(lds_), slot(slot_), red(red_), trace_stash(stash_) {}
 
-  // offsets in floats
-  static constexpr int O_ZP = 3 * SM_RC * LDW, O_D2 = O_ZP + 2 * W * CO * SM_RC, O_YS = O_D2 + CO * SM_RC, O_ROWS = O_YS + 3 * SM_RC,
-                       O_MOM = O_ROWS + 2 * SM_RC;
-  static_assert((O_MOM + W * NMOM * 32) * 4 == sm_fixed_lds(KT, NT, CO, W), "LDS layout");
+  // offsets in floats; what the model keeps in LDS starts at O_OWN
+  static constexpr int O_YS = NB * SM_RC * LDW, O_ROWS = O_YS + NB * SM_RC, O_OWN = O_ROWS + 2 * SM_RC;
+  static_assert(O_OWN * 4 == pipe_lds(KT, NB), "LDS layout");
   __device__ __forceinline__ float* f(int off) const { return (float*)lds + off; }
   __device__ __forceinline__ float* xs(int b) const { return f(b * (SM_RC * LDW)); }
   __device__ __forceinline__ float* ys(int b) const { return f(O_YS + b * SM_RC); }
@@ -233,132 +249,12 @@ struct Small {
     return t;
   }
   __device__ __forceinline__ static int wave() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
-  // does the wave's i-th tile exist?  Only the last one can be missing.
-  __device__ __forceinline__ bool has(int i, int w) const { return i + 1 < NT || w + i * W < nut; }
-
-  // ---- parameters ----------------------------------------------------------
   __device__ __forceinline__ float init_value(int l, int e, bool isb) const {
     const uint64_t kt = key_fold(key_model(it.seed, it.fold), 16 + 2 * l + (isb ? 1 : 0));
     const uint32_t k24 = (uint32_t)(key_fold(kt, (uint64_t)e) >> 40);
     return it.bound[l] * ((float)((int32_t)k24 - 8388608) * 0x1p-23f);
   }
-  // The wave's share of the parameters as it lies in its part of the slot: [register][lane], the registers in the
-  // order each_param() visits them.
-  static constexpr int NREG = sm_regs(KT, NT, CO);
-  __device__ __forceinline__ float* park() const { return slot + wave() * (NREG * 64) + (threadIdx.x & 63); }
-  // fn(index, reference) for the hidden weights of `w`, fs(index, position in NMOM) for everything else
-  template <class F, class S>
-  __device__ __forceinline__ static void each_param(f32x4 (&w)[NT][KT], F fn, S fs) {
-    int n = 0, k = 0;
-#pragma unroll
-    for (int i = 0; i < NT; i++) {
-#pragma unroll
-      for (int kk = 0; kk < KT; kk++)
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-          float x = w[i][kk][e];
-          fn(n++, x);
-          w[i][kk][e] = x;
-        }
-#pragma unroll
-      for (int cc = 0; cc <= CO; cc++) fs(n++, k++);
-    }
-#pragma unroll
-    for (int cc = 0; cc < CO; cc++) fs(n++, k++);
-  }
-  // the register of position k of NMOM
-  __device__ __forceinline__ static float& small_param(Regs& R, int k) {
-    if (k >= NT * (1 + CO)) return R.ow[k - NT * (1 + CO)];
-    const int i = k / (1 + CO), r = k - i * (1 + CO);
-    return r == 0 ? R.bw[i] : R.w2[i][r - 1];
-  }
-  // the lane's share of its gradient, summed over the row of 16 lanes where those hold different rows
-  __device__ __forceinline__ static float small_grad(const Regs& R, int k) {
-    if (k >= NT * (1 + CO)) return sm_row16sum(R.og[k - NT * (1 + CO)]);
-    const int i = k / (1 + CO), r = k - i * (1 + CO);
-    return r == 0 ? R.bg[i] : R.g2[i][r - 1];
-  }
-  __device__ __forceinline__ float* mom(int k, int which) const {
-    return f(O_MOM) + ((wave() * NMOM + k) * 2 + which) * 16 + (threadIdx.x & 15);
-  }
-  // Packed parameters (or one of their moments) `st`, or the initial draw where st is null, into the wave's part of
-  // the slot.  A rolled loop: the registers are filled from the slot afterwards.
-  __device__ __forceinline__ void unpack(const float* st) const {
-    const int lane = threadIdx.x & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
-    const int d = y.d, h = y.h, c = y.c;
-    float* b = park();
-    constexpr int PER = 4 * KT + 1 + CO;
-#pragma unroll 1
-    for (int n = 0; n < NREG; n++) {
-      const int i = n / PER, r = n - i * PER, j = (w_ + i * W) * 16 + li;
-      int l = 0, ci = -1, e = 0;
-      bool isb = false;
-      if (i == NT) {  // output bias
-        l = 1;
-        isb = true;
-        e = n - NT * PER;
-        if (e < c) ci = y.cb[1] + e;
-      } else if (r < 4 * KT) {
-        const int k = (r >> 2) * 16 + 4 * q + (r & 3);
-        e = k * h + j;
-        if (j < h && k < d) ci = y.cw[0] + e;
-      } else if (r == 4 * KT) {
-        isb = true;
-        e = j;
-        if (j < h) ci = y.cb[0] + j;
-      } else {
-        l = 1;
-        const int cc = r - 4 * KT - 1;
-        e = j * c + cc;
-        if (j < h && cc < c) ci = y.cw[1] + e;
-      }
-      float val = 0.f;
-      if (ci >= 0) val = st ? st[ci] : init_value(l, e, isb);
-      b[64 * n] = val;
-    }
-  }
-  __device__ __forceinline__ void load(Regs& R, const float* st) const {
-    const float* b = park();
-    auto take = [&](int n, float& x) { x = b[64 * n]; };
-    auto zero = [&](int, float& x) { x = 0.f; };
-    if (st) {
-      unpack(st + y.P);
-      each_param(R.m, take, [&](int n, int k) { *mom(k, 0) = b[64 * n]; });
-      unpack(st + 2 * y.P);
-      each_param(R.v, take, [&](int n, int k) { *mom(k, 1) = b[64 * n]; });
-    } else {
-      each_param(R.m, zero, [&](int, int k) { *mom(k, 0) = 0.f; });
-      each_param(R.v, zero, [&](int, int k) { *mom(k, 1) = 0.f; });
-    }
-    unpack(st);
-    restore_best(R);
-  }
-  // Keep the current parameters aside / take the kept ones back: every wave its own, no barrier.
-  __device__ __forceinline__ void keep_best(Regs& R) const {
-    float* b = park();
-    each_param(R.w, [&](int n, float& x) { b[64 * n] = x; }, [&](int n, int k) { b[64 * n] = small_param(R, k); });
-  }
-  __device__ __forceinline__ void restore_best(Regs& R) const {
-    const float* b = park();
-    each_param(R.w, [&](int n, float& x) { x = b[64 * n]; }, [&](int n, int k) { small_param(R, k) = b[64 * n]; });
-    // waited for here: the loop's own waits would otherwise have to allow for these loads, at the price of the input
-    // values that are meant to stay in flight
-    __builtin_amdgcn_s_waitcnt(0);
-  }
-  __device__ __forceinline__ static void zero_grad(Regs& R) {
-#pragma unroll
-    for (int i = 0; i < NT; i++) {
-#pragma unroll
-      for (int kk = 0; kk < KT; kk++) R.g[i][kk] = f32x4{0.f, 0.f, 0.f, 0.f};
-      R.bg[i] = 0.f;
-#pragma unroll
-      for (int cc = 0; cc < CO; cc++) R.g2[i][cc] = 0.f;
-    }
-#pragma unroll
-    for (int cc = 0; cc < CO; cc++) R.og[cc] = 0.f;
-  }
 
-  // ---- rows and inputs ------------------------------------------------------
   // The epoch's rows in visiting order -> ep.  The permutation network's round function sees the round and one half
   // of the position only, so its 4 x 2^hb values are tabled first (each wave its own copy): a network evaluation is
   // four LDS reads instead of twelve 64-bit multiplies.  Small data sets table the whole network from it, so that
@@ -369,15 +265,16 @@ struct Small {
     const uint16_t* sl = u16(o_sl);
     if (n_fit <= 1) {
       __syncthreads();
-      if (t_ < n_fit) ep[t_] = sl[0];
+      if (t_ < SM_RC) ep[t_] = sl[0];
       return;
     }
     const PermDomain dm = perm_domain((uint32_t)n_fit);
     const int half = 1 << dm.hb;
-    uint16_t* ft = u16(y.o_ft) + wave() * (4 * half);
+    uint16_t* ft = u16(y.p.o_ft) + wave() * (4 * half);
     for (int i = lane; i < 4 * half; i += 64)
       ft[i] = (uint16_t)((uint32_t)key_fold(ke, ((uint64_t)(i >> dm.hb) << 32) | ((uint32_t)i & dm.mask)) & dm.mask);
     __syncthreads();  // nobody reads the last epoch's order, or the network, any more
+    if (t_ < SM_RC) ep[n_fit + t_] = sl[0];  // the spare entries
     auto network = [&](uint32_t x) {
       uint32_t Lh = x >> dm.hb, Rh = x & dm.mask;
 #pragma unroll
@@ -389,8 +286,8 @@ struct Small {
       return (Lh << dm.hb) | Rh;
     };
     int p = t_;
-    if (y.netted) {
-      uint16_t* net = u16(y.o_net);
+    if (y.p.netted) {
+      uint16_t* net = u16(y.p.o_net);
       for (int x = t_; x < half * half; x += 4 * NTHR) {  // four evaluations in flight
         uint32_t v[4];
 #pragma unroll
@@ -425,58 +322,480 @@ struct Small {
       }
     }
   }
+  // What only the rare paths need is derived there, from pointers the compiler cannot see through: kept for the whole
+  // run it would crowd the scalar registers.
+  struct Lists {
+    const int32_t *tr, *va;
+    RowSplit sp;
+    uint64_t km;
+  };
+  __device__ __forceinline__ static const ConstParams& params() { return *launder((const ConstParams*)__builtin_amdgcn_kernarg_segment_ptr()); }
+  __device__ __forceinline__ const ConstItemDesc& item() const { return *launder(&it); }
+  __device__ __forceinline__ Lists lists() const {
+    const ConstParams& p = params();
+    const ConstItemDesc& i = item();
+    const int fl = i.fold - p.fold_base;  // which row list
+    Lists l;
+    l.tr = p.train_idx + (int64_t)fl * p.n;
+    l.va = p.val_idx + (int64_t)fl * p.n;
+    l.km = key_model(i.seed, i.fold);
+    l.sp = row_split(l.km, i.patience, i.val_frac, uniform(p.counts[2 * fl]));
+    return l;
+  }
   // Row ids of a chunk that is not tabled, into rowlist(par) by the first 64 threads.
-  __device__ __forceinline__ void park_rows(int chunk, int at, int e, int par, const int32_t* tr, const int32_t* va,
-                                            const RowSplit& sp, uint64_t km) const {
+  __device__ __forceinline__ void park_rows(int chunk, int at, int e, int par) const {
     const int r = threadIdx.x;
+    const Lists l = lists();
     if (r >= SM_RC) return;
-    int row = -1;
-    if (r < (chunk & SC_ROWS)) {
-      if (sc_mode(chunk) == ROWS_PLAIN)
-        row = va[at + r];
-      else
-        row = tr[row_index(sp, sc_mode(chunk), key_epoch(km, e), (uint32_t)(at + r))];
-    }
-    rowlist(par)[r] = row;
+    const int p = at + min(r, (chunk & SC_ROWS) - 1);  // past the chunk's rows: its last one again
+    rowlist(par)[r] =
+        sc_mode(chunk) == ROWS_PLAIN ? l.va[p] : l.tr[row_index(l.sp, sc_mode(chunk), key_epoch(l.km, e), (uint32_t)p)];
   }
   // The chunk's input values (and label) requested into registers; `at`: its first row's position in the epoch's
-  // order, or in the list being scored.  Straight-line code: past the chunk's rows and the input's columns the last
-  // valid element is requested again, and commit() puts zeros there.
+  // order, or in the list being scored.  Past the chunk's last row the entries that follow in the list are fetched
+  // (rows the model trains on, or any when it only scores): nothing masks rows, because a row that is not the chunk's
+  // has no loss and a zero delta.  Columns past the inputs stay as clear_tiles() left them.
   __device__ __forceinline__ void fetch(int chunk, int at, int par, float (&xr)[NX], float& yv) const {
-    const int t_ = tid(), k = min(t_ % KS, d - 1), r0 = t_ / KS;
-    const int last = (chunk & SC_ROWS) - 1, mode = sc_mode(chunk);
-    int row[NX], yrow;
+    const int t_ = tid(), k = t_ % KS, r0 = t_ / KS, mode = sc_mode(chunk);
+    uint32_t row[NX], yrow;
     if (tabled && mode != ROWS_PLAIN) {
       const uint16_t* t16 = (mode == ROWS_EPOCH ? u16(o_ep) : u16(o_sl) + n_fit) + at;
 #pragma unroll
-      for (int i = 0; i < NX; i++) row[i] = t16[min(r0 + i * RSTEP, last)];
-      yrow = t16[min(t_ & 63, last)];
+      for (int i = 0; i < NX; i++) row[i] = t16[r0 + i * RSTEP];
+      yrow = t16[t_ & 63];
     } else {
       const int32_t* t32 = rowlist(par);
 #pragma unroll
-      for (int i = 0; i < NX; i++) row[i] = t32[min(r0 + i * RSTEP, last)];
-      yrow = t32[min(t_ & 63, last)];
+      for (int i = 0; i < NX; i++) row[i] = (uint32_t)t32[r0 + i * RSTEP];
+      yrow = (uint32_t)t32[t_ & 63];
     }
+    // 32-bit byte offsets: the host sends matrices of 4 GiB and more elsewhere
+    if (k < d) {
 #pragma unroll
-    for (int i = 0; i < NX; i++) xr[i] = X[row[i] * d + k];  // n*d < 2^31 (checked by the host)
-    yv = __int_as_float(Y[yrow]);  // class id or target: 32 bits either way
+      for (int i = 0; i < NX; i++) xr[i] = *(const GlobalF32*)((const GlobalChar*)X + (row[i] * (uint32_t)d + (uint32_t)k) * 4u);
+    }
+    yv = __int_as_float(*(const GlobalI32*)((const GlobalChar*)Y + yrow * 4u));  // class id or target: 32 bits either way
   }
   // registers -> input tile and labels of buffer b
-  __device__ __forceinline__ void commit(int chunk, int b, const float (&xr)[NX], float yv) const {
+  __device__ __forceinline__ void commit(int b, const float (&xr)[NX], float yv) const {
     float* s = xs(b);
-    const int t_ = tid(), k = t_ % KS, r0 = t_ / KS, rows = chunk & SC_ROWS;
-    if (KS == K0 || k < K0) {
+    const int t_ = tid(), k = t_ % KS, r0 = t_ / KS;
+    if (k < d) {
 #pragma unroll
-      for (int i = 0; i < NX; i++) s[(r0 + i * RSTEP) * LDW + k] = r0 + i * RSTEP < rows && k < d ? xr[i] : 0.f;
+      for (int i = 0; i < NX; i++) s[(r0 + i * RSTEP) * LDW + k] = xr[i];
     }
     if (t_ < SM_RC) ys(b)[t_] = yv;
   }
+  // Zeros into the input tiles (their columns past the inputs are never written) and into the row list's spare entries.
+  __device__ __forceinline__ void clear_tiles(int n_tr) const {
+    for (int i = threadIdx.x; i < NB * SM_RC * LDW; i += NTHR) f(0)[i] = 0.f;
+    if (tabled && threadIdx.x < SM_RC) u16(o_sl)[n_tr + threadIdx.x] = 0;
+  }
 
+  __device__ __forceinline__ void run() {
+    Self& self = *static_cast<Self*>(this);
+    const int fl = it.fold - P.fold_base;  // which row list
+    const int n_tr = uniform(P.counts[2 * fl]), n_va = uniform(P.counts[2 * fl + 1]);
+    const RowSplit sp = row_split(key_model(it.seed, it.fold), it.patience, it.val_frac, n_tr);
+    X = pin((const GlobalF32*)P.X);
+    Y = pin((const GlobalI32*)P.y);
+    d = pin(y.p.d);
+    n_fit = pin(uniform(sp.n_fit));
+    n_classes = pin(P.n_classes);
+    o_sl = pin((int)y.p.o_sl);
+    o_ep = pin((int)y.p.o_ep);
+    tabled = pin(y.p.tabled);
+    self.pin_own();
+    const int bs = pin(uniform(eff_batch(it.batch_size, n_fit)));
+    const int steps = pin(uniform(n_fit > 0 ? (n_fit + bs - 1) / bs : 0));
+    const int epochs = pin(it.epochs);
+    const int traced = pin(uniform(P.trace_item == it.b * P.n_folds + fl ? 1 : 0));
+    const bool resume = traced && P.state_in && steps > 0;
+    const bool watch = it.patience > 0 && steps > 0 && !resume;
+    const int n_hold = pin(uniform(watch ? sp.n_hold : 0));
+    const float mb_last = (float)(n_fit - (steps - 1) * bs);
+    const float inv_full = uniform(1.f / (float)bs), inv_last = uniform(1.f / mb_last);
+    const float am_full = uniform(it.alpha / (float)bs), am_last = uniform(it.alpha / mb_last);
+
+    // ---- the schedule: training chunks, after each epoch the rows set aside, at the end the held fold ----
+    // Position of the chunk whose inputs are requested next: first row `at` in its order, step st of epoch e, `left`
+    // rows of that step from this chunk on.
+    const int last_rows = pin(uniform(n_fit - (steps - 1) * bs)), decide = pin(uniform(watch && !n_hold ? (int)SC_DECIDE : 0));
+    int e = 0, st = 0, at = 0, left = 0;
+    auto training = [&](int flags) {  // the chunk at this position
+      const int ragged = st + 1 == steps ? SC_RAGGED : 0;
+      const int last = left <= SM_RC ? SC_LAST | (ragged ? decide : 0) : 0;
+      return (ROWS_EPOCH << 7) | min(SM_RC, left) | flags | ragged | last | (st == 0 ? SC_EPOCH : 0);
+    };
+    auto list_chunk = [&](int mode, int count) {
+      int ch = (mode << 7) | min(SM_RC, count - at);
+      if (at == 0) ch |= SC_FIRST;
+      if (mode == ROWS_HELD && count - at <= SM_RC) ch |= SC_DECIDE;
+      return ch;
+    };
+    auto score_start = [&]() -> int {
+      at = 0;
+      return n_va > 0 ? list_chunk(ROWS_PLAIN, n_va) : (int)SC_END;
+    };
+    auto step_start = [&]() -> int {  // at (e, st)
+      if (steps == 0 || e >= epochs) return score_start();
+      at = st * bs;
+      left = st + 1 == steps ? last_rows : bs;
+      return training(SC_FIRST);
+    };
+    auto next = [&](int ch) -> int {
+      const int mode = sc_mode(ch), more = left - (ch & SC_ROWS);
+      at += ch & SC_ROWS;
+      if (mode == ROWS_EPOCH && (more > 0 || st + 1 < steps)) {  // the epoch goes on: straight-line code
+        const int opens = more <= 0 ? 1 : 0;
+        st += opens;
+        left = opens ? (st + 1 == steps ? last_rows : bs) : more;
+        return training(opens ? (int)SC_FIRST : 0);
+      }
+      if (mode == ROWS_EPOCH && n_hold) {
+        at = 0;
+        return list_chunk(ROWS_HELD, n_hold);
+      }
+      if (mode == ROWS_HELD && at < n_hold) return list_chunk(ROWS_HELD, n_hold);
+      if (mode == ROWS_EPOCH || mode == ROWS_HELD) {
+        e++;
+        st = 0;
+        return step_start();
+      }
+      return mode == ROWS_PLAIN && at < n_va ? list_chunk(ROWS_PLAIN, n_va) : (int)SC_END;
+    };
+
+    typename Self::State R;
+    int64_t gstep = 0;
+    if (resume) {
+      gstep = P.step_begin;
+      e = (int)(gstep / steps);
+      st = (int)(gstep % steps);
+    }
+    const int e0 = e, st0 = st;
+    int c2 = step_start();  // the chunk at the position above
+    self.load(R, resume ? P.state_in : nullptr);
+
+    OptC oc;
+    const int solver = pin(it.solver);
+    oc.adam = solver == BBO_ADAM;
+    oc.nest = it.nesterov != 0;
+    oc.b1 = pin(it.beta1);
+    oc.b2 = pin(it.beta2);
+    oc.omb1 = uniform(1.f - it.beta1);
+    oc.omb2 = uniform(1.f - it.beta2);
+    oc.eps = pin(it.eps);
+    oc.mu = pin(it.momentum);
+    oc.lr = it.lr;
+    oc.lr_t = it.lr;
+    oc.am = 0.f;
+    float lr_tab = 0.f;  // Adam: the step sizes of 64 steps, one per lane
+    int lr_at = 64;      // ... the next of them
+
+    clear_tiles(n_tr);
+    if (tabled) {  // rows of the training list in the order of the early-stopping cut
+      uint16_t* sl = u16(o_sl);
+      const int32_t* tr = P.train_idx + (int64_t)fl * P.n;
+      for (int p = threadIdx.x; p < n_tr; p += blockDim.x)
+        sl[p] = (uint16_t)tr[sp.n_hold ? (int)perm_index(sp.ksplit, (uint32_t)n_tr, (uint32_t)p) : p];
+    }
+    __syncthreads();
+    float xr[NX], yv = 0.f;
+#pragma unroll
+    for (int i = 0; i < NX; i++) xr[i] = 0.f;
+    int b = 0, par = 0;  // input buffer and exchange parity of the current chunk
+    int built = -1;      // the last epoch whose rows have been tabled
+    int c0 = SC_NONE, c1 = SC_NONE;  // the chunk being worked on; the one whose inputs are on their way in registers
+    int e_lr = st0 > 0 ? e0 : e0 - 1;  // epoch of the step being worked on (set when one opens)
+    double lsum = 0.0, hits = 0.0;  // the lane's share of the summed data loss: of the epoch, or of a scoring pass
+    Plateau plateau;
+    int recording = 0, have_best = 0;
+    float inv_mb = inv_full;
+    if (!oc.adam) oc.lr = uniform(epoch_lr(it.lr, it.power_t, e_lr, n_fit));
+    for (int phase = 0; phase < 2; phase++) {  // training with its stopping rule; the score
+      if (phase == 1 && have_best) self.restore_best(R);  // the best epoch's model is the one scored
+      while ((c0 & SC_MODE) != SC_END && (phase == 1 || sc_mode(c0) != ROWS_PLAIN)) {
+        const int bn = b == NB - 1 ? 0 : b + 1, rows = c0 & SC_ROWS, nrt = (rows + 15) / 16;
+        if (BARRIERS == 1 && sc_mode(c1) <= ROWS_PLAIN) commit(bn, xr, yv);
+        // the rows of the chunk whose inputs are requested next: its epoch's table if it opens one, or a row list
+        if ((c2 & SC_MODE) != SC_END) {
+          if (!tabled || sc_mode(c2) == ROWS_PLAIN) {
+            park_rows(c2, at, e, par);
+          } else if (sc_mode(c2) == ROWS_EPOCH && e != built) {
+            build_epoch(key_epoch(key_model(item().seed, item().fold), e));
+            built = e;
+          }
+        }
+        if (c0 & SC_FIRST) {
+          if (sc_mode(c0) == ROWS_EPOCH) {  // first chunk of a step
+            const bool last = c0 & SC_RAGGED;
+            oc.am = last ? am_last : am_full;
+            inv_mb = last ? inv_last : inv_full;
+            if (c0 & SC_EPOCH) {
+              e_lr++;
+              lsum = 0.0;
+              if (!oc.adam) oc.lr = uniform(epoch_lr(item().lr, item().power_t, e_lr, n_fit));
+            }
+            if (oc.adam) {
+              if (lr_at == 64) {
+                // beta^t of the next 64 steps, a step per lane, by repeated squaring in double
+                lr_at = 0;
+                double q1 = (double)item().beta1, q2 = (double)item().beta2, b1t = 1.0, b2t = 1.0;
+#pragma unroll 1
+                for (uint64_t t = (uint64_t)(gstep + 1) + (threadIdx.x & 63); __any(t != 0); t >>= 1) {
+                  b1t *= t & 1 ? q1 : 1.0;
+                  b2t *= t & 1 ? q2 : 1.0;
+                  q1 *= q1;
+                  q2 *= q2;
+                }
+                lr_tab = (float)((double)item().lr * sqrt(1.0 - b2t) / (1.0 - b1t));
+              }
+              oc.lr_t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lr_tab), lr_at));
+              lr_at++;
+            }
+            if (traced) {
+              recording = gstep >= params().step_begin && gstep < params().step_end ? 1 : 0;
+              if (recording) {
+                const double pen = self.penalty_sum(R);
+                // the step's loss is the difference this step makes to the epoch's sum; both wait in LDS
+                const double before = self.total(lsum);
+                if (threadIdx.x == 0) {
+                  trace_stash[0] = pen;
+                  trace_stash[1] = before;
+                }
+              }
+            }
+            self.zero_grad(R);
+          } else {
+            lsum = hits = 0.0;
+          }
+        }
+        typename Self::Acts acc;
+        const bool live = (c0 & SC_MODE) != SC_NONE;
+        if (live) self.forward(R, b, par, nrt, acc);
+        __syncthreads();  // the outputs' shares, the next chunk's inputs and the rows of the one after it
+        if (BARRIERS == 2 && sc_mode(c1) <= ROWS_PLAIN) commit(bn, xr, yv);
+        if ((c2 & SC_MODE) != SC_END) fetch(c2, at, par, xr, yv);  // in flight until the next chunk is under way
+        if (live) self.outputs(R, b, par, rows, sc_mode(c0) == ROWS_EPOCH, inv_mb, lsum, hits);
+        if (BARRIERS == 2) __syncthreads();  // the output deltas
+        if (sc_mode(c0) == ROWS_EPOCH) {
+          self.backward(R, b, nrt, acc);
+          if (c0 & SC_LAST) {  // last chunk of the step
+            float* rec = nullptr;
+            if (recording) {
+              rec = params().trace_out + (gstep - params().step_begin) * (1 + 2 * (int64_t)y.p.P);
+              self.template record<true>(R, oc.am, rec + 1);
+            }
+            if (oc.adam)
+              self.template update<true>(R, oc);
+            else
+              self.template update<false>(R, oc);
+            if (recording) {
+              self.template record<false>(R, oc.am, rec + 1 + y.p.P);
+              const double after = self.total(lsum);
+              const float mb = c0 & SC_RAGGED ? (float)last_rows : (float)bs;
+              if (threadIdx.x == 0)
+                rec[0] = (float)((after - trace_stash[1] + 0.5 * (double)item().alpha * trace_stash[0]) / (double)mb);
+            }
+            gstep++;
+          }
+        }
+        const int done = c0;
+        c0 = c1;
+        c1 = c2;
+        c2 = next(c2);
+        b = bn;
+        par ^= 1;
+        // the end of an epoch (with the rows set aside, if any): the stopping rule, decided alike in every wave
+        if (done & SC_DECIDE) {
+          const float watched = (float)(self.total(lsum) / (double)(n_hold ? n_hold : n_fit));
+          const int stop = uniform(plateau.stop_after(watched, item().tol, item().patience) ? 1 : 0);
+          if (n_hold && uniform(plateau.improved ? 1 : 0)) {
+            self.keep_best(R);
+            have_best = 1;
+          }
+          if (stop && sc_mode(c0) == ROWS_EPOCH) {  // what is already on its way is dropped, and the pipeline starts over
+            __syncthreads();
+            c2 = score_start();
+            c0 = c1 = SC_NONE;
+          }
+        }
+      }
+    }
+    lsum = self.total(lsum);
+    hits = self.total(hits);
+    if (threadIdx.x == 0) {
+      float* out = P.item_out + 2 * ((int64_t)it.b * P.n_folds + fl);
+      out[0] = n_va > 0 ? (float)(lsum / (double)n_va) : __builtin_nanf("");
+      out[1] = n_va > 0 ? (float)(hits / (double)n_va) : __builtin_nanf("");  // accuracy | mean absolute error
+    }
+  }
+};
+
+// KT: 16-wide k tiles of the input layer.  NT: unit tiles per wave (every wave has NT, or NT - 1, of them).
+// CO: output slots in use (1 and 2 are exact output counts, 4 serves 3 or 4 outputs).  W: waves.
+template <int KT, int NT, int CO, int W>
+struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
+  typedef RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> Base;
+  using Base::Base;
+  using Base::f;
+  using Base::init_value;
+  using Base::it;
+  using Base::n_classes;
+  using Base::red;
+  using Base::slot;
+  using Base::tid;
+  using Base::wave;
+  using Base::xs;
+  using Base::y;
+  using Base::ys;
+  static constexpr int LDW = Base::LDW;
+  int nut = 0;
+  __device__ __forceinline__ void pin_own() { nut = pin(y.nut); }
+  __device__ __forceinline__ static double total(double v) { return sm_wavesum_d(v); }  // every wave has the whole sum
+
+  struct State {
+    f32x4 w[NT][KT], m[NT][KT], v[NT][KT], g[NT][KT];  // hidden layer: lane (unit li, columns 16 kk + 4q + e)
+    float bw[NT], bg[NT];                              // its bias
+    float w2[NT][CO], g2[NT][CO];                      // the unit's row of the output layer, alike in the four q
+    float ow[CO], og[CO];                              // output bias, alike in every lane (og: the lane's share)
+  };
+  // The moments of the last three, which are needed once per step and are alike in the four q, wait in LDS:
+  // [wave][bias, outputs of each tile, then the output bias][first, second][li].
+  static constexpr int NMOM = NT * (1 + CO) + CO;
+
+  struct Acts {
+    f32x4 a[NT][4];  // activations of the wave's tiles: lane (unit li, rows 16 r + 4q..+3)
+  };
+  // offsets in floats
+  static constexpr int O_ZP = Base::O_OWN, O_D2 = O_ZP + 2 * W * CO * SM_RC, O_MOM = O_D2 + CO * SM_RC;
+  static_assert((O_MOM + W * NMOM * 32) * 4 == sm_fixed_lds(KT, NT, CO, W), "LDS layout");
+  // does the wave's i-th tile exist?  Only the last one can be missing.
+  __device__ __forceinline__ bool has(int i, int w) const { return i + 1 < NT || w + i * W < nut; }
+
+  // ---- parameters ----------------------------------------------------------
+  // The wave's share of the parameters as it lies in its part of the slot: [register][lane], the registers in the
+  // order each_param() visits them.
+  static constexpr int NREG = sm_regs(KT, NT, CO);
+  __device__ __forceinline__ float* park() const { return slot + wave() * (NREG * 64) + (threadIdx.x & 63); }
+  // fn(index, reference) for the hidden weights of `w`, fs(index, position in NMOM) for everything else
+  template <class F, class S>
+  __device__ __forceinline__ static void each_param(f32x4 (&w)[NT][KT], F fn, S fs) {
+    int n = 0, k = 0;
+#pragma unroll
+    for (int i = 0; i < NT; i++) {
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          float x = w[i][kk][e];
+          fn(n++, x);
+          w[i][kk][e] = x;
+        }
+#pragma unroll
+      for (int cc = 0; cc <= CO; cc++) fs(n++, k++);
+    }
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++) fs(n++, k++);
+  }
+  // the register of position k of NMOM
+  __device__ __forceinline__ static float& small_param(State& R, int k) {
+    if (k >= NT * (1 + CO)) return R.ow[k - NT * (1 + CO)];
+    const int i = k / (1 + CO), r = k - i * (1 + CO);
+    return r == 0 ? R.bw[i] : R.w2[i][r - 1];
+  }
+  // the lane's share of its gradient, summed over the row of 16 lanes where those hold different rows
+  __device__ __forceinline__ static float small_grad(const State& R, int k) {
+    if (k >= NT * (1 + CO)) return sm_row16sum(R.og[k - NT * (1 + CO)]);
+    const int i = k / (1 + CO), r = k - i * (1 + CO);
+    return r == 0 ? R.bg[i] : R.g2[i][r - 1];
+  }
+  __device__ __forceinline__ float* mom(int k, int which) const {
+    return f(O_MOM) + ((wave() * NMOM + k) * 2 + which) * 16 + (threadIdx.x & 15);
+  }
+  // Packed parameters (or one of their moments) `st`, or the initial draw where st is null, into the wave's part of
+  // the slot.  A rolled loop: the registers are filled from the slot afterwards.
+  __device__ __forceinline__ void unpack(const float* st) const {
+    const int lane = threadIdx.x & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
+    const int d = y.p.d, h = y.h, c = y.c;
+    float* b = park();
+    constexpr int PER = 4 * KT + 1 + CO;
+#pragma unroll 1
+    for (int n = 0; n < NREG; n++) {
+      const int i = n / PER, r = n - i * PER, j = (w_ + i * W) * 16 + li;
+      int l = 0, ci = -1, e = 0;
+      bool isb = false;
+      if (i == NT) {  // output bias
+        l = 1;
+        isb = true;
+        e = n - NT * PER;
+        if (e < c) ci = y.cb[1] + e;
+      } else if (r < 4 * KT) {
+        const int k = (r >> 2) * 16 + 4 * q + (r & 3);
+        e = k * h + j;
+        if (j < h && k < d) ci = y.cw[0] + e;
+      } else if (r == 4 * KT) {
+        isb = true;
+        e = j;
+        if (j < h) ci = y.cb[0] + j;
+      } else {
+        l = 1;
+        const int cc = r - 4 * KT - 1;
+        e = j * c + cc;
+        if (j < h && cc < c) ci = y.cw[1] + e;
+      }
+      float val = 0.f;
+      if (ci >= 0) val = st ? st[ci] : init_value(l, e, isb);
+      b[64 * n] = val;
+    }
+  }
+  __device__ __forceinline__ void load(State& R, const float* st) const {
+    const float* b = park();
+    auto take = [&](int n, float& x) { x = b[64 * n]; };
+    auto zero = [&](int, float& x) { x = 0.f; };
+    if (st) {
+      unpack(st + y.p.P);
+      each_param(R.m, take, [&](int n, int k) { *mom(k, 0) = b[64 * n]; });
+      unpack(st + 2 * y.p.P);
+      each_param(R.v, take, [&](int n, int k) { *mom(k, 1) = b[64 * n]; });
+    } else {
+      each_param(R.m, zero, [&](int, int k) { *mom(k, 0) = 0.f; });
+      each_param(R.v, zero, [&](int, int k) { *mom(k, 1) = 0.f; });
+    }
+    unpack(st);
+    restore_best(R);
+  }
+  // Keep the current parameters aside / take the kept ones back: every wave its own, no barrier.
+  __device__ __forceinline__ void keep_best(State& R) const {
+    float* b = park();
+    each_param(R.w, [&](int n, float& x) { b[64 * n] = x; }, [&](int n, int k) { b[64 * n] = small_param(R, k); });
+  }
+  __device__ __forceinline__ void restore_best(State& R) const {
+    const float* b = park();
+    each_param(R.w, [&](int n, float& x) { x = b[64 * n]; }, [&](int n, int k) { small_param(R, k) = b[64 * n]; });
+    // waited for here: the loop's own waits would otherwise have to allow for these loads, at the price of the input
+    // values that are meant to stay in flight
+    __builtin_amdgcn_s_waitcnt(0);
+  }
+  __device__ __forceinline__ static void zero_grad(State& R) {
+#pragma unroll
+    for (int i = 0; i < NT; i++) {
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++) R.g[i][kk] = f32x4{0.f, 0.f, 0.f, 0.f};
+      R.bg[i] = 0.f;
+#pragma unroll
+      for (int cc = 0; cc < CO; cc++) R.g2[i][cc] = 0.f;
+    }
+#pragma unroll
+    for (int cc = 0; cc < CO; cc++) R.og[cc] = 0.f;
+  }
+
+  // ---- rows and inputs ------------------------------------------------------
   // ---- hidden layer forward; the wave's share of the outputs -> zp ----------------
   // One row tile: products of all the wave's tiles in turn (independent accumulators), ReLU, output-layer share.
   // ALL: the wave's last tile exists.
   template <bool ALL>
-  __device__ __forceinline__ void forward_tile(const Regs& R, const float* s, int r, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
+  __device__ __forceinline__ void forward_tile(const State& R, const float* s, int r, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
     const float* a_ = s + (r * 16 + li) * LDW + 4 * q;
     f32x4 a[KT];
@@ -507,7 +826,7 @@ struct Small {
     for (int cc = 0; cc < CO; cc++) v[cc][r] = sm_fold_quad(p[cc], li & 1, li & 2);
   }
   template <bool ALL, int N>
-  __device__ __forceinline__ void forward_tiles(const Regs& R, const float* s, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
+  __device__ __forceinline__ void forward_tiles(const State& R, const float* s, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
 #pragma unroll
     for (int r = 0; r < 4; r++) {
       if (r < N) {
@@ -519,7 +838,7 @@ struct Small {
     }
   }
   template <bool ALL>
-  __device__ __forceinline__ void forward_chunk(const Regs& R, const float* s, int nrt, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
+  __device__ __forceinline__ void forward_chunk(const State& R, const float* s, int nrt, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
     if (nrt == 4)
       forward_tiles<ALL, 4>(R, s, acc, v);
     else if (nrt == 3)
@@ -529,7 +848,8 @@ struct Small {
     else
       forward_tiles<ALL, 1>(R, s, acc, v);
   }
-  __device__ __forceinline__ void forward(const Regs& R, int b, int par, int nrt, f32x4 (&acc)[NT][4]) const {
+  __device__ __forceinline__ void forward(const State& R, int b, int par, int nrt, Acts& A) const {
+    f32x4 (&acc)[NT][4] = A.a;
     const int w_ = wave();
     float v[CO][4];
     if (has(NT - 1, w_))
@@ -543,7 +863,7 @@ struct Small {
   }
 
   // ---- outputs, loss and output delta of the chunk's rows; the same in every wave ----
-  __device__ __forceinline__ void outputs(Regs& R, int b, int par, int rows, bool train, float inv_mb, double& lsum, double& hits) const {
+  __device__ __forceinline__ void outputs(State& R, int b, int par, int rows, bool train, float inv_mb, double& lsum, double& hits) const {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4, c = CO <= 2 ? CO : y.c;
     const int row = (li >> 2) * 16 + 4 * q + (li & 3);  // the row the folding tree left in this lane
     const float* zp = f(O_ZP) + par * W * (CO * SM_RC) + lane;
@@ -613,7 +933,7 @@ struct Small {
 
   // ---- backward: hidden deltas, output-layer gradient, hidden weight gradient -------
   template <bool ALL>
-  __device__ __forceinline__ void backward_tile(Regs& R, const float* s, int r, const f32x4 (&acc)[NT][4]) const {
+  __device__ __forceinline__ void backward_tile(State& R, const float* s, int r, const f32x4 (&acc)[NT][4]) const {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
     const float* d2 = f(O_D2) + q * 16 + r * 4;
     const float* a_ = s + (r * 16 + 4 * q) * LDW + li;
@@ -654,12 +974,12 @@ struct Small {
       }
   }
   template <bool ALL, int N>
-  __device__ __forceinline__ void backward_tiles(Regs& R, const float* s, const f32x4 (&acc)[NT][4]) const {
+  __device__ __forceinline__ void backward_tiles(State& R, const float* s, const f32x4 (&acc)[NT][4]) const {
 #pragma unroll
     for (int r = 0; r < N; r++) backward_tile<ALL>(R, s, r, acc);
   }
   template <bool ALL>
-  __device__ __forceinline__ void backward_chunk(Regs& R, const float* s, int nrt, const f32x4 (&acc)[NT][4]) const {
+  __device__ __forceinline__ void backward_chunk(State& R, const float* s, int nrt, const f32x4 (&acc)[NT][4]) const {
     if (nrt == 4)
       backward_tiles<ALL, 4>(R, s, acc);
     else if (nrt == 3)
@@ -669,7 +989,8 @@ struct Small {
     else
       backward_tiles<ALL, 1>(R, s, acc);
   }
-  __device__ __forceinline__ void backward(Regs& R, int b, int nrt, const f32x4 (&acc)[NT][4]) const {
+  __device__ __forceinline__ void backward(State& R, int b, int nrt, const Acts& A) const {
+    const f32x4 (&acc)[NT][4] = A.a;
     if (has(NT - 1, wave()))
       backward_chunk<true>(R, xs(b), nrt, acc);
     else
@@ -680,7 +1001,7 @@ struct Small {
   // Pad elements need no mask: their inputs, deltas and weights are zero, and so is their step (0 / eps).  Only an
   // eps of zero would make it 0 / 0; that case clears them afterwards.
   template <bool ADAM>
-  __device__ __forceinline__ void update(Regs& R, const OptC& oc) const {
+  __device__ __forceinline__ void update(State& R, const OptC& oc) const {
     const int w_ = wave();
     OptC o = oc;
     o.adam = ADAM;
@@ -725,9 +1046,9 @@ struct Small {
   }
   // A traced step's gradient (before the update: GRAD) or new parameters into out[P].
   template <bool GRAD>
-  __device__ __forceinline__ void record(const Regs& R, float am, float* out) const {
+  __device__ __forceinline__ void record(const State& R, float am, float* out) const {
     const int t_ = tid(), lane = t_ & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
-    const int d = y.d, h = y.h, c = CO <= 2 ? CO : y.c;
+    const int d = y.p.d, h = y.h, c = CO <= 2 ? CO : y.c;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
       const int j = (w_ + i * W) * 16 + li;
@@ -752,7 +1073,7 @@ struct Small {
       if (t_ == 0 && cc < c) out[y.cb[1] + cc] = x;
     }
   }
-  __device__ __forceinline__ void clear_pads(Regs& R) const {
+  __device__ __forceinline__ void clear_pads(State& R) const {
     const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4, c = CO <= 2 ? CO : y.c;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
@@ -761,7 +1082,7 @@ struct Small {
       for (int kk = 0; kk < KT; kk++)
 #pragma unroll
         for (int e = 0; e < 4; e++)
-          if (!unit || kk * 16 + 4 * q + e >= y.d) R.w[i][kk][e] = R.m[i][kk][e] = R.v[i][kk][e] = 0.f;
+          if (!unit || kk * 16 + 4 * q + e >= y.p.d) R.w[i][kk][e] = R.m[i][kk][e] = R.v[i][kk][e] = 0.f;
 #pragma unroll
       for (int r = 0; r <= CO; r++)
         if (!unit || r > c) {
@@ -780,7 +1101,7 @@ struct Small {
   }
 
   // squared weights, for a traced step's loss
-  __device__ __forceinline__ double penalty_sum(const Regs& R) const {
+  __device__ __forceinline__ double penalty_sum(const State& R) const {
     const int lane = threadIdx.x & 63, q = lane >> 4;
     double s = 0.0;
 #pragma unroll
@@ -797,244 +1118,6 @@ struct Small {
     return block_sum(s, red);
   }
 
-  __device__ __forceinline__ void run() {
-    const int f_ = it.fold, fl = it.fold - P.fold_base;  // fl: which row list
-    const int n_tr = uniform(P.counts[2 * fl]), n_va = uniform(P.counts[2 * fl + 1]);
-    const int32_t* tr = P.train_idx + (int64_t)fl * P.n;
-    const int32_t* va = P.val_idx + (int64_t)fl * P.n;
-    const uint64_t km = key_model(it.seed, f_);
-    const RowSplit sp = row_split(km, it.patience, it.val_frac, n_tr);
-    X = pin((const GlobalF32*)P.X);
-    Y = pin((const GlobalI32*)P.y);
-    d = pin(y.d);
-    n_fit = pin(uniform(sp.n_fit));
-    n_classes = pin(P.n_classes);
-    o_sl = pin((int)y.o_sl);
-    o_ep = pin((int)y.o_ep);
-    tabled = pin(y.tabled);
-    nut = pin(y.nut);
-    const int bs = pin(uniform(eff_batch(it.batch_size, n_fit)));
-    const int steps = pin(uniform(n_fit > 0 ? (n_fit + bs - 1) / bs : 0));
-    const int epochs = pin(it.epochs);
-    const bool traced = P.trace_item == it.b * P.n_folds + fl;
-    const bool resume = traced && P.state_in && steps > 0;
-    const bool watch = it.patience > 0 && steps > 0 && !resume;
-    const int n_hold = pin(uniform(watch ? sp.n_hold : 0));
-    const float mb_last = uniform((float)(n_fit - (steps - 1) * bs));
-    const float inv_full = uniform(1.f / (float)bs), inv_last = uniform(1.f / mb_last);
-    const float am_full = uniform(it.alpha / (float)bs), am_last = uniform(it.alpha / mb_last);
-
-    // ---- the schedule: training chunks, after each epoch the rows set aside, at the end the held fold ----
-    // Position of the chunk whose inputs are requested next: first row `at` in its order, step st of epoch e.
-    int e = 0, st = 0, at = 0;
-    auto step_rows = [&](int s) { return min(bs, n_fit - s * bs); };
-    auto training = [&]() {  // the chunk at (e, st, at)
-      const int in_step = at - st * bs, left = step_rows(st) - in_step;
-      int ch = (ROWS_EPOCH << 7) | min(SM_RC, left);
-      if (in_step == 0) ch |= SC_FIRST;
-      if (left <= SM_RC) ch |= SC_LAST;
-      if (st == 0) ch |= SC_EPOCH;
-      if (st + 1 == steps) ch |= SC_RAGGED;
-      if (st + 1 == steps && left <= SM_RC && watch && !n_hold) ch |= SC_DECIDE;
-      return ch;
-    };
-    auto list_chunk = [&](int mode, int count) {
-      int ch = (mode << 7) | min(SM_RC, count - at);
-      if (at == 0) ch |= SC_FIRST;
-      if (mode == ROWS_HELD && count - at <= SM_RC) ch |= SC_DECIDE;
-      return ch;
-    };
-    auto score_start = [&]() -> int {
-      at = 0;
-      return n_va > 0 ? list_chunk(ROWS_PLAIN, n_va) : (int)SC_END;
-    };
-    auto epoch_start = [&]() -> int {
-      at = st = 0;
-      return steps > 0 && e < epochs ? training() : score_start();
-    };
-    auto next = [&](int ch) -> int {
-      const int mode = sc_mode(ch);
-      at += ch & SC_ROWS;
-      if (mode == ROWS_EPOCH) {
-        if (ch & SC_LAST) st++;
-        if (st < steps) return training();
-        if (n_hold) {
-          at = 0;
-          return list_chunk(ROWS_HELD, n_hold);
-        }
-        e++;
-        return epoch_start();
-      }
-      if (mode == ROWS_HELD) {
-        if (at < n_hold) return list_chunk(ROWS_HELD, n_hold);
-        e++;
-        return epoch_start();
-      }
-      return mode == ROWS_PLAIN && at < n_va ? list_chunk(ROWS_PLAIN, n_va) : (int)SC_END;
-    };
-
-    Regs R;
-    int64_t gstep = 0;
-    int c2 = epoch_start();  // the chunk at the position above
-    if (resume) {
-      gstep = P.step_begin;
-      e = (int)(gstep / steps);
-      st = (int)(gstep % steps);
-      at = st * bs;
-      c2 = e < epochs ? training() : score_start();
-    }
-    load(R, resume ? P.state_in : nullptr);
-
-    OptC oc;
-    const int solver = pin(it.solver);
-    oc.adam = solver == BBO_ADAM;
-    oc.nest = it.nesterov != 0;
-    oc.b1 = pin(it.beta1);
-    oc.b2 = pin(it.beta2);
-    oc.omb1 = uniform(1.f - it.beta1);
-    oc.omb2 = uniform(1.f - it.beta2);
-    oc.eps = pin(it.eps);
-    oc.mu = pin(it.momentum);
-    oc.lr = it.lr;
-    oc.lr_t = it.lr;
-    oc.am = 0.f;
-    float lr_tab = 0.f;      // Adam: the step sizes of 64 steps, one per lane
-    int64_t lr_base = -64;   // ... the first of them
-
-    if (tabled) {  // rows of the training list in the order of the early-stopping cut
-      uint16_t* sl = u16(y.o_sl);
-      for (int p = threadIdx.x; p < n_tr; p += blockDim.x)
-        sl[p] = (uint16_t)tr[sp.n_hold ? (int)perm_index(sp.ksplit, (uint32_t)n_tr, (uint32_t)p) : p];
-      __syncthreads();
-    }
-    float xr[NX], yv = 0.f;
-#pragma unroll
-    for (int i = 0; i < NX; i++) xr[i] = 0.f;
-    int b = 0, par = 0;  // input buffer and exchange parity of the current chunk
-    int built = -1;      // the last epoch whose rows have been tabled
-    int c0 = SC_NONE, c1 = SC_NONE;  // the chunk being worked on; the one whose inputs are on their way in registers
-    int e_lr = e - 1;                // epoch of the step being worked on (set when one opens)
-    if (resume && st > 0) e_lr = e;
-    double lsum = 0.0, hits = 0.0;  // the lane's share of the summed data loss: of the epoch, or of a scoring pass
-    float* rec = nullptr;
-    Plateau plateau;
-    bool have_best = false;
-    float inv_mb = inv_full;
-    for (int phase = 0; phase < 2; phase++) {  // training with its stopping rule; the score
-    if (phase == 1 && have_best) restore_best(R);  // the best epoch's model is the one scored
-    while ((c0 & SC_MODE) != SC_END && (phase == 1 || sc_mode(c0) != ROWS_PLAIN)) {
-      const bool train = sc_mode(c0) == ROWS_EPOCH, live = (c0 & SC_MODE) != SC_NONE;
-      const int bn = b == 2 ? 0 : b + 1, rows = c0 & SC_ROWS, nrt = (rows + 15) / 16;
-      if (sc_mode(c1) <= ROWS_PLAIN) commit(c1, bn, xr, yv);
-      // the rows of the chunk whose inputs are requested next: its epoch's table if it opens one, or a row list
-      if ((c2 & SC_MODE) != SC_END) {
-        if (!tabled || sc_mode(c2) == ROWS_PLAIN) {
-          park_rows(c2, at, e, par, tr, va, sp, km);
-        } else if (sc_mode(c2) == ROWS_EPOCH && e != built) {
-          build_epoch(key_epoch(km, e));
-          built = e;
-        }
-      }
-      if (c0 & SC_FIRST) {
-        if (train) {  // first chunk of a step
-          const bool last = c0 & SC_RAGGED;
-          oc.am = last ? am_last : am_full;
-          inv_mb = last ? inv_last : inv_full;
-          if (c0 & SC_EPOCH) {
-            e_lr++;
-            lsum = 0.0;
-          }
-          if (oc.adam) {
-            if (gstep >= lr_base + 64) {
-              // beta^t of the next 64 steps, a step per lane, by repeated squaring in double
-              lr_base = gstep;
-              float f1 = it.beta1, f2 = it.beta2;
-              asm volatile("" : "+s"(f1), "+s"(f2));  // converted here, not ahead of the loop
-              double q1 = (double)f1, q2 = (double)f2, b1t = 1.0, b2t = 1.0;
-#pragma unroll 1
-              for (uint64_t t = (uint64_t)(gstep + 1) + (threadIdx.x & 63); __any(t != 0); t >>= 1) {
-                b1t *= t & 1 ? q1 : 1.0;
-                b2t *= t & 1 ? q2 : 1.0;
-                q1 *= q1;
-                q2 *= q2;
-              }
-              lr_tab = (float)((double)it.lr * sqrt(1.0 - b2t) / (1.0 - b1t));
-            }
-            oc.lr_t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lr_tab), (int)(gstep - lr_base)));
-          } else {
-            oc.lr = uniform(epoch_lr(it.lr, it.power_t, e_lr, n_fit));
-          }
-          rec = nullptr;
-          if (traced && gstep >= P.step_begin && gstep < P.step_end) {
-            rec = P.trace_out + (gstep - P.step_begin) * (1 + 2 * (int64_t)y.P);
-            const double pen = penalty_sum(R);
-            // the step's loss is the difference this step makes to the epoch's sum; both starting points wait in LDS
-            const double before = sm_wavesum_d(lsum);
-            if (threadIdx.x == 0) {
-              trace_stash[0] = pen;
-              trace_stash[1] = before;
-            }
-          }
-          zero_grad(R);
-        } else {
-          lsum = hits = 0.0;
-        }
-      }
-      f32x4 acc[NT][4];
-      if (live) forward(R, b, par, nrt, acc);
-      __syncthreads();  // the outputs' shares, the next chunk's inputs and the rows of the one after it
-      if ((c2 & SC_MODE) != SC_END) fetch(c2, at, par, xr, yv);  // in flight until the next chunk is under way
-      bool stop = false;
-      if (live) {
-        outputs(R, b, par, rows, train, inv_mb, lsum, hits);
-        if (train) {
-          backward(R, b, nrt, acc);
-          if (c0 & SC_LAST) {  // last chunk of the step
-            if (rec) record<true>(R, oc.am, rec + 1);
-            if (oc.adam)
-              update<true>(R, oc);
-            else
-              update<false>(R, oc);
-            if (rec) {
-              record<false>(R, oc.am, rec + 1 + y.P);
-              const double after = sm_wavesum_d(lsum);
-              const float mb = c0 & SC_RAGGED ? mb_last : (float)bs;
-              if (threadIdx.x == 0) rec[0] = (float)((after - trace_stash[1] + 0.5 * (double)it.alpha * trace_stash[0]) / (double)mb);
-            }
-            gstep++;
-          }
-        }
-        // the end of an epoch (with the rows set aside, if any): the stopping rule, decided alike in every wave
-        if (c0 & SC_DECIDE) {
-          const float watched = (float)(sm_wavesum_d(lsum) / (double)(float)(n_hold ? n_hold : n_fit));
-          stop = plateau.stop_after(watched, it.tol, it.patience);
-          if (n_hold && plateau.improved) {
-            keep_best(R);
-            have_best = true;
-          }
-        }
-      }
-      if (uniform(stop ? 1 : 0) && sc_mode(c1) == ROWS_EPOCH) {  // what is already on its way is dropped, and the pipeline starts over
-        __syncthreads();
-        c2 = score_start();
-        c0 = c1 = SC_NONE;
-      } else {
-        c0 = c1;
-        c1 = c2;
-        c2 = next(c2);
-        b = bn;
-      }
-      par ^= 1;
-    }
-    }
-    lsum = sm_wavesum_d(lsum);
-    hits = sm_wavesum_d(hits);
-    if (threadIdx.x == 0) {
-      float* out = P.item_out + 2 * ((int64_t)it.b * P.n_folds + fl);
-      out[0] = n_va > 0 ? (float)(lsum / (double)n_va) : __builtin_nanf("");
-      out[1] = n_va > 0 ? (float)(hits / (double)n_va) : __builtin_nanf("");  // accuracy | mean absolute error
-    }
-  }
 };
 
 template <int KT, int NT, int CO, int W>
@@ -1050,8 +1133,7 @@ void k_train_small(const TrainParams P) {
     const int item = __builtin_amdgcn_readfirstlane(s_item);
     if (item >= P.n_items) break;
     const __attribute__((address_space(4))) SItem* si = (const __attribute__((address_space(4))) SItem*)P.items + item;
-    Small<KT, NT, CO, W> T{P, si->d, si->y, smem, (float*)(P.slots + (uint64_t)blockIdx.x * P.slot_bytes), red, trace_stash,
-                           nullptr, nullptr, 0, 0, 0, 0, 0, 0, 0};
+    Small<KT, NT, CO, W> T(P, si->d, si->y, smem, (float*)(P.slots + (uint64_t)blockIdx.x * P.slot_bytes), red, trace_stash);
     T.run();
   }
 }
