@@ -900,11 +900,9 @@ int kernel_class(const int32_t* dims, int L, int64_t n, int dtype) {
     return n * (int64_t)d < 0x7fffffff && linear_eligible(dims, L) ? KC_LINEAR : KC_GENERIC;
   }
   if (n * (int64_t)d >= 0x7fffffff) return KC_GENERIC;
-  if ((uint64_t)n * (uint64_t)d < (1ull << 30) && small_eligible(dims, L)) return KC_SMALL;  // 32-bit byte offsets into X
-  if (mid_eligible(dims, L)) {
-    MLay my;
-    make_mlay(my, dims, n);
-    if (my.lds_total <= MD_LDS_LIMIT) return KC_MID;
+  if ((uint64_t)n * (uint64_t)d < (1ull << 30)) {  // 32-bit byte offsets into X
+    if (small_eligible(dims, L)) return KC_SMALL;
+    if (mid_cut(dims, L).waves) return KC_MID;
   }
   return linear_eligible(dims, L) ? KC_LINEAR : KC_GENERIC;
 }
@@ -920,7 +918,12 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     SubPlan sp;
     sp.kc = kc;
     sp.cut = cut;
-    sp.item_bytes = kc == KC_TILED ? sizeof(TItem) : (kc == KC_SMALL ? sizeof(SItem) : (kc == KC_MID ? sizeof(MItem) : sizeof(ItemDesc)));
+    switch (kc) {
+      case KC_TILED: sp.item_bytes = sizeof(TItem); break;
+      case KC_SMALL: sp.item_bytes = sizeof(SItem); break;
+      case KC_MID: sp.item_bytes = sizeof(MItem); break;
+      default: sp.item_bytes = sizeof(ItemDesc);
+    }
     pl.sub.push_back(std::move(sp));
     return pl.sub.back();
   };
@@ -954,7 +957,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
       params += (double)it.dims[l] * it.dims[l + 1];
     }
     const int k = kernel_class(it.dims, it.L, n, dtype);
-    const SmallCut cut = k == KC_SMALL ? small_cut(it.dims) : SmallCut{0, 0, 0, 0};
+    const SmallCut cut = k == KC_SMALL ? small_cut(it.dims) : (k == KC_MID ? mid_cut(it.dims, it.L) : SmallCut{0, 0, 0, 0});
     SubPlan& sp = launch_of(k, cut);
     uint64_t slot_bytes = 0;
     uint32_t lds_bytes = 0;
@@ -970,8 +973,8 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
       lds_bytes = sy.lds_total;
     } else if (k == KC_MID) {
       MLay my;
-      make_mlay(my, it.dims, n);  // the moments of both layers live in global memory
-      slot_bytes = my.g_total;
+      make_mlay(my, it.dims, n, cut);
+      slot_bytes = 4ull * my.slot_floats;
       lds_bytes = my.lds_total;
     } else if (k == KC_GENERIC) {
       Layout y;
@@ -1003,6 +1006,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     if (rc) return rc;
     size_t units = sp.items.size();
     if (k == KC_SMALL) max_slots *= small_per_cu(sp.cut, sp.lds_bytes);
+    if (k == KC_MID) max_slots *= md_per_cu(sp.cut, sp.lds_bytes);
     if (k == KC_LINEAR) {
       // as many workgroups as the LDS lets a CU hold, each of `waves` wavefronts with a model apiece
       const int c_out = n_classes >= 2 ? n_classes : 1;
@@ -1238,7 +1242,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
           MItem mi;
           memset(&mi, 0, sizeof(mi));
           mi.d = sp.items[i];
-          make_mlay(mi.y, sp.items[i].dims, n);
+          make_mlay(mi.y, sp.items[i].dims, n, sp.cut);
           memcpy(at + i * sizeof(MItem), &mi, sizeof(MItem));
         } else {
           memcpy(at + i * sizeof(ItemDesc), &sp.items[i], sizeof(ItemDesc));
@@ -1302,8 +1306,8 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
          : (t.kt == 3 ? small_kernel3(t.nt, t.waves, t.co) : small_kernel4(t.nt, t.waves, t.co)));
       threads = 64 * t.waves;
     } else if (k == KC_MID) {
-      fn = mid_kernel(md_kt(d));
-      threads = MD_THREADS;
+      fn = mid_kernel(sp.cut.kt, sp.cut.nt, sp.cut.waves);
+      threads = 64 * sp.cut.waves;
     } else if (k == KC_LINEAR) {
       fn = linear_kernel(ln_co(c_out), ln_ki(d));
       threads = 64 * sp.waves;

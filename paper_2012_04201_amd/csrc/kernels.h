@@ -10,5 +10,5 @@ BBO_HIDDEN const void* small_kernel1(int nt, int waves, int co);
 BBO_HIDDEN const void* small_kernel2(int nt, int waves, int co);
 BBO_HIDDEN const void* small_kernel3(int nt, int waves, int co);
 BBO_HIDDEN const void* small_kernel4(int nt, int waves, int co);
-BBO_HIDDEN const void* mid_kernel(int kt);             // 16-wide k tiles of the input layer
-BBO_HIDDEN const void* linear_kernel(int co, int ki);  // padded outputs, rows of W per lane
+BBO_HIDDEN const void* mid_kernel(int kt, int nt, int waves);  // k tiles of the input layer, unit tiles per wave, waves
+BBO_HIDDEN const void* linear_kernel(int co, int ki);          // padded outputs, rows of W per lane
