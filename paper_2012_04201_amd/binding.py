@@ -53,6 +53,7 @@ class BboError(RuntimeError):
 
 
 _lib = None
+_pack = None
 
 
 def lib():
@@ -75,28 +76,42 @@ def _check(rc):
 
 
 def make_hparams(dicts):
-    arr = (HParams * max(len(dicts), 1))()
-    for h, dct in zip(arr, dicts):
-        hidden = list(dct.get("hidden", []))
-        h.n_hidden = len(hidden)
-        for i, w in enumerate(hidden[:MAX_HIDDEN]):
-            h.hidden[i] = int(w)
-        h.solver = SGD if dct.get("solver", "adam") == "sgd" else ADAM
-        h.nesterov = int(bool(dct.get("nesterov", False)))
-        h.batch_size = int(dct.get("batch_size", 0))
-        h.epochs = int(dct.get("epochs", 1))
-        h.lr = float(dct.get("lr", 1e-3))
-        h.alpha = float(dct.get("alpha", 0.0))
-        h.momentum = float(dct.get("momentum", 0.9))
-        h.beta1 = float(dct.get("beta1", 0.9))
-        h.beta2 = float(dct.get("beta2", 0.999))
-        h.eps = float(dct.get("eps", 1e-8))
-        h.seed = int(dct.get("seed", 0))
-        h.power_t = float(dct.get("power_t", 0.0))
-        h.tol = float(dct.get("tol", 0.0))
-        h.n_iter_no_change = int(dct.get("n_iter_no_change", 0))
-        h.validation_fraction = float(dct.get("validation_fraction", 0.0))
+    """The records of a list of suggestions."""
+    global _pack
+    if _pack is None:
+        from . import _pack as native  # built with the library
+        _pack = native.pack
+    if not isinstance(dicts, (list, tuple)):
+        dicts = list(dicts)
+    n = len(dicts)
+    arr = (HParams * max(n, 1))()
+    done = _pack(dicts, C.addressof(arr))
+    while done < n:  # a suggestion of other types than plain Python's
+        _set_hparams(arr[done], dicts[done])
+        done = _pack(dicts, C.addressof(arr), done + 1)
     return arr
+
+
+def _set_hparams(h, dct):
+    hidden = list(dct.get("hidden", []))
+    h.n_hidden = len(hidden)
+    for i, w in enumerate(hidden[:MAX_HIDDEN]):
+        h.hidden[i] = int(w)
+    h.solver = SGD if dct.get("solver", "adam") == "sgd" else ADAM
+    h.nesterov = int(bool(dct.get("nesterov", False)))
+    h.batch_size = int(dct.get("batch_size", 0))
+    h.epochs = int(dct.get("epochs", 1))
+    h.lr = float(dct.get("lr", 1e-3))
+    h.alpha = float(dct.get("alpha", 0.0))
+    h.momentum = float(dct.get("momentum", 0.9))
+    h.beta1 = float(dct.get("beta1", 0.9))
+    h.beta2 = float(dct.get("beta2", 0.999))
+    h.eps = float(dct.get("eps", 1e-8))
+    h.seed = int(dct.get("seed", 0))
+    h.power_t = float(dct.get("power_t", 0.0))
+    h.tol = float(dct.get("tol", 0.0))
+    h.n_iter_no_change = int(dct.get("n_iter_no_change", 0))
+    h.validation_fraction = float(dct.get("validation_fraction", 0.0))
 
 
 def _ptr(t):

@@ -1,6 +1,7 @@
-"""Builds libbbo_mlp.so (HIP, gfx950) in-tree with hipcc, the kernel families side by side."""
+"""Builds libbbo_mlp.so (HIP, gfx950) in-tree with hipcc, the kernel families side by side, and the packer of suggestions."""
 import os
 import subprocess
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -17,7 +18,7 @@ def _run(cmd):
     res = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + err)
+        raise RuntimeError(cmd[0] + " failed:\n" + err)
     return err
 
 
@@ -31,6 +32,8 @@ def build_lib(verbose=False):
     err = "\n".join(e for e in errs if e.strip())
     if verbose and err:
         print(err)
+    _run(["gcc", "-O2", "-shared", "-fPIC", "-Wall", "-I" + sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "pack_hparams.c"), "-o", os.path.join(HERE, "_pack.so")])
     return LIB
 
 

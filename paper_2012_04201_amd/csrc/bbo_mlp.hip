@@ -252,6 +252,7 @@ struct Trainer {
   const Layout& y;
   char* slot;
   double* red;
+  int fl;  // which row list
 
   __device__ OpT* op(uint64_t off) const { return (OpT*)(slot + off); }
   __device__ float* fp(uint64_t off) const { return (float*)(slot + off); }
@@ -260,7 +261,7 @@ struct Trainer {
   // Initial parameters: Glorot-uniform, element i of the packed W[in][out],
   // b[out] order hashed with the tensor's key.
   __device__ void init_params() const {
-    const uint64_t km = key_model(it.seed, it.fold);
+    const uint64_t km = key_model(it.seed, fl + P.fold_base);
     for (int l = 0; l < y.L; l++) {
       const int fi = y.dims[l], fo = y.dims[l + 1], ld = y.ld[l];
       float* W = fp(y.w[l]);
@@ -540,11 +541,10 @@ struct Trainer {
   }
 
   __device__ void run() const {
-    const int f = it.fold, fl = it.fold - P.fold_base;  // fl: which row list
     const int n_tr = P.counts[2 * fl], n_va = P.counts[2 * fl + 1];
     const int32_t* tr = P.train_idx + (int64_t)fl * P.n;
     const int32_t* va = P.val_idx + (int64_t)fl * P.n;
-    const uint64_t km = key_model(it.seed, f);
+    const uint64_t km = key_model(it.seed, fl + P.fold_base);
     const RowSplit sp = row_split(km, it.patience, it.val_frac, n_tr);
     const int n_fit = sp.n_fit;
     const int bs = eff_batch(it.batch_size, n_fit);
@@ -667,11 +667,11 @@ __global__ __launch_bounds__(NTHREADS) void k_train(const TrainParams P) {
     const int item = s_item;
     if (item >= P.n_items) break;
     if (threadIdx.x == 0) {
-      desc = ((const ItemDesc*)P.items)[item];
+      desc = ((const ItemDesc*)P.items)[item / P.n_folds];
       make_layout(lay, desc.dims, desc.L, desc.rows_cap, Op<OpT>::KSTEP, (int)sizeof(OpT));
     }
     __syncthreads();
-    Trainer<OpT> T{P, desc, lay, slot, red};
+    Trainer<OpT> T{P, desc, lay, slot, red, item % P.n_folds};
     T.run();
   }
 }
@@ -795,20 +795,19 @@ void fill_dims(const bbo_mlp_hparams& h, int d, int n_classes, int32_t* dims, in
   dims[*L] = n_classes >= 2 ? n_classes : 1;
 }
 
-// One launch: the items of a call that run on one variant of one kernel.
+// One launch: the suggestions of a call that run on one variant of one kernel, with all their folds.
 struct SubPlan {
   int kc = KC_GENERIC;          // kernel
   SmallCut cut = {0, 0, 0, 0};  // register-resident kernel: how its models are cut (all alike in one launch)
-  std::vector<ItemDesc> items;  // most expensive first
-  std::vector<double> cost;     // estimated, by item (before sorting)
+  std::vector<int32_t> order;   // its suggestions, most expensive first
   uint64_t slot_bytes = 0;      // global memory per resident workgroup
   int n_slots = 0;              // workgroups to launch
   uint32_t lds_bytes = 0;       // dynamic LDS per workgroup
   int waves = 0;                // linear kernel: wavefronts per workgroup
-  size_t item_bytes = 0;        // size of its item record
-  uint64_t o_items = 0;         // workspace byte offset of its item array
+  size_t item_bytes = 0;        // size of a suggestion's record
+  uint64_t o_items = 0;         // workspace byte offset of its records
   uint64_t o_slots = 0;         // ... and of its workgroups' slots
-  double longest = 0;           // estimated cost of its most expensive item
+  double longest = 0;           // estimated cost of its most expensive suggestion
 };
 
 constexpr int MAX_LAUNCHES = 64;  // queue counters in the workspace
@@ -907,14 +906,45 @@ int kernel_class(const int32_t* dims, int L, int64_t n, int dtype) {
   return linear_eligible(dims, L) ? KC_LINEAR : KC_GENERIC;
 }
 
+// The record of suggestion b.
+void fill_item(ItemDesc& it, const bbo_mlp_hparams& h, int b, int64_t n, int d, int n_classes, int kstep) {
+  fill_dims(h, d, n_classes, it.dims, &it.L);
+  it.seed = h.seed;
+  it.b = b;
+  it.solver = h.solver;
+  it.nesterov = h.nesterov;
+  it.batch_size = h.batch_size;
+  it.epochs = h.epochs;
+  it.lr = h.lr;
+  it.alpha = h.alpha;
+  it.momentum = h.momentum;
+  it.beta1 = h.beta1;
+  it.beta2 = h.beta2;
+  it.eps = h.eps;
+  it.power_t = h.power_t;
+  it.tol = h.tol;
+  it.patience = h.n_iter_no_change;
+  it.val_frac = h.validation_fraction;
+  const int64_t bs = (h.batch_size <= 0 || h.batch_size > n) ? n : h.batch_size;
+  it.rows_cap = rup((int)std::max<int64_t>(bs, 1), kstep);
+  for (int l = 0; l < it.L; l++) it.bound[l] = (float)std::sqrt(6.0 / (double)(it.dims[l] + it.dims[l + 1]));
+}
+
+// The launches of a call, their workgroups and where everything lies in the workspace.
 int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_base, const bbo_mlp_hparams* hp, int B,
               int dtype) {
   const int kstep = dtype == BBO_F32 ? 16 : 32, opsz = dtype == BBO_F32 ? 4 : 2;
   const double n_tr_est = n_folds > 1 && fold_base >= 0 ? (double)n * (n_folds - 1) / n_folds : (double)n;
   pl.sub.clear();
+  std::vector<double> cost(B);
+  int last = 0;  // suggestions of the same shape come in runs
   auto launch_of = [&](int kc, const SmallCut& cut) -> SubPlan& {
-    for (SubPlan& sp : pl.sub)
+    const int n_sub = (int)pl.sub.size();
+    for (int i = 0; i < n_sub; i++) {
+      SubPlan& sp = pl.sub[last];
       if (sp.kc == kc && sp.cut.nt == cut.nt && sp.cut.waves == cut.waves) return sp;
+      last = last + 1 < n_sub ? last + 1 : 0;
+    }
     SubPlan sp;
     sp.kc = kc;
     sp.cut = cut;
@@ -929,82 +959,57 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
   };
   for (int b = 0; b < B; b++) {
     const bbo_mlp_hparams& h = hp[b];
-    ItemDesc it;
-    memset(&it, 0, sizeof(it));
-    fill_dims(h, d, n_classes, it.dims, &it.L);
-    it.seed = h.seed;
-    it.b = b;
-    it.solver = h.solver;
-    it.nesterov = h.nesterov;
-    it.batch_size = h.batch_size;
-    it.epochs = h.epochs;
-    it.lr = h.lr;
-    it.alpha = h.alpha;
-    it.momentum = h.momentum;
-    it.beta1 = h.beta1;
-    it.beta2 = h.beta2;
-    it.eps = h.eps;
-    it.power_t = h.power_t;
-    it.tol = h.tol;
-    it.patience = h.n_iter_no_change;
-    it.val_frac = h.validation_fraction;
+    int32_t dims[MAXL + 1];
+    int L;
+    fill_dims(h, d, n_classes, dims, &L);
     const int64_t bs = (h.batch_size <= 0 || h.batch_size > n) ? n : h.batch_size;
-    it.rows_cap = rup((int)std::max<int64_t>(bs, 1), kstep);
     double fps = 0, params = 0;
-    for (int l = 0; l < it.L; l++) {
-      it.bound[l] = (float)std::sqrt(6.0 / (double)(it.dims[l] + it.dims[l + 1]));
-      fps += 2.0 * it.dims[l] * it.dims[l + 1] * (l == 0 ? 2 : 3);
-      params += (double)it.dims[l] * it.dims[l + 1];
+    for (int l = 0; l < L; l++) {
+      fps += 2.0 * dims[l] * dims[l + 1] * (l == 0 ? 2 : 3);
+      params += (double)dims[l] * dims[l + 1];
     }
-    const int k = kernel_class(it.dims, it.L, n, dtype);
-    const SmallCut cut = k == KC_SMALL ? small_cut(it.dims) : (k == KC_MID ? mid_cut(it.dims, it.L) : SmallCut{0, 0, 0, 0});
+    const int k = kernel_class(dims, L, n, dtype);
+    const SmallCut cut = k == KC_SMALL ? small_cut(dims) : (k == KC_MID ? mid_cut(dims, L) : SmallCut{0, 0, 0, 0});
     SubPlan& sp = launch_of(k, cut);
     uint64_t slot_bytes = 0;
     uint32_t lds_bytes = 0;
     if (k == KC_TILED) {
       TLay ty;
-      make_tlay(ty, it.dims, it.L);
+      make_tlay(ty, dims, L);
       slot_bytes = ty.total;
       lds_bytes = ty.lds_total;
     } else if (k == KC_SMALL) {
       SLay sy;
-      make_slay(sy, it.dims, n, cut);
+      make_slay(sy, dims, n, cut);
       slot_bytes = 4ull * sy.slot_floats;
       lds_bytes = sy.lds_total;
     } else if (k == KC_MID) {
       MLay my;
-      make_mlay(my, it.dims, n, cut);
+      make_mlay(my, dims, n, cut);
       slot_bytes = 4ull * my.slot_floats;
       lds_bytes = my.lds_total;
     } else if (k == KC_GENERIC) {
       Layout y;
-      make_layout(y, it.dims, it.L, it.rows_cap, kstep, opsz);
+      make_layout(y, dims, L, rup((int)std::max<int64_t>(bs, 1), kstep), kstep, opsz);
       slot_bytes = y.total;
     }  // KC_LINEAR: a model per wavefront, nothing kept in global memory
     sp.slot_bytes = std::max(sp.slot_bytes, slot_bytes);
     sp.lds_bytes = std::max(sp.lds_bytes, lds_bytes);
     const double steps = std::ceil(n_tr_est / (double)std::max<int64_t>(bs, 1));
-    const double c = (double)h.epochs * (n_tr_est * fps + steps * (params * 24.0 + 2.0e4));
-    for (int f = 0; f < n_folds; f++) {
-      it.fold = f + fold_base;
-      sp.items.push_back(it);
-      sp.cost.push_back(c);
-    }
+    cost[b] = (double)h.epochs * (n_tr_est * fps + steps * (params * 24.0 + 2.0e4));
+    sp.order.push_back(b);
   }
   pl.n_items = (size_t)B * n_folds;
   if (pl.sub.size() > (size_t)MAX_LAUNCHES) return fail(BBO_UNSUPPORTED, "too many kernel variants in one call");
   for (SubPlan& sp : pl.sub) {
     const int k = sp.kc;
-    std::vector<int> order(sp.items.size());
-    for (size_t i = 0; i < order.size(); i++) order[i] = (int)i;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b2) { return sp.cost[a] > sp.cost[b2]; });
-    std::vector<ItemDesc> sorted(sp.items.size());
-    for (size_t i = 0; i < order.size(); i++) sorted[i] = sp.items[order[i]];
-    sp.items.swap(sorted);
+    std::sort(sp.order.begin(), sp.order.end(),
+              [&](int a, int b2) { return cost[a] != cost[b2] ? cost[a] > cost[b2] : a < b2; });
+    const size_t n_items = sp.order.size() * n_folds;
     int max_slots = 0;
     int rc = k == KC_GENERIC ? device_slots(dtype, &max_slots) : device_cus(&max_slots);
     if (rc) return rc;
-    size_t units = sp.items.size();
+    size_t units = n_items;
     if (k == KC_SMALL) max_slots *= small_per_cu(sp.cut, sp.lds_bytes);
     if (k == KC_MID) max_slots *= md_per_cu(sp.cut, sp.lds_bytes);
     if (k == KC_LINEAR) {
@@ -1013,12 +1018,12 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
       sp.waves = ln_waves(d, c_out, n);
       sp.lds_bytes = (uint32_t)sp.waves * ln_wave_bytes(d, c_out, n);
       max_slots *= std::max(1, std::min(8, (int)(160u * 1024u / sp.lds_bytes)));
-      units = (sp.items.size() + sp.waves - 1) / sp.waves;
+      units = (n_items + sp.waves - 1) / sp.waves;
     }
     sp.slot_bytes = (sp.slot_bytes + 255) & ~(uint64_t)255;
     if (k == KC_LINEAR) sp.slot_bytes = 0;
     sp.n_slots = (int)std::min<size_t>(units, (size_t)max_slots);
-    sp.longest = sp.cost[order[0]];
+    sp.longest = cost[sp.order[0]];
   }
   // the launch with the longest single model is enqueued first: nothing can make up for starting that one late
   std::stable_sort(pl.sub.begin(), pl.sub.end(), [](const SubPlan& a, const SubPlan& b2) { return a.longest > b2.longest; });
@@ -1030,7 +1035,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
   };
   const uint64_t nn = (uint64_t)std::max<int64_t>(n, 1);
   pl.o_items = off;
-  for (SubPlan& sp : pl.sub) sp.o_items = take(sp.item_bytes * sp.items.size());
+  for (SubPlan& sp : pl.sub) sp.o_items = take(sp.item_bytes * sp.order.size());
   pl.items_bytes = off - pl.o_items;
   pl.o_queue = take(4 * MAX_LAUNCHES);
   pl.o_out = take(8ull * std::max<size_t>(pl.n_items, 1));
@@ -1054,7 +1059,8 @@ struct Staging {
 };
 thread_local std::vector<Staging> g_stage;
 
-int stage_items(const void* src, size_t bytes, void* dst, hipStream_t s) {
+// The thread's staging buffer with room for `bytes`, free to be written.
+int stage_buffer(size_t bytes, Staging** out) {
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   Staging* st = nullptr;
@@ -1077,7 +1083,10 @@ int stage_items(const void* src, size_t bytes, void* dst, hipStream_t s) {
     HIP_TRY(hipHostMalloc(&st->ptr, bytes, hipHostMallocDefault));
     st->cap = bytes;
   }
-  memcpy(st->ptr, src, bytes);
+  *out = st;
+  return BBO_OK;
+}
+int stage_send(Staging* st, size_t bytes, void* dst, hipStream_t s) {
   HIP_TRY(hipMemcpyAsync(dst, st->ptr, bytes, hipMemcpyHostToDevice, s));
   HIP_TRY(hipEventRecord(st->ev, s));
   st->pending = true;
@@ -1218,39 +1227,40 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
   if (workspace_bytes < pl.total) return fail(BBO_WORKSPACE_TOO_SMALL, "workspace too small");
   hipStream_t s = (hipStream_t)stream;
   char* ws = (char*)workspace;
+  // (first, so that it runs while the host fills the records in)
+  int32_t* queues = (int32_t*)(ws + pl.o_queue);  // one work-queue counter per launch, reset by k_fold_lists
+  hipLaunchKernelGGL(k_fold_lists, dim3(n_folds), dim3(NTHREADS), 0, s, fold_idx, n, (int32_t*)(ws + pl.o_train),
+                     (int32_t*)(ws + pl.o_val), (int32_t*)(ws + pl.o_counts), queues, MAX_LAUNCHES, fold_base);
+  HIP_TRY(hipGetLastError());
   {
-    // the item arrays of all kernels, laid out as in the workspace, in one staged copy
+    // the records of all launches, laid out as in the workspace, in one copy
     static thread_local std::vector<char> blob;  // kept between calls
-    blob.assign(pl.items_bytes, 0);
+    Staging* st = nullptr;
+    char* records;
+    if (static_ws) {
+      blob.resize(pl.items_bytes);
+      records = blob.data();
+    } else {
+      if ((rc = stage_buffer(pl.items_bytes, &st))) return rc;
+      records = (char*)st->ptr;
+    }
+    const int kstep = dtype == BBO_F32 ? 16 : 32;
     for (const SubPlan& sp : pl.sub) {
-      const int k = sp.kc;
-      char* at = blob.data() + (sp.o_items - pl.o_items);
-      for (size_t i = 0; i < sp.items.size(); i++) {
-        if (k == KC_TILED) {
-          TItem ti;
-          memset(&ti, 0, sizeof(ti));
-          ti.d = sp.items[i];
-          make_tlay(ti.y, sp.items[i].dims, sp.items[i].L);
-          memcpy(at + i * sizeof(TItem), &ti, sizeof(TItem));
-        } else if (k == KC_SMALL) {
-          SItem si;
-          memset(&si, 0, sizeof(si));
-          si.d = sp.items[i];
-          make_slay(si.y, sp.items[i].dims, n, sp.cut);
-          memcpy(at + i * sizeof(SItem), &si, sizeof(SItem));
-        } else if (k == KC_MID) {
-          MItem mi;
-          memset(&mi, 0, sizeof(mi));
-          mi.d = sp.items[i];
-          make_mlay(mi.y, sp.items[i].dims, n, sp.cut);
-          memcpy(at + i * sizeof(MItem), &mi, sizeof(MItem));
-        } else {
-          memcpy(at + i * sizeof(ItemDesc), &sp.items[i], sizeof(ItemDesc));
+      char* at = records + (sp.o_items - pl.o_items);
+      for (const int32_t b : sp.order) {
+        memset(at, 0, sp.item_bytes);
+        ItemDesc& it = *(ItemDesc*)at;  // every record begins with it
+        fill_item(it, hp[b], b, n, d, n_classes, kstep);
+        switch (sp.kc) {
+          case KC_TILED: make_tlay(((TItem*)at)->y, it.dims, it.L); break;
+          case KC_SMALL: make_slay(((SItem*)at)->y, it.dims, n, sp.cut); break;
+          case KC_MID: make_mlay(((MItem*)at)->y, it.dims, n, sp.cut); break;
         }
+        at += sp.item_bytes;
       }
     }
-    rc = static_ws ? poke_items(blob.data(), blob.size(), ws + pl.o_items, s)
-                   : stage_items(blob.data(), blob.size(), ws + pl.o_items, s);
+    rc = static_ws ? poke_items(records, pl.items_bytes, ws + pl.o_items, s)
+                   : stage_send(st, pl.items_bytes, ws + pl.o_items, s);
     if (rc) return rc;
   }
 
@@ -1274,10 +1284,6 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
   P.state_in = traced ? state_in : nullptr;
   P.x_bf16 = dtype == BBO_BF16;
 
-  int32_t* queues = (int32_t*)(ws + pl.o_queue);  // one work-queue counter per launch, reset by k_fold_lists
-  hipLaunchKernelGGL(k_fold_lists, dim3(n_folds), dim3(NTHREADS), 0, s, fold_idx, n, (int32_t*)(ws + pl.o_train),
-                     (int32_t*)(ws + pl.o_val), (int32_t*)(ws + pl.o_counts), queues, MAX_LAUNCHES, fold_base);
-  HIP_TRY(hipGetLastError());
   // one launch per kernel variant that has items, side by side: the first on the caller's stream
   const int n_side = std::min<int>((int)pl.sub.size() - 1, SIDE_STREAMS);
   SideStreams* side = nullptr;
@@ -1293,7 +1299,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
     P.slots = ws + sp.o_slots;
     P.queue = queues + li;
     P.slot_bytes = sp.slot_bytes;
-    P.n_items = (int)sp.items.size();
+    P.n_items = (int)(sp.order.size() * n_folds);
     const int c_out = n_classes >= 2 ? n_classes : 1;
     const void* fn;
     int threads = NTHREADS;

@@ -107,9 +107,10 @@ __device__ inline PermDomain perm_domain(uint32_t n) {
 // ---------------------------------------------------------------------------
 // Item description and per-item memory layout
 // ---------------------------------------------------------------------------
+// One suggestion; its folds share the record.
 struct ItemDesc {
   uint64_t seed;
-  int32_t b, fold, L, solver, nesterov, batch_size, epochs, rows_cap;
+  int32_t b, L, solver, nesterov, batch_size, epochs, rows_cap;
   float lr, alpha, momentum, beta1, beta2, eps;
   float power_t, tol;
   int32_t patience;
@@ -228,13 +229,13 @@ struct TrainParams {
   const int32_t* train_idx;
   const int32_t* val_idx;
   const int32_t* counts;
-  const void* items;  // ItemDesc[] (generic kernel) or TItem[] (tiled kernel), most expensive first
+  const void* items;  // records of the suggestions, most expensive first: the kernel's own (ItemDesc and layout)
   int32_t* queue;
   float* item_out;  // [B*K][2]
   char* slots;
   uint64_t slot_bytes;
   int64_t n;
-  int32_t d, n_classes, n_folds, n_items;
+  int32_t d, n_classes, n_folds, n_items;  // item i: fold list i % n_folds of suggestion i / n_folds
   int32_t fold_base;  // fold of list 0: 0 for cross-validation, -1 for the hold-out split
   // trace
   int32_t trace_item;  // b*K+fold or -1

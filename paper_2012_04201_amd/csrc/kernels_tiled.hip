@@ -16,8 +16,8 @@ __global__ __launch_bounds__(TB_THREADS) void k_train_tiled(const TrainParams P)
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item);
     if (item >= P.n_items) break;
-    const __attribute__((address_space(4))) TItem* ti = (const __attribute__((address_space(4))) TItem*)P.items + item;
-    Tiled T{P, ti->d, ti->y, slot, smem, red};
+    const __attribute__((address_space(4))) TItem* ti = (const __attribute__((address_space(4))) TItem*)P.items + item / P.n_folds;
+    Tiled T{P, ti->d, ti->y, slot, smem, red, item % P.n_folds};
     T.run();
   }
 }

@@ -307,12 +307,11 @@ struct Linear {
     }
   }
 
-  __device__ void run(const ItemDesc& it) const {
-    const int f = it.fold, fl = f - P.fold_base;
+  __device__ void run(const ItemDesc& it, int fl) const {  // fl: which row list
     const int n_tr = P.counts[2 * fl], n_va = P.counts[2 * fl + 1];
     const int32_t* tr = P.train_idx + (int64_t)fl * P.n;
     const int32_t* va = P.val_idx + (int64_t)fl * P.n;
-    const uint64_t km = key_model(it.seed, f);
+    const uint64_t km = key_model(it.seed, fl + P.fold_base);
     const RowSplit sp = row_split(km, it.patience, it.val_frac, n_tr);
     const int n_fit = sp.n_fit;
     const int bs = eff_batch(it.batch_size, n_fit);
@@ -557,7 +556,7 @@ __global__ __launch_bounds__(256) void k_train_linear(const TrainParams P) {
     __builtin_amdgcn_wave_barrier();
     const int item = __builtin_amdgcn_readfirstlane(atomicAdd(P.queue, lane == 0 ? 1 : 0));
     if (item >= P.n_items) break;
-    T.run(((const ItemDesc*)P.items)[item]);
+    T.run(((const ItemDesc*)P.items)[item / P.n_folds], item % P.n_folds);
   }
 }
 

@@ -617,8 +617,9 @@ void k_train_mid(const TrainParams P) {
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item);
     if (item >= P.n_items) break;
-    const __attribute__((address_space(4))) MItem* mi = (const __attribute__((address_space(4))) MItem*)P.items + item;
-    Mid<KT, NT, W> T(P, mi->d, mi->y, smem, (float*)(P.slots + (uint64_t)blockIdx.x * P.slot_bytes), red, trace_stash);
+    const __attribute__((address_space(4))) MItem* mi = (const __attribute__((address_space(4))) MItem*)P.items + item / P.n_folds;
+    Mid<KT, NT, W> T(P, mi->d, mi->y, smem, (float*)(P.slots + (uint64_t)blockIdx.x * P.slot_bytes), red, trace_stash,
+                       item % P.n_folds);
     T.run();
   }
 }

@@ -223,6 +223,7 @@ struct RowPipe {
   float* slot;
   double* red;
   double* trace_stash;  // thread 0's own
+  int fl;               // which row list
   // What every chunk needs of the item and the call, held in scalar registers: left to itself the compiler reloads
   // each field where it is used, a few hundred cycles every time.
   const GlobalF32* X = nullptr;
@@ -230,8 +231,8 @@ struct RowPipe {
   int d = 0, n_fit = 0, n_classes = 0, o_sl = 0, o_ep = 0, tabled = 0;
 
   __device__ __forceinline__ RowPipe(const TrainParams& P_, const ConstItemDesc& it_, ConstLay& y_, char* lds_, float* slot_,
-                                     double* red_, double* stash_)
-      : P(P_), it(it_), y(y_), lds(lds_), slot(slot_), red(red_), trace_stash(stash_) {}
+                                     double* red_, double* stash_, int fl_)
+      : P(P_), it(it_), y(y_), lds(lds_), slot(slot_), red(red_), trace_stash(stash_), fl(fl_) {}
 
   // offsets in floats; what the model keeps in LDS starts at O_OWN
   static constexpr int O_YS = NB * SM_RC * LDW, O_ROWS = O_YS + NB * SM_RC, O_OWN = O_ROWS + 2 * SM_RC;
@@ -250,7 +251,7 @@ struct RowPipe {
   }
   __device__ __forceinline__ static int wave() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
   __device__ __forceinline__ float init_value(int l, int e, bool isb) const {
-    const uint64_t kt = key_fold(key_model(it.seed, it.fold), 16 + 2 * l + (isb ? 1 : 0));
+    const uint64_t kt = key_fold(key_model(it.seed, fl + P.fold_base), 16 + 2 * l + (isb ? 1 : 0));
     const uint32_t k24 = (uint32_t)(key_fold(kt, (uint64_t)e) >> 40);
     return it.bound[l] * ((float)((int32_t)k24 - 8388608) * 0x1p-23f);
   }
@@ -334,11 +335,10 @@ struct RowPipe {
   __device__ __forceinline__ Lists lists() const {
     const ConstParams& p = params();
     const ConstItemDesc& i = item();
-    const int fl = i.fold - p.fold_base;  // which row list
     Lists l;
     l.tr = p.train_idx + (int64_t)fl * p.n;
     l.va = p.val_idx + (int64_t)fl * p.n;
-    l.km = key_model(i.seed, i.fold);
+    l.km = key_model(i.seed, fl + p.fold_base);
     l.sp = row_split(l.km, i.patience, i.val_frac, uniform(p.counts[2 * fl]));
     return l;
   }
@@ -394,9 +394,8 @@ struct RowPipe {
 
   __device__ __forceinline__ void run() {
     Self& self = *static_cast<Self*>(this);
-    const int fl = it.fold - P.fold_base;  // which row list
     const int n_tr = uniform(P.counts[2 * fl]), n_va = uniform(P.counts[2 * fl + 1]);
-    const RowSplit sp = row_split(key_model(it.seed, it.fold), it.patience, it.val_frac, n_tr);
+    const RowSplit sp = row_split(key_model(it.seed, fl + P.fold_base), it.patience, it.val_frac, n_tr);
     X = pin((const GlobalF32*)P.X);
     Y = pin((const GlobalI32*)P.y);
     d = pin(y.p.d);
@@ -522,7 +521,7 @@ struct RowPipe {
           if (!tabled || sc_mode(c2) == ROWS_PLAIN) {
             park_rows(c2, at, e, par);
           } else if (sc_mode(c2) == ROWS_EPOCH && e != built) {
-            build_epoch(key_epoch(key_model(item().seed, item().fold), e));
+            build_epoch(key_epoch(key_model(item().seed, fl + params().fold_base), e));
             built = e;
           }
         }
@@ -1132,8 +1131,9 @@ void k_train_small(const TrainParams P) {
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item);
     if (item >= P.n_items) break;
-    const __attribute__((address_space(4))) SItem* si = (const __attribute__((address_space(4))) SItem*)P.items + item;
-    Small<KT, NT, CO, W> T(P, si->d, si->y, smem, (float*)(P.slots + (uint64_t)blockIdx.x * P.slot_bytes), red, trace_stash);
+    const __attribute__((address_space(4))) SItem* si = (const __attribute__((address_space(4))) SItem*)P.items + item / P.n_folds;
+    Small<KT, NT, CO, W> T(P, si->d, si->y, smem, (float*)(P.slots + (uint64_t)blockIdx.x * P.slot_bytes), red, trace_stash,
+                           item % P.n_folds);
     T.run();
   }
 }

@@ -186,6 +186,7 @@ struct Tiled {
   char* slot;
   char* lds;
   double* red;
+  int fl;  // which row list
 
   // The thread index as a value the compiler cannot see through: what a phase derives from it (lane
   // coordinates, LDS and global addresses) is then recomputed where it is used, in a few instructions, instead
@@ -232,7 +233,7 @@ struct Tiled {
   }
 
   __device__ __forceinline__ void init_params() const {
-    const uint64_t km = key_model(it.seed, it.fold);
+    const uint64_t km = key_model(it.seed, fl + P.fold_base);
     for (int l = 0; l < y.L; l++) {
       const int fi = y.U[l], fo = y.U[l + 1];
       const uint64_t kw = key_fold(km, 16 + 2 * l), kb = key_fold(km, 16 + 2 * l + 1);
@@ -1321,11 +1322,11 @@ struct Tiled {
   }
 
   __device__ __forceinline__ void run() const {
-    const int f = it.fold, fl = it.fold - P.fold_base, L = y.L;  // fl: which row list
+    const int L = y.L;
     const int n_tr = P.counts[2 * fl], n_va = P.counts[2 * fl + 1];
     const int32_t* tr = P.train_idx + (int64_t)fl * P.n;
     const int32_t* va = P.val_idx + (int64_t)fl * P.n;
-    const uint64_t km = key_model(it.seed, f);
+    const uint64_t km = key_model(it.seed, fl + P.fold_base);
     const RowSplit sp = row_split(km, it.patience, it.val_frac, n_tr);
     const int n_fit = sp.n_fit;
     const int bs = eff_batch(it.batch_size, n_fit);
