@@ -51,6 +51,7 @@
 #include "train_small_f32.h"
 #include "train_mid_f32.h"
 #include "train_linear_f32.h"
+#include "train_linear_lds_f32.h"
 
 static_assert(sizeof(bbo_mlp_hparams) == 88, "the hyper-parameter record is part of the ABI");
 
@@ -803,7 +804,8 @@ struct SubPlan {
   uint64_t slot_bytes = 0;      // global memory per resident workgroup
   int n_slots = 0;              // workgroups to launch
   uint32_t lds_bytes = 0;       // dynamic LDS per workgroup
-  int waves = 0;                // linear kernel: wavefronts per workgroup
+  int waves = 0;                // linear kernels: wavefronts per workgroup
+  int dd = 0;                   // linear kernel with the data set in LDS: its padded columns; 0: the other one
   size_t item_bytes = 0;        // size of a suggestion's record
   uint64_t o_items = 0;         // workspace byte offset of its records
   uint64_t o_slots = 0;         // ... and of its workgroups' slots
@@ -1012,7 +1014,14 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     size_t units = n_items;
     if (k == KC_SMALL) max_slots *= small_per_cu(sp.cut, sp.lds_bytes);
     if (k == KC_MID) max_slots *= md_per_cu(sp.cut, sp.lds_bytes);
-    if (k == KC_LINEAR) {
+    const LinLds ll = k == KC_LINEAR && dtype == BBO_F32 ? ll_plan(n, d, n_classes >= 2 ? n_classes : 1) : LinLds{0, 0, 0, 0};
+    if (ll.waves) {
+      // one workgroup per CU; a call with few models spreads them over the CUs (four wavefronts to copy the data set)
+      sp.dd = ll.dd;
+      sp.waves = (int)std::min<size_t>(ll.waves, std::max<size_t>(4, (n_items + max_slots - 1) / max_slots));
+      sp.lds_bytes = ll.shared + sp.waves * ll.wave_bytes;
+      units = n_items;
+    } else if (k == KC_LINEAR) {
       // as many workgroups as the LDS lets a CU hold, each of `waves` wavefronts with a model apiece
       const int c_out = n_classes >= 2 ? n_classes : 1;
       sp.waves = ln_waves(d, c_out, n);
@@ -1315,7 +1324,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
       fn = mid_kernel(sp.cut.kt, sp.cut.nt, sp.cut.waves);
       threads = 64 * sp.cut.waves;
     } else if (k == KC_LINEAR) {
-      fn = linear_kernel(ln_co(c_out), ln_ki(d));
+      fn = sp.dd ? linear_lds_kernel(sp.dd, c_out) : linear_kernel(ln_co(c_out), ln_ki(d));
       threads = 64 * sp.waves;
     } else {
       fn = dtype == BBO_F32 ? (const void*)k_train<float> : (const void*)k_train<__bf16>;

@@ -1,0 +1,379 @@
+// Training / scoring kernel for fp32 models without a hidden layer and with one or two outputs (linear and logistic
+// regression, two-class softmax) on data sets that fit into a CU's LDS: the case of thousands of them in one call.
+// train_linear_f32.h takes every other linear model.
+//
+// As there, a wavefront trains one model and there is no workgroup barrier in the training loop; several wavefronts form
+// a workgroup only to share the inputs: the workgroup copies the whole data set into LDS once (row stride D + 4, a 1 in
+// column d for the bias, labels behind it) and each of its wavefronts then works through models from the queue.
+//
+//   forward   lane = row: the row is read from LDS into registers (16 bytes a read; stride / 4 is odd, so that scattered
+//             rows spread over the banks), the weights are broadcast reads of the wave's own copy.
+//   outputs   loss and output delta in the lane.
+//   gradient  the lane keeps D x CO sums x[k] * delta[j] of its own rows in registers over the chunks of the step; at the
+//             step's end they are folded over the 64 lanes, a halving at a time, which leaves lane t with the sums of
+//             parameters t, t + 64 in the packed order W[in][out], b[out].
+//   update    in the owning lane, which refreshes the wave's copy of the weights.
+//
+// What bounds it: vector instructions, about 2 D CO per 64 rows for the products and 3 D CO per step for the folds, with the
+// LDS reads of the rows next.  The kernel before gathered each chunk's rows from global memory into LDS (a dozen
+// instructions per element) and walked them again row by row for the gradient: 10,240 models of 569 x 30, two outputs, 20
+// epochs took 4.9 ms and take 1.7 ms.
+#pragma once
+#include "common.h"
+#include "train_small_f32.h"  // folding sums
+
+namespace {
+
+constexpr uint32_t LL_LDS_LIMIT = 160 * 1024 - 64;
+
+// Wavefronts per SIMD the registers of a variant are budgeted for: the lane's row, its sums and about 64 more (weights on
+// their way, the optimizer's and the folds' temporaries).
+__host__ __device__ constexpr int ll_occupancy(int dd, int co) {
+  return dd + dd * co + 64 <= 128 ? 4 : (dd + dd * co + 64 <= 168 ? 3 : 2);
+}
+struct LinLds {
+  int32_t dd, waves;           // columns (inputs and bias padded to a multiple of 8); wavefronts per workgroup, 0: not a case for it
+  uint32_t shared, wave_bytes; // LDS of the data set and of each wavefront
+};
+// LDS of a wavefront: weights, the training list in the order of the early-stopping cut, the epoch's row order, the round
+// function of the permutation
+__host__ __device__ inline uint32_t ll_wave_bytes(int dd, int co, int64_t n) {
+  int hb = 1;
+  while ((1 << (2 * hb)) < n) hb++;
+  return (uint32_t)((dd * co * 4 + 2 * ((2 * n + 15) & ~15) + ((4 << hb) * 2)) + 15) & ~15u;
+}
+// By the size of the data set and the model alone: at least a wavefront per SIMD must fit beside the data set, or the
+// SIMDs idle and gathering rows from global memory is the better way.
+__host__ inline LinLds ll_plan(int64_t n, int d, int c) {
+  LinLds l = {0, 0, 0, 0};
+  if (c > 2 || d > 63 || n < 1 || n > 4096) return l;
+  l.dd = rup(d + 1, 8);
+  l.shared = (uint32_t)((n * (l.dd + 4) * 4 + n * 4 + 15) & ~15);
+  l.wave_bytes = ll_wave_bytes(l.dd, c, n);
+  if (l.shared + 4 * l.wave_bytes > LL_LDS_LIMIT) return l;
+  const int fit = (int)((LL_LDS_LIMIT - l.shared) / l.wave_bytes), most = 4 * ll_occupancy(l.dd, c);
+  l.waves = fit < most ? fit : most;
+  return l;
+}
+
+template <int D, int CO>
+struct LinearLds {
+  static constexpr int S = D + 4, NQ = D / 4, NV = D * CO, M = (NV + 15) / 16, M1 = (M + 1) / 2, NB = (M1 + 1) / 2;
+  const TrainParams& P;
+  const float *xs, *ys;
+  float* ws;
+  uint16_t *sl, *ep, *ft;
+  int lane, d, n_classes, Pn;
+
+  __device__ __forceinline__ void load_row(int row, f32x4 (&x)[NQ]) const {
+    const float* p = xs + row * S;
+#pragma unroll
+    for (int q = 0; q < NQ; q++) x[q] = *(const f32x4*)(p + 4 * q);
+  }
+  __device__ __forceinline__ void forward(const f32x4 (&x)[NQ], float (&z)[CO]) const {
+#pragma unroll
+    for (int j = 0; j < CO; j++) z[j] = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV / 4; i++) {
+      const f32x4 w = *(const f32x4*)(ws + 4 * i);
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const int k = (4 * i + u) / CO, j = (4 * i + u) % CO;
+        z[j] += x[k / 4][k % 4] * w[u];
+      }
+    }
+  }
+  // output deltas (TRAIN) and, if `loss`, the loss and second score of the lane's row
+  template <bool TRAIN>
+  __device__ __forceinline__ void outputs(const float (&z)[CO], bool valid, float y, float inv_mb, bool loss, float (&dl)[CO],
+                                          double& lsum, double& hits) const {
+    const float scale = valid ? inv_mb : 0.f;
+    if constexpr (CO == 2) {
+      const int yr = __float_as_int(y);
+      const float mx = fmaxf(z[0], z[1]);
+      const float e0 = expf(z[0] - mx), e1 = expf(z[1] - mx), se = e0 + e1;
+      if (loss && valid) {
+        lsum += (double)(mx + logf(se) - (yr == 1 ? z[1] : z[0]));
+        hits += (z[1] > z[0] ? 1 : 0) == yr ? 1.0 : 0.0;
+      }
+      if (TRAIN) {
+        const float rs = 1.f / se;
+        dl[0] = (e0 * rs - (yr == 0 ? 1.f : 0.f)) * scale;
+        dl[1] = (e1 * rs - (yr == 1 ? 1.f : 0.f)) * scale;
+      }
+    } else if (n_classes == 1) {
+      const int yr = __float_as_int(y);
+      const float zz = z[0];
+      if (loss && valid) {
+        lsum += (double)(fmaxf(zz, 0.f) + log1pf(expf(-fabsf(zz))) - (yr ? zz : 0.f));
+        hits += (zz > 0.f) == (yr != 0) ? 1.0 : 0.0;
+      }
+      if (TRAIN) dl[0] = (1.f / (1.f + expf(-zz)) - (float)yr) * scale;
+    } else {
+      const float e0 = z[0] - y;
+      if (loss && valid) {
+        lsum += TRAIN ? 0.5 * (double)e0 * (double)e0 : (double)e0 * (double)e0;
+        hits += (double)fabsf(e0);  // the absolute error
+      }
+      if (TRAIN) dl[0] = e0 * scale;
+    }
+    if (TRAIN && !valid) {  // (a row that is not there must not put an infinity of another row into the sums)
+#pragma unroll
+      for (int j = 0; j < CO; j++) dl[j] = 0.f;
+    }
+  }
+  // sums over the 64 lanes: s[b] of lane t is that of g[t + 64 b]
+  __device__ __forceinline__ void fold(const float (&g)[NV], float (&s)[NB]) const {
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8, b4 = lane & 16, b5 = lane & 32;
+    float r[2 * M1];
+#pragma unroll
+    for (int i = 0; i < 2 * M1; i++) {
+      float v[4];
+#pragma unroll
+      for (int t = 0; t < 4; t++) {
+        float p[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) p[e] = 16 * i + 4 * t + e < NV ? g[16 * i + 4 * t + e < NV ? 16 * i + 4 * t + e : 0] : 0.f;
+        v[t] = 16 * i + 4 * t < NV ? sm_fold_quad(p, b0, b1) : 0.f;
+      }
+      r[i] = 16 * i < NV ? sm_fold_row(v, b2, b3) : 0.f;
+    }
+    float h[2 * NB];
+#pragma unroll
+    for (int i = 0; i < 2 * NB; i++)
+      h[i] = i < M1 ? (b4 ? r[2 * i + 1] : r[2 * i]) + __shfl_xor(b4 ? r[2 * i] : r[2 * i + 1], 16) : 0.f;
+#pragma unroll
+    for (int b = 0; b < NB; b++) s[b] = (b5 ? h[2 * b + 1] : h[2 * b]) + __shfl_xor(b5 ? h[2 * b] : h[2 * b + 1], 32);
+  }
+  // the epoch's rows in visiting order (see train_linear_f32.h)
+  __device__ __forceinline__ void epoch_order(uint64_t ke, int n_fit) const {
+    if (n_fit <= 1) {
+      if (lane < n_fit) ep[lane] = sl[0];
+    } else {
+      const PermDomain dm = perm_domain((uint32_t)n_fit);
+      for (int i = lane; i < (4 << dm.hb); i += 64)
+        ft[i] = (uint16_t)((uint32_t)key_fold(ke, ((uint64_t)(i >> dm.hb) << 32) | ((uint32_t)i & dm.mask)) & dm.mask);
+      __builtin_amdgcn_wave_barrier();
+      int p = lane;
+      uint32_t x = (uint32_t)p;
+      while (p < n_fit) {
+        uint32_t Lh = x >> dm.hb, Rh = x & dm.mask;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const uint32_t t = Lh ^ ft[(r << dm.hb) + Rh];
+          Lh = Rh;
+          Rh = t;
+        }
+        x = (Lh << dm.hb) | Rh;
+        if (x < (uint32_t)n_fit) {
+          ep[p] = sl[x];
+          p += 64;
+          x = (uint32_t)p;
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  __device__ __forceinline__ void put_weights(const float (&w)[NB]) const {
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+      if (lane + 64 * b < NV) ws[lane + 64 * b] = w[b];
+    __builtin_amdgcn_wave_barrier();
+  }
+  // loss and second score, summed per lane, of `count` rows
+  template <class RowAt>
+  __device__ __forceinline__ void score_rows(int count, RowAt row_at, double& lsum, double& hits) const {
+    for (int off = 0; off < count; off += 64) {
+      const bool valid = off + lane < count;
+      const int row = row_at(valid ? off + lane : count - 1);
+      f32x4 x[NQ];
+      load_row(row, x);
+      float z[CO], dl[CO];
+      forward(x, z);
+      outputs<false>(z, valid, ys[row], 0.f, true, dl, lsum, hits);
+    }
+  }
+
+  __device__ __forceinline__ void run(const ConstItemDesc& it, int fl) const {  // fl: which row list
+    const int n_tr = uniform(P.counts[2 * fl]), n_va = uniform(P.counts[2 * fl + 1]);
+    const int32_t* tr = P.train_idx + (int64_t)fl * P.n;
+    const int32_t* va = P.val_idx + (int64_t)fl * P.n;
+    const uint64_t km = key_model(it.seed, fl + P.fold_base);
+    const RowSplit sp = row_split(km, it.patience, it.val_frac, n_tr);
+    const int n_fit = sp.n_fit, n_hold = sp.n_hold;
+    const int bs = eff_batch(it.batch_size, n_fit);
+    const int steps = n_fit > 0 ? (n_fit + bs - 1) / bs : 0;
+    const float alpha = it.alpha;
+    const bool traced = P.trace_item == it.b * P.n_folds + fl;
+    const bool resume = traced && P.state_in && steps > 0;
+
+    OptC oc;
+    oc.adam = it.solver == BBO_ADAM;
+    oc.nest = it.nesterov != 0;
+    oc.b1 = it.beta1;
+    oc.b2 = it.beta2;
+    oc.omb1 = 1.f - it.beta1;
+    oc.omb2 = 1.f - it.beta2;
+    oc.eps = it.eps;
+    oc.mu = it.momentum;
+    oc.lr = it.lr;
+    oc.lr_t = it.lr;
+    oc.am = 0.f;
+
+    for (int p = lane; p < n_tr; p += 64) sl[p] = (uint16_t)tr[n_hold ? (int)perm_index(sp.ksplit, (uint32_t)n_tr, (uint32_t)p) : p];
+    float w[NB], m[NB], v[NB], wb[NB];
+    const int n_w = d * CO;  // weights in front, biases behind
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+      const int i = lane + 64 * b;
+      w[b] = m[b] = v[b] = wb[b] = 0.f;
+      if (i < Pn) {
+        if (resume) {
+          w[b] = P.state_in[i];
+          m[b] = P.state_in[Pn + i];
+          v[b] = P.state_in[2 * Pn + i];
+        } else {
+          const uint32_t k24 = (uint32_t)(key_fold(key_fold(km, i < n_w ? 16 : 17), (uint64_t)(i < n_w ? i : i - n_w)) >> 40);
+          w[b] = it.bound[0] * ((float)((int32_t)k24 - 8388608) * 0x1p-23f);
+        }
+      }
+    }
+    put_weights(w);
+
+    int64_t gstep = resume ? P.step_begin : 0;
+    const int e0 = resume ? (int)(gstep / steps) : 0, st0 = resume ? (int)(gstep % steps) : 0;
+    float lr_tab = 0.f;  // Adam: the step sizes of 64 steps, one per lane
+    int lr_at = 64;      // ... the next of them
+    Plateau plateau;
+    bool have_best = false;
+    const bool watch = it.patience > 0 && steps > 0 && !resume;
+    const bool loss = traced || (watch && !n_hold);
+    for (int e = e0; e < it.epochs && steps > 0; e++) {
+      epoch_order(key_epoch(km, e), n_fit);
+      if (!oc.adam) oc.lr = epoch_lr(it.lr, it.power_t, e, n_fit);
+      double esum = 0.0, unused = 0.0;  // the lane's share of the epoch's summed data loss
+      for (int st = e == e0 ? st0 : 0; st < steps; st++, gstep++) {
+        const int lo = st * bs, hi = min(lo + bs, n_fit);
+        const float mb = (float)(hi - lo), inv_mb = 1.f / mb;
+        float g[NV];
+#pragma unroll
+        for (int i = 0; i < NV; i++) g[i] = 0.f;
+        double lstep = 0.0;
+        for (int at = lo; at < hi; at += 64) {
+          asm volatile("" ::: "memory");  // the weights are read again for every chunk, not kept in registers
+          const int row = ep[min(at + lane, hi - 1)];
+          f32x4 x[NQ];
+          load_row(row, x);
+          float z[CO], dl[CO];
+          forward(x, z);
+          outputs<true>(z, at + lane < hi, ys[row], inv_mb, loss, dl, lstep, unused);
+#pragma unroll
+          for (int i = 0; i < NV; i++) g[i] += x[i / CO / 4][i / CO % 4] * dl[i % CO];
+        }
+        float gs[NB];
+        fold(g, gs);
+        esum += lstep;
+        oc.am = alpha / mb;
+        if (oc.adam) {
+          if (lr_at == 64) {
+            // beta^t of the next 64 steps, a step per lane, by repeated squaring in double
+            lr_at = 0;
+            double q1 = (double)it.beta1, q2 = (double)it.beta2, b1t = 1.0, b2t = 1.0;
+#pragma unroll 1
+            for (uint64_t t = (uint64_t)(gstep + 1) + lane; __any(t != 0); t >>= 1) {
+              b1t *= t & 1 ? q1 : 1.0;
+              b2t *= t & 1 ? q2 : 1.0;
+              q1 *= q1;
+              q2 *= q2;
+            }
+            lr_tab = (float)((double)it.lr * sqrt(1.0 - b2t) / (1.0 - b1t));
+          }
+          oc.lr_t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lr_tab), lr_at));
+          lr_at++;
+        }
+        float* rec = nullptr;
+        if (traced && gstep >= P.step_begin && gstep < P.step_end) {
+          rec = P.trace_out + (gstep - P.step_begin) * (1 + 2 * (int64_t)Pn);
+          double pen = 0.0;
+#pragma unroll
+          for (int b = 0; b < NB; b++)
+            if (lane + 64 * b < n_w) pen += (double)w[b] * (double)w[b];
+          const double data = sm_wavesum_d(lstep) / (double)mb;
+          pen = sm_wavesum_d(pen);
+          if (lane == 0) rec[0] = (float)(data + 0.5 * (double)alpha * pen / (double)mb);
+        }
+#pragma unroll
+        for (int b = 0; b < NB; b++) {
+          const int i = lane + 64 * b;
+          if (i < Pn) {
+            const float gg = gs[b] + (i < n_w ? oc.am * w[b] : 0.f);
+            opt_update(oc, gg, w[b], m[b], v[b]);
+            if (rec) {
+              rec[1 + i] = gg;
+              rec[1 + Pn + i] = w[b];
+            }
+          }
+        }
+        put_weights(w);
+      }
+      if (watch) {
+        float watched = (float)(sm_wavesum_d(esum) / (double)n_fit);
+        if (n_hold) {  // the loss of the rows set aside for early stopping, under the weights the epoch ends with
+          double hl = 0.0, hh = 0.0;
+          score_rows(n_hold, [&](int p) { return (int)sl[n_fit + p]; }, hl, hh);
+          watched = (float)(sm_wavesum_d(hl) / (double)n_hold);
+        }
+        const bool stop = plateau.stop_after(watched, it.tol, it.patience);
+        if (n_hold && plateau.improved) {
+#pragma unroll
+          for (int b = 0; b < NB; b++) wb[b] = w[b];
+          have_best = true;
+        }
+        if (stop) break;
+      }
+    }
+    if (have_best) put_weights(wb);  // early stopping on held-out rows scores the best epoch's model
+
+    double lsum = 0.0, hits = 0.0;
+    score_rows(n_va, [&](int p) { return va[p]; }, lsum, hits);
+    lsum = sm_wavesum_d(lsum);
+    hits = sm_wavesum_d(hits);
+    if (lane == 0) {
+      float* out = P.item_out + 2 * ((int64_t)it.b * P.n_folds + fl);
+      out[0] = n_va > 0 ? (float)(lsum / (double)n_va) : __builtin_nanf("");
+      out[1] = n_va > 0 ? (float)(hits / (double)n_va) : __builtin_nanf("");  // accuracy | mean absolute error
+    }
+  }
+};
+
+// The launch gives a workgroup the LDS of the data set and ll_wave_bytes() for each of its wavefronts.
+template <int D, int CO>
+__global__ __attribute__((amdgpu_flat_work_group_size(64, 256 * ll_occupancy(D, CO)),
+                          amdgpu_waves_per_eu(ll_occupancy(D, CO), ll_occupancy(D, CO))))
+void k_train_linear_lds(const TrainParams P) {
+  extern __shared__ __align__(16) char ll_lds[];
+  typedef LinearLds<D, CO> T;
+  const int n = (int)P.n, d = P.d;
+  float *xs = (float*)ll_lds, *ys = xs + n * T::S;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < n * T::S; i += blockDim.x) {
+    const int r = i / T::S, k = i - r * T::S;
+    xs[i] = k < d ? ((const float*)P.X)[r * d + k] : (k == d ? 1.f : 0.f);
+  }
+  for (int i = threadIdx.x; i < n; i += blockDim.x) ys[i] = ((const float*)P.y)[i];  // (class ids as they are)
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  char* own = ll_lds + (((uint32_t)(n * T::S + n) * 4 + 15) & ~15u) + wave * ll_wave_bytes(D, CO, n);
+  const uint32_t list = (2 * n + 15) & ~15u;
+  T t{P, xs, ys, (float*)own, (uint16_t*)(own + T::NV * 4), (uint16_t*)(own + T::NV * 4 + list),
+      (uint16_t*)(own + T::NV * 4 + 2 * list), lane, d, P.n_classes, (d + 1) * CO};
+  for (;;) {
+    // every lane takes part in the pop (see k_train_linear)
+    __builtin_amdgcn_wave_barrier();
+    const int item = __builtin_amdgcn_readfirstlane(atomicAdd(P.queue, lane == 0 ? 1 : 0));
+    if (item >= P.n_items) break;
+    t.run(((ConstItemDesc*)P.items)[item / P.n_folds], item % P.n_folds);
+  }
+}
+
+}  // namespace

@@ -16,15 +16,20 @@ WIDE_HEAD = [
     (150, 16, 5, [64], 0), (150, 5, 16, [65], 33), (203, 48, 7, [129], 64), (203, 64, 10, [128], 63), (203, 64, 2, [129], 65),
     (203, 65, 12, [128], 17), (203, 80, 10, [256], 100), (203, 96, 1, [200], 80), (203, 97, 3, [64], 50), (203, 112, 0, [128], 64),
     (203, 127, 16, [16], 1), (203, 127, 10, [128], 90), (5000, 64, 10, [40], 1000)]
+# (the last two of each: the data set no longer fits into LDS, too many inputs)
+LINEAR = [(n, d, c, [], bs) for c in (0, 1, 2) for n, d, bs in (
+    (150, 7, 0), (151, 8, 17), (203, 15, 64), (203, 16, 1), (300, 31, 65), (300, 32, 130), (520, 47, 33), (520, 55, 200),
+    (520, 60, 63), (400, 63, 128), (1500, 7, 700), (4000, 30, 900), (203, 64, 50))]
 
 
-@pytest.mark.parametrize("n,d,c,hidden,bs", ONE_SMALL_LAYER + WIDE_HEAD)
+@pytest.mark.parametrize("n,d,c,hidden,bs", ONE_SMALL_LAYER + WIDE_HEAD + LINEAR)
 @pytest.mark.parametrize("solver", ["adam", "sgd"])
 def test_steps_and_score_at_the_edges_of_a_cut(bb, oracle, n, d, c, hidden, bs, solver):  # noqa: F811
     hp = {"hidden": hidden, "solver": solver, "nesterov": True, "batch_size": bs, "alpha": 0.3, "lr": 0.003,
           "momentum": 0.9, "epochs": 2, "seed": 99 + n}
     cls = bb.bbo_mlp_kernel_class(n, d, c, hp, 0)
-    assert cls == (bb.KERNEL_SMALL if (n, d, c, hidden, bs) in ONE_SMALL_LAYER else bb.KERNEL_MID)
+    assert cls == (bb.KERNEL_LINEAR if not hidden else
+                   bb.KERNEL_SMALL if (n, d, c, hidden, bs) in ONE_SMALL_LAYER else bb.KERNEL_MID)
     cfg = small_problem(n + d, n, d, c)
     c_out, f = c if c >= 2 else 1, 1
     n_tr = int((cfg["fold_idx"] != f).sum())
