@@ -139,7 +139,8 @@ int bbo_mlp_cv_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t 
  * host memory (the item list travels as kernel arguments).  Same arguments,
  * same kernels and bit-identical results otherwise.
  *   limit   the problem's bbo_mlp_workspace_bytes() must not exceed
- *           BBO_STATIC_SCRATCH_BYTES, and its item records (a few hundred
+ *           BBO_STATIC_SCRATCH_BYTES (some calls that need more fit as well,
+ *           on fewer workgroups or one kernel after the other), and its item records (a few hundred
  *           bytes per suggestion and fold) BBO_STATIC_MAX_ITEM_BYTES; beyond
  *           that the call returns BBO_WORKSPACE_TOO_SMALL and enqueues nothing.
  *   sharing every call on a device uses that device's one array: calls that

@@ -11,13 +11,11 @@
 // gradient is never stored.  (Models without a hidden layer are the exception:
 // a wavefront each, on the vector ALU; see train_linear_f32.h.)
 //
-// Five training kernels share this scheme: the LDS-tiled bf16 kernel
-// (train_tiled_bf16.h), the two LDS-resident fp32 kernels (train_small_f32.h,
-// train_mid_f32.h), the wavefront-per-model fp32 kernel (train_linear_f32.h)
-// and the generic kernel below, which takes every shape the header admits.  The planner gives each
-// suggestion to the fastest kernel that takes its shape and launches every
-// kernel that got items, one after the other, each with its own item array
-// and queue counter.
+// The training kernels share this scheme: the LDS-tiled bf16 kernel (train_tiled_bf16.h), the register-resident fp32
+// kernels for one hidden layer (train_small_f32.h, train_mid_f32.h) and for two or three (train_deep_f32.h), the kernels
+// for models without one (train_linear_lds_f32.h, train_linear_f32.h) and the generic kernel below, which takes every
+// shape the header admits.  The planner gives each suggestion to the fastest kernel that takes its shape and launches
+// every kernel variant that got items, side by side, each with its own item array and queue counter.
 //
 // Operand layout.  MFMA operands are read straight from memory as 16-byte
 // vectors along the contracted index, so every tensor is kept in the layout
@@ -50,6 +48,7 @@
 #include "train_tiled_bf16.h"
 #include "train_small_f32.h"
 #include "train_mid_f32.h"
+#include "train_deep_f32.h"
 #include "train_linear_f32.h"
 #include "train_linear_lds_f32.h"
 
@@ -190,7 +189,7 @@ __device__ inline float row_loss(const float* z, int c, int n_classes, const voi
 
 // The training kernels.  Every suggestion of a call goes to the fastest kernel that takes its shape, so
 // a suggestion's scores do not depend on which other suggestions share its call.
-enum { KC_TILED = 0, KC_SMALL = 1, KC_LINEAR = 2, KC_GENERIC = 3, KC_MID = 4 };
+enum { KC_TILED = 0, KC_SMALL = 1, KC_LINEAR = 2, KC_GENERIC = 3, KC_MID = 4, KC_DEEP = 5 };
 
 // ---------------------------------------------------------------------------
 // Fold lists (ascending), one workgroup per list; also resets the work queues.
@@ -817,7 +816,8 @@ constexpr int MAX_LAUNCHES = 64;  // queue counters in the workspace
 struct Plan {
   std::vector<SubPlan> sub;
   size_t n_items = 0;
-  // workspace byte offsets; the launches run side by side, each with slots of its own
+  bool in_turn = false;  // the launches share one slot region and run one after the other
+  // workspace byte offsets; otherwise they run side by side, each with slots of its own
   uint64_t o_items = 0, items_bytes = 0, o_queue = 0, o_out = 0, o_train = 0, o_val = 0, o_counts = 0, total = 0;
 };
 
@@ -904,6 +904,9 @@ int kernel_class(const int32_t* dims, int L, int64_t n, int dtype) {
   if ((uint64_t)n * (uint64_t)d < (1ull << 30)) {  // 32-bit byte offsets into X
     if (small_eligible(dims, L)) return KC_SMALL;
     if (mid_cut(dims, L).waves) return KC_MID;
+    // (every shape it holds: one model of 128-128 on 569 x 30 takes 14.7 us a step against 64 at one row, 100 against 220
+    // at full batches, 200 models x 5 folds of 16-16-16 at 64 rows 0.52 ms against 2.5)
+    if (deep_cut(dims, L).waves) return KC_DEEP;
   }
   return linear_eligible(dims, L) ? KC_LINEAR : KC_GENERIC;
 }
@@ -934,7 +937,7 @@ void fill_item(ItemDesc& it, const bbo_mlp_hparams& h, int b, int64_t n, int d, 
 
 // The launches of a call, their workgroups and where everything lies in the workspace.
 int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_base, const bbo_mlp_hparams* hp, int B,
-              int dtype) {
+              int dtype, bool static_ws = false) {
   const int kstep = dtype == BBO_F32 ? 16 : 32, opsz = dtype == BBO_F32 ? 4 : 2;
   const double n_tr_est = n_folds > 1 && fold_base >= 0 ? (double)n * (n_folds - 1) / n_folds : (double)n;
   pl.sub.clear();
@@ -954,6 +957,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
       case KC_TILED: sp.item_bytes = sizeof(TItem); break;
       case KC_SMALL: sp.item_bytes = sizeof(SItem); break;
       case KC_MID: sp.item_bytes = sizeof(MItem); break;
+      case KC_DEEP: sp.item_bytes = sizeof(DItem); break;
       default: sp.item_bytes = sizeof(ItemDesc);
     }
     pl.sub.push_back(std::move(sp));
@@ -971,7 +975,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
       params += (double)dims[l] * dims[l + 1];
     }
     const int k = kernel_class(dims, L, n, dtype);
-    const SmallCut cut = k == KC_SMALL ? small_cut(dims) : (k == KC_MID ? mid_cut(dims, L) : SmallCut{0, 0, 0, 0});
+    const SmallCut cut = k == KC_SMALL ? small_cut(dims) : (k == KC_MID ? mid_cut(dims, L) : (k == KC_DEEP ? deep_cut(dims, L) : SmallCut{0, 0, 0, 0}));
     SubPlan& sp = launch_of(k, cut);
     uint64_t slot_bytes = 0;
     uint32_t lds_bytes = 0;
@@ -990,6 +994,11 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
       make_mlay(my, dims, n, cut);
       slot_bytes = 4ull * my.slot_floats;
       lds_bytes = my.lds_total;
+    } else if (k == KC_DEEP) {
+      DLay dy;
+      make_dlay(dy, dims, L, n, cut);
+      slot_bytes = 4ull * dy.slot_floats;
+      lds_bytes = dy.lds_total;
     } else if (k == KC_GENERIC) {
       Layout y;
       make_layout(y, dims, L, rup((int)std::max<int64_t>(bs, 1), kstep), kstep, opsz);
@@ -1014,6 +1023,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     size_t units = n_items;
     if (k == KC_SMALL) max_slots *= small_per_cu(sp.cut, sp.lds_bytes);
     if (k == KC_MID) max_slots *= md_per_cu(sp.cut, sp.lds_bytes);
+    if (k == KC_DEEP) max_slots *= deep_per_cu(sp.cut, sp.lds_bytes);
     const LinLds ll = k == KC_LINEAR && dtype == BBO_F32 ? ll_plan(n, d, n_classes >= 2 ? n_classes : 1) : LinLds{0, 0, 0, 0};
     if (ll.waves) {
       // one workgroup per CU; a call with few models spreads them over the CUs (four wavefronts to copy the data set)
@@ -1051,7 +1061,21 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
   pl.o_train = take(4ull * nn * n_folds);
   pl.o_val = take(4ull * nn * n_folds);
   pl.o_counts = take(8ull * n_folds);
-  for (SubPlan& sp : pl.sub) sp.o_slots = take(std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256));
+  // The allocation-free entry point's memory is what it is: a call that needs more runs its launches in turn on shared
+  // slots, and the register-resident kernels on as few as half the workgroups.
+  uint64_t sum = 0, most = 0;
+  for (SubPlan& sp : pl.sub) {
+    const uint64_t room = off < BBO_STATIC_SCRATCH_BYTES ? BBO_STATIC_SCRATCH_BYTES - off : 0;
+    if (static_ws && (sp.kc == KC_SMALL || sp.kc == KC_MID || sp.kc == KC_DEEP) && sp.slot_bytes * sp.n_slots > room &&
+        sp.slot_bytes * ((sp.n_slots + 1) / 2) <= room)
+      sp.n_slots = (int)(room / sp.slot_bytes);
+    const uint64_t bytes = std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256);  // (slots are multiples of 256)
+    sum += bytes;
+    most = std::max(most, bytes);
+  }
+  pl.in_turn = static_ws && off + sum > BBO_STATIC_SCRATCH_BYTES;
+  for (SubPlan& sp : pl.sub) sp.o_slots = pl.in_turn ? off : take(std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256));
+  if (pl.in_turn) take(most);
   pl.total = off;
   return BBO_OK;
 }
@@ -1225,7 +1249,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
       return fail(BBO_INVALID_ARG, "trace buffer too small");
   }
   Plan pl;
-  rc = make_plan(pl, n, d, n_classes, n_folds, fold_base, hp, B, dtype);
+  rc = make_plan(pl, n, d, n_classes, n_folds, fold_base, hp, B, dtype, static_ws);
   if (rc) return rc;
   if (static_ws && (pl.total > BBO_STATIC_SCRATCH_BYTES || pl.items_bytes > BBO_STATIC_MAX_ITEM_BYTES))
     return fail(BBO_WORKSPACE_TOO_SMALL,
@@ -1264,6 +1288,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
           case KC_TILED: make_tlay(((TItem*)at)->y, it.dims, it.L); break;
           case KC_SMALL: make_slay(((SItem*)at)->y, it.dims, n, sp.cut); break;
           case KC_MID: make_mlay(((MItem*)at)->y, it.dims, n, sp.cut); break;
+          case KC_DEEP: make_dlay(((DItem*)at)->y, it.dims, it.L, n, sp.cut); break;
         }
         at += sp.item_bytes;
       }
@@ -1294,7 +1319,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
   P.x_bf16 = dtype == BBO_BF16;
 
   // one launch per kernel variant that has items, side by side: the first on the caller's stream
-  const int n_side = std::min<int>((int)pl.sub.size() - 1, SIDE_STREAMS);
+  const int n_side = pl.in_turn ? 0 : std::min<int>((int)pl.sub.size() - 1, SIDE_STREAMS);
   SideStreams* side = nullptr;
   if (n_side > 0) {
     if ((rc = side_streams(n_side, &side))) return rc;
@@ -1322,6 +1347,9 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
       threads = 64 * t.waves;
     } else if (k == KC_MID) {
       fn = mid_kernel(sp.cut.kt, sp.cut.nt, sp.cut.waves);
+      threads = 64 * sp.cut.waves;
+    } else if (k == KC_DEEP) {
+      fn = sp.cut.nt == 2 ? deep_kernel2(sp.cut.kt, sp.cut.waves) : deep_kernel3(sp.cut.kt, sp.cut.waves);
       threads = 64 * sp.cut.waves;
     } else if (k == KC_LINEAR) {
       fn = sp.dd ? linear_lds_kernel(sp.dd, c_out) : linear_kernel(ln_co(c_out), ln_ki(d));
@@ -1464,7 +1492,8 @@ int bbo_mlp_kernel_class(int64_t n, int32_t d, int32_t n_classes, const bbo_mlp_
   int32_t dims[MAXL + 1];
   int L;
   fill_dims(*hp, d, n_classes, dims, &L);
-  return kernel_class(dims, L, n, dtype);
+  const int k = kernel_class(dims, L, n, dtype);
+  return k == KC_DEEP ? KC_GENERIC : k;  // to the outside, the several-layer fp32 models' kernel is part of the generic one
 }
 
 const char* bbo_mlp_last_error(void) { return g_err.c_str(); }

@@ -1,0 +1,14 @@
+// The fp32 training kernel for three hidden layers: exactly the cuts deep_cut() makes.
+#include "train_deep_f32.h"
+
+#include "kernels.h"
+
+const void* deep_kernel3(int kt, int waves) {
+  switch (kt) {
+    case 1: return waves == 4 ? (const void*)k_train_deep<1, 3, 4> : (const void*)k_train_deep<1, 3, 8>;
+    case 2: return waves == 4 ? (const void*)k_train_deep<2, 3, 4> : (const void*)k_train_deep<2, 3, 8>;
+    case 3: return waves == 4 ? (const void*)k_train_deep<3, 3, 4> : (const void*)k_train_deep<3, 3, 8>;
+    case 4: return waves == 4 ? (const void*)k_train_deep<4, 3, 4> : (const void*)k_train_deep<4, 3, 8>;
+  }
+  return nullptr;
+}

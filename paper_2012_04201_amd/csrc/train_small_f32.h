@@ -209,10 +209,11 @@ __device__ __forceinline__ int sc_mode(int ch) { return (ch & SC_MODE) >> 7; }
 //   W         waves
 //   BARRIERS  1: a chunk has one barrier, between forward() and outputs(); its inputs were put into LDS before the
 //             barrier of the chunk before, so three input tiles rotate.  2: one more between outputs() and
-//             backward(), and two input tiles are enough.
+//             backward(), and two input tiles are enough.  3: forward() begins with a barrier of its own, the chunk ends
+//             with one, and the next chunk's inputs take the place of the last one's: one input tile.
 template <class Self, class Lay, int KT, int W, int BARRIERS>
 struct RowPipe {
-  static constexpr int K0 = 16 * KT, LDW = sm_ldw(KT), NB = BARRIERS == 1 ? 3 : 2;
+  static constexpr int K0 = 16 * KT, LDW = sm_ldw(KT), NB = 4 - BARRIERS;
   static constexpr int KS = K0 <= 16 ? 16 : (K0 <= 32 ? 32 : (K0 <= 64 ? 64 : 128));  // lanes per row when inputs are fetched
   static constexpr int NTHR = 64 * W, RSTEP = NTHR / KS, NX = SM_RC / RSTEP;          // rows per pass, passes
   typedef const __attribute__((address_space(4))) Lay ConstLay;
@@ -574,9 +575,9 @@ struct RowPipe {
         if (live) self.forward(R, b, par, nrt, acc);
         __syncthreads();  // the outputs' shares, the next chunk's inputs and the rows of the one after it
         if (BARRIERS == 2 && sc_mode(c1) <= ROWS_PLAIN) commit(bn, xr, yv);
-        if ((c2 & SC_MODE) != SC_END) fetch(c2, at, par, xr, yv);  // in flight until the next chunk is under way
+        if (BARRIERS < 3 && (c2 & SC_MODE) != SC_END) fetch(c2, at, par, xr, yv);  // in flight until the next chunk is under way
         if (live) self.outputs(R, b, par, rows, sc_mode(c0) == ROWS_EPOCH, inv_mb, lsum, hits);
-        if (BARRIERS == 2) __syncthreads();  // the output deltas
+        if (BARRIERS >= 2) __syncthreads();  // the output deltas
         if (sc_mode(c0) == ROWS_EPOCH) {
           self.backward(R, b, nrt, acc);
           if (c0 & SC_LAST) {  // last chunk of the step
@@ -598,6 +599,11 @@ struct RowPipe {
             }
             gstep++;
           }
+        }
+        if (BARRIERS == 3) {
+          __syncthreads();  // the chunk's inputs have been read for the last time
+          if (sc_mode(c1) <= ROWS_PLAIN) commit(bn, xr, yv);
+          if ((c2 & SC_MODE) != SC_END) fetch(c2, at, par, xr, yv);
         }
         const int done = c0;
         c0 = c1;
