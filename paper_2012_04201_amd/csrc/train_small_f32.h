@@ -521,8 +521,9 @@ struct RowPipe {
         if ((c2 & SC_MODE) != SC_END) {
           if (!tabled || sc_mode(c2) == ROWS_PLAIN) {
             park_rows(c2, at, e, par);
-          } else if (sc_mode(c2) == ROWS_EPOCH && e != built) {
-            build_epoch(key_epoch(key_model(item().seed, fl + params().fold_base), e));
+          } else if (sc_mode(c2) == ROWS_EPOCH && (steps > 1 ? e != built : built < 0)) {
+            // (an epoch of one step takes all rows at once: their order says nothing, and the first epoch's serves all)
+            build_epoch(key_epoch(key_model(item().seed, fl + params().fold_base), steps > 1 ? e : 0));
             built = e;
           }
         }
