@@ -68,6 +68,8 @@ constexpr int TB_MAXU = 256;  // padded units per level
 constexpr int TB_WAVES = 8;   // waves per workgroup (2 per SIMD); wave w owns rows 32w..32w+31 in the output layer and the spills
 constexpr int TB_THREADS = 64 * TB_WAVES;
 constexpr int TB_STATE_AHEAD = 2;  // tiles of optimizer state in flight per wave
+constexpr int TB_STATE_AHEAD_HALF = 4;  // ... in minibatches of at most 128 rows, whose operands leave registers free
+constexpr uint64_t TB_CACHED_SLOTS = 280ull << 20;  // see state_loads_cached()
 constexpr uint32_t TB_LDS_LIMIT = 160 * 1024 - 1024;  // dynamic LDS available to the kernel
 // The LDS layout is the same for every model (sized for the widest): the row stride and every offset are
 // compile-time constants, so LDS addresses need no arithmetic beyond the lane's base.
@@ -872,8 +874,9 @@ struct Tiled {
     }
   }
 
-  // The same for the common case: a layer below the last one, the whole minibatch in one chunk.  All 8 row
-  // blocks are contracted: rows past a ragged chunk carry zero deltas (backward_data) and finite activations.
+  // The same for the common case: a layer below the last one, the whole minibatch in one chunk.  All KB (8, or 4 up to
+  // 128 rows: half the LDS reads a tile, and room for twice the state in flight; 61.7 -> 57.9 us for a step of 64 rows of
+  // a lone 128-256-256-10 model) row blocks are contracted: rows past a ragged chunk carry zero deltas (backward_data) and finite activations.
   // Straight-line code per tile, so that the waits on memory are exact and the optimizer state really is in
   // flight TB_STATE_AHEAD tiles ahead: the in x out tiles of the layer are numbered in-tile-major and each
   // wave takes one contiguous eighth of them (its state is one contiguous stream per array, its activation
@@ -881,7 +884,7 @@ struct Tiled {
   // tiles (ones operand) are dealt round-robin and their state is fetched before anything else.  Pad
   // elements of edge tiles keep their zeros through selects, not branches.
   // LD: cache policy of the state LOADS (see state_load_hint()); the stores are always non-temporal.
-  template <bool ADAM, bool FROM_X, int LD>
+  template <bool ADAM, bool FROM_X, int LD, int KB>
   __device__ __forceinline__ void wgrad_stream(int l, const OptC& oc, int par_next, float* rec) const {
     const int t_ = tid(), lane = t_ & 63, li = lane & 15, q = lane >> 4;
     const int w = uniform(t_ >> 6);
@@ -898,7 +901,7 @@ struct Tiled {
     const int Mt = uniform(y.UP[l]) / 16, Nt = uniform(y.UP[l + 1]) / 16, Mr = (fi + 15) / 16, Ne = (fo + 15) / 16;
     const int cw = y.cw[l], cb = y.cb[l], Pn = y.P;
     const int TT = Mr * Ne, t0 = w * TT / TB_WAVES, t1 = (w + 1) * TT / TB_WAVES;
-    constexpr int D = TB_STATE_AHEAD;
+    constexpr int D = KB == 8 ? TB_STATE_AHEAD : TB_STATE_AHEAD_HALF;
     struct St {
       f32x4 w, m, v;
     };
@@ -906,9 +909,9 @@ struct Tiled {
     // the lane's delta operand of out tile 0, row block 0: rows 8q + li/4 (+4), units 4 (li%4)..
     const char* bl = buf() + ((size_t)(8 * q + (li >> 2)) * S + 4 * (li & 3)) * 2;
     const size_t kbs = (size_t)32 * S * 2, hs = (size_t)4 * S * 2;
-    auto delta_operands = [&](int nt, bf16x8(&b)[8]) {
+    auto delta_operands = [&](int nt, bf16x8(&b)[KB]) {
 #pragma unroll
-      for (int kb = 0; kb < 8; kb++) {
+      for (int kb = 0; kb < KB; kb++) {
         union {
           struct {
             s16x4 lo, hi;
@@ -953,11 +956,11 @@ struct Tiled {
           const_cast<void*>(P.X), 0, FROM_X ? (uint32_t)((uint64_t)P.n * (uint64_t)fi * 2) : 0u, 0x00020000);
       const int32_t* rl = rowlist();
       char* patch = lds + TB_LDS_STAGE + w * 2048;
-      auto load_a = [&](int mt, i32x4(&a)[8]) {
+      auto load_a = [&](int mt, i32x4(&a)[KB]) {
         if (FROM_X) {
           const int u0 = mt * 16 + (lane & 1) * 8;
 #pragma unroll
-          for (int kb = 0; kb < 8; kb++) {
+          for (int kb = 0; kb < KB; kb++) {
             const int row = rl[kb * 32 + (lane >> 1)];
             const bool ok = row >= 0 && u0 < fi && mt <= mt_last;
             const uint32_t vo = ok ? (uint32_t)(row * fi + u0) * 2 : OUT_OF_RANGE;
@@ -966,15 +969,15 @@ struct Tiled {
         } else {
           const uint32_t vo = lane_t + (mt > mt_last ? OUT_OF_RANGE : 0u);
 #pragma unroll
-          for (int kb = 0; kb < 8; kb++)
+          for (int kb = 0; kb < KB; kb++)
             a[kb] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rT, vo, mt * 8192 + kb * 1024, 0));
         }
       };
       // fetched form -> MFMA operand form
-      auto operand = [&](const i32x4(&raw)[8], i32x4(&a)[8]) {
+      auto operand = [&](const i32x4(&raw)[KB], i32x4(&a)[KB]) {
         if (FROM_X) {
 #pragma unroll
-          for (int kb = 0; kb < 8; kb++) {
+          for (int kb = 0; kb < KB; kb++) {
             char* pk = patch + (kb & 1) * 1024;
             *(i32x4*)(pk + lane * 16) = raw[kb];
             a[kb] = as_i32x4(lds_operand_tr(pk, 16, 0, 0, li, q));
@@ -983,7 +986,7 @@ struct Tiled {
           // register moves written out: the prefetched operand's registers are free before the next fetch
           // is issued, so the fetch lands in them directly instead of in temporaries that must be waited for
 #pragma unroll
-          for (int kb = 0; kb < 8; kb++)
+          for (int kb = 0; kb < KB; kb++)
 #pragma unroll
             for (int e = 0; e < 4; e++) asm volatile("v_mov_b32 %0, %1" : "=v"(a[kb][e]) : "v"(raw[kb][e]));
         }
@@ -1006,7 +1009,7 @@ struct Tiled {
       St st[D + 1];
 #pragma unroll
       for (int k = 0; k <= D; k++) st[k] = St{zero4, zero4, zero4};
-      i32x4 a[8], an[8];
+      i32x4 a[KB], an[KB];
       load_a(mt, an);
 #pragma unroll
       for (int k = 0; k < D; k++) load_st(st[k]);
@@ -1014,11 +1017,11 @@ struct Tiled {
       load_a(mt + 1, an);
       auto tile = [&](St& cur, St& pre) __attribute__((always_inline)) {
         load_st(pre);
-        bf16x8 b[8];
+        bf16x8 b[KB];
         delta_operands(nt, b);
         f32x4 g = zero4;
 #pragma unroll
-        for (int kb = 0; kb < 8; kb++) g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a[kb]), b[kb], g, 0, 0, 0);
+        for (int kb = 0; kb < KB; kb++) g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a[kb]), b[kb], g, 0, 0, 0);
         // the lane holds in units i0..i0+3 of out unit j
         const int j = nt * 16 + li, i0 = mt * 16 + 4 * q;
         const int tb = (mt * Nt + nt) * 1024;
@@ -1087,11 +1090,11 @@ struct Tiled {
     for (int i = 0; i < 2; i++) {
       const int nt = w + 8 * i;
       if (nt < Ne) {
-        bf16x8 b[8];
+        bf16x8 b[KB];
         delta_operands(nt, b);
         f32x4 g = zero4;
 #pragma unroll
-        for (int kb = 0; kb < 8; kb++) g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b[kb], g, 0, 0, 0);
+        for (int kb = 0; kb < KB; kb++) g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b[kb], g, 0, 0, 0);
         const int j = nt * 16 + li;
         if (q == 0 && j < fo) {  // r = 0 of lane group 0 holds the bias gradient of out unit j
           float wr = bw_[i], mr = bm_[i], vr = bv_[i];
@@ -1112,7 +1115,7 @@ struct Tiled {
   // chunk, rows past it carry zero deltas): wave w takes in tiles w and w + 8, their state is requested before anything else, and the
   // two tile bodies are straight-line code.  The activation operand comes from the buffer, the delta from its
   // own buffer, both through the transposing read.  The bias tile goes to the wave with the fewest tiles.
-  template <bool ADAM, int LD>
+  template <bool ADAM, int LD, int KB>
   __device__ __forceinline__ void wgrad_last(const OptC& oc, int par_next, float* rec) const {
     const int l = y.L - 1;
     const int t_ = tid(), lane = t_ & 63, li = lane & 15, q = lane >> 4;
@@ -1160,16 +1163,16 @@ struct Tiled {
     float bm_ = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rBm, (uint32_t)li * 4, 0, 0));
     float bv_ = ADAM ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rBv, (uint32_t)li * 4, 0, 0)) : 0.f;
     // the delta operand is the same for every tile
-    bf16x8 b[8];
+    bf16x8 b[KB];
 #pragma unroll
-    for (int kb = 0; kb < 8; kb++) b[kb] = lds_operand_tr(dbuf(), 16, kb * 32, 0, li, q);
+    for (int kb = 0; kb < KB; kb++) b[kb] = lds_operand_tr(dbuf(), 16, kb * 32, 0, li, q);
 #pragma unroll
     for (int k = 0; k < 2; k++) {
       const int mt = w + 8 * k;
       if (mt < Mr) {
         f32x4 g = zero4;
 #pragma unroll
-        for (int kb = 0; kb < 8; kb++)
+        for (int kb = 0; kb < KB; kb++)
           g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_operand_tr(buf(), TB_S, kb * 32, mt * 16, li, q), b[kb], g, 0, 0, 0);
         // the lane holds in units i0..i0+3 of out unit li
         const int i0 = mt * 16 + 4 * q;
@@ -1211,7 +1214,7 @@ struct Tiled {
       const bf16x8 a1 = as_bf16x8(i32x4{ones, ones, ones, ones});
       f32x4 g = zero4;
 #pragma unroll
-      for (int kb = 0; kb < 8; kb++) g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b[kb], g, 0, 0, 0);
+      for (int kb = 0; kb < KB; kb++) g = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b[kb], g, 0, 0, 0);
       if (q == 0 && li < fo) {  // r = 0 of lane group 0 holds the bias gradient of out unit li
         float wr = bw_, mr = bm_, vr = bv_;
         opt_update(oc, g[0], wr, mr, vr);
@@ -1231,40 +1234,45 @@ struct Tiled {
   // copies, spills and input rows that are re-read within a step.  But a share of the workgroups does better
   // with ordinary loads (measured on the scale-up workload: every fourth workgroup of an XCD, 64 of 256, is the
   // optimum, 5 % off the pass; all of them is 13 % slower than none).  The stores are non-temporal for everyone.
-  __device__ __forceinline__ static bool state_loads_cached() { return ((blockIdx.x >> 3) & 3) == 0; }
+  // Where the memory-side cache (256 MB) holds the state of all models in flight, ordinary loads win outright; that is
+  // up to half the chip's worth of models of any width, and up to TB_CACHED_SLOTS of slots (the state is half of them).
+  // us per step of 64 rows, non-temporal in three of four -> ordinary: 64 models of 128-256-256-10 94 -> 66, 128 of them
+  // 110 -> 101, 128 of 128-192-192-10 78 -> 54, 160 of them (264 MB of slots) 82 -> 70; 200 (330 MB) would go 83 -> 87.
+  __device__ __forceinline__ bool state_loads_cached() const {
+    return gridDim.x <= 128 || gridDim.x * P.slot_bytes <= TB_CACHED_SLOTS || ((blockIdx.x >> 3) & 3) == 0;
+  }
 
   __device__ __forceinline__ void wgrad(int l, int KB, bool first, bool last, const OptC& oc, int par_next,
                                         float* rec) const {
     const bool cached = state_loads_cached();
-    if (first && last && l + 1 < y.L) {
-      if (l == 0) {
-        if (oc.adam) {
-          if (cached)
-            wgrad_stream<true, true, 0>(l, oc, par_next, rec);
-          else
-            wgrad_stream<true, true, 2>(l, oc, par_next, rec);
-        } else {
-          wgrad_stream<false, true, 2>(l, oc, par_next, rec);
-        }
-      } else {
-        if (oc.adam) {
-          if (cached)
-            wgrad_stream<true, false, 0>(l, oc, par_next, rec);
-          else
-            wgrad_stream<true, false, 2>(l, oc, par_next, rec);
-        } else {
-          wgrad_stream<false, false, 2>(l, oc, par_next, rec);
-        }
-      }
-    } else if (first && last) {
-      if (oc.adam) {
-        if (cached)
-          wgrad_last<true, 0>(oc, par_next, rec);
+    // layers and cache policies of one optimizer and number of row blocks
+    auto one_chunk = [&](auto adam, auto blocks) __attribute__((always_inline)) {
+      constexpr bool ADAM = decltype(adam)::value;
+      constexpr int B = decltype(blocks)::value;
+      if (l + 1 == y.L) {
+        if (ADAM && cached)
+          wgrad_last<ADAM, 0, B>(oc, par_next, rec);
         else
-          wgrad_last<true, 2>(oc, par_next, rec);
+          wgrad_last<ADAM, 2, B>(oc, par_next, rec);
+      } else if (l == 0) {
+        if (ADAM && cached)
+          wgrad_stream<ADAM, true, 0, B>(l, oc, par_next, rec);
+        else
+          wgrad_stream<ADAM, true, 2, B>(l, oc, par_next, rec);
       } else {
-        wgrad_last<false, 2>(oc, par_next, rec);
+        if (ADAM && cached)
+          wgrad_stream<ADAM, false, 0, B>(l, oc, par_next, rec);
+        else
+          wgrad_stream<ADAM, false, 2, B>(l, oc, par_next, rec);
       }
+    };
+    if (first && last) {
+      if (!oc.adam)
+        one_chunk(std::false_type{}, std::integral_constant<int, 8>{});
+      else if (KB > 4)
+        one_chunk(std::true_type{}, std::integral_constant<int, 8>{});
+      else
+        one_chunk(std::true_type{}, std::integral_constant<int, 4>{});
     } else {
       wgrad_t(l, KB, first, last, oc, par_next, rec);
     }
