@@ -69,7 +69,7 @@ constexpr int TB_WAVES = 8;   // waves per workgroup (2 per SIMD); wave w owns r
 constexpr int TB_THREADS = 64 * TB_WAVES;
 constexpr int TB_STATE_AHEAD = 2;  // tiles of optimizer state in flight per wave
 constexpr int TB_STATE_AHEAD_HALF = 4;  // ... in minibatches of at most 128 rows, whose operands leave registers free
-constexpr uint64_t TB_CACHED_SLOTS = 280ull << 20;  // see state_loads_cached()
+constexpr uint64_t TB_CACHED_SLOTS = 280ull << 20;  // see state_cached()
 constexpr uint32_t TB_LDS_LIMIT = 160 * 1024 - 1024;  // dynamic LDS available to the kernel
 // The LDS layout is the same for every model (sized for the widest): the row stride and every offset are
 // compile-time constants, so LDS addresses need no arithmetic beyond the lane's base.
@@ -883,7 +883,7 @@ struct Tiled {
   // operand changes at most every Ne tiles and the next one is fetched a whole in tile early); the bias
   // tiles (ones operand) are dealt round-robin and their state is fetched before anything else.  Pad
   // elements of edge tiles keep their zeros through selects, not branches.
-  // LD: cache policy of the state LOADS (see state_load_hint()); the stores are always non-temporal.
+  // LD: cache policy of the state, loads and stores (2: non-temporal; see state_cached())
   template <bool ADAM, bool FROM_X, int LD, int KB>
   __device__ __forceinline__ void wgrad_stream(int l, const OptC& oc, int par_next, float* rec) const {
     const int t_ = tid(), lane = t_ & 63, li = lane & 15, q = lane >> 4;
@@ -939,7 +939,6 @@ struct Tiled {
       // return zeros without touching memory; the instruction stream stays the same for every tile.
       const uint32_t lane16 = (uint32_t)lane * 16, lane_t = (uint32_t)(li * 64 + q * 16), lane_oi = (uint32_t)(li * 32 + q * 8);
       constexpr uint32_t OUT_OF_RANGE = 0x40000000u;
-      constexpr int NT_HINT = 2;  // cache policy bit 1: non-temporal
       const uint32_t state_bytes = (uint32_t)Mt * Nt * 1024;
       const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(W, 0, state_bytes, 0x00020000);
       const __amdgpu_buffer_rsrc_t rM = __builtin_amdgcn_make_buffer_rsrc(Mo, 0, state_bytes, 0x00020000);
@@ -1050,9 +1049,9 @@ struct Tiled {
         else
           update(std::false_type{});
         const uint32_t vs = lane16 + (i0 >= fi || j >= fo ? OUT_OF_RANGE : 0u);  // all-pad lanes: nothing to write back
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, wv), rW, vs, tb, NT_HINT);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, mv), rM, vs, tb, NT_HINT);
-        if (ADAM) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, vv), rV, vs, tb, NT_HINT);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, wv), rW, vs, tb, LD);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, mv), rM, vs, tb, LD);
+        if (ADAM) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, vv), rV, vs, tb, LD);
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, pk), rO, lane_oi, (nt * Mt + mt) * 512, 0);
         if (rec) {
 #pragma unroll
@@ -1134,7 +1133,6 @@ struct Tiled {
     char* trp = lds + TB_LDS_TR + w * 512;
     const uint32_t lane16 = (uint32_t)lane * 16, lane_oi = (uint32_t)(li * 32 + q * 8);
     constexpr uint32_t OUT_OF_RANGE = 0x40000000u;
-    constexpr int NT_HINT = 2;
     const uint32_t state_bytes = (uint32_t)Mt * 1024;
     const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(W, 0, state_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t rM = __builtin_amdgcn_make_buffer_rsrc(Mo, 0, state_bytes, 0x00020000);
@@ -1190,9 +1188,9 @@ struct Tiled {
           pk[r] = (__bf16)wv[r];
         }
         const uint32_t vs = lane16 + (li < fo && i0 < fi ? 0u : OUT_OF_RANGE);  // all-pad lanes: nothing to write back
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, wv), rW, vs, mt * 1024, NT_HINT);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, mv), rM, vs, mt * 1024, NT_HINT);
-        if (ADAM) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, vv), rV, vs, mt * 1024, NT_HINT);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, wv), rW, vs, mt * 1024, LD);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, mv), rM, vs, mt * 1024, LD);
+        if (ADAM) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, vv), rV, vs, mt * 1024, LD);
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, pk), rO, lane_oi, mt * 512, 0);
         // [out][in] -> [in][out] through the wave's LDS patch and the transposing read
         *(bf16x4*)(trp + (li * 16 + 4 * q) * 2) = pk;
@@ -1229,22 +1227,24 @@ struct Tiled {
     }
   }
 
-  // Cache policy of the optimizer-state loads.  The state of all models in flight (about 200 MB) is far more
+  // Cache policy of the optimizer state.  The state of all models in flight (about 200 MB) is far more
   // than the caches hold, so it streams with the non-temporal hint, which keeps it from evicting the operand
   // copies, spills and input rows that are re-read within a step.  But a share of the workgroups does better
   // with ordinary loads (measured on the scale-up workload: every fourth workgroup of an XCD, 64 of 256, is the
-  // optimum, 5 % off the pass; all of them is 13 % slower than none).  The stores are non-temporal for everyone.
+  // optimum, 5 % off the pass; all of them is 13 % slower than none).
   // Where the memory-side cache (256 MB) holds the state of all models in flight, ordinary loads win outright; that is
   // up to half the chip's worth of models of any width, and up to TB_CACHED_SLOTS of slots (the state is half of them).
   // us per step of 64 rows, non-temporal in three of four -> ordinary: 64 models of 128-256-256-10 94 -> 66, 128 of them
   // 110 -> 101, 128 of 128-192-192-10 78 -> 54, 160 of them (264 MB of slots) 82 -> 70; 200 (330 MB) would go 83 -> 87.
-  __device__ __forceinline__ bool state_loads_cached() const {
+  // With ordinary stores as well: those 160 models 69 -> 59, 256 of 128-256-10 50 -> 42, 128 of 128-256-256-10 99 -> 95,
+  // a full chip of wide models the same.
+  __device__ __forceinline__ bool state_cached() const {
     return gridDim.x <= 128 || gridDim.x * P.slot_bytes <= TB_CACHED_SLOTS || ((blockIdx.x >> 3) & 3) == 0;
   }
 
   __device__ __forceinline__ void wgrad(int l, int KB, bool first, bool last, const OptC& oc, int par_next,
                                         float* rec) const {
-    const bool cached = state_loads_cached();
+    const bool cached = state_cached();
     // layers and cache policies of one optimizer and number of row blocks
     auto one_chunk = [&](auto adam, auto blocks) __attribute__((always_inline)) {
       constexpr bool ADAM = decltype(adam)::value;
