@@ -25,7 +25,8 @@ PEAK_VALU_TFLOPS = 157.3  # fp32 vector: 256 CUs x 128 lanes x 2 flop (multiply-
 PEAK_HBM_GBS = 8000.0
 # the sources each workload's training kernel is built from (the host code in bbo_mlp.hip does not count)
 KERNEL_SOURCES = {"k_train_tiled": ["common.h", "train_tiled_bf16.h"], "k_train_small": ["common.h", "train_small_f32.h"],
-                  "k_train_linear": ["common.h", "train_linear_f32.h"], "k_train": ["common.h", "bbo_mlp.hip"],
+                  "k_train_linear": ["common.h", "train_linear_f32.h", "train_linear_lds_f32.h"],
+                  "k_train": ["common.h", "bbo_mlp.hip"],
                   "k_train_mid": ["common.h", "train_small_f32.h", "train_mid_f32.h"]}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.txt")
 
