@@ -137,7 +137,9 @@ int bbo_mlp_cv_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t 
  * the workspace is a static device array inside the library, so the call takes
  * no workspace and makes no allocation of any kind on the device or in pinned
  * host memory (the item list travels as kernel arguments).  Same arguments,
- * same kernels and bit-identical results otherwise.
+ * same kernels and bit-identical results otherwise.  A host thread's first call
+ * whose suggestions need several kernels creates up to three streams and their
+ * events, unless the call is being captured, where the kernels follow each other.
  *   limit   the problem's bbo_mlp_workspace_bytes() must not exceed
  *           BBO_STATIC_SCRATCH_BYTES (some calls that need more fit as well,
  *           on fewer workgroups or one kernel after the other), and its item records (a few hundred

@@ -1319,7 +1319,14 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
   P.x_bf16 = dtype == BBO_BF16;
 
   // one launch per kernel variant that has items, side by side: the first on the caller's stream
-  const int n_side = pl.in_turn ? 0 : std::min<int>((int)pl.sub.size() - 1, SIDE_STREAMS);
+  // (into a graph they are captured one after the other: no stream is created, or drawn into the capture, behind the
+  // caller's back)
+  int n_side = pl.in_turn ? 0 : std::min<int>((int)pl.sub.size() - 1, SIDE_STREAMS);
+  if (n_side > 0) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &capture));
+    if (capture != hipStreamCaptureStatusNone) n_side = 0;
+  }
   SideStreams* side = nullptr;
   if (n_side > 0) {
     if ((rc = side_streams(n_side, &side))) return rc;
