@@ -1499,8 +1499,7 @@ int bbo_mlp_kernel_class(int64_t n, int32_t d, int32_t n_classes, const bbo_mlp_
   int32_t dims[MAXL + 1];
   int L;
   fill_dims(*hp, d, n_classes, dims, &L);
-  const int k = kernel_class(dims, L, n, dtype);
-  return k == KC_DEEP ? KC_GENERIC : k;  // to the outside, the several-layer fp32 models' kernel is part of the generic one
+  return kernel_class(dims, L, n, dtype);
 }
 
 const char* bbo_mlp_last_error(void) { return g_err.c_str(); }

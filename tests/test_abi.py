@@ -69,7 +69,12 @@ def test_kernel_class_is_a_property_of_the_suggestion(bb):
     assert k(500, 127, 17, [64]) == bb.KERNEL_GENERIC     # more than 16 outputs
     assert k(500, 128, 16, [64]) == bb.KERNEL_GENERIC     # more than 127 inputs
     assert k(500, 100, 10, [256]) == bb.KERNEL_GENERIC    # both weight matrices no longer fit one CU's LDS
-    assert k(569, 30, 2, [100, 50]) == bb.KERNEL_GENERIC  # two hidden layers in fp32
+    assert k(569, 30, 2, [100, 50]) == bb.KERNEL_DEEP     # two hidden layers in fp32
+    assert k(569, 64, 16, [128, 16, 128]) == bb.KERNEL_DEEP
+    assert k(569, 65, 2, [100, 50]) == bb.KERNEL_GENERIC  # more than 64 inputs
+    assert k(569, 30, 17, [100, 50]) == bb.KERNEL_GENERIC
+    assert k(569, 30, 2, [100, 129]) == bb.KERNEL_GENERIC
+    assert k(569, 30, 2, [16, 16, 16, 16]) == bb.KERNEL_GENERIC
     assert k(569, 30, 2, []) == bb.KERNEL_LINEAR
     assert k(1797, 64, 10, []) == bb.KERNEL_LINEAR
     assert k(500, 256, 4, []) == bb.KERNEL_LINEAR

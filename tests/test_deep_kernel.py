@@ -22,6 +22,8 @@ SHAPES = [
 def test_steps_and_score_at_the_edges_of_a_cut(bb, oracle, n, d, c, hidden, bs, solver):  # noqa: F811
     hp = {"hidden": hidden, "solver": solver, "nesterov": True, "batch_size": bs, "alpha": 0.3, "lr": 0.003,
           "momentum": 0.9, "epochs": 2, "seed": 99 + n}
+    edge = (n, d, c, hidden, bs) in SHAPES[-2:]
+    assert bb.bbo_mlp_kernel_class(n, d, c, hp, 0) == (bb.KERNEL_GENERIC if edge else bb.KERNEL_DEEP)
     cfg = small_problem(n + d, n, d, c)
     c_out, f = c if c >= 2 else 1, 1
     n_tr = int((cfg["fold_idx"] != f).sum())
