@@ -1170,6 +1170,40 @@ int side_streams(int n, SideStreams** out) {
   return BBO_OK;
 }
 
+// The side streams of one call, from the fork to the join.  Whichever way the call returns, the caller's stream is
+// behind what was launched on them by then: after an error the caller may give the workspace back.
+struct Fork {
+  SideStreams* side = nullptr;
+  hipStream_t caller = nullptr;
+  int n = 0;  // streams forked and not yet joined
+  Fork() = default;
+  Fork(const Fork&) = delete;
+  ~Fork() { (void)join(); }
+  hipError_t fork(SideStreams* st, hipStream_t s, int count) {
+    side = st;
+    caller = s;
+    hipError_t e = hipEventRecord(side->fork, s);
+    for (int i = 0; i < count && e == hipSuccess; i++) {
+      e = hipStreamWaitEvent(side->s[i], side->fork, 0);
+      if (e == hipSuccess) n = i + 1;
+    }
+    return e;
+  }
+  hipError_t join() {
+    hipError_t first = hipSuccess;
+    for (int i = 0; i < n; i++) {
+      hipError_t e = hipEventRecord(side->join[i], side->s[i]);
+      if (e == hipSuccess) e = hipStreamWaitEvent(caller, side->join[i], 0);
+      if (e != hipSuccess) {
+        (void)hipStreamSynchronize(side->s[i]);
+        if (first == hipSuccess) first = e;
+      }
+    }
+    n = 0;
+    return first;
+  }
+};
+
 // Device address of `scratch` on the current device, looked up once per device.
 int scratch_address(void** out) {
   constexpr int MAX_DEV = 64;
@@ -1327,11 +1361,11 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
     HIP_TRY(hipStreamIsCapturing(s, &capture));
     if (capture != hipStreamCaptureStatusNone) n_side = 0;
   }
-  SideStreams* side = nullptr;
+  Fork side;
   if (n_side > 0) {
-    if ((rc = side_streams(n_side, &side))) return rc;
-    HIP_TRY(hipEventRecord(side->fork, s));
-    for (int i = 0; i < n_side; i++) HIP_TRY(hipStreamWaitEvent(side->s[i], side->fork, 0));
+    SideStreams* streams = nullptr;
+    if ((rc = side_streams(n_side, &streams))) return rc;
+    HIP_TRY(side.fork(streams, s, n_side));
   }
   for (size_t li = 0; li < pl.sub.size(); li++) {
     const SubPlan& sp = pl.sub[li];
@@ -1368,13 +1402,10 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
     if (sp.lds_bytes && (rc = ensure_dynamic_lds(fn, sp.lds_bytes))) return rc;
     void* args[] = {&P};
     const int lane = (int)(li % (size_t)(n_side + 1));
-    HIP_TRY(hipLaunchKernel(fn, dim3(sp.n_slots), dim3(threads), args, sp.lds_bytes, lane ? side->s[lane - 1] : s));
+    HIP_TRY(hipLaunchKernel(fn, dim3(sp.n_slots), dim3(threads), args, sp.lds_bytes, lane ? side.side->s[lane - 1] : s));
     HIP_TRY(hipGetLastError());
   }
-  for (int i = 0; i < n_side; i++) {
-    HIP_TRY(hipEventRecord(side->join[i], side->s[i]));
-    HIP_TRY(hipStreamWaitEvent(s, side->join[i], 0));
-  }
+  HIP_TRY(side.join());
   hipLaunchKernelGGL(k_reduce, dim3((B + 255) / 256), dim3(256), 0, s, P.item_out, B, n_folds, scores, status,
                      per_fold);
   HIP_TRY(hipGetLastError());
