@@ -13,9 +13,11 @@
  *   - "device" pointers are HIP device memory on the current device; "host"
  *     pointers are ordinary host memory.  The caller owns every buffer.  The
  *     library allocates no device memory and keeps no state between calls
- *     (it keeps a small pinned host staging buffer per host thread and
- *     device; bbo_mlp_cv_eval_static is the one call that brings its own
- *     device workspace, a static array inside the library).
+ *     (it keeps, per host thread and device, a small pinned host staging buffer
+ *     and, from the first call whose suggestions need several kernels, up to
+ *     three streams on which those run side by side;
+ *     bbo_mlp_cv_eval_static is the one call that uses neither and brings its
+ *     own device workspace, a static array inside the library).
  *   - Work is enqueued on the caller's stream and the call returns without
  *     waiting for it; outputs are valid once the stream has been synchronised.
  *   - Every function returns BBO_OK or an error code; bbo_mlp_last_error()
@@ -136,15 +138,16 @@ int bbo_mlp_cv_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t 
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the workspace is a static device array inside the library, so the call takes
  * no workspace and makes no allocation of any kind on the device or in pinned
- * host memory (the item list travels as kernel arguments).  Same arguments,
- * same kernels and bit-identical results otherwise.  A host thread's first call
- * whose suggestions need several kernels creates up to three streams and their
- * events, unless the call is being captured, where the kernels follow each other.
+ * host memory (the item list travels as kernel arguments), and no stream or
+ * event: where its suggestions need several kernels, these follow each other on
+ * the caller's stream (bbo_mlp_cv_eval runs them side by side).  Same arguments,
+ * same kernels and bit-identical results otherwise.
  *   limit   the problem's bbo_mlp_workspace_bytes() must not exceed
- *           BBO_STATIC_SCRATCH_BYTES (some calls that need more fit as well,
- *           on fewer workgroups or one kernel after the other), and its item records (a few hundred
- *           bytes per suggestion and fold) BBO_STATIC_MAX_ITEM_BYTES; beyond
- *           that the call returns BBO_WORKSPACE_TOO_SMALL and enqueues nothing.
+ *           BBO_STATIC_SCRATCH_BYTES (some calls that need more fit as well:
+ *           its kernels share their part of it and may run on fewer
+ *           workgroups), and its item records (a few hundred bytes per
+ *           suggestion) BBO_STATIC_MAX_ITEM_BYTES; beyond that the call
+ *           returns BBO_WORKSPACE_TOO_SMALL and enqueues nothing.
  *   sharing every call on a device uses that device's one array: calls that
  *           overlap in time on one device (different streams or threads) race.
  *           Calls one after the other on one stream are fine; nothing is

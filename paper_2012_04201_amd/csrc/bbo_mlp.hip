@@ -1061,19 +1061,18 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
   pl.o_train = take(4ull * nn * n_folds);
   pl.o_val = take(4ull * nn * n_folds);
   pl.o_counts = take(8ull * n_folds);
-  // The allocation-free entry point's memory is what it is: a call that needs more runs its launches in turn on shared
-  // slots, and the register-resident kernels on as few as half the workgroups.
-  uint64_t sum = 0, most = 0;
+  // The allocation-free entry point runs its launches in turn on shared slots: side by side they would need streams,
+  // which it may not create.  Its memory is what it is: where a call needs more, the register-resident kernels run on as
+  // few as half their workgroups.
+  uint64_t most = 0;
   for (SubPlan& sp : pl.sub) {
     const uint64_t room = off < BBO_STATIC_SCRATCH_BYTES ? BBO_STATIC_SCRATCH_BYTES - off : 0;
     if (static_ws && (sp.kc == KC_SMALL || sp.kc == KC_MID || sp.kc == KC_DEEP) && sp.slot_bytes * sp.n_slots > room &&
         sp.slot_bytes * ((sp.n_slots + 1) / 2) <= room)
       sp.n_slots = (int)(room / sp.slot_bytes);
-    const uint64_t bytes = std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256);  // (slots are multiples of 256)
-    sum += bytes;
-    most = std::max(most, bytes);
+    most = std::max(most, std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256));  // (slots are multiples of 256)
   }
-  pl.in_turn = static_ws && off + sum > BBO_STATIC_SCRATCH_BYTES;
+  pl.in_turn = static_ws;
   for (SubPlan& sp : pl.sub) sp.o_slots = pl.in_turn ? off : take(std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256));
   if (pl.in_turn) take(most);
   pl.total = off;

@@ -114,3 +114,14 @@ def test_a_call_that_fails_half_way_leaves_no_stream_behind(child, knob):
     assert any(l[0] == "launch" and l[1] != "900" for log in failed for l in log)
     for log in failed:
         assert not unjoined(log), log
+
+
+@pytest.mark.parametrize("n,d,c,K,shapes,dtype", [
+    (300, 30, 3, 5, eval(MIXED), 0), (150, 4, 3, 5, [[8], [40]], 0), (600, 24, 4, 3, [[40, 24], [], [300]], 1),
+    (569, 30, 2, 5, [[50], [100], [150], [200]] * 40, 0)])
+def test_the_allocation_free_entry_creates_nothing(child, n, d, c, K, shapes, dtype):
+    """Its kernels follow each other on the caller's stream: no stream, event or host buffer is made or used, in a
+    thread's first call as in any other."""
+    log = child("rc = evaluate_static(%d, %d, %d, %d, %r, %d); assert rc == 0; print(json.dumps(log()))" %
+                (n, d, c, K, shapes, dtype))
+    assert {l[0] for l in log} == {"launch"} and {l[1] for l in log} == {"900"}
