@@ -110,7 +110,11 @@ int bbo_mlp_workspace_bytes(int64_t n, int32_t d, int32_t n_classes, int32_t n_f
  *   status    device, int32 [B]: 0 ok, 1 the first score is not finite
  *   per_fold  device, float32 [B][n_folds][2], or NULL
  *   workspace device, >= bbo_mlp_workspace_bytes() bytes, 256-byte aligned;
- *             contents are scratch
+ *             contents are scratch.  A workspace made for as many suggestions
+ *             of wider layers will do too: where it has less than this call's
+ *             bytes, the call's kernels share their part of it and follow each
+ *             other, on half their workgroups or more (same results);
+ *             BBO_WORKSPACE_TOO_SMALL if it does not hold that either
  *   stream    hipStream_t (NULL = default stream)
  *
  * Model: layers z = a W + b with ReLU between them; softmax cross-entropy over

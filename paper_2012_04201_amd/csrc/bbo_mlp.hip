@@ -935,9 +935,10 @@ void fill_item(ItemDesc& it, const bbo_mlp_hparams& h, int b, int64_t n, int d, 
   for (int l = 0; l < it.L; l++) it.bound[l] = (float)std::sqrt(6.0 / (double)(it.dims[l] + it.dims[l + 1]));
 }
 
-// The launches of a call, their workgroups and where everything lies in the workspace.
+// The launches of a call, their workgroups and where everything lies in a workspace of `room` bytes (pl.total may exceed
+// them: then the call does not fit).  one_stream: the launches may not run side by side.
 int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_base, const bbo_mlp_hparams* hp, int B,
-              int dtype, bool static_ws = false) {
+              int dtype, uint64_t room = UINT64_MAX, bool one_stream = false) {
   const int kstep = dtype == BBO_F32 ? 16 : 32, opsz = dtype == BBO_F32 ? 4 : 2;
   const double n_tr_est = n_folds > 1 && fold_base >= 0 ? (double)n * (n_folds - 1) / n_folds : (double)n;
   pl.sub.clear();
@@ -1061,20 +1062,29 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
   pl.o_train = take(4ull * nn * n_folds);
   pl.o_val = take(4ull * nn * n_folds);
   pl.o_counts = take(8ull * n_folds);
-  // The allocation-free entry point runs its launches in turn on shared slots: side by side they would need streams,
-  // which it may not create.  Its memory is what it is: where a call needs more, the register-resident kernels run on as
-  // few as half their workgroups.
-  uint64_t most = 0;
-  for (SubPlan& sp : pl.sub) {
-    const uint64_t room = off < BBO_STATIC_SCRATCH_BYTES ? BBO_STATIC_SCRATCH_BYTES - off : 0;
-    if (static_ws && (sp.kc == KC_SMALL || sp.kc == KC_MID || sp.kc == KC_DEEP) && sp.slot_bytes * sp.n_slots > room &&
-        sp.slot_bytes * ((sp.n_slots + 1) / 2) <= room)
-      sp.n_slots = (int)(room / sp.slot_bytes);
-    most = std::max(most, std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256));  // (slots are multiples of 256)
+  // Side by side every launch has slots of its own.  Where that is more than the workspace holds the launches run in
+  // turn on shared slots, and the register-resident kernels on as few as half their workgroups: a workspace sized for the
+  // widest models of a search holds any mix of narrower ones, though these come in more variants, and the variants of
+  // less than a CU's registers in more workgroups.
+  auto slots_of = [](const SubPlan& sp) {  // (slots are multiples of 256)
+    return std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256);
+  };
+  uint64_t sum = 0, most = 0;
+  for (const SubPlan& sp : pl.sub) sum += slots_of(sp);
+  pl.in_turn = one_stream || off + sum > room;
+  if (pl.in_turn) {
+    const uint64_t left = off < room ? room - off : 0;
+    for (SubPlan& sp : pl.sub) {
+      if ((sp.kc == KC_SMALL || sp.kc == KC_MID || sp.kc == KC_DEEP) && sp.slot_bytes * sp.n_slots > left &&
+          sp.slot_bytes * ((sp.n_slots + 1) / 2) <= left)
+        sp.n_slots = (int)(left / sp.slot_bytes);
+      sp.o_slots = off;
+      most = std::max(most, slots_of(sp));
+    }
+    take(most);
+  } else {
+    for (SubPlan& sp : pl.sub) sp.o_slots = take(slots_of(sp));
   }
-  pl.in_turn = static_ws;
-  for (SubPlan& sp : pl.sub) sp.o_slots = pl.in_turn ? off : take(std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256));
-  if (pl.in_turn) take(most);
   pl.total = off;
   return BBO_OK;
 }
@@ -1282,7 +1292,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
       return fail(BBO_INVALID_ARG, "trace buffer too small");
   }
   Plan pl;
-  rc = make_plan(pl, n, d, n_classes, n_folds, fold_base, hp, B, dtype, static_ws);
+  rc = make_plan(pl, n, d, n_classes, n_folds, fold_base, hp, B, dtype, workspace_bytes, static_ws);
   if (rc) return rc;
   if (static_ws && (pl.total > BBO_STATIC_SCRATCH_BYTES || pl.items_bytes > BBO_STATIC_MAX_ITEM_BYTES))
     return fail(BBO_WORKSPACE_TOO_SMALL,
@@ -1426,7 +1436,10 @@ int bbo_mlp_workspace_bytes(int64_t n, int32_t d, int32_t n_classes, int32_t n_f
   Plan pl;
   rc = make_plan(pl, n, d, n_classes, n_folds, 0, hp, B, dtype);
   if (rc) return rc;
-  *out = (size_t)pl.total;
+  // (records at their largest, whatever kernel they are for: the size of a call's records does not decide whether a
+  // workspace made for as many other models holds it)
+  constexpr size_t record = std::max({sizeof(ItemDesc), sizeof(TItem), sizeof(SItem), sizeof(MItem), sizeof(DItem)});
+  *out = (size_t)(pl.total + std::max<uint64_t>(record * (uint64_t)B + 256 * MAX_LAUNCHES, pl.items_bytes) - pl.items_bytes);
   return BBO_OK;
 }
 

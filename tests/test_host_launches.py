@@ -125,3 +125,34 @@ def test_the_allocation_free_entry_creates_nothing(child, n, d, c, K, shapes, dt
     log = child("rc = evaluate_static(%d, %d, %d, %d, %r, %d); assert rc == 0; print(json.dumps(log()))" %
                 (n, d, c, K, shapes, dtype))
     assert {l[0] for l in log} == {"launch"} and {l[1] for l in log} == {"900"}
+
+
+@pytest.mark.parametrize("n,d,c,K,dtype,widest,narrower", [
+    (569, 30, 2, 5, 0, [224], [[50 + 3 * i % 175] for i in range(256)]),   # variants side by side need three times the room
+    (569, 30, 2, 5, 0, [224], [[192]] * 256),                              # more workgroups a CU, more room in all
+    (569, 13, 2, 5, 0, [224], [[10]] * 512),
+    (1797, 64, 10, 5, 0, [256], [[20 + i % 236] for i in range(256)]),
+    (569, 30, 2, 5, 0, [128, 128, 128], [[128, 128, 128], [64, 60, 64]] * 128),
+    (1268, 43, 1, 4, 0, [46, 237, 155], [[46, 237, 155], [46, 237, 150], [46, 100, 100]] * 100),  # and larger records
+    (600, 64, 10, 5, 1, [256, 256], [[256, 256], [256, 128], [64, 64], []] * 100),
+    (569, 30, 2, 5, 0, [224], [[20], [100], [200], [224]] * 2)])
+def test_a_workspace_for_the_widest_models_holds_a_mix_of_narrower_ones(child, n, d, c, K, dtype, widest, narrower):
+    B = len(narrower)
+    out = child("""
+        n, d, c, K, dtype, widest, narrower, B = %r
+        ws = need(n, d, c, K, [widest] * B, dtype)
+        full = need(n, d, c, K, narrower, dtype)
+        rcs, logs = [], []
+        for room in (ws, full, 256):
+            rcs.append(evaluate(n, d, c, K, narrower, room, dtype))
+            logs.append(log())
+        print(json.dumps([ws, full, rcs, logs]))
+    """ % ((n, d, c, K, dtype, widest, narrower, B),))
+    ws, full, rcs, (tight, roomy, none) = out
+    assert rcs == [0, 0, 3] and none == []
+    grids = lambda log: sorted((int(l[3]), int(l[4]), int(l[2])) for l in log if l[0] == "launch")
+    streams = lambda log: {l[1] for l in log if l[0] == "launch"}
+    for (t0, l0, g), (t1, l1, g1) in zip(grids(tight), grids(roomy)):  # the same launches, on half the workgroups or more
+        assert (t0, l0) == (t1, l1) and g <= g1 <= 2 * g + 1
+    assert len(grids(tight)) == len(grids(roomy))
+    assert streams(tight) in (streams(roomy), {"900"}) and (ws < full or streams(tight) == streams(roomy))

@@ -61,3 +61,24 @@ def test_variants_side_by_side_score_as_alone(bb):  # noqa: F811
             s1, st1 = bb.bbo_mlp_cv_eval(X, y, 7, ft, 5, [hps[i]], 0)
             torch.cuda.synchronize()
             assert torch.equal(s[i], s1[0]) and torch.equal(st[i:i + 1], st1), hps[i]
+
+
+@pytest.mark.parametrize("n,d,c,widest,narrower,dtype", [
+    (300, 30, 2, [224], [[20 + 5 * i % 205] for i in range(256)], 0),
+    (300, 30, 2, [224], [[192]] * 256, 0),
+    (200, 64, 10, [256], [[20 + 7 * i % 230] for i in range(120)], 0),
+    (200, 30, 2, [128, 128, 128], [[128, 128, 128], [64, 60, 64]] * 60, 0),
+    (200, 24, 3, [300, 200], [[300, 200], [250, 150], [40, 24], []] * 40, 0),
+    (300, 64, 10, [256, 256], [[256, 256], [256, 128], [64, 64], []] * 20, 1)])
+def test_a_workspace_for_the_widest_models_gives_a_narrower_mix_the_same_bits(bb, n, d, c, widest, narrower, dtype):  # noqa: F811
+    cfg = small_problem(9, n, d, c, bf16=bool(dtype))
+    X, y, ft = bb.to_device(cfg)
+    hps = [{"hidden": h, "batch_size": 50, "epochs": 1, "lr": 0.003, "seed": i} for i, h in enumerate(narrower)]
+    want, want_st = bb.bbo_mlp_cv_eval(X, y, c, ft, 5, hps, dtype)
+    size = bb.bbo_mlp_workspace_bytes(n, d, c, 5, [dict(h, hidden=widest) for h in hps], dtype)
+    ws = bb.alloc_workspace(size + 4096, X.device)
+    ws[size:] = 0xA5  # what lies behind the workspace stays as it is
+    for _ in range(2):
+        s, st = bb.bbo_mlp_cv_eval(X, y, c, ft, 5, hps, dtype, workspace=ws[:size])
+        torch.cuda.synchronize()
+        assert torch.equal(s, want) and torch.equal(st, want_st) and bool((ws[size:] == 0xA5).all())
