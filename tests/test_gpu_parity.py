@@ -175,8 +175,8 @@ TRACE_CASES = [
     (180, 9, 0, [17, 18, 19], "sgd", True, 48, 0.01),
     (90, 3, 3, [1], "adam", False, 5, 0.0),
     (180, 9, 3, [9, 1, 5, 7], "adam", False, 48, 0.01),   # the maximum depth, one hidden layer a single unit wide
-    # the LDS-resident kernel without its per-epoch row table (rows permuted on the fly): more than 4,096 rows,
-    # and a hidden layer so wide that the table no longer fits beside the weights
+    # the register-resident kernel past the rows whose permutation network is tabled whole, and at its widest
+    # (rows permuted on the fly, past 65,535 of them: test_kernel_cuts.py)
     (5000, 20, 3, [40], "adam", False, 700, 0.01),
     (1500, 30, 2, [224], "adam", False, 100, 0.01),
 ]
@@ -323,7 +323,7 @@ def test_random_shapes_bf16_steps(bb, oracle, seed):
 
 
 def random_fp32_case(seed):
-    """A seeded random fp32 shape: even seeds inside what the LDS-resident kernel takes (one hidden layer,
+    """A seeded random fp32 shape: even seeds inside what the register-resident kernel takes (one hidden layer,
     d <= 63, width <= 224, <= 4 outputs), odd seeds anything else the header admits (mostly the generic kernel)."""
     r = np.random.default_rng(8000 + seed)
     if seed % 2 == 0:
@@ -367,7 +367,7 @@ def test_random_shapes_fp32_steps(bb, oracle, seed):
 
 
 def random_mid_case(seed, fits):
-    """A seeded random shape for the wider LDS-resident fp32 kernel: one hidden layer, up to 127 inputs and
+    """A seeded random shape for the wider register-resident fp32 kernel: one hidden layer, up to 127 inputs and
     16 outputs, shapes the narrower kernel does not take (64 inputs or more, or more than 4 outputs)."""
     r = np.random.default_rng(8500 + seed)
     if seed % 2 == 0:
@@ -376,7 +376,7 @@ def random_mid_case(seed, fits):
         d, c = int(r.integers(1, 128)), int(r.integers(5, 17))
     n = int(r.integers(60, 600))
     h = int(r.integers(1, 257))
-    while not fits(n, d, c, h):  # the hidden weights must fit in LDS beside the input tile
+    while not fits(n, d, c, h):  # weights and gradients must fit in registers
         h = int(r.integers(1, h))
     bs = int(r.choice([0, 1, 5, 16, 63, 64, 65, 100, 130, 200]))
     return n, d, c, [h], bs, str(r.choice(["adam", "sgd"])), bool(r.integers(0, 2)), float(r.choice([0.0, 0.05, 2.0]))
@@ -421,11 +421,13 @@ def test_random_shapes_mid_kernel_steps_and_scores(bb, oracle, seed):
 
 LOGIT_SHAPES = [
     # n, d, hidden, solver, batch, dtype: every training kernel, one and several chunks of rows
-    (300, 20, [40], "adam", 50, 0),         # LDS-resident fp32
-    (210, 9, [130], "sgd", 0, 0),           # LDS-resident fp32, full batch, ragged row tiles
-    (150, 6, [], "adam", 32, 0),            # no hidden layer
+    (300, 20, [40], "adam", 50, 0),         # register-resident fp32
+    (210, 9, [130], "sgd", 0, 0),           # register-resident fp32, full batch, ragged row tiles
+    (150, 6, [], "adam", 32, 0),            # no hidden layer, data set in LDS
+    (150, 70, [], "adam", 32, 0),           # no hidden layer, too many inputs for that
+    (260, 40, [33, 21], "adam", 64, 0),     # fp32, two or three hidden layers
     (260, 70, [33, 21], "adam", 64, 0),     # generic fp32
-    (280, 80, [50], "adam", 70, 0),         # wider LDS-resident fp32 (64 inputs or more), two chunks per step
+    (280, 80, [50], "adam", 70, 0),         # wider register-resident fp32 (64 inputs or more), two chunks per step
     (400, 64, [96, 80], "adam", 128, 1),    # LDS-tiled bf16, one chunk
     (640, 128, [200], "sgd", 300, 1),       # LDS-tiled bf16, two chunks
     (330, 36, [50, 40, 30], "adam", 77, 1), # generic bf16 (three hidden layers)
@@ -641,8 +643,9 @@ def test_linear_models_many_on_one_launch(bb, oracle):
 
 CONTROL_SHAPES = [
     # n, d, classes, hidden, batch, dtype: one shape per training kernel
-    (300, 20, 3, [40], 50, 0),        # LDS-resident fp32
-    (330, 64, 10, [72], 48, 0),       # wider LDS-resident fp32
+    (300, 20, 3, [40], 50, 0),        # register-resident fp32
+    (330, 64, 10, [72], 48, 0),       # wider register-resident fp32
+    (260, 40, 5, [33, 21], 64, 0),    # fp32, two or three hidden layers
     (260, 70, 5, [33, 21], 64, 0),    # generic fp32
     (400, 64, 10, [96, 80], 128, 1),  # LDS-tiled bf16
 ]
@@ -704,12 +707,17 @@ def test_plateau_stop_epoch_and_score(bb, oracle, n, d, c, hidden, bs, dtype):
 
 EARLY_STOP_SHAPES = [
     # n, d, classes, hidden, batch, dtype, kernel: every training kernel
-    (300, 20, 3, [40], 50, 0, "SMALL"),          # LDS-resident fp32, row order tabled per epoch
-    (5000, 20, 2, [24], 700, 0, "SMALL"),        # LDS-resident fp32, rows permuted on the fly
-    (330, 64, 10, [72], 48, 0, "MID"),           # wider LDS-resident fp32, row order tabled per epoch
-    (5000, 70, 5, [60], 700, 0, "MID"),          # wider LDS-resident fp32, rows permuted on the fly
+    (300, 20, 3, [40], 50, 0, "SMALL"),          # register-resident fp32, permutation network tabled whole
+    (5000, 20, 2, [24], 700, 0, "SMALL"),        # ... its round function and the row order tabled
+    (66000, 4, 2, [16], 1500, 0, "SMALL"),       # ... rows permuted on the fly (row ids past 16 bits are not tabled)
+    (330, 64, 10, [72], 48, 0, "MID"),           # wider register-resident fp32, the same three
+    (5000, 70, 5, [60], 700, 0, "MID"),
+    (66000, 6, 5, [24], 1500, 0, "MID"),
+    (260, 40, 5, [33, 21], 64, 0, "DEEP"),       # fp32, two or three hidden layers, tabled and permuted on the fly
+    (66000, 5, 2, [20, 16], 1500, 0, "DEEP"),
     (260, 70, 5, [33, 21], 64, 0, "GENERIC"),
-    (240, 12, 0, [], 32, 0, "LINEAR"),           # wavefront per model, row order tabled
+    (240, 12, 0, [], 32, 0, "LINEAR"),           # no hidden layer, data set in LDS
+    (240, 12, 4, [], 32, 0, "LINEAR"),           # wavefront per model, row order tabled
     (5000, 9, 3, [], 600, 0, "LINEAR"),          # wavefront per model, rows permuted on the fly
     (400, 64, 10, [96, 80], 128, 1, "TILED"),
     (700, 128, 10, [200], 300, 1, "TILED"),      # minibatches of two chunks of rows

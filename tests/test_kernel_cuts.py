@@ -15,7 +15,7 @@ ONE_SMALL_LAYER = [
 WIDE_HEAD = [
     (150, 16, 5, [64], 0), (150, 5, 16, [65], 33), (203, 48, 7, [129], 64), (203, 64, 10, [128], 63), (203, 64, 2, [129], 65),
     (203, 65, 12, [128], 17), (203, 80, 10, [256], 100), (203, 96, 1, [200], 80), (203, 97, 3, [64], 50), (203, 112, 0, [128], 64),
-    (203, 127, 16, [16], 1), (203, 127, 10, [128], 90), (5000, 64, 10, [40], 1000)]
+    (203, 127, 16, [16], 1), (203, 127, 10, [128], 90), (5000, 64, 10, [40], 1000), (66000, 6, 5, [24], 9000)]
 # (the last two of each: the data set no longer fits into LDS, too many inputs)
 LINEAR = [(n, d, c, [], bs) for c in (0, 1, 2) for n, d, bs in (
     (150, 7, 0), (151, 8, 17), (203, 15, 64), (203, 16, 1), (300, 31, 65), (300, 32, 130), (520, 47, 33), (520, 55, 200),

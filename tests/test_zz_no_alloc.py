@@ -40,7 +40,7 @@ def both_ways(bb, cfg):
 
 
 def test_static_workspace_entry_matches_twice_the_second_call_smaller(bb, oracle):
-    # first call: the regression workload (SGD, 40 models with a hidden layer: LDS-resident kernel with its
+    # first call: the regression workload (SGD, 40 models with a hidden layer: register-resident kernel with its
     # per-workgroup slots in the workspace) plus models without a hidden layer (wavefront-per-model kernel)
     big = inputs.make_config(2, epochs=6)
     big["hparams"] = big["hparams"] + [dict(h, hidden=[]) for h in big["hparams"][:3]]
