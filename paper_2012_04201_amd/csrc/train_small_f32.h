@@ -75,16 +75,22 @@ __host__ __device__ constexpr int sm_regs(int kt, int nt, int co) { return nt * 
 
 // The cut depends on the shape alone, never on the call: the order in which the waves' partial outputs are added
 // is part of a suggestion's result, and that must not depend on its companions.
+constexpr SmallCut sm_cut(int kt, int nut, int co) {  // nut: unit tiles
+  const int ntmax = kt == 4 ? 1 : (kt == 3 || co == 4 ? 2 : 3);
+  int waves = kt == 1 && nut <= 2 ? 2 : 4;  // two waves could not hold the inputs of a wider chunk in flight
+  if (nut > waves * ntmax) waves = 8;
+  return SmallCut{kt, (nut + waves - 1) / waves, co, waves};
+}
 __host__ inline SmallCut small_cut(const int32_t* dims) {
-  SmallCut s;
-  const int nut = rup(dims[1], 16) / 16;
-  s.kt = rup(dims[0], 16) / 16;
-  s.co = dims[2] <= 2 ? dims[2] : 4;
-  const int ntmax = s.kt == 4 ? 1 : (s.kt == 3 || s.co == 4 ? 2 : 3);
-  s.waves = s.kt == 1 && nut <= 2 ? 2 : 4;  // two waves could not hold the inputs of a wider chunk in flight
-  if (nut > s.waves * ntmax) s.waves = 8;
-  s.nt = (nut + s.waves - 1) / s.waves;
-  return s;
+  return sm_cut(rup(dims[0], 16) / 16, rup(dims[1], 16) / 16, dims[2] <= 2 ? dims[2] : 4);
+}
+// is there a model with this cut?
+constexpr bool sm_occurs(int kt, int nt, int co, int waves) {
+  for (int nut = 1; nut <= 224 / 16; nut++) {
+    const SmallCut s = sm_cut(kt, nut, co);
+    if (s.nt == nt && s.waves == waves) return true;
+  }
+  return false;
 }
 
 // LDS of the row pipeline: input tiles, labels, row lists

@@ -1,4 +1,5 @@
-"""Static check of the wavefront-per-model kernel's generated code (no GPU needed).
+"""Static checks of the built kernels (no GPU needed): which variants there are, and the loop nest of the
+wavefront-per-model kernel's generated code.
 
 Every wavefront of that kernel pops its next model from the work queue with all 64 lanes taking part.
 A pop under `if (lane == 0)` compiled into a kernel that never ended: the loop body finishes with
@@ -41,3 +42,32 @@ def test_linear_kernel_loop_nest_is_the_sources(tmp_path):
         assert max(depth) == 5, depth
         body = "\n".join(lines[s:e])
         assert "global_atomic_add" in body and "s_endpgm" in body
+
+
+@pytest.mark.skipif(shutil.which("nm") is None, reason="nm not on PATH")
+def test_the_library_holds_the_variants_that_the_cuts_can_ask_for():
+    """The register-resident kernels are compiled for each way a model of their shapes is cut, and for no other."""
+    lib = os.path.join(ROOT, "paper_2012_04201_amd", "libbbo_mlp.so")
+    if not os.path.exists(lib):
+        from paper_2012_04201_amd import build
+        build.build_lib()
+    names = subprocess.run(["nm", "-C", lib], capture_output=True, text=True, check=True).stdout
+    built = lambda k: sorted(tuple(int(x) for x in m.split(",")) for m in
+                             re.findall(r"__device_stub__k_train_%s<([0-9, ]+)>" % k, names))
+    tiles = lambda x: -(-x // 16)
+    small, mid = set(), set()
+    for d in range(1, 128):
+        for h in range(1, 257):
+            kt, nut = tiles(d), tiles(h)
+            for c in (1, 2, 4):
+                if d <= 63 and h <= 224:
+                    per_wave = 1 if kt == 4 else (2 if kt == 3 or c == 4 else 3)
+                    waves = 2 if kt == 1 and nut <= 2 else 4
+                    waves = 8 if nut > waves * per_wave else waves
+                    small.add((kt, -(-nut // waves), c, waves))
+            waves = 4 if nut <= 4 else 8  # (with 5 to 16 outputs every shape is one of the wider kernel's)
+            if kt * -(-nut // waves) <= 12:
+                mid.add((kt, -(-nut // waves), waves))
+    assert built("small") == sorted(small)
+    assert built("mid") == sorted(mid)
+    assert built("deep") == sorted((kt, layers, waves) for kt in range(1, 5) for layers in (2, 3) for waves in (4, 8))
