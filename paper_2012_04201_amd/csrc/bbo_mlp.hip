@@ -15,7 +15,8 @@
 // kernels for one hidden layer (train_small_f32.h, train_mid_f32.h) and for two or three (train_deep_f32.h), the kernels
 // for models without one (train_linear_lds_f32.h, train_linear_f32.h) and the generic kernel below, which takes every
 // shape the header admits.  The planner gives each suggestion to the fastest kernel that takes its shape and launches
-// every kernel variant that got items, side by side, each with its own item array and queue counter.
+// every kernel variant that got items, each with its own item array and queue counter: side by side, or one after the
+// other where the workspace does not hold that, on the static workspace and under capture.
 //
 // Operand layout.  MFMA operands are read straight from memory as 16-byte
 // vectors along the contracted index, so every tensor is kept in the layout

@@ -2,7 +2,7 @@
 // to 16 outputs) on the row pipeline of train_small_f32.h.
 //
 // One workgroup trains one model.  Wave w owns unit tile w (16 units) of every level: its weights and their gradients
-// stay in registers for the whole run, as blocks of four values a lane in the layout the MFMA (16x16x4 fp32) both takes
+// stay in registers for the whole run (as far as these reach: dp_near()), as blocks of four values a lane in the layout the MFMA (16x16x4 fp32) both takes
 // them in and leaves their gradient in (lane: unit li, columns 4q..4q+3 of a k tile).  The levels of a chunk of 64 rows
 // lie in LDS, row-major, because every wave needs all of them; a level's deltas are written over its activations.
 //
@@ -52,7 +52,9 @@ __host__ inline SmallCut deep_cut(const int32_t* dims, int L) {
 }
 // Blocks of four values a lane holds: input layer, hidden layers, output layer, biases.
 __host__ __device__ constexpr int dp_blocks(int kt, int h, int waves) { return kt + (h - 1) * waves + 2; }
-// The moments live in registers up to here (with weights and gradients four times the blocks, of 256 registers).
+// The moments live in registers up to here (with weights and gradients four times the blocks, of 256 registers).  Without
+// them the widest cuts still overflow: by the compiler's report three layers on eight waves spill 59, 117, 151 and 172
+// vector registers at one to four input tiles, every other variant 14 at most.
 __host__ __device__ constexpr bool dp_near(int kt, int h, int waves) { return dp_blocks(kt, h, waves) <= 8; }
 __host__ __device__ constexpr uint32_t dp_fixed_lds(int kt, int h, int waves) {
   // levels, the output layer's blocks, output deltas

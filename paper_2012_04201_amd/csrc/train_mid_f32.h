@@ -68,7 +68,9 @@ struct MItem {
 // How a model is cut, by shape alone (a suggestion's scores may not depend on its companions); waves == 0: not a shape
 // of this kernel.  One tile a wave while eight waves reach (more models a CU with four), else two: one tile leaves the
 // registers for everything, and eight waves of one tile beat four of two by a quarter even with the chip full (64-100-10,
-// 1000 models: 3.2 ms against 3.9).  Beyond kt * nt = 12 the weights and gradients alone overflow the registers.
+// 1000 models: 3.2 ms against 3.9).  Beyond kt * nt = 12 the weights and gradients alone overflow the registers; close to
+// it they crowd others out: by the compiler's report <5,2,8> spills 53 vector registers and <6,2,8> 261, <3,2,8> and
+// <4,2,8> 18, the others 3 at most.
 __host__ inline SmallCut mid_cut(const int32_t* dims, int L) {
   SmallCut m = {0, 0, 0, 0};
   if (L != 2 || dims[0] > 127 || dims[1] > 256 || dims[2] > 16) return m;

@@ -2,7 +2,8 @@
 // studies" shape: up to 63 inputs, hidden width up to 224, up to 4 outputs).
 //
 // One workgroup of W waves trains one model.  Wave w owns the hidden-unit tiles (16 units) w, w + W, .. for the
-// whole run, and everything that belongs to them stays in its registers from the first draw to the score: the
+// whole run, and everything that belongs to them stays in its registers (as far as these reach: sm_occupancy()) from the
+// first draw to the score: the
 // hidden layer's weights, both moments and the step's gradient, and the units' rows of the output layer with
 // theirs.  That works because the MFMA (16x16x4 fp32) wants a weight in the same lane as operand of the forward
 // product as it leaves its gradient in: lane (unit li, columns 4q..4q+3 of a k tile).  The output bias is kept by
@@ -19,8 +20,9 @@
 //
 // Inputs are fetched two chunks ahead: requested into registers right after a chunk's barrier, put into LDS before
 // the next one (three input tiles in rotation, so that neither needs a barrier of its own).  The rows of an epoch
-// are tabled in LDS (16-bit row ids, two tables in turn); the rows set aside for early stopping are scored by the
-// same loop as chunks of their own between two epochs, and so are the held fold's rows at the end.
+// are tabled in LDS (16-bit row ids; one table, written anew when the epoch's first chunk is about to be requested); the
+// rows set aside for early stopping are scored by the same loop as chunks of their own between two epochs, and so are
+// the held fold's rows at the end.  A set of more than 65,535 rows, or whose tables do not fit, is permuted chunk by chunk.
 //
 // What bounds it: with the chip full, the matrix pipe shares its SIMD with the vector work around it (ReLU, output
 // layer, softmax, update), and two to four waves per SIMD have to cover each other's latencies; with few models,
@@ -145,7 +147,10 @@ __host__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n, const Sm
   y.lds_total = y.p.total;
 }
 
-// Waves per SIMD the registers of a variant are budgeted for (512 registers per lane and SIMD).
+// Waves per SIMD the registers of a variant are budgeted for (512 registers per lane and SIMD).  The largest variants of a
+// budget do not fit it altogether: by the compiler's report <2,3,2,4> (129 to 192 units, 17 to 32 inputs, two outputs)
+// spills 64 vector registers, <2,3,1,4> 18, <2,1,4,4> 62, <3,2,4,4> and <3,2,4,8> 82 and 62, <4,2,.,8> (129 units and more,
+// 49 inputs and more) 89, 158 and 223 at one, two and four output slots; the others 3 at most.
 __host__ __device__ constexpr int sm_occupancy(int kt, int nt, int co) {
   return nt == 1 && kt <= 2 ? 4 : 2;
 }

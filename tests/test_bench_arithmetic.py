@@ -2,6 +2,7 @@
 small cases and compared with the figures the workloads are specified with; the kernel-source fingerprint that
 gates the recorded counter traffic; the refusal of more than one GPU."""
 import os
+import re
 import subprocess
 import sys
 
@@ -61,6 +62,16 @@ def test_kernel_fingerprint_ignores_comments_only(tmp_path, monkeypatch):
     assert bench.kernel_source_hash("k_train_small") == h0
     p.write_text(text.replace("SM_RC = 64", "SM_RC = 32", 1))
     assert bench.kernel_source_hash("k_train_small") != h0
+
+
+def test_kernel_fingerprint_covers_the_headers_its_sources_include():
+    src = os.path.join(ROOT, "paper_2012_04201_amd", "csrc")
+    for kernel, names in bench.KERNEL_SOURCES.items():
+        bench.kernel_source_hash(kernel)
+        for name in names:
+            if name.endswith(".h"):
+                text = open(os.path.join(src, name)).read()
+                assert set(re.findall(r'#include "(\w+\.h)"', text)) <= set(names), (kernel, name)
 
 
 def test_more_than_one_gpu_is_refused_before_anything_runs():
