@@ -9,15 +9,19 @@
 //   forward   lane = row: the row is read from LDS into registers (16 bytes a read; stride / 4 is odd, so that scattered
 //             rows spread over the banks), the weights are broadcast reads of the wave's own copy.
 //   outputs   loss and output delta in the lane.
-//   gradient  the lane keeps D x CO sums x[k] * delta[j] of its own rows in registers over the chunks of the step; at the
-//             step's end they are folded over the 64 lanes, a halving at a time, which leaves lane t with the sums of
-//             parameters t, t + 64 in the packed order W[in][out], b[out].
+//   gradient  the lane keeps D sums x[k] * delta of its own rows in registers over the chunks of the step; at the step's
+//             end they are folded over the 64 lanes, a halving at a time, which leaves lane t with the sum of column t.
 //   update    in the owning lane, which refreshes the wave's copy of the weights.
 //
-// What bounds it: vector instructions, about 2 D CO per 64 rows for the products and 3 D CO per step for the folds, with the
-// LDS reads of the rows next.  The kernel before gathered each chunk's rows from global memory into LDS (a dozen
-// instructions per element) and walked them again row by row for the gradient: 10,240 models of 569 x 30, two outputs, 20
-// epochs took 4.9 ms and take 1.7 ms.
+// Two classes are worked on as one column.  Their softmax, its loss and both deltas depend on z[1] - z[0] alone, and the
+// deltas are p and -p, p the probability of the class that is not the row's: the products run over the differences of the
+// weights, one sum per column serves both gradients, and the weights themselves, their moments and their updates stay two
+// (the classes of a column in lanes t and t + 32, or in one lane where there are more columns than 32).
+//
+// What bounds it: vector instructions, about 2 D per 64 rows for the products and 3 D per step for the folds, with the LDS
+// reads of the rows next.  10,240 models of 569 x 30, two classes, 20 epochs, took 1.67 ms a call with a column per class
+// and folds through the LDS crossbar, and take 1.11 ms.  (Gathering each chunk's rows from global memory, as
+// train_linear_f32.h does: 4.9 ms.)
 #pragma once
 #include "common.h"
 #include "train_small_f32.h"  // folding sums
@@ -28,19 +32,17 @@ constexpr uint32_t LL_LDS_LIMIT = 160 * 1024 - 64;
 
 // Wavefronts per SIMD the registers of a variant are budgeted for: the lane's row, its sums and about 64 more (weights on
 // their way, the optimizer's and the folds' temporaries).
-__host__ __device__ constexpr int ll_occupancy(int dd, int co) {
-  return dd + dd * co + 64 <= 128 ? 4 : (dd + dd * co + 64 <= 168 ? 3 : 2);
-}
+__host__ __device__ constexpr int ll_occupancy(int dd) { return 2 * dd + 64 <= 128 ? 4 : (2 * dd + 64 <= 168 ? 3 : 2); }
 struct LinLds {
   int32_t dd, waves;           // columns (inputs and bias padded to a multiple of 8); wavefronts per workgroup, 0: not a case for it
   uint32_t shared, wave_bytes; // LDS of the data set and of each wavefront
 };
 // LDS of a wavefront: weights, the training list in the order of the early-stopping cut, the epoch's row order, the round
 // function of the permutation
-__host__ __device__ inline uint32_t ll_wave_bytes(int dd, int co, int64_t n) {
+__host__ __device__ inline uint32_t ll_wave_bytes(int dd, int64_t n) {
   int hb = 1;
   while ((1 << (2 * hb)) < n) hb++;
-  return (uint32_t)((dd * co * 4 + 2 * ((2 * n + 15) & ~15) + ((4 << hb) * 2)) + 15) & ~15u;
+  return (uint32_t)((dd * 4 + 2 * ((2 * n + 15) & ~15) + ((4 << hb) * 2)) + 15) & ~15u;
 }
 // By the size of the data set and the model alone: at least a wavefront per SIMD must fit beside the data set, or the
 // SIMDs idle and gathering rows from global memory is the better way.
@@ -49,16 +51,18 @@ __host__ inline LinLds ll_plan(int64_t n, int d, int c) {
   if (c > 2 || d > 63 || n < 1 || n > 4096) return l;
   l.dd = rup(d + 1, 8);
   l.shared = (uint32_t)((n * (l.dd + 4) * 4 + n * 4 + 15) & ~15);
-  l.wave_bytes = ll_wave_bytes(l.dd, c, n);
+  l.wave_bytes = ll_wave_bytes(l.dd, n);
   if (l.shared + 4 * l.wave_bytes > LL_LDS_LIMIT) return l;
-  const int fit = (int)((LL_LDS_LIMIT - l.shared) / l.wave_bytes), most = 4 * ll_occupancy(l.dd, c);
+  const int fit = (int)((LL_LDS_LIMIT - l.shared) / l.wave_bytes), most = 4 * ll_occupancy(l.dd);
   l.waves = fit < most ? fit : most;
   return l;
 }
 
 template <int D, int CO>
 struct LinearLds {
-  static constexpr int S = D + 4, NQ = D / 4, NV = D * CO, M = (NV + 15) / 16, M1 = (M + 1) / 2, NB = (M1 + 1) / 2;
+  static constexpr int S = D + 4, NQ = D / 4, M = (D + 15) / 16;
+  static constexpr bool SPLIT = CO == 2 && D <= 32;  // the classes of a column in lanes t and t + 32
+  static constexpr int NB = CO == 2 && !SPLIT ? 2 : 1;  // parameters of a lane
   const TrainParams& P;
   const float *xs, *ys;
   float* ws;
@@ -70,80 +74,63 @@ struct LinearLds {
 #pragma unroll
     for (int q = 0; q < NQ; q++) x[q] = *(const f32x4*)(p + 4 * q);
   }
-  __device__ __forceinline__ void forward(const f32x4 (&x)[NQ], float (&z)[CO]) const {
+  // the output, or with two classes z[1] - z[0]
+  __device__ __forceinline__ float forward(const f32x4 (&x)[NQ]) const {
+    float z = 0.f;
 #pragma unroll
-    for (int j = 0; j < CO; j++) z[j] = 0.f;
-#pragma unroll
-    for (int i = 0; i < NV / 4; i++) {
+    for (int i = 0; i < NQ; i++) {
       const f32x4 w = *(const f32x4*)(ws + 4 * i);
 #pragma unroll
-      for (int u = 0; u < 4; u++) {
-        const int k = (4 * i + u) / CO, j = (4 * i + u) % CO;
-        z[j] += x[k / 4][k % 4] * w[u];
-      }
+      for (int u = 0; u < 4; u++) z += x[i][u] * w[u];
     }
+    return z;
   }
-  // output deltas (TRAIN) and, if `loss`, the loss and second score of the lane's row
+  // output delta (TRAIN; with two classes that of class 1) and, if `loss`, the loss and second score of the lane's row
   template <bool TRAIN>
-  __device__ __forceinline__ void outputs(const float (&z)[CO], bool valid, float y, float inv_mb, bool loss, float (&dl)[CO],
-                                          double& lsum, double& hits) const {
-    const float scale = valid ? inv_mb : 0.f;
+  __device__ __forceinline__ float outputs(float z, bool valid, float y, float inv_mb, bool loss, double& lsum, double& hits) const {
+    float dl = 0.f;
     if constexpr (CO == 2) {
-      const int yr = __float_as_int(y);
-      const float mx = fmaxf(z[0], z[1]);
-      const float e0 = expf(z[0] - mx), e1 = expf(z[1] - mx), se = e0 + e1;
+      const bool one = __float_as_int(y) == 1;
       if (loss && valid) {
-        lsum += (double)(mx + logf(se) - (yr == 1 ? z[1] : z[0]));
-        hits += (z[1] > z[0] ? 1 : 0) == yr ? 1.0 : 0.0;
+        lsum += (double)sm_two_class_loss(z, one);
+        hits += (z > 0.f) == one ? 1.0 : 0.0;
       }
-      if (TRAIN) {
-        const float rs = 1.f / se;
-        dl[0] = (e0 * rs - (yr == 0 ? 1.f : 0.f)) * scale;
-        dl[1] = (e1 * rs - (yr == 1 ? 1.f : 0.f)) * scale;
-      }
+      if (TRAIN) dl = sm_two_class_delta(z, one) * inv_mb;
     } else if (n_classes == 1) {
       const int yr = __float_as_int(y);
-      const float zz = z[0];
       if (loss && valid) {
-        lsum += (double)(fmaxf(zz, 0.f) + log1pf(expf(-fabsf(zz))) - (yr ? zz : 0.f));
-        hits += (zz > 0.f) == (yr != 0) ? 1.0 : 0.0;
+        lsum += (double)(fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - (yr ? z : 0.f));
+        hits += (z > 0.f) == (yr != 0) ? 1.0 : 0.0;
       }
-      if (TRAIN) dl[0] = (1.f / (1.f + expf(-zz)) - (float)yr) * scale;
+      if (TRAIN) dl = (1.f / (1.f + expf(-z)) - (float)yr) * inv_mb;
     } else {
-      const float e0 = z[0] - y;
+      const float e0 = z - y;
       if (loss && valid) {
         lsum += TRAIN ? 0.5 * (double)e0 * (double)e0 : (double)e0 * (double)e0;
         hits += (double)fabsf(e0);  // the absolute error
       }
-      if (TRAIN) dl[0] = e0 * scale;
+      if (TRAIN) dl = e0 * inv_mb;
     }
-    if (TRAIN && !valid) {  // (a row that is not there must not put an infinity of another row into the sums)
-#pragma unroll
-      for (int j = 0; j < CO; j++) dl[j] = 0.f;
-    }
+    return valid ? dl : 0.f;  // (a row that is not there must not put an infinity of another row into the sums)
   }
-  // sums over the 64 lanes: s[b] of lane t is that of g[t + 64 b]
-  __device__ __forceinline__ void fold(const float (&g)[NV], float (&s)[NB]) const {
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8, b4 = lane & 16, b5 = lane & 32;
-    float r[2 * M1];
+  // sum over the 64 lanes of g[t] for column t = lane, or lane mod 32 where there are no more than 32
+  __device__ __forceinline__ float fold(const float (&g)[D]) const {
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
+    float r[4];
 #pragma unroll
-    for (int i = 0; i < 2 * M1; i++) {
+    for (int i = 0; i < 4; i++) {
       float v[4];
 #pragma unroll
       for (int t = 0; t < 4; t++) {
         float p[4];
 #pragma unroll
-        for (int e = 0; e < 4; e++) p[e] = 16 * i + 4 * t + e < NV ? g[16 * i + 4 * t + e < NV ? 16 * i + 4 * t + e : 0] : 0.f;
-        v[t] = 16 * i + 4 * t < NV ? sm_fold_quad(p, b0, b1) : 0.f;
+        for (int e = 0; e < 4; e++) p[e] = 16 * i + 4 * t + e < D ? g[16 * i + 4 * t + e < D ? 16 * i + 4 * t + e : 0] : 0.f;
+        v[t] = 16 * i + 4 * t < D ? sm_fold_quad(p, b0, b1) : 0.f;
       }
-      r[i] = 16 * i < NV ? sm_fold_row(v, b2, b3) : 0.f;
+      r[i] = 16 * i < D ? sm_fold_row(v, b2, b3) : 0.f;
     }
-    float h[2 * NB];
-#pragma unroll
-    for (int i = 0; i < 2 * NB; i++)
-      h[i] = i < M1 ? (b4 ? r[2 * i + 1] : r[2 * i]) + __shfl_xor(b4 ? r[2 * i] : r[2 * i + 1], 16) : 0.f;
-#pragma unroll
-    for (int b = 0; b < NB; b++) s[b] = (b5 ? h[2 * b + 1] : h[2 * b]) + __shfl_xor(b5 ? h[2 * b] : h[2 * b + 1], 32);
+    const float lo = sm_fold16(r[0], r[1]);
+    return sm_fold32(lo, M > 2 ? sm_fold16(r[2], r[3]) : lo);
   }
   // the epoch's rows in visiting order (see train_linear_f32.h)
   __device__ __forceinline__ void epoch_order(uint64_t ke, int n_fit) const {
@@ -174,10 +161,15 @@ struct LinearLds {
     }
     __builtin_amdgcn_wave_barrier();
   }
+  // The lane's column and its b-th parameter: class, place in the packed order W[in][out], b[out] (from Pn on: none).
+  __device__ __forceinline__ int column() const { return SPLIT ? lane & 31 : lane; }
+  __device__ __forceinline__ int cls(int b) const { return SPLIT ? lane >> 5 : b; }
+  __device__ __forceinline__ int packed(int b) const { return column() * CO + cls(b); }
   __device__ __forceinline__ void put_weights(const float (&w)[NB]) const {
-#pragma unroll
-    for (int b = 0; b < NB; b++)
-      if (lane + 64 * b < NV) ws[lane + 64 * b] = w[b];
+    float x = w[NB - 1];
+    if constexpr (SPLIT) x = __shfl_xor(x, 32) - x;  // (class 0 of a column is in the lower lane)
+    if constexpr (NB == 2) x -= w[0];
+    if (lane < D) ws[lane] = x;
     __builtin_amdgcn_wave_barrier();
   }
   // loss and second score, summed per lane, of `count` rows
@@ -188,9 +180,7 @@ struct LinearLds {
       const int row = row_at(valid ? off + lane : count - 1);
       f32x4 x[NQ];
       load_row(row, x);
-      float z[CO], dl[CO];
-      forward(x, z);
-      outputs<false>(z, valid, ys[row], 0.f, true, dl, lsum, hits);
+      outputs<false>(forward(x), valid, ys[row], 0.f, true, lsum, hits);
     }
   }
 
@@ -225,7 +215,7 @@ struct LinearLds {
     const int n_w = d * CO;  // weights in front, biases behind
 #pragma unroll
     for (int b = 0; b < NB; b++) {
-      const int i = lane + 64 * b;
+      const int i = packed(b);
       w[b] = m[b] = v[b] = wb[b] = 0.f;
       if (i < Pn) {
         if (resume) {
@@ -255,23 +245,20 @@ struct LinearLds {
       for (int st = e == e0 ? st0 : 0; st < steps; st++, gstep++) {
         const int lo = st * bs, hi = min(lo + bs, n_fit);
         const float mb = (float)(hi - lo), inv_mb = 1.f / mb;
-        float g[NV];
+        float g[D];
 #pragma unroll
-        for (int i = 0; i < NV; i++) g[i] = 0.f;
+        for (int i = 0; i < D; i++) g[i] = 0.f;
         double lstep = 0.0;
         for (int at = lo; at < hi; at += 64) {
           asm volatile("" ::: "memory");  // the weights are read again for every chunk, not kept in registers
           const int row = ep[min(at + lane, hi - 1)];
           f32x4 x[NQ];
           load_row(row, x);
-          float z[CO], dl[CO];
-          forward(x, z);
-          outputs<true>(z, at + lane < hi, ys[row], inv_mb, loss, dl, lstep, unused);
+          const float dl = outputs<true>(forward(x), at + lane < hi, ys[row], inv_mb, loss, lstep, unused);
 #pragma unroll
-          for (int i = 0; i < NV; i++) g[i] += x[i / CO / 4][i / CO % 4] * dl[i % CO];
+          for (int i = 0; i < D; i++) g[i] += x[i / 4][i % 4] * dl;
         }
-        float gs[NB];
-        fold(g, gs);
+        const float gs = fold(g);
         esum += lstep;
         oc.am = alpha / mb;
         if (oc.adam) {
@@ -297,16 +284,16 @@ struct LinearLds {
           double pen = 0.0;
 #pragma unroll
           for (int b = 0; b < NB; b++)
-            if (lane + 64 * b < n_w) pen += (double)w[b] * (double)w[b];
+            if (packed(b) < n_w) pen += (double)w[b] * (double)w[b];
           const double data = sm_wavesum_d(lstep) / (double)mb;
           pen = sm_wavesum_d(pen);
           if (lane == 0) rec[0] = (float)(data + 0.5 * (double)alpha * pen / (double)mb);
         }
 #pragma unroll
         for (int b = 0; b < NB; b++) {
-          const int i = lane + 64 * b;
+          const int i = packed(b);
           if (i < Pn) {
-            const float gg = gs[b] + (i < n_w ? oc.am * w[b] : 0.f);
+            const float gg = (CO == 2 && cls(b) == 0 ? -gs : gs) + (i < n_w ? oc.am * w[b] : 0.f);
             opt_update(oc, gg, w[b], m[b], v[b]);
             if (rec) {
               rec[1 + i] = gg;
@@ -348,8 +335,8 @@ struct LinearLds {
 
 // The launch gives a workgroup the LDS of the data set and ll_wave_bytes() for each of its wavefronts.
 template <int D, int CO>
-__global__ __attribute__((amdgpu_flat_work_group_size(64, 256 * ll_occupancy(D, CO)),
-                          amdgpu_waves_per_eu(ll_occupancy(D, CO), ll_occupancy(D, CO))))
+__global__ __attribute__((amdgpu_flat_work_group_size(64, 256 * ll_occupancy(D)),
+                          amdgpu_waves_per_eu(ll_occupancy(D), ll_occupancy(D))))
 void k_train_linear_lds(const TrainParams P) {
   extern __shared__ __align__(16) char ll_lds[];
   typedef LinearLds<D, CO> T;
@@ -363,10 +350,10 @@ void k_train_linear_lds(const TrainParams P) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) ys[i] = ((const float*)P.y)[i];  // (class ids as they are)
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  char* own = ll_lds + (((uint32_t)(n * T::S + n) * 4 + 15) & ~15u) + wave * ll_wave_bytes(D, CO, n);
+  char* own = ll_lds + (((uint32_t)(n * T::S + n) * 4 + 15) & ~15u) + wave * ll_wave_bytes(D, n);
   const uint32_t list = (2 * n + 15) & ~15u;
-  T t{P, xs, ys, (float*)own, (uint16_t*)(own + T::NV * 4), (uint16_t*)(own + T::NV * 4 + list),
-      (uint16_t*)(own + T::NV * 4 + 2 * list), lane, d, P.n_classes, (d + 1) * CO};
+  T t{P, xs, ys, (float*)own, (uint16_t*)(own + D * 4), (uint16_t*)(own + D * 4 + list),
+      (uint16_t*)(own + D * 4 + 2 * list), lane, d, P.n_classes, (d + 1) * CO};
   for (;;) {
     // every lane takes part in the pop (see k_train_linear)
     __builtin_amdgcn_wave_barrier();

@@ -165,10 +165,24 @@ template <int CTRL>
 __device__ __forceinline__ float sm_dpp(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
 }
+// Halvings over the four 16-lane rows of a wave.  sm_fold16: rows 0, 1 get the sums of a over rows 0 and 1 and of b over
+// rows 0 and 1, rows 2, 3 the same of rows 2 and 3; sm_fold32: the lower half gets the sum of a over both halves, the upper
+// half that of b.  (The swaps return a pair; an element of it must be read as the integer it is: a bit cast of the
+// element itself takes the first one.)
+__device__ __forceinline__ float sm_fold16(float a, float b) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  const uint32_t x = s[0], y = s[1];
+  return __uint_as_float(x) + __uint_as_float(y);
+}
+__device__ __forceinline__ float sm_fold32(float a, float b) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  const uint32_t x = s[0], y = s[1];
+  return __uint_as_float(x) + __uint_as_float(y);
+}
 // Sum over the four 16-lane rows of a wave, the same bits in every lane.
 __device__ __forceinline__ float sm_rowsum(float v) {
-  v += __shfl_xor(v, 16);
-  return v + __shfl_xor(v, 32);
+  v = sm_fold16(v, v);
+  return sm_fold32(v, v);
 }
 // Sum over the 16 lanes of a row, the same bits in every lane.
 __device__ __forceinline__ float sm_row16sum(float v) {
@@ -194,6 +208,18 @@ __device__ __forceinline__ float sm_fold_row(const float (&v)[4], bool b2, bool 
   const float B = (b3 ? v[3] : v[1]) + sm_dpp<0x128>(b3 ? v[1] : v[3]);
   const float x = sm_dpp<0x141>(b2 ? A : B);       // lane i gets 7 - i of its eight,
   return (b2 ? B : A) + sm_dpp<0x1B>(x);           // and the reversal of the quad makes that i ^ 4
+}
+
+// Two classes by the difference of their logits, z = z[1] - z[0], of a row of class `one`.  The delta of class 1 (before
+// the division by the step's rows; class 0 has its negative): the probability of the other class, which does not cancel
+// as p - 1 does.  An infinite difference is a NaN in both, as it is with the logits apart.
+__device__ __forceinline__ float sm_two_class_delta(float z, bool one) {
+  const float p = fmaf(z, 0.f, 1.f / (1.f + expf(one ? z : -z)));
+  return one ? -p : p;
+}
+__device__ __forceinline__ float sm_two_class_loss(float z, bool one) {
+  const float s = one ? -z : z;  // of the other class over the row's own
+  return fmaf(z, 0.f, fmaxf(s, 0.f) + log1pf(expf(-fabsf(s))));
 }
 
 // What the phases of a chunk need to know about it, packed into one scalar (two chunks are in the pipeline behind
