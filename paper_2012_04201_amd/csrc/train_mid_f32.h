@@ -345,7 +345,7 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2> {
   }
 
   // ---- outputs: group g of four rows belongs to wave g mod W; lane (output li, row 4g + q) ----
-  __device__ __forceinline__ void outputs(State& R, int b, int, int rows, bool train, float inv_mb, double& lsum, double& hits) const {
+  __device__ __forceinline__ void outputs(State& R, int b, int, int rows, bool train, bool loss, float inv_mb, double& lsum, double& hits) const {
     const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4, groups = (rows + 3) / 4;
     float* d3 = f(O_D3);
 #pragma unroll
@@ -367,8 +367,10 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2> {
         const float zz = li < c ? z : -INFINITY;
         const float mx = r16_max(zz);
         const float ex = li < c ? expf(zz - mx) : 0.f, se = r16_sum(ex);
-        if (valid && li == 0) lsum += (double)(mx + logf(se));
-        if (valid && li == yr && li < c) lsum -= (double)zz;  // (a label outside [0, c) matches no class)
+        if (loss) {
+          if (valid && li == 0) lsum += (double)(mx + logf(se));
+          if (valid && li == yr && li < c) lsum -= (double)zz;  // (a label outside [0, c) matches no class)
+        }
         if (!train) {
           const int best = r16_min(zz == mx ? li : 99);
           if (valid && li == 0) hits += best == yr ? 1.0 : 0.0;
@@ -378,15 +380,19 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2> {
         // one logit, labels 0/1: log(1 + e^z) - y z, delta (sigmoid(z) - y)/m
         const int yr = __float_as_int(yv);
         if (valid && li == 0) {
-          lsum += (double)(fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - (yr ? z : 0.f));
-          hits += (z > 0.f) == (yr != 0) ? 1.0 : 0.0;
+          if (loss) {
+            lsum += (double)(fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - (yr ? z : 0.f));
+            hits += (z > 0.f) == (yr != 0) ? 1.0 : 0.0;
+          }
           dl = (1.f / (1.f + expf(-z)) - (float)yr) * inv_mb;
         }
       } else {
         const float e0 = z - yv;
         if (valid && li == 0) {
-          lsum += train ? 0.5 * (double)e0 * (double)e0 : (double)e0 * (double)e0;
-          hits += (double)fabsf(e0);  // the absolute error
+          if (loss) {
+            lsum += train ? 0.5 * (double)e0 * (double)e0 : (double)e0 * (double)e0;
+            hits += (double)fabsf(e0);  // the absolute error
+          }
           dl = e0 * inv_mb;
         }
       }

@@ -1,5 +1,6 @@
 // Register-resident training / scoring kernel for small fp32 models with one hidden layer (the "many concurrent
-// studies" shape: up to 63 inputs, hidden width up to 224, up to 4 outputs).
+// studies" shape: up to 63 inputs, hidden width up to 224, up to 4 outputs).  Two classes are one output column, the
+// difference of the logits (see sm_two_class_delta()).
 //
 // One workgroup of W waves trains one model.  Wave w owns the hidden-unit tiles (16 units) w, w + W, .. for the
 // whole run, and everything that belongs to them stays in its registers (as far as these reach: sm_occupancy()) from the
@@ -26,7 +27,10 @@
 //
 // What bounds it: with the chip full, the matrix pipe shares its SIMD with the vector work around it (ReLU, output
 // layer, softmax, update), and two to four waves per SIMD have to cover each other's latencies; with few models,
-// the chain of a step's dependent phases.  The form before this one kept the weights in LDS and the moments in L2, at
+// the chain of a step's dependent phases.  The optimizer's work on the small parameters (biases, output layer: alike in the
+// four lane groups q) is done four parameters at a time, one per q; the loss of a training chunk is computed only where the
+// stopping rule or a trace reads it.  With the output columns of two classes merged, these took 10,240 models 569 x 30 from
+// 30.7 to 27.4 ms and 40 models of 10,000 x 45 from 4.02 to 3.59.  The form before this one kept the weights in LDS and the moments in L2, at
 // two workgroups per CU whatever the width and two barriers per chunk.  Before and after, per call: 10,240 models
 // 569 x 30, 50..200 units, 20 epochs 45.3 -> 32.4 ms; 40 models 506 x 13, SGD, 30 epochs 3.41 -> 1.74 ms; 40 models of
 // 10,000 x 45 rows, 3 epochs 10.9 -> 4.45 ms; 40 models 150 x 4, 20 epochs 0.39 -> 0.25 ms.
@@ -100,8 +104,9 @@ __host__ __device__ constexpr uint32_t pipe_lds(int kt, int buffers) {
   return (buffers * SM_RC * sm_ldw(kt) + buffers * SM_RC + 2 * SM_RC) * 4;
 }
 // LDS of a variant of k_train_small ahead of the row tables
-__host__ __device__ constexpr uint32_t sm_fixed_lds(int kt, int nt, int co, int waves) {
-  return pipe_lds(kt, 3) + (2 * waves * co * SM_RC + co * SM_RC + waves * (nt * (1 + co) + co) * 32) * 4;
+__host__ __device__ constexpr int sm_columns(int co) { return co == 2 ? 1 : co; }
+__host__ __device__ constexpr uint32_t sm_fixed_lds(int kt, int co, int waves) {
+  return pipe_lds(kt, 3) + (2 * waves + 1) * sm_columns(co) * SM_RC * 4;
 }
 
 // ... and the row tables behind `fixed` bytes of everything else
@@ -142,17 +147,19 @@ __host__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n, const Sm
   y.cb[0] = d * y.h;
   y.cw[1] = y.cb[0] + y.h;
   y.cb[1] = y.cw[1] + y.h * y.c;
-  make_pipelay(y.p, d, y.cb[1] + y.c, n, s.waves, sm_fixed_lds(s.kt, s.nt, s.co, s.waves));
+  make_pipelay(y.p, d, y.cb[1] + y.c, n, s.waves, sm_fixed_lds(s.kt, s.co, s.waves));
   y.slot_floats = (uint32_t)(s.waves * sm_regs(s.kt, s.nt, s.co) * 64);
   y.lds_total = y.p.total;
 }
 
 // Waves per SIMD the registers of a variant are budgeted for (512 registers per lane and SIMD).  The largest variants of a
-// budget do not fit it altogether: by the compiler's report <2,3,2,4> (129 to 192 units, 17 to 32 inputs, two outputs)
-// spills 64 vector registers, <2,3,1,4> 18, <2,1,4,4> 62, <3,2,4,4> and <3,2,4,8> 82 and 62, <4,2,.,8> (129 units and more,
-// 49 inputs and more) 89, 158 and 223 at one, two and four output slots; the others 3 at most.
+// budget do not fit it altogether: by the compiler's report <2,3,1,4> and <2,3,2,4> (129 to 192 units, 17 to 32 inputs)
+// spill 18 and 35 vector registers, <3,2,4,4> and <3,2,4,8> 105 and 89, <4,2,.,8> (129 units and more, 49 inputs and more)
+// 73, 95 and 210 at one, two and four output slots; the others 8 at most.  Four output slots need more than the 128
+// registers of four waves even at one tile: at three, 569 x 30, three classes, 16 units, 32 rows a step, 400 suggestions take
+// 622 us a call instead of 857.
 __host__ __device__ constexpr int sm_occupancy(int kt, int nt, int co) {
-  return nt == 1 && kt <= 2 ? 4 : 2;
+  return nt == 1 && kt <= 2 ? (co == 4 ? 3 : 4) : 2;
 }
 // workgroups a CU holds
 __host__ inline int small_per_cu(const SmallCut& s, uint32_t lds_bytes) {
@@ -458,6 +465,7 @@ struct RowPipe {
     // Position of the chunk whose inputs are requested next: first row `at` in its order, step st of epoch e, `left`
     // rows of that step from this chunk on.
     const int last_rows = pin(uniform(n_fit - (steps - 1) * bs)), decide = pin(uniform(watch && !n_hold ? (int)SC_DECIDE : 0));
+    const int train_loss = traced | decide;  // somebody reads the loss of training chunks
     int e = 0, st = 0, at = 0, left = 0;
     auto training = [&](int flags) {  // the chunk at this position
       const int ragged = st + 1 == steps ? SC_RAGGED : 0;
@@ -614,7 +622,10 @@ struct RowPipe {
         __syncthreads();  // the outputs' shares, the next chunk's inputs and the rows of the one after it
         if (BARRIERS == 2 && sc_mode(c1) <= ROWS_PLAIN) commit(bn, xr, yv);
         if (BARRIERS < 3 && (c2 & SC_MODE) != SC_END) fetch(c2, at, par, xr, yv);  // in flight until the next chunk is under way
-        if (live) self.outputs(R, b, par, rows, sc_mode(c0) == ROWS_EPOCH, inv_mb, lsum, hits);
+        if (live) {
+          const bool train = sc_mode(c0) == ROWS_EPOCH;
+          self.outputs(R, b, par, rows, train, !train || train_loss, inv_mb, lsum, hits);
+        }
         if (BARRIERS >= 2) __syncthreads();  // the output deltas
         if (sc_mode(c0) == ROWS_EPOCH) {
           self.backward(R, b, nrt, acc);
@@ -697,64 +708,109 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
   __device__ __forceinline__ void pin_own() { nut = pin(y.nut); }
   __device__ __forceinline__ static double total(double v) { return sm_wavesum_d(v); }  // every wave has the whole sum
 
+  // Output columns the products run over: two classes are one, the difference z[1] - z[0], on which their softmax, loss
+  // and deltas (p and -p) depend alone.
+  static constexpr int ZO = sm_columns(CO);
+  // The small parameters: the bias and the row of the output layer of each tile's unit li, then the output bias.  The
+  // optimizer works on four at a time: parameter k in the lanes of row q = k % 4, group k / 4.
+  static constexpr int NSMALL = NT * (1 + CO) + CO, NG = (NSMALL + 3) / 4;
   struct State {
     f32x4 w[NT][KT], m[NT][KT], v[NT][KT], g[NT][KT];  // hidden layer: lane (unit li, columns 16 kk + 4q + e)
-    float bw[NT], bg[NT];                              // its bias
-    float w2[NT][CO], g2[NT][CO];                      // the unit's row of the output layer, alike in the four q
-    float ow[CO], og[CO];                              // output bias, alike in every lane (og: the lane's share)
+    float pw[NG], pm[NG], pv[NG];                      // the small parameters and their moments
+    float bw[NT], w2[NT][ZO], ow[ZO];                  // the same as the products want them: alike in the four q
+    float bg[NT], g2[NT][ZO], og[ZO];                  // the lane's share of their gradients
   };
-  // The moments of the last three, which are needed once per step and are alike in the four q, wait in LDS:
-  // [wave][bias, outputs of each tile, then the output bias][first, second][li].
-  static constexpr int NMOM = NT * (1 + CO) + CO;
 
   struct Acts {
     f32x4 a[NT][4];  // activations of the wave's tiles: lane (unit li, rows 16 r + 4q..+3)
   };
   // offsets in floats
-  static constexpr int O_ZP = Base::O_OWN, O_D2 = O_ZP + 2 * W * CO * SM_RC, O_MOM = O_D2 + CO * SM_RC;
-  static_assert((O_MOM + W * NMOM * 32) * 4 == sm_fixed_lds(KT, NT, CO, W), "LDS layout");
+  static constexpr int O_ZP = Base::O_OWN, O_D2 = O_ZP + 2 * W * ZO * SM_RC, O_TOP = O_D2 + ZO * SM_RC;
+  static_assert(O_TOP * 4 == sm_fixed_lds(KT, CO, W), "LDS layout");
   // does the wave's i-th tile exist?  Only the last one can be missing.
   __device__ __forceinline__ bool has(int i, int w) const { return i + 1 < NT || w + i * W < nut; }
 
   // ---- parameters ----------------------------------------------------------
   // The wave's share of the parameters as it lies in its part of the slot: [register][lane], the registers in the
   // order each_param() visits them.
-  static constexpr int NREG = sm_regs(KT, NT, CO);
+  static constexpr int NREG = sm_regs(KT, NT, CO), PER = 4 * KT + 1 + CO;
   __device__ __forceinline__ float* park() const { return slot + wave() * (NREG * 64) + (threadIdx.x & 63); }
-  // fn(index, reference) for the hidden weights of `w`, fs(index, position in NMOM) for everything else
-  template <class F, class S>
-  __device__ __forceinline__ static void each_param(f32x4 (&w)[NT][KT], F fn, S fs) {
-    int n = 0, k = 0;
+  // fn(index, reference) for the hidden weights of `w`
+  template <class F>
+  __device__ __forceinline__ static void each_hidden(f32x4 (&w)[NT][KT], F fn) {
 #pragma unroll
-    for (int i = 0; i < NT; i++) {
+    for (int i = 0; i < NT; i++)
 #pragma unroll
       for (int kk = 0; kk < KT; kk++)
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           float x = w[i][kk][e];
-          fn(n++, x);
+          fn(i * PER + 4 * kk + e, x);
           w[i][kk][e] = x;
         }
+  }
+  // small parameter k: of tile k / (1 + CO), 0 its bias, else an output; from NT (1 + CO) on the output bias
+  __device__ __forceinline__ static int small_register(int k) {
+    return k >= NT * (1 + CO) ? NT * PER + k - NT * (1 + CO) : k / (1 + CO) * PER + 4 * KT + k % (1 + CO);
+  }
+  __device__ __forceinline__ static constexpr bool small_weight(int k) { return k < NT * (1 + CO) && k % (1 + CO) != 0; }
+  // fn(reference, place in the slot) for the lane's small parameters
+  template <class F>
+  __device__ __forceinline__ void each_small(float (&p)[NG], F fn) const {
+    const int lane = threadIdx.x & 63, li = lane & 15, q = lane >> 4;
+    float* b = slot + wave() * (NREG * 64) + li;
 #pragma unroll
-      for (int cc = 0; cc <= CO; cc++) fs(n++, k++);
+    for (int g = 0; g < NG; g++) {
+      p[g] = 4 * g + q < NSMALL ? p[g] : 0.f;
+      if (4 * g + q < NSMALL) fn(p[g], b + 64 * small_register(4 * g + q));
+    }
+  }
+  // pw -> bw, w2, ow
+  __device__ __forceinline__ static void spread(State& R) {
+    float x[4 * NG];
+#pragma unroll
+    for (int g = 0; g < NG; g++) {
+      const uint32_t p = __float_as_uint(R.pw[g]);
+      const auto h = __builtin_amdgcn_permlane32_swap(p, p, false, false);
+      const uint32_t lo = h[0], hi = h[1];
+      const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+      const uint32_t x0 = a[0], x1 = a[1], x2 = b[0], x3 = b[1];
+      x[4 * g] = __uint_as_float(x0);
+      x[4 * g + 1] = __uint_as_float(x1);
+      x[4 * g + 2] = __uint_as_float(x2);
+      x[4 * g + 3] = __uint_as_float(x3);
     }
 #pragma unroll
-    for (int cc = 0; cc < CO; cc++) fs(n++, k++);
+    for (int i = 0; i <= NT; i++) {
+      const float* o = x + i * (1 + CO) + (i < NT ? 1 : 0);
+      if (i < NT) R.bw[i < NT ? i : 0] = o[-1];
+#pragma unroll
+      for (int cc = 0; cc < ZO; cc++) (i < NT ? R.w2[i < NT ? i : 0][cc] : R.ow[cc]) = CO == 2 ? o[1] - o[0] : o[cc];
+    }
   }
-  // the register of position k of NMOM
-  __device__ __forceinline__ static float& small_param(State& R, int k) {
-    if (k >= NT * (1 + CO)) return R.ow[k - NT * (1 + CO)];
-    const int i = k / (1 + CO), r = k - i * (1 + CO);
-    return r == 0 ? R.bw[i] : R.w2[i][r - 1];
+  // the gradients of the lane's small parameters, summed over the wave
+  __device__ __forceinline__ static void small_grads(const State& R, float (&gp)[NG]) {
+    float x[4 * NG];
+#pragma unroll
+    for (int k = 0; k < 4 * NG; k++) {
+      const int i = k / (1 + CO), r = k % (1 + CO), c0 = k - NT * (1 + CO);
+      x[k] = 0.f;
+      if (k >= NSMALL) continue;
+      if (c0 >= 0)
+        x[k] = sm_row16sum(CO == 2 ? (c0 == 0 ? -R.og[0] : R.og[0]) : R.og[c0 < 0 || CO == 2 ? 0 : c0]);
+      else if (r == 0)
+        x[k] = R.bg[i < NT ? i : 0];
+      else
+        x[k] = CO == 2 ? (r == 1 ? -R.g2[i < NT ? i : 0][0] : R.g2[i < NT ? i : 0][0]) : R.g2[i < NT ? i : 0][CO == 2 ? 0 : r - 1];
+    }
+#pragma unroll
+    for (int g = 0; g < NG; g++) gp[g] = sm_fold32(sm_fold16(x[4 * g], x[4 * g + 1]), sm_fold16(x[4 * g + 2], x[4 * g + 3]));
   }
-  // the lane's share of its gradient, summed over the row of 16 lanes where those hold different rows
-  __device__ __forceinline__ static float small_grad(const State& R, int k) {
-    if (k >= NT * (1 + CO)) return sm_row16sum(R.og[k - NT * (1 + CO)]);
-    const int i = k / (1 + CO), r = k - i * (1 + CO);
-    return r == 0 ? R.bg[i] : R.g2[i][r - 1];
-  }
-  __device__ __forceinline__ float* mom(int k, int which) const {
-    return f(O_MOM) + ((wave() * NMOM + k) * 2 + which) * 16 + (threadIdx.x & 15);
+  // the penalty's factor for the lane's parameter of group g: none on the biases
+  __device__ __forceinline__ static float small_penalty(int g, int q, float am) {
+    const int weights = (small_weight(4 * g) ? 1 : 0) | (small_weight(4 * g + 1) ? 2 : 0) | (small_weight(4 * g + 2) ? 4 : 0) |
+                        (small_weight(4 * g + 3) ? 8 : 0);
+    return (weights >> q) & 1 ? am : 0.f;
   }
   // Packed parameters (or one of their moments) `st`, or the initial draw where st is null, into the wave's part of
   // the slot.  A rolled loop: the registers are filled from the slot afterwards.
@@ -762,7 +818,6 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
     const int lane = threadIdx.x & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
     const int d = y.p.d, h = y.h, c = y.c;
     float* b = park();
-    constexpr int PER = 4 * KT + 1 + CO;
 #pragma unroll 1
     for (int n = 0; n < NREG; n++) {
       const int i = n / PER, r = n - i * PER, j = (w_ + i * W) * 16 + li;
@@ -795,15 +850,21 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
   __device__ __forceinline__ void load(State& R, const float* st) const {
     const float* b = park();
     auto take = [&](int n, float& x) { x = b[64 * n]; };
-    auto zero = [&](int, float& x) { x = 0.f; };
+    auto take_small = [](float& x, const float* at) { x = *at; };
+    auto zero = [](int, float& x) { x = 0.f; };
+    auto zero_small = [](float& x, const float*) { x = 0.f; };
     if (st) {
       unpack(st + y.p.P);
-      each_param(R.m, take, [&](int n, int k) { *mom(k, 0) = b[64 * n]; });
+      each_hidden(R.m, take);
+      each_small(R.pm, take_small);
       unpack(st + 2 * y.p.P);
-      each_param(R.v, take, [&](int n, int k) { *mom(k, 1) = b[64 * n]; });
+      each_hidden(R.v, take);
+      each_small(R.pv, take_small);
     } else {
-      each_param(R.m, zero, [&](int, int k) { *mom(k, 0) = 0.f; });
-      each_param(R.v, zero, [&](int, int k) { *mom(k, 1) = 0.f; });
+      each_hidden(R.m, zero);
+      each_small(R.pm, zero_small);
+      each_hidden(R.v, zero);
+      each_small(R.pv, zero_small);
     }
     unpack(st);
     restore_best(R);
@@ -811,11 +872,14 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
   // Keep the current parameters aside / take the kept ones back: every wave its own, no barrier.
   __device__ __forceinline__ void keep_best(State& R) const {
     float* b = park();
-    each_param(R.w, [&](int n, float& x) { b[64 * n] = x; }, [&](int n, int k) { b[64 * n] = small_param(R, k); });
+    each_hidden(R.w, [&](int n, float& x) { b[64 * n] = x; });
+    each_small(R.pw, [](float& x, float* at) { *at = x; });
   }
   __device__ __forceinline__ void restore_best(State& R) const {
     const float* b = park();
-    each_param(R.w, [&](int n, float& x) { x = b[64 * n]; }, [&](int n, int k) { small_param(R, k) = b[64 * n]; });
+    each_hidden(R.w, [&](int n, float& x) { x = b[64 * n]; });
+    each_small(R.pw, [](float& x, const float* at) { x = *at; });
+    spread(R);
     // waited for here: the loop's own waits would otherwise have to allow for these loads, at the price of the input
     // values that are meant to stay in flight
     __builtin_amdgcn_s_waitcnt(0);
@@ -827,10 +891,10 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
       for (int kk = 0; kk < KT; kk++) R.g[i][kk] = f32x4{0.f, 0.f, 0.f, 0.f};
       R.bg[i] = 0.f;
 #pragma unroll
-      for (int cc = 0; cc < CO; cc++) R.g2[i][cc] = 0.f;
+      for (int cc = 0; cc < ZO; cc++) R.g2[i][cc] = 0.f;
     }
 #pragma unroll
-    for (int cc = 0; cc < CO; cc++) R.og[cc] = 0.f;
+    for (int cc = 0; cc < ZO; cc++) R.og[cc] = 0.f;
   }
 
   // ---- rows and inputs ------------------------------------------------------
@@ -838,7 +902,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
   // One row tile: products of all the wave's tiles in turn (independent accumulators), ReLU, output-layer share.
   // ALL: the wave's last tile exists.
   template <bool ALL>
-  __device__ __forceinline__ void forward_tile(const State& R, const float* s, int r, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
+  __device__ __forceinline__ void forward_tile(const State& R, const float* s, int r, f32x4 (&acc)[NT][4], float (&v)[ZO][4]) const {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
     const float* a_ = s + (r * 16 + li) * LDW + 4 * q;
     f32x4 a[KT];
@@ -854,7 +918,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
         for (int i = 0; i < NT; i++)
           if (i + 1 < NT || ALL) acc[i][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], R.w[i][kk][e], acc[i][r], 0, 0, 0);
       }
-    float p[CO][4];
+    float p[ZO][4];
 #pragma unroll
     for (int e = 0; e < 4; e++) {
 #pragma unroll
@@ -862,26 +926,26 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
         const float av = fmaxf(acc[i][r][e], 0.f);
         acc[i][r][e] = av;
 #pragma unroll
-        for (int cc = 0; cc < CO; cc++) p[cc][e] = i == 0 ? av * R.w2[0][cc] : p[cc][e] + av * R.w2[i][cc];
+        for (int cc = 0; cc < ZO; cc++) p[cc][e] = i == 0 ? av * R.w2[0][cc] : p[cc][e] + av * R.w2[i][cc];
       }
     }
 #pragma unroll
-    for (int cc = 0; cc < CO; cc++) v[cc][r] = sm_fold_quad(p[cc], li & 1, li & 2);
+    for (int cc = 0; cc < ZO; cc++) v[cc][r] = sm_fold_quad(p[cc], li & 1, li & 2);
   }
   template <bool ALL, int N>
-  __device__ __forceinline__ void forward_tiles(const State& R, const float* s, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
+  __device__ __forceinline__ void forward_tiles(const State& R, const float* s, f32x4 (&acc)[NT][4], float (&v)[ZO][4]) const {
 #pragma unroll
     for (int r = 0; r < 4; r++) {
       if (r < N) {
         forward_tile<ALL>(R, s, r, acc, v);
       } else {
 #pragma unroll
-        for (int cc = 0; cc < CO; cc++) v[cc][r] = 0.f;
+        for (int cc = 0; cc < ZO; cc++) v[cc][r] = 0.f;
       }
     }
   }
   template <bool ALL>
-  __device__ __forceinline__ void forward_chunk(const State& R, const float* s, int nrt, f32x4 (&acc)[NT][4], float (&v)[CO][4]) const {
+  __device__ __forceinline__ void forward_chunk(const State& R, const float* s, int nrt, f32x4 (&acc)[NT][4], float (&v)[ZO][4]) const {
     if (nrt == 4)
       forward_tiles<ALL, 4>(R, s, acc, v);
     else if (nrt == 3)
@@ -894,41 +958,49 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
   __device__ __forceinline__ void forward(const State& R, int b, int par, int nrt, Acts& A) const {
     f32x4 (&acc)[NT][4] = A.a;
     const int w_ = wave();
-    float v[CO][4];
+    float v[ZO][4];
     if (has(NT - 1, w_))
       forward_chunk<true>(R, xs(b), nrt, acc, v);
     else
       forward_chunk<false>(R, xs(b), nrt, acc, v);
     const int lane = tid() & 63, li = lane & 15;
-    float* zp = f(O_ZP) + (par * W + w_) * (CO * SM_RC) + lane;
+    float* zp = f(O_ZP) + (par * W + w_) * (ZO * SM_RC) + lane;
 #pragma unroll
-    for (int cc = 0; cc < CO; cc++) zp[cc * SM_RC] = sm_fold_row(v[cc], li & 4, li & 8);
+    for (int cc = 0; cc < ZO; cc++) zp[cc * SM_RC] = sm_fold_row(v[cc], li & 4, li & 8);
   }
 
   // ---- outputs, loss and output delta of the chunk's rows; the same in every wave ----
-  __device__ __forceinline__ void outputs(State& R, int b, int par, int rows, bool train, float inv_mb, double& lsum, double& hits) const {
+  // (train: the delta is wanted; loss: the loss is, and when scoring the hits)
+  __device__ __forceinline__ void outputs(State& R, int b, int par, int rows, bool train, bool loss, float inv_mb, double& lsum, double& hits) const {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4, c = CO <= 2 ? CO : y.c;
     const int row = (li >> 2) * 16 + 4 * q + (li & 3);  // the row the folding tree left in this lane
-    const float* zp = f(O_ZP) + par * W * (CO * SM_RC) + lane;
-    float z[CO];
+    const float* zp = f(O_ZP) + par * W * (ZO * SM_RC) + lane;
+    float z[ZO];
 #pragma unroll
-    for (int cc = 0; cc < CO; cc++) z[cc] = R.ow[cc];
+    for (int cc = 0; cc < ZO; cc++) z[cc] = R.ow[cc];
 #pragma unroll
     for (int ww = 0; ww < W; ww++) {
 #pragma unroll
-      for (int cc = 0; cc < CO; cc++) z[cc] += zp[(ww * CO + cc) * SM_RC];
+      for (int cc = 0; cc < ZO; cc++) z[cc] += zp[(ww * ZO + cc) * SM_RC];
     }
     const float yv = ys(b)[row];
-    float dl[CO];
+    const int yr = __float_as_int(yv);
+    float dl[ZO];
 #pragma unroll
-    for (int cc = 0; cc < CO; cc++) dl[cc] = 0.f;
+    for (int cc = 0; cc < ZO; cc++) dl[cc] = 0.f;
     if (row < rows) {
-      if (n_classes >= 2) {
-        const int yr = __float_as_int(yv);
+      if constexpr (CO == 2) {
+        const bool one = yr == 1;
+        if (loss) {
+          lsum += (double)sm_two_class_loss(z[0], one);
+          hits += (z[0] > 0.f) == one ? 1.0 : 0.0;
+        }
+        dl[0] = sm_two_class_delta(z[0], one) * inv_mb;
+      } else if (CO == 4) {
         float mx = z[0], zy = z[0];
         int best = 0;
 #pragma unroll
-        for (int cc = 1; cc < CO; cc++)
+        for (int cc = 1; cc < ZO; cc++)
           if (cc < c) {
             if (z[cc] > mx) {
               mx = z[cc];
@@ -936,37 +1008,42 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
             }
             zy = cc == yr ? z[cc] : zy;
           }
-        float ex[CO], se = 0.f;
+        float ex[ZO], se = 0.f;
 #pragma unroll
-        for (int cc = 0; cc < CO; cc++)
+        for (int cc = 0; cc < ZO; cc++)
           if (cc < c) {
             ex[cc] = expf(z[cc] - mx);
             se += ex[cc];
           }
-        lsum += (double)(mx + logf(se) - zy);
-        hits += best == yr ? 1.0 : 0.0;
+        if (loss) {
+          lsum += (double)(mx + logf(se) - zy);
+          hits += best == yr ? 1.0 : 0.0;
+        }
         const float inv = 1.f / se;
 #pragma unroll
-        for (int cc = 0; cc < CO; cc++)
+        for (int cc = 0; cc < ZO; cc++)
           if (cc < c) dl[cc] = (ex[cc] * inv - (cc == yr ? 1.f : 0.f)) * inv_mb;
       } else if (n_classes == 1) {
         // one logit, labels 0/1: log(1 + e^z) - y z, delta (sigmoid(z) - y)/m
-        const int yr = __float_as_int(yv);
         const float zz = z[0];
-        lsum += (double)(fmaxf(zz, 0.f) + log1pf(expf(-fabsf(zz))) - (yr ? zz : 0.f));
-        hits += (zz > 0.f) == (yr != 0) ? 1.0 : 0.0;
+        if (loss) {
+          lsum += (double)(fmaxf(zz, 0.f) + log1pf(expf(-fabsf(zz))) - (yr ? zz : 0.f));
+          hits += (zz > 0.f) == (yr != 0) ? 1.0 : 0.0;
+        }
         dl[0] = (1.f / (1.f + expf(-zz)) - (float)yr) * inv_mb;
       } else {
         const float e0 = z[0] - yv;
-        lsum += train ? 0.5 * (double)e0 * (double)e0 : (double)e0 * (double)e0;
-        hits += (double)fabsf(e0);
+        if (loss) {
+          lsum += train ? 0.5 * (double)e0 * (double)e0 : (double)e0 * (double)e0;
+          hits += (double)fabsf(e0);
+        }
         dl[0] = e0 * inv_mb;
       }
     }
     if (train) {
       float* d2 = f(O_D2) + lane;  // every wave writes the same values, and reads back only what it wrote itself
 #pragma unroll
-      for (int cc = 0; cc < CO; cc++) {
+      for (int cc = 0; cc < ZO; cc++) {
         d2[cc * SM_RC] = dl[cc];
         R.og[cc] += dl[cc];
       }
@@ -980,10 +1057,10 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
     const float* d2 = f(O_D2) + q * 16 + r * 4;
     const float* a_ = s + (r * 16 + 4 * q) * LDW + li;
-    f32x4 dv[CO];
+    f32x4 dv[ZO];
     float a[KT][4];
 #pragma unroll
-    for (int cc = 0; cc < CO; cc++) dv[cc] = *(const f32x4*)(d2 + cc * SM_RC);
+    for (int cc = 0; cc < ZO; cc++) dv[cc] = *(const f32x4*)(d2 + cc * SM_RC);
 #pragma unroll
     for (int kk = 0; kk < KT; kk++)
 #pragma unroll
@@ -998,7 +1075,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
           float sum = dv[0][e] * R.w2[i][0];
           R.g2[i][0] += av * dv[0][e];
 #pragma unroll
-          for (int cc = 1; cc < CO; cc++) {
+          for (int cc = 1; cc < ZO; cc++) {
             sum += dv[cc][e] * R.w2[i][cc];
             R.g2[i][cc] += av * dv[cc][e];
           }
@@ -1062,36 +1139,19 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
             R.v[i][kk][e] = vr;
           }
       }
-    // everything else: sums over the row groups, the moments from LDS, all requested before the first is needed
-    float g[NMOM], m[NMOM], v[NMOM];
+    const int q = (tid() & 63) >> 4;
+    float gp[NG];
+    small_grads(R, gp);
 #pragma unroll
-    for (int k = 0; k < NMOM; k++) {
-      m[k] = *mom(k, 0);
-      v[k] = ADAM ? *mom(k, 1) : 0.f;
-      g[k] = small_grad(R, k);
-    }
-#pragma unroll
-    for (int k = 0; k < NMOM; k++) g[k] += __shfl_xor(g[k], 16);
-#pragma unroll
-    for (int k = 0; k < NMOM; k++) g[k] += __shfl_xor(g[k], 32);
-#pragma unroll
-    for (int k = 0; k < NMOM; k++) {
-      float& w = small_param(R, k);
-      const bool weight = k < NT * (1 + CO) && k % (1 + CO) != 0;  // no penalty on the biases
-      opt_update(o, weight ? g[k] + o.am * w : g[k], w, m[k], v[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < NMOM; k++) {
-      *mom(k, 0) = m[k];
-      if (ADAM) *mom(k, 1) = v[k];
-    }
+    for (int g = 0; g < NG; g++) opt_update(o, gp[g] + small_penalty(g, q, o.am) * R.pw[g], R.pw[g], R.pm[g], R.pv[g]);
     if (ADAM && o.eps == 0.f) clear_pads(R);
+    spread(R);
   }
   // A traced step's gradient (before the update: GRAD) or new parameters into out[P].
   template <bool GRAD>
   __device__ __forceinline__ void record(const State& R, float am, float* out) const {
     const int t_ = tid(), lane = t_ & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
-    const int d = y.p.d, h = y.h, c = CO <= 2 ? CO : y.c;
+    const int d = y.p.d, h = y.h;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
       const int j = (w_ + i * W) * 16 + li;
@@ -1102,22 +1162,25 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
           const int k = kk * 16 + 4 * q + e;
           if (j < h && k < d) out[y.cw[0] + k * h + j] = GRAD ? R.g[i][kk][e] + am * R.w[i][kk][e] : R.w[i][kk][e];
         }
-      const float b = GRAD ? sm_rowsum(R.bg[i]) : R.bw[i];
-      if (j < h && q == 0) out[y.cb[0] + j] = b;
-#pragma unroll
-      for (int cc = 0; cc < CO; cc++) {
-        const float x = GRAD ? sm_rowsum(R.g2[i][cc]) + am * R.w2[i][cc] : R.w2[i][cc];
-        if (j < h && q == 0 && cc < c) out[y.cw[1] + j * c + cc] = x;
-      }
     }
+    float gp[NG];
+    if (GRAD) small_grads(R, gp);
 #pragma unroll
-    for (int cc = 0; cc < CO; cc++) {
-      const float x = GRAD ? sm_rowsum(sm_row16sum(R.og[cc])) : R.ow[cc];
-      if (t_ == 0 && cc < c) out[y.cb[1] + cc] = x;
+    for (int g = 0; g < NG; g++) {
+      const int ci = small_packed(4 * g + q);
+      const float x = GRAD ? gp[g] + small_penalty(g, q, am) * R.pw[g] : R.pw[g];
+      if (ci >= 0 && (4 * g + q < NT * (1 + CO) || t_ - 16 * q == 0)) out[ci] = x;  // (the output bias once)
     }
   }
+  // where the lane's small parameter k stands in the packed parameters; -1: a pad
+  __device__ __forceinline__ int small_packed(int k) const {
+    const int j = (wave() + k / (1 + CO) * W) * 16 + (threadIdx.x & 15), r = k % (1 + CO), c = CO <= 2 ? CO : y.c;
+    if (k >= NSMALL) return -1;
+    if (k >= NT * (1 + CO)) return k - NT * (1 + CO) < c ? y.cb[1] + k - NT * (1 + CO) : -1;
+    return j >= y.h || r > c ? -1 : (r == 0 ? y.cb[0] + j : y.cw[1] + j * c + r - 1);
+  }
   __device__ __forceinline__ void clear_pads(State& R) const {
-    const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4, c = CO <= 2 ? CO : y.c;
+    const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
       const bool unit = (w_ + i * W) * 16 + li < y.h;
@@ -1126,26 +1189,15 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
 #pragma unroll
         for (int e = 0; e < 4; e++)
           if (!unit || kk * 16 + 4 * q + e >= y.p.d) R.w[i][kk][e] = R.m[i][kk][e] = R.v[i][kk][e] = 0.f;
-#pragma unroll
-      for (int r = 0; r <= CO; r++)
-        if (!unit || r > c) {
-          const int k = i * (1 + CO) + r;
-          small_param(R, k) = 0.f;
-          *mom(k, 0) = *mom(k, 1) = 0.f;
-        }
     }
 #pragma unroll
-    for (int cc = 0; cc < CO; cc++)
-      if (cc >= c) {
-        const int k = NT * (1 + CO) + cc;
-        R.ow[cc] = 0.f;
-        *mom(k, 0) = *mom(k, 1) = 0.f;
-      }
+    for (int g = 0; g < NG; g++)
+      if (small_packed(4 * g + q) < 0) R.pw[g] = R.pm[g] = R.pv[g] = 0.f;
   }
 
   // squared weights, for a traced step's loss
   __device__ __forceinline__ double penalty_sum(const State& R) const {
-    const int lane = threadIdx.x & 63, q = lane >> 4;
+    const int q = (threadIdx.x & 63) >> 4;
     double s = 0.0;
 #pragma unroll
     for (int i = 0; i < NT; i++) {
@@ -1153,11 +1205,9 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
       for (int kk = 0; kk < KT; kk++)
 #pragma unroll
         for (int e = 0; e < 4; e++) s += (double)R.w[i][kk][e] * (double)R.w[i][kk][e];
-      if (q == 0) {
-#pragma unroll
-        for (int cc = 0; cc < CO; cc++) s += (double)R.w2[i][cc] * (double)R.w2[i][cc];
-      }
     }
+#pragma unroll
+    for (int g = 0; g < NG; g++) s += (double)small_penalty(g, q, 1.f) * (double)R.pw[g] * (double)R.pw[g];
     return block_sum(s, red);
   }
 
