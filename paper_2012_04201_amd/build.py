@@ -8,7 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbbo_mlp.so")
-SOURCES = ["kernels_tiled.hip", "kernels_deep3.hip", "kernels_deep2.hip", "kernels_mid.hip", "kernels_small2.hip",
+SOURCES = ["kernels_tiled.hip", "kernels_deep3.hip", "kernels_deep2.hip", "kernels_mid.hip", "kernels_full.hip", "kernels_small2.hip",
            "kernels_small1.hip", "kernels_small3.hip", "kernels_small4.hip", "kernels_linear_lds.hip", "kernels_linear.hip", "bbo_mlp.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]

@@ -48,6 +48,7 @@
 #include "kernels.h"
 #include "train_tiled_bf16.h"
 #include "train_small_f32.h"
+#include "train_full_f32.h"
 #include "train_mid_f32.h"
 #include "train_deep_f32.h"
 #include "train_linear_f32.h"
@@ -190,7 +191,7 @@ __device__ inline float row_loss(const float* z, int c, int n_classes, const voi
 
 // The training kernels.  Every suggestion of a call goes to the fastest kernel that takes its shape, so
 // a suggestion's scores do not depend on which other suggestions share its call.
-enum { KC_TILED = 0, KC_SMALL = 1, KC_LINEAR = 2, KC_GENERIC = 3, KC_MID = 4, KC_DEEP = 5 };
+enum { KC_TILED = 0, KC_SMALL = 1, KC_LINEAR = 2, KC_GENERIC = 3, KC_MID = 4, KC_DEEP = 5, KC_FULL = 6 };
 
 // ---------------------------------------------------------------------------
 // Fold lists (ascending), one workgroup per list; also resets the work queues.
@@ -936,6 +937,36 @@ void fill_item(ItemDesc& it, const bbo_mlp_hparams& h, int b, int64_t n, int d, 
   for (int l = 0; l < it.L; l++) it.bound[l] = (float)std::sqrt(6.0 / (double)(it.dims[l] + it.dims[l + 1]));
 }
 
+constexpr int FULL_MERGED = 256;  // models: a CU each
+// Full-batch models of different widths go into one launch, that of the widest, where they are few: a fork to another
+// stream and the join cost more (tiny study, 8 suggestions of one and two unit tiles: 154 us a call, 105 in one launch)
+// than the unit tiles that the narrower models do not have.  These are zeros in every sum, so the results are the same bits.
+void merge_full(Plan& pl, int n_folds) {
+  SubPlan* widest = nullptr;
+  size_t models = 0, launches = 0;
+  for (SubPlan& sp : pl.sub)
+    if (sp.kc == KC_FULL) {
+      launches++;
+      models += sp.order.size() * n_folds;
+      if (!widest || sp.cut.nt > widest->cut.nt) widest = &sp;
+    }
+  if (launches < 2 || models > (size_t)FULL_MERGED) return;
+  std::vector<SubPlan> kept;
+  SubPlan all = *widest;
+  all.order.clear();
+  for (SubPlan& sp : pl.sub) {
+    if (sp.kc != KC_FULL) {
+      kept.push_back(std::move(sp));
+      continue;
+    }
+    all.order.insert(all.order.end(), sp.order.begin(), sp.order.end());
+    all.slot_bytes = std::max(all.slot_bytes, sp.slot_bytes);
+    all.lds_bytes = std::max(all.lds_bytes, sp.lds_bytes);
+  }
+  kept.push_back(std::move(all));
+  pl.sub = std::move(kept);
+}
+
 // The launches of a call, their workgroups and where everything lies in a workspace of `room` bytes (pl.total may exceed
 // them: then the call does not fit).  one_stream: the launches may not run side by side.
 int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_base, const bbo_mlp_hparams* hp, int B,
@@ -958,6 +989,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     switch (kc) {
       case KC_TILED: sp.item_bytes = sizeof(TItem); break;
       case KC_SMALL: sp.item_bytes = sizeof(SItem); break;
+      case KC_FULL: sp.item_bytes = sizeof(FItem); break;
       case KC_MID: sp.item_bytes = sizeof(MItem); break;
       case KC_DEEP: sp.item_bytes = sizeof(DItem); break;
       default: sp.item_bytes = sizeof(ItemDesc);
@@ -976,8 +1008,10 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
       fps += 2.0 * dims[l] * dims[l + 1] * (l == 0 ? 2 : 3);
       params += (double)dims[l] * dims[l + 1];
     }
-    const int k = kernel_class(dims, L, n, dtype);
-    const SmallCut cut = k == KC_SMALL ? small_cut(dims) : (k == KC_MID ? mid_cut(dims, L) : (k == KC_DEEP ? deep_cut(dims, L) : SmallCut{0, 0, 0, 0}));
+    int k = kernel_class(dims, L, n, dtype);
+    const SmallCut full = k == KC_SMALL ? full_cut(dims, L, n, h.batch_size) : SmallCut{0, 0, 0, 0};
+    if (full.waves) k = KC_FULL;  // (a form of the small kernel for models that take all rows at once)
+    const SmallCut cut = k == KC_FULL ? full : k == KC_SMALL ? small_cut(dims) : (k == KC_MID ? mid_cut(dims, L) : (k == KC_DEEP ? deep_cut(dims, L) : SmallCut{0, 0, 0, 0}));
     SubPlan& sp = launch_of(k, cut);
     uint64_t slot_bytes = 0;
     uint32_t lds_bytes = 0;
@@ -991,6 +1025,9 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
       make_slay(sy, dims, n, cut);
       slot_bytes = 4ull * sy.slot_floats;
       lds_bytes = sy.lds_total;
+    } else if (k == KC_FULL) {
+      slot_bytes = fu_slot_bytes(cut);
+      lds_bytes = fu_lds(cut.kt, cut.nt, cut.co, cut.waves, n);
     } else if (k == KC_MID) {
       MLay my;
       make_mlay(my, dims, n, cut);
@@ -1013,6 +1050,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     sp.order.push_back(b);
   }
   pl.n_items = (size_t)B * n_folds;
+  merge_full(pl, n_folds);
   if (pl.sub.size() > (size_t)MAX_LAUNCHES) return fail(BBO_UNSUPPORTED, "too many kernel variants in one call");
   for (SubPlan& sp : pl.sub) {
     const int k = sp.kc;
@@ -1024,6 +1062,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     if (rc) return rc;
     size_t units = n_items;
     if (k == KC_SMALL) max_slots *= small_per_cu(sp.cut, sp.lds_bytes);
+    if (k == KC_FULL) max_slots *= full_per_cu(sp.cut, sp.lds_bytes);
     if (k == KC_MID) max_slots *= md_per_cu(sp.cut, sp.lds_bytes);
     if (k == KC_DEEP) max_slots *= deep_per_cu(sp.cut, sp.lds_bytes);
     const LinLds ll = k == KC_LINEAR && dtype == BBO_F32 ? ll_plan(n, d, n_classes >= 2 ? n_classes : 1) : LinLds{0, 0, 0, 0};
@@ -1076,7 +1115,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
   if (pl.in_turn) {
     const uint64_t left = off < room ? room - off : 0;
     for (SubPlan& sp : pl.sub) {
-      if ((sp.kc == KC_SMALL || sp.kc == KC_MID || sp.kc == KC_DEEP) && sp.slot_bytes * sp.n_slots > left &&
+      if ((sp.kc == KC_SMALL || sp.kc == KC_FULL || sp.kc == KC_MID || sp.kc == KC_DEEP) && sp.slot_bytes * sp.n_slots > left &&
           sp.slot_bytes * ((sp.n_slots + 1) / 2) <= left)
         sp.n_slots = (int)(left / sp.slot_bytes);
       sp.o_slots = off;
@@ -1331,6 +1370,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
         switch (sp.kc) {
           case KC_TILED: make_tlay(((TItem*)at)->y, it.dims, it.L); break;
           case KC_SMALL: make_slay(((SItem*)at)->y, it.dims, n, sp.cut); break;
+          case KC_FULL: make_flay(((FItem*)at)->y, it.dims); break;
           case KC_MID: make_mlay(((MItem*)at)->y, it.dims, n, sp.cut); break;
           case KC_DEEP: make_dlay(((DItem*)at)->y, it.dims, it.L, n, sp.cut); break;
         }
@@ -1396,6 +1436,9 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
       fn = t.kt == 1 ? small_kernel1(t.nt, t.waves, t.co) : (t.kt == 2 ? small_kernel2(t.nt, t.waves, t.co)
          : (t.kt == 3 ? small_kernel3(t.nt, t.waves, t.co) : small_kernel4(t.nt, t.waves, t.co)));
       threads = 64 * t.waves;
+    } else if (k == KC_FULL) {
+      fn = full_kernel(sp.cut.kt, sp.cut.nt, sp.cut.co, sp.cut.waves);
+      threads = 64 * sp.cut.waves;
     } else if (k == KC_MID) {
       fn = mid_kernel(sp.cut.kt, sp.cut.nt, sp.cut.waves);
       threads = 64 * sp.cut.waves;
@@ -1439,7 +1482,7 @@ int bbo_mlp_workspace_bytes(int64_t n, int32_t d, int32_t n_classes, int32_t n_f
   if (rc) return rc;
   // (records at their largest, whatever kernel they are for: the size of a call's records does not decide whether a
   // workspace made for as many other models holds it)
-  constexpr size_t record = std::max({sizeof(ItemDesc), sizeof(TItem), sizeof(SItem), sizeof(MItem), sizeof(DItem)});
+  constexpr size_t record = std::max({sizeof(ItemDesc), sizeof(TItem), sizeof(SItem), sizeof(FItem), sizeof(MItem), sizeof(DItem)});
   *out = (size_t)(pl.total + std::max<uint64_t>(record * (uint64_t)B + 256 * MAX_LAUNCHES, pl.items_bytes) - pl.items_bytes);
   return BBO_OK;
 }

@@ -287,16 +287,18 @@ struct OptC {
   float b1, b2, omb1, omb2, eps, lr_t, mu, lr, am;
 };
 
+// (The multiply-adds are written out: of a sum of two products the compiler may contract either, and models that move
+// between the variants of a kernel keep their bits.)
 __device__ inline void opt_update(const OptC& c, float g, float& w, float& m, float& v) {
   if (c.adam) {
-    m = c.b1 * m + c.omb1 * g;
-    v = c.b2 * v + c.omb2 * (g * g);
+    m = fmaf(c.b1, m, c.omb1 * g);
+    v = fmaf(c.b2, v, c.omb2 * (g * g));
     // hardware reciprocal and square root (1 ulp each): far inside the per-step tolerance
-    w = w - (c.lr_t * m) * __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(v) + c.eps);
+    w = fmaf(-(c.lr_t * m), __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(v) + c.eps), w);
   } else {
-    const float u = c.mu * m - c.lr * g;
+    const float u = fmaf(c.mu, m, -(c.lr * g));
     m = u;
-    w = w + (c.nest ? c.mu * u - c.lr * g : u);
+    w = w + (c.nest ? fmaf(c.mu, u, -(c.lr * g)) : u);
   }
 }
 

@@ -362,7 +362,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3> {
           for (int r = R0; r < R0 + N; r++)
 #pragma unroll
             for (int e = 0; e < 4; e++) {
-              const float x = fmaxf(acc[r][e], 0.f);
+              const float x = sm_relu(acc[r][e]);
               o[(r * 16 + e) * LDH] = x;
               bits |= (x > 0.f ? 1u : 0u) << (4 * r + e);
             }

@@ -217,6 +217,10 @@ __device__ __forceinline__ float sm_fold_row(const float (&v)[4], bool b2, bool 
   return (b2 ? B : A) + sm_dpp<0x1B>(x);           // and the reversal of the quad makes that i ^ 4
 }
 
+// max(x, 0), and 0 for a NaN, in one instruction: fmaxf() puts another in front that quiets NaNs where the compiler cannot
+// know that there are none, as in a matrix product's result.
+__device__ __forceinline__ float sm_relu(float x) { return __builtin_amdgcn_fmed3f(x, 0.f, INFINITY); }
+
 // Two classes by the difference of their logits, z = z[1] - z[0], of a row of class `one`.  The delta of class 1 (before
 // the division by the step's rows; class 0 has its negative): the probability of the other class, which does not cancel
 // as p - 1 does.  An infinite difference is a NaN in both, as it is with the logits apart.
@@ -227,6 +231,67 @@ __device__ __forceinline__ float sm_two_class_delta(float z, bool one) {
 __device__ __forceinline__ float sm_two_class_loss(float z, bool one) {
   const float s = one ? -z : z;  // of the other class over the row's own
   return fmaf(z, 0.f, fmaxf(s, 0.f) + log1pf(expf(-fabsf(s))));
+}
+
+// Output deltas of a lane's row from its outputs (two classes: their difference) and, if `loss`, its loss and second score.
+template <int CO>
+__device__ __forceinline__ void sm_outputs(const float (&z)[sm_columns(CO)], float yv, bool valid, int c, int n_classes, bool train,
+                                           bool loss, float inv_mb, float (&dl)[sm_columns(CO)], double& lsum, double& hits) {
+  constexpr int ZO = sm_columns(CO);
+  const int yr = __float_as_int(yv);
+#pragma unroll
+  for (int cc = 0; cc < ZO; cc++) dl[cc] = 0.f;
+  if (!valid) return;
+  if constexpr (CO == 2) {
+    const bool one = yr == 1;
+    if (loss) {
+      lsum += (double)sm_two_class_loss(z[0], one);
+      hits += (z[0] > 0.f) == one ? 1.0 : 0.0;
+    }
+    dl[0] = sm_two_class_delta(z[0], one) * inv_mb;
+  } else if constexpr (CO > 2) {
+    float mx = z[0], zy = z[0];
+    int best = 0;
+#pragma unroll
+    for (int cc = 1; cc < ZO; cc++)
+      if (cc < c) {
+        if (z[cc] > mx) {
+          mx = z[cc];
+          best = cc;
+        }
+        zy = cc == yr ? z[cc] : zy;
+      }
+    float ex[ZO], se = 0.f;
+#pragma unroll
+    for (int cc = 0; cc < ZO; cc++)
+      if (cc < c) {
+        ex[cc] = expf(z[cc] - mx);
+        se += ex[cc];
+      }
+    if (loss) {
+      lsum += (double)(mx + logf(se) - zy);
+      hits += best == yr ? 1.0 : 0.0;
+    }
+    const float inv = 1.f / se;
+#pragma unroll
+    for (int cc = 0; cc < ZO; cc++)
+      if (cc < c) dl[cc] = (ex[cc] * inv - (cc == yr ? 1.f : 0.f)) * inv_mb;
+  } else if (n_classes == 1) {
+    // one logit, labels 0/1: log(1 + e^z) - y z, delta (sigmoid(z) - y)/m
+    const float zz = z[0];
+    if (loss) {
+      lsum += (double)(fmaxf(zz, 0.f) + log1pf(expf(-fabsf(zz))) - (yr ? zz : 0.f));
+      hits += (zz > 0.f) == (yr != 0) ? 1.0 : 0.0;
+    }
+    dl[0] = (1.f / (1.f + expf(-zz)) - (float)yr) * inv_mb;
+  } else {
+    const float e0 = z[0] - yv;
+    if (loss) {
+      lsum += train ? 0.5 * (double)e0 * (double)e0 : (double)e0 * (double)e0;
+      hits += (double)fabsf(e0);  // the absolute error
+    }
+    dl[0] = e0 * inv_mb;
+  }
 }
 
 // What the phases of a chunk need to know about it, packed into one scalar (two chunks are in the pipeline behind
@@ -923,7 +988,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
     for (int e = 0; e < 4; e++) {
 #pragma unroll
       for (int i = 0; i < NT; i++) {
-        const float av = fmaxf(acc[i][r][e], 0.f);
+        const float av = sm_relu(acc[i][r][e]);
         acc[i][r][e] = av;
 #pragma unroll
         for (int cc = 0; cc < ZO; cc++) p[cc][e] = i == 0 ? av * R.w2[0][cc] : p[cc][e] + av * R.w2[i][cc];
@@ -984,62 +1049,8 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
       for (int cc = 0; cc < ZO; cc++) z[cc] += zp[(ww * ZO + cc) * SM_RC];
     }
     const float yv = ys(b)[row];
-    const int yr = __float_as_int(yv);
     float dl[ZO];
-#pragma unroll
-    for (int cc = 0; cc < ZO; cc++) dl[cc] = 0.f;
-    if (row < rows) {
-      if constexpr (CO == 2) {
-        const bool one = yr == 1;
-        if (loss) {
-          lsum += (double)sm_two_class_loss(z[0], one);
-          hits += (z[0] > 0.f) == one ? 1.0 : 0.0;
-        }
-        dl[0] = sm_two_class_delta(z[0], one) * inv_mb;
-      } else if (CO == 4) {
-        float mx = z[0], zy = z[0];
-        int best = 0;
-#pragma unroll
-        for (int cc = 1; cc < ZO; cc++)
-          if (cc < c) {
-            if (z[cc] > mx) {
-              mx = z[cc];
-              best = cc;
-            }
-            zy = cc == yr ? z[cc] : zy;
-          }
-        float ex[ZO], se = 0.f;
-#pragma unroll
-        for (int cc = 0; cc < ZO; cc++)
-          if (cc < c) {
-            ex[cc] = expf(z[cc] - mx);
-            se += ex[cc];
-          }
-        if (loss) {
-          lsum += (double)(mx + logf(se) - zy);
-          hits += best == yr ? 1.0 : 0.0;
-        }
-        const float inv = 1.f / se;
-#pragma unroll
-        for (int cc = 0; cc < ZO; cc++)
-          if (cc < c) dl[cc] = (ex[cc] * inv - (cc == yr ? 1.f : 0.f)) * inv_mb;
-      } else if (n_classes == 1) {
-        // one logit, labels 0/1: log(1 + e^z) - y z, delta (sigmoid(z) - y)/m
-        const float zz = z[0];
-        if (loss) {
-          lsum += (double)(fmaxf(zz, 0.f) + log1pf(expf(-fabsf(zz))) - (yr ? zz : 0.f));
-          hits += (zz > 0.f) == (yr != 0) ? 1.0 : 0.0;
-        }
-        dl[0] = (1.f / (1.f + expf(-zz)) - (float)yr) * inv_mb;
-      } else {
-        const float e0 = z[0] - yv;
-        if (loss) {
-          lsum += train ? 0.5 * (double)e0 * (double)e0 : (double)e0 * (double)e0;
-          hits += (double)fabsf(e0);
-        }
-        dl[0] = e0 * inv_mb;
-      }
-    }
+    sm_outputs<CO>(z, yv, row < rows, c, n_classes, train, loss, inv_mb, dl, lsum, hits);
     if (train) {
       float* d2 = f(O_D2) + lane;  // every wave writes the same values, and reads back only what it wrote itself
 #pragma unroll
