@@ -173,7 +173,7 @@ def gpu_evaluator(cfg, device="cuda:0"):
 
     def evaluate(hps):
         scores, status = binding.bbo_mlp_cv_eval(X, y, c, ft, K, hps, dt)
-        return scores[:, 0].cpu().numpy()
+        return scores.cpu().numpy()[:, 0].copy()  # (both columns in one copy: the first alone takes a kernel to pack it)
 
     return evaluate
 
