@@ -72,7 +72,7 @@ __host__ inline void make_dlay(DLay& y, const int32_t* dims, int L, int64_t n, c
     y.cb[l] = c;
     c += dims[l + 1];
   }
-  make_pipelay(y.p, dims[0], c, n, m.waves, dp_fixed_lds(m.kt, m.nt, m.waves));
+  make_pipelay(y.p, dims[0], c, n, dp_fixed_lds(m.kt, m.nt, m.waves));
   // the slot: parameters as they are drawn, later the best epoch's; moments; transposed hidden weights.  Only the tiles
   // there are take room: a narrow model's slot is no larger than one of the kernel for any shape.
   int owners = 0, turned = 0;

@@ -99,7 +99,7 @@ __host__ inline void make_mlay(MLay& y, const int32_t* dims, int64_t n, const Sm
   y.cb[0] = d * y.h;
   y.cw[1] = y.cb[0] + y.h;
   y.cb[1] = y.cw[1] + y.h * y.c;
-  make_pipelay(y.p, d, y.cb[1] + y.c, n, m.waves, md_fixed_lds(m.kt, m.nt, m.waves));
+  make_pipelay(y.p, d, y.cb[1] + y.c, n, md_fixed_lds(m.kt, m.nt, m.waves));
   y.slot_floats = (uint32_t)(m.waves * (md_regs(m.kt, m.nt) + (m.nt - md_near(m.kt, m.nt)) * 8 * m.kt) * 64);
   y.lds_total = y.p.total;
 }

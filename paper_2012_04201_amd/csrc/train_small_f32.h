@@ -110,7 +110,7 @@ __host__ __device__ constexpr uint32_t sm_fixed_lds(int kt, int co, int waves) {
 }
 
 // ... and the row tables behind `fixed` bytes of everything else
-__host__ inline void make_pipelay(PipeLay& y, int d, int P, int64_t n, int waves, uint32_t fixed) {
+__host__ inline void make_pipelay(PipeLay& y, int d, int P, int64_t n, uint32_t fixed) {
   y.d = d;
   y.P = P;
   uint32_t o = 0;
@@ -121,10 +121,10 @@ __host__ inline void make_pipelay(PipeLay& y, int d, int P, int64_t n, int waves
   };
   take(fixed);
   // 16-bit tables: the fold's row list in the order of the early-stopping cut, the epoch's row order, the round
-  // function of the permutation network (a copy per wave) and, up to SM_NET rows, the whole network
+  // function of the permutation network and, up to SM_NET rows, the whole network
   int hb = 1;
   while ((1 << (2 * hb)) < n) hb++;
-  const uint32_t ft = (uint32_t)(waves * (4 << hb) * 2), net = n <= SM_NET ? 2u << (2 * hb) : 0u;
+  const uint32_t ft = (uint32_t)((4 << hb) * 2), net = n <= SM_NET ? 2u << (2 * hb) : 0u;
   const uint32_t tab = (uint32_t)(2 * (n + SM_RC));  // (a chunk may read its row ids past the end: spare entries)
   y.tabled = n >= 1 && n <= 0xffff && o + ft + net + 2 * tab <= SM_LDS_LIMIT;
   y.netted = net > 0;  // (sized for n rows; the fold's own network is never wider)
@@ -147,7 +147,7 @@ __host__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n, const Sm
   y.cb[0] = d * y.h;
   y.cw[1] = y.cb[0] + y.h;
   y.cb[1] = y.cw[1] + y.h * y.c;
-  make_pipelay(y.p, d, y.cb[1] + y.c, n, s.waves, sm_fixed_lds(s.kt, s.co, s.waves));
+  make_pipelay(y.p, d, y.cb[1] + y.c, n, sm_fixed_lds(s.kt, s.co, s.waves));
   y.slot_floats = (uint32_t)(s.waves * sm_regs(s.kt, s.nt, s.co) * 64);
   y.lds_total = y.p.total;
 }
@@ -295,19 +295,25 @@ __device__ __forceinline__ void sm_outputs(const float (&z)[sm_columns(CO)], flo
 }
 
 // What the phases of a chunk need to know about it, packed into one scalar (two chunks are in the pipeline behind
-// the position that is being advanced): its rows (0..64), its mode, and flags.
+// the position that is being advanced): its rows (0..64), what it is, and flags, one bit for each question that the loop
+// asks of a chunk.  Scalar work is slow for the few waves of a SIMD (8 cycles an instruction, 26 a taken branch, 32 for a
+// value fetched back from a spill), and all of it lies on the chain of a step.
 enum {
   SC_ROWS = 0x7f,
-  SC_MODE = 0x380,       // RowMode << 7, or one of the next two
-  SC_END = 3 << 7,       // past the last chunk
-  SC_NONE = 4 << 7,      // the pipeline is filling
-  SC_FIRST = 1 << 10,    // first chunk of a step, or of a scoring pass
-  SC_LAST = 1 << 11,     // last chunk of a step
-  SC_RAGGED = 1 << 12,   // the epoch's last step
-  SC_EPOCH = 1 << 13,    // the epoch's first step
-  SC_DECIDE = 1 << 14,   // the stopping rule is applied after it
+  SC_TRAIN = 1 << 7,     // rows of an epoch's step
+  SC_HELD = 1 << 8,      // rows set aside
+  SC_PLAIN = 1 << 9,     // the held fold
+  SC_LIVE = 7 << 7,      // any of these: the pipeline is neither filling nor running dry
+  SC_END = 1 << 10,      // past the last chunk
+  SC_FIRST = 1 << 11,    // first chunk of a step, or of a scoring pass
+  SC_LAST = 1 << 12,     // last chunk of a step
+  SC_RAGGED = 1 << 13,   // the epoch's last step
+  SC_EPOCH = 1 << 14,    // the epoch's first step
+  SC_DECIDE = 1 << 15,   // the stopping rule is applied after it
+  SC_SLOW = 1 << 16,     // first chunk of a step that opens with more than the next learning rate
+  SC_PARK = 1 << 17,     // its rows are looked up chunk by chunk
+  SC_TABLE = 1 << 18,    // its epoch's rows are to be tabled
 };
-__device__ __forceinline__ int sc_mode(int ch) { return (ch & SC_MODE) >> 7; }
 
 // The row pipeline of a training run, shared by the kernels that take their inputs through LDS in chunks of 64 rows:
 // the schedule, the rows of an epoch, the inputs two chunks ahead, the stopping rules, tracing and the scores.  `Self`
@@ -367,11 +373,12 @@ struct RowPipe {
   }
 
   // The epoch's rows in visiting order -> ep.  The permutation network's round function sees the round and one half
-  // of the position only, so its 4 x 2^hb values are tabled first (each wave its own copy): a network evaluation is
-  // four LDS reads instead of twelve 64-bit multiplies.  Small data sets table the whole network from it, so that
-  // the walk back into the list is one read per hop; a lane whose position has landed starts its next one.
+  // of the position only, so its 4 x 2^hb values are tabled first: a network evaluation is four LDS reads instead of twelve
+  // 64-bit multiplies.  Small data sets table the whole network from it, so that the walk back into the list is one read
+  // per hop; a lane whose position has landed starts its next one, and several positions of a lane walk side by side,
+  // because each hop waits for LDS.
   __device__ __forceinline__ void build_epoch(uint64_t ke) const {
-    const int t_ = tid(), lane = t_ & 63;
+    const int t_ = tid();
     uint16_t* ep = u16(o_ep);
     const uint16_t* sl = u16(o_sl);
     if (n_fit <= 1) {
@@ -381,8 +388,8 @@ struct RowPipe {
     }
     const PermDomain dm = perm_domain((uint32_t)n_fit);
     const int half = 1 << dm.hb;
-    uint16_t* ft = u16(y.p.o_ft) + wave() * (4 * half);
-    for (int i = lane; i < 4 * half; i += 64)
+    uint16_t* ft = u16(y.p.o_ft);
+    for (int i = t_; i < 4 * half; i += NTHR)
       ft[i] = (uint16_t)((uint32_t)key_fold(ke, ((uint64_t)(i >> dm.hb) << 32) | ((uint32_t)i & dm.mask)) & dm.mask);
     __syncthreads();  // nobody reads the last epoch's order, or the network, any more
     if (t_ < SM_RC) ep[n_fit + t_] = sl[0];  // the spare entries
@@ -396,8 +403,8 @@ struct RowPipe {
       }
       return (Lh << dm.hb) | Rh;
     };
-    int p = t_;
     if (y.p.netted) {
+      int p = t_;
       uint16_t* net = u16(y.p.o_net);
       for (int x = t_; x < half * half; x += 4 * NTHR) {  // four evaluations in flight
         uint32_t v[4];
@@ -422,14 +429,25 @@ struct RowPipe {
         ep[p2] = rz;
       }
     } else {
-      uint32_t x = (uint32_t)p;
-      while (p < n_fit) {
-        x = network(x);
-        if (x < (uint32_t)n_fit) {
-          ep[p] = sl[x];
-          p += NTHR;
-          x = (uint32_t)p;
-        }
+      constexpr int U = 4;
+      int pos[U];
+      uint32_t x[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        pos[u] = t_ + u * NTHR;
+        x[u] = (uint32_t)pos[u];
+      }
+      // (n_fit > SM_NET / 2: every lane has several positions, and the first of them is the last to run out)
+      while (pos[0] < n_fit || pos[1] < n_fit || pos[2] < n_fit || pos[3] < n_fit) {
+#pragma unroll
+        for (int u = 0; u < U; u++) x[u] = network(pos[u] < n_fit ? x[u] : 0u);
+#pragma unroll
+        for (int u = 0; u < U; u++)
+          if (pos[u] < n_fit && x[u] < (uint32_t)n_fit) {
+            ep[pos[u]] = sl[x[u]];
+            pos[u] += U * NTHR;
+            x[u] = (uint32_t)pos[u];
+          }
       }
     }
   }
@@ -458,18 +476,18 @@ struct RowPipe {
     const Lists l = lists();
     if (r >= SM_RC) return;
     const int p = at + min(r, (chunk & SC_ROWS) - 1);  // past the chunk's rows: its last one again
-    rowlist(par)[r] =
-        sc_mode(chunk) == ROWS_PLAIN ? l.va[p] : l.tr[row_index(l.sp, sc_mode(chunk), key_epoch(l.km, e), (uint32_t)p)];
+    rowlist(par)[r] = chunk & SC_PLAIN ? l.va[p]
+                                       : l.tr[row_index(l.sp, chunk & SC_HELD ? ROWS_HELD : ROWS_EPOCH, key_epoch(l.km, e), (uint32_t)p)];
   }
   // The chunk's input values (and label) requested into registers; `at`: its first row's position in the epoch's
   // order, or in the list being scored.  Past the chunk's last row the entries that follow in the list are fetched
   // (rows the model trains on, or any when it only scores): nothing masks rows, because a row that is not the chunk's
-  // has no loss and a zero delta.  Columns past the inputs stay as clear_tiles() left them.
+  // has no loss and a zero delta.  Columns past the inputs stay zero in the registers.
   __device__ __forceinline__ void fetch(int chunk, int at, int par, float (&xr)[NX], float& yv) const {
-    const int t_ = tid(), k = t_ % KS, r0 = t_ / KS, mode = sc_mode(chunk);
+    const int t_ = tid(), k = t_ % KS, r0 = t_ / KS;
     uint32_t row[NX], yrow;
-    if (tabled && mode != ROWS_PLAIN) {
-      const uint16_t* t16 = (mode == ROWS_EPOCH ? u16(o_ep) : u16(o_sl) + n_fit) + at;
+    if (!(chunk & SC_PARK)) {
+      const uint16_t* t16 = (chunk & SC_TRAIN ? u16(o_ep) : u16(o_sl) + n_fit) + at;
 #pragma unroll
       for (int i = 0; i < NX; i++) row[i] = t16[r0 + i * RSTEP];
       yrow = t16[t_ & 63];
@@ -486,11 +504,11 @@ struct RowPipe {
     }
     yv = __int_as_float(*(const GlobalI32*)((const GlobalChar*)Y + yrow * 4u));  // class id or target: 32 bits either way
   }
-  // registers -> input tile and labels of buffer b
+  // registers -> input tile and labels of buffer b (columns past the inputs: fetch() leaves zeros in them)
   __device__ __forceinline__ void commit(int b, const float (&xr)[NX], float yv) const {
     float* s = xs(b);
     const int t_ = tid(), k = t_ % KS, r0 = t_ / KS;
-    if (k < d) {
+    if (KS == K0 || k < K0) {
 #pragma unroll
       for (int i = 0; i < NX; i++) s[(r0 + i * RSTEP) * LDW + k] = xr[i];
     }
@@ -531,59 +549,74 @@ struct RowPipe {
     // rows of that step from this chunk on.
     const int last_rows = pin(uniform(n_fit - (steps - 1) * bs)), decide = pin(uniform(watch && !n_hold ? (int)SC_DECIDE : 0));
     const int train_loss = traced | decide;  // somebody reads the loss of training chunks
-    int e = 0, st = 0, at = 0, left = 0;
+    const int untabled = tabled ? 0 : (int)SC_PARK;
+    int e = 0, at = 0, left = 0;
+    int step_flags = 0;  // SC_RAGGED and SC_EPOCH of the step at this position
+    int opened = 0;      // an epoch's rows have been asked for
     auto training = [&](int flags) {  // the chunk at this position
-      const int ragged = st + 1 == steps ? SC_RAGGED : 0;
-      const int last = left <= SM_RC ? SC_LAST | (ragged ? decide : 0) : 0;
-      return (ROWS_EPOCH << 7) | min(SM_RC, left) | flags | ragged | last | (st == 0 ? SC_EPOCH : 0);
+      return min(SM_RC, left) | SC_TRAIN | flags | step_flags |
+             (left <= SM_RC ? SC_LAST | (step_flags & SC_RAGGED ? decide : 0) : 0) | untabled;
     };
-    auto list_chunk = [&](int mode, int count) {
-      int ch = (mode << 7) | min(SM_RC, count - at);
+    auto list_chunk = [&](int what, int count) {
+      int ch = what | min(SM_RC, count - at);
       if (at == 0) ch |= SC_FIRST;
-      if (mode == ROWS_HELD && count - at <= SM_RC) ch |= SC_DECIDE;
+      if (what & SC_HELD) {
+        ch |= untabled;
+        if (count - at <= SM_RC) ch |= SC_DECIDE;
+      } else {
+        ch |= SC_PARK;
+      }
       return ch;
     };
     auto score_start = [&]() -> int {
       at = 0;
-      return n_va > 0 ? list_chunk(ROWS_PLAIN, n_va) : (int)SC_END;
+      return n_va > 0 ? list_chunk(SC_PLAIN, n_va) : (int)SC_END;
     };
-    auto step_start = [&]() -> int {  // at (e, st)
+    auto epoch_start = [&](int st) -> int {  // at step st of epoch e
       if (steps == 0 || e >= epochs) return score_start();
       at = st * bs;
       left = st + 1 == steps ? last_rows : bs;
-      return training(SC_FIRST);
+      step_flags = (st == 0 ? SC_EPOCH : 0) | (st + 1 == steps ? SC_RAGGED : 0);
+      // (an epoch of one step takes all rows at once: their order says nothing, and the first epoch's serves all)
+      const int table = !untabled && (steps > 1 || !opened) ? (int)SC_TABLE : 0;
+      opened = 1;
+      return training(SC_FIRST | SC_SLOW | table);
     };
     auto next = [&](int ch) -> int {
-      const int mode = sc_mode(ch), more = left - (ch & SC_ROWS);
       at += ch & SC_ROWS;
-      if (mode == ROWS_EPOCH && (more > 0 || st + 1 < steps)) {  // the epoch goes on: straight-line code
-        const int opens = more <= 0 ? 1 : 0;
-        st += opens;
-        left = opens ? (st + 1 == steps ? last_rows : bs) : more;
-        return training(opens ? (int)SC_FIRST : 0);
-      }
-      if (mode == ROWS_EPOCH && n_hold) {
-        at = 0;
-        return list_chunk(ROWS_HELD, n_hold);
-      }
-      if (mode == ROWS_HELD && at < n_hold) return list_chunk(ROWS_HELD, n_hold);
-      if (mode == ROWS_EPOCH || mode == ROWS_HELD) {
+      if (ch & SC_TRAIN) {
+        left -= ch & SC_ROWS;
+        if (left > 0) return training(0);
+        if (at < n_fit) {  // the epoch goes on
+          left = min(bs, n_fit - at);
+          step_flags = at + left == n_fit ? SC_RAGGED : 0;
+          return training(SC_FIRST | (traced | step_flags ? (int)SC_SLOW : 0));
+        }
+        if (n_hold) {
+          at = 0;
+          return list_chunk(SC_HELD, n_hold);
+        }
         e++;
-        st = 0;
-        return step_start();
+        return epoch_start(0);
       }
-      return mode == ROWS_PLAIN && at < n_va ? list_chunk(ROWS_PLAIN, n_va) : (int)SC_END;
+      if (ch & SC_HELD) {
+        if (at < n_hold) return list_chunk(SC_HELD, n_hold);
+        e++;
+        return epoch_start(0);
+      }
+      return ch & SC_PLAIN && at < n_va ? list_chunk(SC_PLAIN, n_va) : (int)SC_END;
     };
 
     typename Self::State R;
     int64_t gstep = 0;
+    int st0 = 0;
     if (resume) {
       gstep = P.step_begin;
       e = (int)(gstep / steps);
-      st = (int)(gstep % steps);
+      st0 = (int)(gstep % steps);
     }
-    const int e0 = e, st0 = st;
-    int c2 = step_start();  // the chunk at the position above
+    int e_lr = st0 > 0 ? e : e - 1;  // epoch of the step being worked on (set when one opens)
+    int c2 = epoch_start(st0);       // the chunk at the position above
     self.load(R, resume ? P.state_in : nullptr);
 
     OptC oc;
@@ -614,9 +647,7 @@ struct RowPipe {
 #pragma unroll
     for (int i = 0; i < NX; i++) xr[i] = 0.f;
     int b = 0, par = 0;  // input buffer and exchange parity of the current chunk
-    int built = -1;      // the last epoch whose rows have been tabled
-    int c0 = SC_NONE, c1 = SC_NONE;  // the chunk being worked on; the one whose inputs are on their way in registers
-    int e_lr = st0 > 0 ? e0 : e0 - 1;  // epoch of the step being worked on (set when one opens)
+    int c0 = 0, c1 = 0;  // the chunk being worked on; the one whose inputs are on their way in registers
     double lsum = 0.0, hits = 0.0;  // the lane's share of the summed data loss: of the epoch, or of a scoring pass
     Plateau plateau;
     int recording = 0, have_best = 0;
@@ -624,28 +655,40 @@ struct RowPipe {
     if (!oc.adam) oc.lr = uniform(epoch_lr(it.lr, it.power_t, e_lr, n_fit));
     for (int phase = 0; phase < 2; phase++) {  // training with its stopping rule; the score
       if (phase == 1 && have_best) self.restore_best(R);  // the best epoch's model is the one scored
-      while ((c0 & SC_MODE) != SC_END && (phase == 1 || sc_mode(c0) != ROWS_PLAIN)) {
+      const int stop_at = phase == 0 ? SC_PLAIN | SC_END : (int)SC_END;
+      while (!(c0 & stop_at)) {
         const int bn = b == NB - 1 ? 0 : b + 1, rows = c0 & SC_ROWS, nrt = (rows + 15) / 16;
-        if (BARRIERS == 1 && sc_mode(c1) <= ROWS_PLAIN) commit(bn, xr, yv);
+        if (BARRIERS == 1 && (c1 & SC_LIVE)) commit(bn, xr, yv);
         // the rows of the chunk whose inputs are requested next: its epoch's table if it opens one, or a row list
-        if ((c2 & SC_MODE) != SC_END) {
-          if (!tabled || sc_mode(c2) == ROWS_PLAIN) {
+        if (c2 & (SC_PARK | SC_TABLE)) {
+          if (c2 & SC_PARK)
             park_rows(c2, at, e, par);
-          } else if (sc_mode(c2) == ROWS_EPOCH && (steps > 1 ? e != built : built < 0)) {
-            // (an epoch of one step takes all rows at once: their order says nothing, and the first epoch's serves all)
+          else
             build_epoch(key_epoch(key_model(item().seed, fl + params().fold_base), steps > 1 ? e : 0));
-            built = e;
-          }
         }
         if (c0 & SC_FIRST) {
-          if (sc_mode(c0) == ROWS_EPOCH) {  // first chunk of a step
-            const bool last = c0 & SC_RAGGED;
-            oc.am = last ? am_last : am_full;
-            inv_mb = last ? inv_last : inv_full;
-            if (c0 & SC_EPOCH) {
-              e_lr++;
-              lsum = 0.0;
-              if (!oc.adam) oc.lr = uniform(epoch_lr(item().lr, item().power_t, e_lr, n_fit));
+          if (c0 & SC_TRAIN) {  // first chunk of a step
+            if (c0 & SC_SLOW) {
+              const bool last = c0 & SC_RAGGED;
+              oc.am = last ? am_last : am_full;
+              inv_mb = last ? inv_last : inv_full;
+              if (c0 & SC_EPOCH) {
+                e_lr++;
+                lsum = 0.0;
+                if (!oc.adam) oc.lr = uniform(epoch_lr(item().lr, item().power_t, e_lr, n_fit));
+              }
+              if (traced) {
+                recording = gstep >= params().step_begin && gstep < params().step_end ? 1 : 0;
+                if (recording) {
+                  const double pen = self.penalty_sum(R);
+                  // the step's loss is the difference this step makes to the epoch's sum; both wait in LDS
+                  const double before = self.total(lsum);
+                  if (threadIdx.x == 0) {
+                    trace_stash[0] = pen;
+                    trace_stash[1] = before;
+                  }
+                }
+              }
             }
             if (oc.adam) {
               if (lr_at == 64) {
@@ -664,35 +707,23 @@ struct RowPipe {
               oc.lr_t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lr_tab), lr_at));
               lr_at++;
             }
-            if (traced) {
-              recording = gstep >= params().step_begin && gstep < params().step_end ? 1 : 0;
-              if (recording) {
-                const double pen = self.penalty_sum(R);
-                // the step's loss is the difference this step makes to the epoch's sum; both wait in LDS
-                const double before = self.total(lsum);
-                if (threadIdx.x == 0) {
-                  trace_stash[0] = pen;
-                  trace_stash[1] = before;
-                }
-              }
-            }
             self.zero_grad(R);
           } else {
             lsum = hits = 0.0;
           }
         }
         typename Self::Acts acc;
-        const bool live = (c0 & SC_MODE) != SC_NONE;
+        const bool live = c0 & SC_LIVE;
         if (live) self.forward(R, b, par, nrt, acc);
         __syncthreads();  // the outputs' shares, the next chunk's inputs and the rows of the one after it
-        if (BARRIERS == 2 && sc_mode(c1) <= ROWS_PLAIN) commit(bn, xr, yv);
-        if (BARRIERS < 3 && (c2 & SC_MODE) != SC_END) fetch(c2, at, par, xr, yv);  // in flight until the next chunk is under way
+        if (BARRIERS == 2 && (c1 & SC_LIVE)) commit(bn, xr, yv);
+        if (BARRIERS < 3 && (c2 & SC_LIVE)) fetch(c2, at, par, xr, yv);  // in flight until the next chunk is under way
         if (live) {
-          const bool train = sc_mode(c0) == ROWS_EPOCH;
+          const bool train = c0 & SC_TRAIN;
           self.outputs(R, b, par, rows, train, !train || train_loss, inv_mb, lsum, hits);
         }
         if (BARRIERS >= 2) __syncthreads();  // the output deltas
-        if (sc_mode(c0) == ROWS_EPOCH) {
+        if (c0 & SC_TRAIN) {
           self.backward(R, b, nrt, acc);
           if (c0 & SC_LAST) {  // last chunk of the step
             float* rec = nullptr;
@@ -716,8 +747,8 @@ struct RowPipe {
         }
         if (BARRIERS == 3) {
           __syncthreads();  // the chunk's inputs have been read for the last time
-          if (sc_mode(c1) <= ROWS_PLAIN) commit(bn, xr, yv);
-          if ((c2 & SC_MODE) != SC_END) fetch(c2, at, par, xr, yv);
+          if (c1 & SC_LIVE) commit(bn, xr, yv);
+          if (c2 & SC_LIVE) fetch(c2, at, par, xr, yv);
         }
         const int done = c0;
         c0 = c1;
@@ -733,10 +764,10 @@ struct RowPipe {
             self.keep_best(R);
             have_best = 1;
           }
-          if (stop && sc_mode(c0) == ROWS_EPOCH) {  // what is already on its way is dropped, and the pipeline starts over
+          if (stop && (c0 & SC_TRAIN)) {  // what is already on its way is dropped, and the pipeline starts over
             __syncthreads();
             c2 = score_start();
-            c0 = c1 = SC_NONE;
+            c0 = c1 = 0;
           }
         }
       }
