@@ -58,7 +58,7 @@ __host__ __device__ constexpr int dp_blocks(int kt, int h, int waves) { return k
 __host__ __device__ constexpr bool dp_near(int kt, int h, int waves) { return dp_blocks(kt, h, waves) <= 8; }
 __host__ __device__ constexpr uint32_t dp_fixed_lds(int kt, int h, int waves) {
   // levels, the output layer's blocks, output deltas
-  return pipe_lds(kt, 1) + (h * SM_RC * (16 * waves + 4) + waves * 256 + SM_RC * MD_RS) * 4;
+  return pipe_lds(kt, 1, false) + (h * SM_RC * (16 * waves + 4) + waves * 256 + SM_RC * MD_RS) * 4;
 }
 __host__ inline void make_dlay(DLay& y, const int32_t* dims, int L, int64_t n, const SmallCut& m) {
   int c = 0;
@@ -97,8 +97,8 @@ __host__ inline int deep_per_cu(const SmallCut& m, uint32_t lds_bytes) {
 
 // H: hidden layers.  W: waves, and the most 16-unit tiles a hidden level has.
 template <int KT, int H, int W>
-struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3> {
-  typedef RowPipe<Deep<KT, H, W>, DLay, KT, W, 3> Base;
+struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
+  typedef RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> Base;
   using Base::Base;
   using Base::f;
   using Base::init_value;

@@ -88,7 +88,7 @@ __host__ __device__ constexpr int md_near(int kt, int nt) {
 }
 __host__ __device__ constexpr uint32_t md_fixed_lds(int kt, int nt, int waves) {
   // partial outputs, deltas, and per wave: the patch, the moments of w2, the bias moments
-  return pipe_lds(kt, 2) + (waves * SM_RC * MD_RS + SM_RC * MD_RS + waves * (16 * MD_RS + nt * 2 * 256 + (nt + 1) * 32)) * 4;
+  return pipe_lds(kt, 2, false) + (waves * SM_RC * MD_RS + SM_RC * MD_RS + waves * (16 * MD_RS + nt * 2 * 256 + (nt + 1) * 32)) * 4;
 }
 __host__ inline void make_mlay(MLay& y, const int32_t* dims, int64_t n, const SmallCut& m) {
   const int d = dims[0];
@@ -111,8 +111,8 @@ __host__ inline int md_per_cu(const SmallCut& m, uint32_t lds_bytes) {
 }
 
 template <int KT, int NT, int W>
-struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2> {
-  typedef RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2> Base;
+struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
+  typedef RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> Base;
   using Base::Base;
   using Base::f;
   using Base::init_value;

@@ -30,7 +30,8 @@
 // the chain of a step's dependent phases.  The optimizer's work on the small parameters (biases, output layer: alike in the
 // four lane groups q) is done four parameters at a time, one per q; the loss of a training chunk is computed only where the
 // stopping rule or a trace reads it.  With the output columns of two classes merged, these took 10,240 models 569 x 30 from
-// 30.7 to 27.4 ms and 40 models of 10,000 x 45 from 4.02 to 3.59.  The form before this one kept the weights in LDS and the moments in L2, at
+// 30.7 to 27.4 ms and 40 models of 10,000 x 45 from 4.02 to 3.59; products in split bfloat16 (sm_split()) and the leaner
+// schedule then to 24.2 and 3.56.  The form before this one kept the weights in LDS and the moments in L2, at
 // two workgroups per CU whatever the width and two barriers per chunk.  Before and after, per call: 10,240 models
 // 569 x 30, 50..200 units, 20 epochs 45.3 -> 32.4 ms; 40 models 506 x 13, SGD, 30 epochs 3.41 -> 1.74 ms; 40 models of
 // 10,000 x 45 rows, 3 epochs 10.9 -> 4.45 ms; 40 models 150 x 4, 20 epochs 0.39 -> 0.25 ms.
@@ -99,14 +100,29 @@ constexpr bool sm_occurs(int kt, int nt, int co, int waves) {
   return false;
 }
 
+// Inputs in three bfloat16 planes (see SmPlanes): blocks of 32 columns, elements of a row (the pad spreads the rows over
+// the banks), bytes of a tile of 64 rows.
+__host__ __device__ constexpr int sm_blocks(int kt) { return (kt + 1) / 2; }
+__host__ __device__ constexpr int sm_ldb(int kt) { return 32 * sm_blocks(kt) + 8; }
+__host__ __device__ constexpr uint32_t sm_tile_bytes(int kt, bool planes) {
+  return planes ? 3 * SM_RC * sm_ldb(kt) * 2 : SM_RC * sm_ldw(kt) * 4;
+}
 // LDS of the row pipeline: input tiles, labels, row lists
-__host__ __device__ constexpr uint32_t pipe_lds(int kt, int buffers) {
-  return (buffers * SM_RC * sm_ldw(kt) + buffers * SM_RC + 2 * SM_RC) * 4;
+__host__ __device__ constexpr uint32_t pipe_lds(int kt, int buffers, bool planes) {
+  return buffers * sm_tile_bytes(kt, planes) + (buffers * SM_RC + 2 * SM_RC) * 4;
 }
 // LDS of a variant of k_train_small ahead of the row tables
 __host__ __device__ constexpr int sm_columns(int co) { return co == 2 ? 1 : co; }
-__host__ __device__ constexpr uint32_t sm_fixed_lds(int kt, int co, int waves) {
-  return pipe_lds(kt, 3) + (2 * waves + 1) * sm_columns(co) * SM_RC * 4;
+// Products in split bfloat16 (see SmPlanes)?  With two input tiles, and with four where they fill the wave's registers least:
+// one tile is half of such a product, three are three quarters of two.  569 x 30 and 569 x 60, two classes, 400 suggestions,
+// us a call with fp32 products and split: 200 units, 30 inputs, 128 rows a step 1483 and 1175, 32 rows 2018 and 1917; 64
+// units, 60 inputs 813 and 643, 1122 and 984.  What does not fit spills and loses: one unit tile and two input tiles (four
+// waves a SIMD) 430 and 287 the other way, 128 units and 45 inputs 1648 and 1299.
+__host__ __device__ constexpr bool sm_split(int kt, int nt, int co) { return (kt == 2 && nt >= 2) || (kt == 4 && nt == 1 && co <= 2); }
+// With four input tiles three buffers of planes would leave room for one workgroup a CU: two, and a second barrier.
+__host__ __device__ constexpr int sm_barriers(int kt, int nt, int co) { return kt == 4 && sm_split(kt, nt, co) ? 2 : 1; }
+__host__ __device__ constexpr uint32_t sm_fixed_lds(int kt, int nt, int co, int waves) {
+  return pipe_lds(kt, 4 - sm_barriers(kt, nt, co), sm_split(kt, nt, co)) + (2 * waves + 1) * sm_columns(co) * SM_RC * 4;
 }
 
 // ... and the row tables behind `fixed` bytes of everything else
@@ -147,15 +163,15 @@ __host__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n, const Sm
   y.cb[0] = d * y.h;
   y.cw[1] = y.cb[0] + y.h;
   y.cb[1] = y.cw[1] + y.h * y.c;
-  make_pipelay(y.p, d, y.cb[1] + y.c, n, sm_fixed_lds(s.kt, s.co, s.waves));
+  make_pipelay(y.p, d, y.cb[1] + y.c, n, sm_fixed_lds(s.kt, s.nt, s.co, s.waves));
   y.slot_floats = (uint32_t)(s.waves * sm_regs(s.kt, s.nt, s.co) * 64);
   y.lds_total = y.p.total;
 }
 
 // Waves per SIMD the registers of a variant are budgeted for (512 registers per lane and SIMD).  The largest variants of a
 // budget do not fit it altogether: by the compiler's report <2,3,1,4> and <2,3,2,4> (129 to 192 units, 17 to 32 inputs)
-// spill 18 and 35 vector registers, <3,2,4,4> and <3,2,4,8> 105 and 89, <4,2,.,8> (129 units and more, 49 inputs and more)
-// 73, 95 and 210 at one, two and four output slots; the others 8 at most.  Four output slots need more than the 128
+// spill 95 and 97 vector registers, <3,2,4,4> and <3,2,4,8> 103 and 68, <4,2,.,8> (129 units and more, 49 inputs and more)
+// 79, 157 and 211 at one, two and four output slots; the others 18 at most.  Four output slots need more than the 128
 // registers of four waves even at one tile: at three, 569 x 30, three classes, 16 units, 32 rows a step, 400 suggestions take
 // 622 us a call instead of 857.
 __host__ __device__ constexpr int sm_occupancy(int kt, int nt, int co) {
@@ -294,6 +310,59 @@ __device__ __forceinline__ void sm_outputs(const float (&z)[sm_columns(CO)], flo
   }
 }
 
+// A float in three bfloat16 parts, x = h + m + l: each the rest rounded to nearest, so that the sum is exact (8 + 8 + 8 bits
+// of 24).  A product of two such numbers is summed over six of the nine pairs, smallest first; the three left out are below
+// 2^-24 of it.  Per 32 contracted elements that is six matrix instructions of 16 cycles instead of eight of 32, and the
+// result is closer to the exact one: over 64 normal pairs 9.4e-8 relative rms against 1.45e-7 of the fp32 instructions.
+// (Infinities come out as NaN, hence sm_relu_nan().)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+struct SmPlanes {  // eight elements a lane, as operands
+  u32x4 h, m, l;
+};
+__device__ __forceinline__ uint32_t sm_pack(float a, float b) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const f32x2 x = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+}
+__device__ __forceinline__ float sm_low(uint32_t v) { return __uint_as_float(v << 16); }
+__device__ __forceinline__ float sm_high(uint32_t v) { return __uint_as_float(v & 0xffff0000u); }
+__device__ __forceinline__ void sm_split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  h = sm_pack(a, b);
+  a -= sm_low(h);
+  b -= sm_high(h);
+  m = sm_pack(a, b);
+  l = sm_pack(a - sm_low(m), b - sm_high(m));
+}
+__device__ __forceinline__ f32x4 sm_mfma(const u32x4& a, const u32x4& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// The s-th of the six products, smallest first.
+template <int S>
+__device__ __forceinline__ f32x4 sm_product(const SmPlanes& a, const SmPlanes& b, const f32x4& c) {
+  if constexpr (S == 0) return sm_mfma(a.l, b.h, c);
+  if constexpr (S == 1) return sm_mfma(a.h, b.l, c);
+  if constexpr (S == 2) return sm_mfma(a.m, b.m, c);
+  if constexpr (S == 3) return sm_mfma(a.m, b.h, c);
+  if constexpr (S == 4) return sm_mfma(a.h, b.m, c);
+  return sm_mfma(a.h, b.h, c);
+}
+// N independent sums, c[i] += a . b[i], one product of each in turn
+template <int N, int S = 0>
+__device__ __forceinline__ void sm_products(const SmPlanes& a, const SmPlanes* b, f32x4* c) {
+#pragma unroll
+  for (int i = 0; i < N; i++) c[i] = sm_product<S>(a, b[i], c[i]);
+  if constexpr (S < 5) sm_products<N, S + 1>(a, b, c);
+}
+__device__ __forceinline__ float sm_relu_nan(float x) { return __builtin_elementwise_maximum(x, 0.f); }
+// Transposing LDS read of 16-bit elements: of the 16 x 4 elements that a row of 16 lanes addresses (lane t: four columns of
+// row t / 4 from column 4 (t mod 4) on) lane t gets column t of the four rows.
+__device__ __forceinline__ u32x2 sm_read_tr(const char* p) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)p));
+}
+
 // What the phases of a chunk need to know about it, packed into one scalar (two chunks are in the pipeline behind
 // the position that is being advanced): its rows (0..64), what it is, and flags, one bit for each question that the loop
 // asks of a chunk.  Scalar work is slow for the few waves of a SIMD (8 cycles an instruction, 26 a taken branch, 32 for a
@@ -326,11 +395,15 @@ enum {
 //             barrier of the chunk before, so three input tiles rotate.  2: one more between outputs() and
 //             backward(), and two input tiles are enough.  3: forward() begins with a barrier of its own, the chunk ends
 //             with one, and the next chunk's inputs take the place of the last one's: one input tile.
-template <class Self, class Lay, int KT, int W, int BARRIERS>
+//   PLANES    the inputs lie in LDS as three bfloat16 planes, [plane][row][block of 32 columns], a block in the order in which
+//             a lane reads eight elements at a time: column 16 t + 4q + e of the block's tile t at 8q + 4t + e
+template <class Self, class Lay, int KT, int W, int BARRIERS, bool PLANES>
 struct RowPipe {
-  static constexpr int K0 = 16 * KT, LDW = sm_ldw(KT), NB = 4 - BARRIERS;
-  static constexpr int KS = K0 <= 16 ? 16 : (K0 <= 32 ? 32 : (K0 <= 64 ? 64 : 128));  // lanes per row when inputs are fetched
-  static constexpr int NTHR = 64 * W, RSTEP = NTHR / KS, NX = SM_RC / RSTEP;          // rows per pass, passes
+  static constexpr int K0 = 16 * KT, LDW = sm_ldw(KT), LDB = sm_ldb(KT), NB = 4 - BARRIERS, PC = PLANES ? 2 : 1;
+  static constexpr int KL = K0 / PC;  // lanes per row when inputs are fetched, PC columns each
+  static constexpr int KS = KL <= 16 ? 16 : (KL <= 32 ? 32 : (KL <= 64 ? 64 : 128));
+  static constexpr int NTHR = 64 * W, RSTEP = NTHR / KS, NP = SM_RC / RSTEP, NX = NP * PC;  // rows per pass, passes, values
+  static constexpr uint32_t TILE = sm_tile_bytes(KT, PLANES), PLANE = SM_RC * LDB * 2;
   typedef const __attribute__((address_space(4))) Lay ConstLay;
   const TrainParams& P;
   const ConstItemDesc& it;
@@ -351,10 +424,33 @@ struct RowPipe {
       : P(P_), it(it_), y(y_), lds(lds_), slot(slot_), red(red_), trace_stash(stash_), fl(fl_) {}
 
   // offsets in floats; what the model keeps in LDS starts at O_OWN
-  static constexpr int O_YS = NB * SM_RC * LDW, O_ROWS = O_YS + NB * SM_RC, O_OWN = O_ROWS + 2 * SM_RC;
-  static_assert(O_OWN * 4 == pipe_lds(KT, NB), "LDS layout");
+  static constexpr int O_YS = NB * (int)(TILE / 4), O_ROWS = O_YS + NB * SM_RC, O_OWN = O_ROWS + 2 * SM_RC;
+  static_assert(O_OWN * 4 == pipe_lds(KT, NB, PLANES), "LDS layout");
   __device__ __forceinline__ float* f(int off) const { return (float*)lds + off; }
-  __device__ __forceinline__ float* xs(int b) const { return f(b * (SM_RC * LDW)); }
+  __device__ __forceinline__ float* xs(int b) const { return f(b * (int)(TILE / 4)); }
+  __device__ __forceinline__ const char* planes(int b) const { return lds + b * TILE; }
+  // Operands of a row tile's block of 32 columns: lane (row li, eight columns of the lane's q) ...
+  __device__ __forceinline__ static SmPlanes by_row(const char* x, int r, int kb) {
+    const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
+    const char* a = x + ((r * 16 + li) * LDB + kb * 32 + 8 * q) * 2;
+    return SmPlanes{*(const u32x4*)a, *(const u32x4*)(a + PLANE), *(const u32x4*)(a + 2 * PLANE)};
+  }
+  // ... and of two row tiles r, r + 1 (without `both` zeros in place of the second) of a tile of 16 columns turned over:
+  // lane (column li, rows 4q..+3 of each)
+  template <bool BOTH>
+  __device__ __forceinline__ static SmPlanes by_column(const char* x, int r, int kk) {
+    const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
+    const char* a = x + ((r * 16 + 4 * q + (li >> 2)) * LDB + (kk >> 1) * 32 + 8 * (li & 3) + 4 * (kk & 1)) * 2;
+    u32x4 p[3];
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+      const u32x2 lo = sm_read_tr(a + i * PLANE);
+      u32x2 hi = u32x2{0u, 0u};
+      if (BOTH) hi = sm_read_tr(a + i * PLANE + 16 * LDB * 2);
+      p[i] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
+    return SmPlanes{p[0], p[1], p[2]};
+  }
   __device__ __forceinline__ float* ys(int b) const { return f(O_YS + b * SM_RC); }
   __device__ __forceinline__ int32_t* rowlist(int par) const { return (int32_t*)lds + O_ROWS + par * SM_RC; }
   __device__ __forceinline__ uint16_t* u16(uint32_t off) const { return (uint16_t*)(lds + off); }
@@ -484,39 +580,57 @@ struct RowPipe {
   // (rows the model trains on, or any when it only scores): nothing masks rows, because a row that is not the chunk's
   // has no loss and a zero delta.  Columns past the inputs stay zero in the registers.
   __device__ __forceinline__ void fetch(int chunk, int at, int par, float (&xr)[NX], float& yv) const {
-    const int t_ = tid(), k = t_ % KS, r0 = t_ / KS;
-    uint32_t row[NX], yrow;
+    const int t_ = tid(), k = t_ % KS * PC, r0 = t_ / KS;
+    uint32_t row[NP], yrow;
     if (!(chunk & SC_PARK)) {
       const uint16_t* t16 = (chunk & SC_TRAIN ? u16(o_ep) : u16(o_sl) + n_fit) + at;
 #pragma unroll
-      for (int i = 0; i < NX; i++) row[i] = t16[r0 + i * RSTEP];
+      for (int i = 0; i < NP; i++) row[i] = t16[r0 + i * RSTEP];
       yrow = t16[t_ & 63];
     } else {
       const int32_t* t32 = rowlist(par);
 #pragma unroll
-      for (int i = 0; i < NX; i++) row[i] = (uint32_t)t32[r0 + i * RSTEP];
+      for (int i = 0; i < NP; i++) row[i] = (uint32_t)t32[r0 + i * RSTEP];
       yrow = (uint32_t)t32[t_ & 63];
     }
     // 32-bit byte offsets: the host sends matrices of 4 GiB and more elsewhere
     if (k < d) {
 #pragma unroll
-      for (int i = 0; i < NX; i++) xr[i] = *(const GlobalF32*)((const GlobalChar*)X + (row[i] * (uint32_t)d + (uint32_t)k) * 4u);
+      for (int i = 0; i < NP; i++) xr[i * PC] = *(const GlobalF32*)((const GlobalChar*)X + (row[i] * (uint32_t)d + (uint32_t)k) * 4u);
+    }
+    if (PLANES && k + 1 < d) {
+#pragma unroll
+      for (int i = 0; i < NP; i++)
+        xr[i * PC + PC - 1] = *(const GlobalF32*)((const GlobalChar*)X + (row[i] * (uint32_t)d + (uint32_t)k) * 4u + 4u);
     }
     yv = __int_as_float(*(const GlobalI32*)((const GlobalChar*)Y + yrow * 4u));  // class id or target: 32 bits either way
   }
   // registers -> input tile and labels of buffer b (columns past the inputs: fetch() leaves zeros in them)
   __device__ __forceinline__ void commit(int b, const float (&xr)[NX], float yv) const {
-    float* s = xs(b);
-    const int t_ = tid(), k = t_ % KS, r0 = t_ / KS;
-    if (KS == K0 || k < K0) {
+    const int t_ = tid(), k = t_ % KS * PC, r0 = t_ / KS;
+    if (KS == KL || k < K0) {
+      if constexpr (PLANES) {
+        char* s = lds + b * TILE + (r0 * LDB + (k >> 5) * 32 + ((k >> 2) & 3) * 8 + ((k >> 4) & 1) * 4 + (k & 3)) * 2;
 #pragma unroll
-      for (int i = 0; i < NX; i++) s[(r0 + i * RSTEP) * LDW + k] = xr[i];
+        for (int i = 0; i < NP; i++) {
+          uint32_t h, m, l;
+          sm_split2(xr[2 * i], xr[2 * i + 1], h, m, l);
+          char* o = s + i * RSTEP * LDB * 2;
+          *(uint32_t*)o = h;
+          *(uint32_t*)(o + PLANE) = m;
+          *(uint32_t*)(o + 2 * PLANE) = l;
+        }
+      } else {
+        float* s = xs(b);
+#pragma unroll
+        for (int i = 0; i < NX; i++) s[(r0 + i * RSTEP) * LDW + k] = xr[i];
+      }
     }
     if (t_ < SM_RC) ys(b)[t_] = yv;
   }
-  // Zeros into the input tiles (their columns past the inputs are never written) and into the row list's spare entries.
+  // Zeros into the input tiles (an absent tile's half of a block is never written) and into the row list's spare entries.
   __device__ __forceinline__ void clear_tiles(int n_tr) const {
-    for (int i = threadIdx.x; i < NB * SM_RC * LDW; i += NTHR) f(0)[i] = 0.f;
+    for (int i = threadIdx.x; i < NB * (int)(TILE / 4); i += NTHR) f(0)[i] = 0.f;
     if (tabled && threadIdx.x < SM_RC) u16(o_sl)[n_tr + threadIdx.x] = 0;
   }
 
@@ -782,11 +896,51 @@ struct RowPipe {
   }
 };
 
+// The weights of a wave's hidden units: lane (unit li, columns 16 kk + 4q + e), as floats or as the three planes of two
+// tiles of columns, which hold the same numbers.
+template <int KT, int NT, bool SPLIT>
+struct HiddenWeights {
+  f32x4 w[NT][KT];
+  __device__ __forceinline__ f32x4 get(int i, int kk) const { return w[i][kk]; }
+  __device__ __forceinline__ void put(int i, int kk, const f32x4& x) { w[i][kk] = x; }
+};
+template <int KT, int NT>
+struct HiddenWeights<KT, NT, true> {
+  SmPlanes p[sm_blocks(KT)][NT];
+  static constexpr bool MASTER = KT * NT <= 4;
+  f32x4 w[MASTER ? NT : 1][MASTER ? KT : 1];
+  __device__ __forceinline__ f32x4 get(int i, int kk) const {
+    if constexpr (MASTER) return w[i][kk];
+    const SmPlanes& s = p[kk >> 1][i];
+    f32x4 x;
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+      const int j = 2 * (kk & 1) + e;
+      x[2 * e] = (sm_low(s.h[j]) + sm_low(s.m[j])) + sm_low(s.l[j]);
+      x[2 * e + 1] = (sm_high(s.h[j]) + sm_high(s.m[j])) + sm_high(s.l[j]);
+    }
+    return x;
+  }
+  __device__ __forceinline__ void put(int i, int kk, const f32x4& x) {
+    if constexpr (MASTER) w[i][kk] = x;
+    SmPlanes& s = p[kk >> 1][i];
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+      uint32_t h, m, l;
+      sm_split2(x[2 * e], x[2 * e + 1], h, m, l);
+      s.h[2 * (kk & 1) + e] = h;
+      s.m[2 * (kk & 1) + e] = m;
+      s.l[2 * (kk & 1) + e] = l;
+    }
+    if (KT % 2 && kk == KT - 1) s.h[2] = s.h[3] = s.m[2] = s.m[3] = s.l[2] = s.l[3] = 0u;
+  }
+};
+
 // KT: 16-wide k tiles of the input layer.  NT: unit tiles per wave (every wave has NT, or NT - 1, of them).
 // CO: output slots in use (1 and 2 are exact output counts, 4 serves 3 or 4 outputs).  W: waves.
 template <int KT, int NT, int CO, int W>
-struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
-  typedef RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> Base;
+struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO), sm_split(KT, NT, CO)> {
+  typedef RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO), sm_split(KT, NT, CO)> Base;
   using Base::Base;
   using Base::f;
   using Base::init_value;
@@ -810,8 +964,11 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
   // The small parameters: the bias and the row of the output layer of each tile's unit li, then the output bias.  The
   // optimizer works on four at a time: parameter k in the lanes of row q = k % 4, group k / 4.
   static constexpr int NSMALL = NT * (1 + CO) + CO, NG = (NSMALL + 3) / 4;
+  static constexpr bool SPLIT = sm_split(KT, NT, CO);
+  static constexpr int KB = sm_blocks(KT);
   struct State {
-    f32x4 w[NT][KT], m[NT][KT], v[NT][KT], g[NT][KT];  // hidden layer: lane (unit li, columns 16 kk + 4q + e)
+    HiddenWeights<KT, NT, SPLIT> w;
+    f32x4 m[NT][KT], v[NT][KT], g[NT][KT];  // hidden layer: lane (unit li, columns 16 kk + 4q + e)
     float pw[NG], pm[NG], pv[NG];                      // the small parameters and their moments
     float bw[NT], w2[NT][ZO], ow[ZO];                  // the same as the products want them: alike in the four q
     float bg[NT], g2[NT][ZO], og[ZO];                  // the lane's share of their gradients
@@ -822,7 +979,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
   };
   // offsets in floats
   static constexpr int O_ZP = Base::O_OWN, O_D2 = O_ZP + 2 * W * ZO * SM_RC, O_TOP = O_D2 + ZO * SM_RC;
-  static_assert(O_TOP * 4 == sm_fixed_lds(KT, CO, W), "LDS layout");
+  static_assert(O_TOP * 4 == sm_fixed_lds(KT, NT, CO, W), "LDS layout");
   // does the wave's i-th tile exist?  Only the last one can be missing.
   __device__ __forceinline__ bool has(int i, int w) const { return i + 1 < NT || w + i * W < nut; }
 
@@ -831,7 +988,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
   // order each_param() visits them.
   static constexpr int NREG = sm_regs(KT, NT, CO), PER = 4 * KT + 1 + CO;
   __device__ __forceinline__ float* park() const { return slot + wave() * (NREG * 64) + (threadIdx.x & 63); }
-  // fn(index, reference) for the hidden weights of `w`
+  // fn(index, reference) for the hidden weights or one of their moments
   template <class F>
   __device__ __forceinline__ static void each_hidden(f32x4 (&w)[NT][KT], F fn) {
 #pragma unroll
@@ -844,6 +1001,22 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
           fn(i * PER + 4 * kk + e, x);
           w[i][kk][e] = x;
         }
+  }
+  template <class F>
+  __device__ __forceinline__ static void each_hidden(HiddenWeights<KT, NT, SPLIT>& w, F fn) {
+#pragma unroll
+    for (int i = 0; i < NT; i++)
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++) {
+        f32x4 x = w.get(i, kk);
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          float y_ = x[e];
+          fn(i * PER + 4 * kk + e, y_);
+          x[e] = y_;
+        }
+        w.put(i, kk, x);
+      }
   }
   // small parameter k: of tile k / (1 + CO), 0 its bias, else an output; from NT (1 + CO) on the output bias
   __device__ __forceinline__ static int small_register(int k) {
@@ -998,28 +1171,34 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
   // One row tile: products of all the wave's tiles in turn (independent accumulators), ReLU, output-layer share.
   // ALL: the wave's last tile exists.
   template <bool ALL>
-  __device__ __forceinline__ void forward_tile(const State& R, const float* s, int r, f32x4 (&acc)[NT][4], float (&v)[ZO][4]) const {
+  __device__ __forceinline__ void forward_tile(const State& R, int b, int r, f32x4 (&acc)[NT][4], float (&v)[ZO][4]) const {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
-    const float* a_ = s + (r * 16 + li) * LDW + 4 * q;
-    f32x4 a[KT];
+    f32x4 c[NT];
 #pragma unroll
-    for (int kk = 0; kk < KT; kk++) a[kk] = *(const f32x4*)(a_ + kk * 16);
+    for (int i = 0; i < NT; i++) c[i] = f32x4{R.bw[i], R.bw[i], R.bw[i], R.bw[i]};
+    if constexpr (SPLIT) {
 #pragma unroll
-    for (int i = 0; i < NT; i++) acc[i][r] = f32x4{R.bw[i], R.bw[i], R.bw[i], R.bw[i]};
+      for (int kb = 0; kb < KB; kb++) sm_products<NT - (ALL ? 0 : 1)>(Base::by_row(Base::planes(b), r, kb), R.w.p[kb], c);
+    } else {
+      const float* a_ = xs(b) + (r * 16 + li) * LDW + 4 * q;
+      f32x4 a[KT];
 #pragma unroll
-    for (int kk = 0; kk < KT; kk++)
+      for (int kk = 0; kk < KT; kk++) a[kk] = *(const f32x4*)(a_ + kk * 16);
 #pragma unroll
-      for (int e = 0; e < 4; e++) {
+      for (int kk = 0; kk < KT; kk++)
 #pragma unroll
-        for (int i = 0; i < NT; i++)
-          if (i + 1 < NT || ALL) acc[i][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], R.w[i][kk][e], acc[i][r], 0, 0, 0);
-      }
+        for (int e = 0; e < 4; e++) {
+#pragma unroll
+          for (int i = 0; i < NT; i++)
+            if (i + 1 < NT || ALL) c[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], R.w.w[i][kk][e], c[i], 0, 0, 0);
+        }
+    }
     float p[ZO][4];
 #pragma unroll
     for (int e = 0; e < 4; e++) {
 #pragma unroll
       for (int i = 0; i < NT; i++) {
-        const float av = sm_relu(acc[i][r][e]);
+        const float av = SPLIT ? sm_relu_nan(c[i][e]) : sm_relu(c[i][e]);
         acc[i][r][e] = av;
 #pragma unroll
         for (int cc = 0; cc < ZO; cc++) p[cc][e] = i == 0 ? av * R.w2[0][cc] : p[cc][e] + av * R.w2[i][cc];
@@ -1029,11 +1208,11 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
     for (int cc = 0; cc < ZO; cc++) v[cc][r] = sm_fold_quad(p[cc], li & 1, li & 2);
   }
   template <bool ALL, int N>
-  __device__ __forceinline__ void forward_tiles(const State& R, const float* s, f32x4 (&acc)[NT][4], float (&v)[ZO][4]) const {
+  __device__ __forceinline__ void forward_tiles(const State& R, int b, f32x4 (&acc)[NT][4], float (&v)[ZO][4]) const {
 #pragma unroll
     for (int r = 0; r < 4; r++) {
       if (r < N) {
-        forward_tile<ALL>(R, s, r, acc, v);
+        forward_tile<ALL>(R, b, r, acc, v);
       } else {
 #pragma unroll
         for (int cc = 0; cc < ZO; cc++) v[cc][r] = 0.f;
@@ -1041,24 +1220,24 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
     }
   }
   template <bool ALL>
-  __device__ __forceinline__ void forward_chunk(const State& R, const float* s, int nrt, f32x4 (&acc)[NT][4], float (&v)[ZO][4]) const {
+  __device__ __forceinline__ void forward_chunk(const State& R, int b, int nrt, f32x4 (&acc)[NT][4], float (&v)[ZO][4]) const {
     if (nrt == 4)
-      forward_tiles<ALL, 4>(R, s, acc, v);
+      forward_tiles<ALL, 4>(R, b, acc, v);
     else if (nrt == 3)
-      forward_tiles<ALL, 3>(R, s, acc, v);
+      forward_tiles<ALL, 3>(R, b, acc, v);
     else if (nrt == 2)
-      forward_tiles<ALL, 2>(R, s, acc, v);
+      forward_tiles<ALL, 2>(R, b, acc, v);
     else
-      forward_tiles<ALL, 1>(R, s, acc, v);
+      forward_tiles<ALL, 1>(R, b, acc, v);
   }
   __device__ __forceinline__ void forward(const State& R, int b, int par, int nrt, Acts& A) const {
     f32x4 (&acc)[NT][4] = A.a;
     const int w_ = wave();
     float v[ZO][4];
     if (has(NT - 1, w_))
-      forward_chunk<true>(R, xs(b), nrt, acc, v);
+      forward_chunk<true>(R, b, nrt, acc, v);
     else
-      forward_chunk<false>(R, xs(b), nrt, acc, v);
+      forward_chunk<false>(R, b, nrt, acc, v);
     const int lane = tid() & 63, li = lane & 15;
     float* zp = f(O_ZP) + (par * W + w_) * (ZO * SM_RC) + lane;
 #pragma unroll
@@ -1094,20 +1273,13 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
   }
 
   // ---- backward: hidden deltas, output-layer gradient, hidden weight gradient -------
+  // the hidden deltas of a row tile, and its shares of the small parameters' gradients
   template <bool ALL>
-  __device__ __forceinline__ void backward_tile(State& R, const float* s, int r, const f32x4 (&acc)[NT][4]) const {
-    const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
-    const float* d2 = f(O_D2) + q * 16 + r * 4;
-    const float* a_ = s + (r * 16 + 4 * q) * LDW + li;
+  __device__ __forceinline__ void deltas(State& R, int r, const f32x4 (&acc)[NT][4], f32x4 (&dh)[NT]) const {
+    const float* d2 = f(O_D2) + ((tid() & 63) >> 4) * 16 + r * 4;
     f32x4 dv[ZO];
-    float a[KT][4];
 #pragma unroll
     for (int cc = 0; cc < ZO; cc++) dv[cc] = *(const f32x4*)(d2 + cc * SM_RC);
-#pragma unroll
-    for (int kk = 0; kk < KT; kk++)
-#pragma unroll
-      for (int e = 0; e < 4; e++) a[kk][e] = a_[e * LDW + kk * 16];
-    f32x4 dh[NT];
 #pragma unroll
     for (int i = 0; i < NT; i++)
       if (i + 1 < NT || ALL) {
@@ -1126,6 +1298,18 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
           R.bg[i] += x;
         }
       }
+  }
+  template <bool ALL>
+  __device__ __forceinline__ void backward_tile(State& R, const float* s, int r, const f32x4 (&acc)[NT][4]) const {
+    const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
+    const float* a_ = s + (r * 16 + 4 * q) * LDW + li;
+    float a[KT][4];
+#pragma unroll
+    for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) a[kk][e] = a_[e * LDW + kk * 16];
+    f32x4 dh[NT];
+    deltas<ALL>(R, r, acc, dh);
 #pragma unroll
     for (int kk = 0; kk < KT; kk++)
 #pragma unroll
@@ -1135,28 +1319,66 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
           if (i + 1 < NT || ALL) R.g[i][kk] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], dh[i][e], R.g[i][kk], 0, 0, 0);
       }
   }
-  template <bool ALL, int N>
-  __device__ __forceinline__ void backward_tiles(State& R, const float* s, const f32x4 (&acc)[NT][4]) const {
+  // row tiles r and r + 1 (BOTH), which fill the 32 contracted rows of a product
+  template <bool ALL, bool BOTH>
+  __device__ __forceinline__ void backward_pair(State& R, const char* x, int r, const f32x4 (&acc)[NT][4]) const {
+    constexpr int TILES = NT - (ALL ? 0 : 1);
+    if constexpr (TILES > 0) {
+      SmPlanes dp[TILES];
 #pragma unroll
-    for (int r = 0; r < N; r++) backward_tile<ALL>(R, s, r, acc);
+      for (int t = 0; t < 2; t++) {
+        f32x4 dh[NT];
+        if (t == 0 || BOTH) deltas<ALL>(R, r + t, acc, dh);
+#pragma unroll
+        for (int i = 0; i < TILES; i++)
+#pragma unroll
+          for (int e = 0; e < 2; e++) {
+            uint32_t h = 0u, m = 0u, l = 0u;
+            if (t == 0 || BOTH) sm_split2(dh[i][2 * e], dh[i][2 * e + 1], h, m, l);
+            dp[i].h[2 * t + e] = h;
+            dp[i].m[2 * t + e] = m;
+            dp[i].l[2 * t + e] = l;
+          }
+      }
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++) {
+        f32x4 c[TILES];
+#pragma unroll
+        for (int i = 0; i < TILES; i++) c[i] = R.g[i][kk];
+        sm_products<TILES>(Base::template by_column<BOTH>(x, r, kk), dp, c);
+#pragma unroll
+        for (int i = 0; i < TILES; i++) R.g[i][kk] = c[i];
+      }
+    }
+  }
+  template <bool ALL, int N>
+  __device__ __forceinline__ void backward_tiles(State& R, int b, const f32x4 (&acc)[NT][4]) const {
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int r = 0; r + 1 < N; r += 2) backward_pair<ALL, true>(R, Base::planes(b), r, acc);
+      if constexpr (N % 2) backward_pair<ALL, false>(R, Base::planes(b), N - 1, acc);
+    } else {
+#pragma unroll
+      for (int r = 0; r < N; r++) backward_tile<ALL>(R, xs(b), r, acc);
+    }
   }
   template <bool ALL>
-  __device__ __forceinline__ void backward_chunk(State& R, const float* s, int nrt, const f32x4 (&acc)[NT][4]) const {
+  __device__ __forceinline__ void backward_chunk(State& R, int b, int nrt, const f32x4 (&acc)[NT][4]) const {
     if (nrt == 4)
-      backward_tiles<ALL, 4>(R, s, acc);
+      backward_tiles<ALL, 4>(R, b, acc);
     else if (nrt == 3)
-      backward_tiles<ALL, 3>(R, s, acc);
+      backward_tiles<ALL, 3>(R, b, acc);
     else if (nrt == 2)
-      backward_tiles<ALL, 2>(R, s, acc);
+      backward_tiles<ALL, 2>(R, b, acc);
     else
-      backward_tiles<ALL, 1>(R, s, acc);
+      backward_tiles<ALL, 1>(R, b, acc);
   }
   __device__ __forceinline__ void backward(State& R, int b, int nrt, const Acts& A) const {
     const f32x4 (&acc)[NT][4] = A.a;
     if (has(NT - 1, wave()))
-      backward_chunk<true>(R, xs(b), nrt, acc);
+      backward_chunk<true>(R, b, nrt, acc);
     else
-      backward_chunk<false>(R, xs(b), nrt, acc);
+      backward_chunk<false>(R, b, nrt, acc);
   }
 
   // ---- optimizer step -------------------------------------------------------------
@@ -1171,15 +1393,18 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
     for (int i = 0; i < NT; i++)
       if (has(i, w_)) {
 #pragma unroll
-        for (int kk = 0; kk < KT; kk++)
+        for (int kk = 0; kk < KT; kk++) {
+          f32x4 x = R.w.get(i, kk);
 #pragma unroll
           for (int e = 0; e < 4; e++) {
-            float wr = R.w[i][kk][e], mr = R.m[i][kk][e], vr = R.v[i][kk][e];
+            float wr = x[e], mr = R.m[i][kk][e], vr = R.v[i][kk][e];
             opt_update(o, R.g[i][kk][e] + o.am * wr, wr, mr, vr);
-            R.w[i][kk][e] = wr;
+            x[e] = wr;
             R.m[i][kk][e] = mr;
             R.v[i][kk][e] = vr;
           }
+          R.w.put(i, kk, x);
+        }
       }
     const int q = (tid() & 63) >> 4;
     float gp[NG];
@@ -1198,12 +1423,14 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
     for (int i = 0; i < NT; i++) {
       const int j = (w_ + i * W) * 16 + li;
 #pragma unroll
-      for (int kk = 0; kk < KT; kk++)
+      for (int kk = 0; kk < KT; kk++) {
+        const f32x4 x = R.w.get(i, kk);
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           const int k = kk * 16 + 4 * q + e;
-          if (j < h && k < d) out[y.cw[0] + k * h + j] = GRAD ? R.g[i][kk][e] + am * R.w[i][kk][e] : R.w[i][kk][e];
+          if (j < h && k < d) out[y.cw[0] + k * h + j] = GRAD ? R.g[i][kk][e] + am * x[e] : x[e];
         }
+      }
     }
     float gp[NG];
     if (GRAD) small_grads(R, gp);
@@ -1227,10 +1454,13 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
     for (int i = 0; i < NT; i++) {
       const bool unit = (w_ + i * W) * 16 + li < y.h;
 #pragma unroll
-      for (int kk = 0; kk < KT; kk++)
+      for (int kk = 0; kk < KT; kk++) {
+        f32x4 x = R.w.get(i, kk);
 #pragma unroll
         for (int e = 0; e < 4; e++)
-          if (!unit || kk * 16 + 4 * q + e >= y.p.d) R.w[i][kk][e] = R.m[i][kk][e] = R.v[i][kk][e] = 0.f;
+          if (!unit || kk * 16 + 4 * q + e >= y.p.d) x[e] = R.m[i][kk][e] = R.v[i][kk][e] = 0.f;
+        R.w.put(i, kk, x);
+      }
     }
 #pragma unroll
     for (int g = 0; g < NG; g++)
@@ -1244,9 +1474,11 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, 1> {
 #pragma unroll
     for (int i = 0; i < NT; i++) {
 #pragma unroll
-      for (int kk = 0; kk < KT; kk++)
+      for (int kk = 0; kk < KT; kk++) {
+        const f32x4 x = R.w.get(i, kk);
 #pragma unroll
-        for (int e = 0; e < 4; e++) s += (double)R.w[i][kk][e] * (double)R.w[i][kk][e];
+        for (int e = 0; e < 4; e++) s += (double)x[e] * (double)x[e];
+      }
     }
 #pragma unroll
     for (int g = 0; g < NG; g++) s += (double)small_penalty(g, q, 1.f) * (double)R.pw[g] * (double)R.pw[g];
