@@ -915,7 +915,7 @@ int kernel_class(const int32_t* dims, int L, int64_t n, int dtype) {
   if (n * (int64_t)d >= 0x7fffffff) return KC_GENERIC;
   if ((uint64_t)n * (uint64_t)d < (1ull << 30)) {  // 32-bit byte offsets into X
     if (small_eligible(dims, L)) return KC_SMALL;
-    if (mid_cut(dims, L).waves) return KC_MID;
+    if (mid_cut(dims, L, 0).waves) return KC_MID;
     // (every shape it holds: one model of 128-128 on 569 x 30 takes 14.7 us a step against 64 at one row, 100 against 220
     // at full batches, 200 models x 5 folds of 16-16-16 at 64 rows 0.52 ms against 2.5)
     if (deep_cut(dims, L).waves) return KC_DEEP;
@@ -990,7 +990,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     const int n_sub = (int)pl.sub.size();
     for (int i = 0; i < n_sub; i++) {
       SubPlan& sp = pl.sub[last];
-      if (sp.kc == kc && sp.cut.nt == cut.nt && sp.cut.waves == cut.waves) return sp;
+      if (sp.kc == kc && sp.cut.nt == cut.nt && sp.cut.co == cut.co && sp.cut.waves == cut.waves) return sp;
       last = last + 1 < n_sub ? last + 1 : 0;
     }
     SubPlan sp;
@@ -1021,7 +1021,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     int k = kernel_class(dims, L, n, dtype);
     const SmallCut full = k == KC_SMALL ? full_cut(dims, L, n, h.batch_size) : SmallCut{0, 0, 0, 0};
     if (full.waves) k = KC_FULL;  // (a form of the small kernel for models that take all rows at once)
-    const SmallCut cut = k == KC_FULL ? full : k == KC_SMALL ? small_cut(dims) : (k == KC_MID ? mid_cut(dims, L) : (k == KC_DEEP ? deep_cut(dims, L) : SmallCut{0, 0, 0, 0}));
+    const SmallCut cut = k == KC_FULL ? full : k == KC_SMALL ? small_cut(dims) : (k == KC_MID ? mid_cut(dims, L, h.batch_size) : (k == KC_DEEP ? deep_cut(dims, L) : SmallCut{0, 0, 0, 0}));
     SubPlan& sp = launch_of(k, cut);
     uint64_t slot_bytes = 0;
     uint32_t lds_bytes = 0;
@@ -1457,7 +1457,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
       fn = full_kernel(sp.cut.kt, sp.cut.nt, sp.cut.co, sp.cut.waves);
       threads = 64 * sp.cut.waves;
     } else if (k == KC_MID) {
-      fn = mid_kernel(sp.cut.kt, sp.cut.nt, sp.cut.waves);
+      fn = mid_kernel(sp.cut.kt, sp.cut.nt, sp.cut.waves, sp.cut.co);
       threads = 64 * sp.cut.waves;
     } else if (k == KC_DEEP) {
       fn = sp.cut.nt == 2 ? deep_kernel2(sp.cut.kt, sp.cut.waves) : deep_kernel3(sp.cut.kt, sp.cut.waves);

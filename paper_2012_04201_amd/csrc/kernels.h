@@ -11,7 +11,7 @@ BBO_HIDDEN const void* small_kernel2(int nt, int waves, int co);
 BBO_HIDDEN const void* small_kernel3(int nt, int waves, int co);
 BBO_HIDDEN const void* small_kernel4(int nt, int waves, int co);
 BBO_HIDDEN const void* full_kernel(int kt, int nt, int co, int waves);  // k tiles of the input layer, unit tiles, outputs, waves
-BBO_HIDDEN const void* mid_kernel(int kt, int nt, int waves);  // k tiles of the input layer, unit tiles per wave, waves
+BBO_HIDDEN const void* mid_kernel(int kt, int nt, int waves, bool split);  // k tiles of the input layer, unit tiles per wave, waves, products
 BBO_HIDDEN const void* deep_kernel2(int kt, int waves);         // k tiles of the input layer, waves; two hidden layers
 BBO_HIDDEN const void* deep_kernel3(int kt, int waves);         // three
 BBO_HIDDEN const void* linear_lds_kernel(int dd, int co);      // padded inputs and bias, outputs

@@ -65,30 +65,40 @@ struct MItem {
   MLay y;
 };
 
-// How a model is cut, by shape alone (a suggestion's scores may not depend on its companions); waves == 0: not a shape
+// Input-layer products in split bfloat16 (see SmPlanes)?  With eight waves and two to five input tiles (six and more leave no
+// LDS for two buffers of planes); with two unit tiles a wave the weights' planes push the moments out of the registers and an
+// update takes 8000 cycles instead of 4500, which pays from 64 rows a step on.  us a call with fp32 products and split, 900
+// rows, 3 epochs: 64-100-10, 200 suggestions, 32 and 160 rows a step 1930 and 1750, 1458 and 1219; 64-200-10 3050 and 3586,
+// 2285 and 2101.  (Four waves: 64-64-10, 32 rows 1555 and 1566.)
+__host__ __device__ constexpr bool md_splittable(int kt, int nt, int waves) {
+  return waves == 8 && kt >= 2 && kt <= 5 && kt * nt <= 8;
+}
+// How a model is cut, by shape and batch size alone (a suggestion's scores may not depend on its companions); waves == 0: not a shape
 // of this kernel.  One tile a wave while eight waves reach (more models a CU with four), else two: one tile leaves the
 // registers for everything, and eight waves of one tile beat four of two by a quarter even with the chip full (64-100-10,
 // 1000 models: 3.2 ms against 3.9).  Beyond kt * nt = 12 the weights and gradients alone overflow the registers; close to
 // it they crowd others out: by the compiler's report <5,2,8> spills 53 vector registers and <6,2,8> 261, <3,2,8> and
 // <4,2,8> 18, the others 3 at most.
-__host__ inline SmallCut mid_cut(const int32_t* dims, int L) {
+__host__ inline SmallCut mid_cut(const int32_t* dims, int L, int32_t batch_size) {
   SmallCut m = {0, 0, 0, 0};
   if (L != 2 || dims[0] > 127 || dims[1] > 256 || dims[2] > 16) return m;
   const int nut = rup(dims[1], 16) / 16, waves = nut <= 4 ? 4 : 8;
   m.kt = rup(dims[0], 16) / 16;
   m.nt = (nut + waves - 1) / waves;
   m.waves = m.kt * m.nt <= 12 ? waves : 0;
+  // (co: split products)
+  m.co = md_splittable(m.kt, m.nt, waves) && (m.nt == 1 || batch_size <= 0 || batch_size > SM_RC) ? 1 : 0;
   return m;
 }
 __host__ __device__ constexpr int md_regs(int kt, int nt) { return nt * (4 * kt + 1 + 4) + 1; }
 // Tiles of a wave whose hidden moments live in registers; the others' stay in global memory (the slot) and are read and
 // written once per step, when the activations' registers are free.
-__host__ __device__ constexpr int md_near(int kt, int nt) {
-  return nt == 1 ? (kt <= 6 ? 1 : 0) : (kt <= 3 ? 2 : (kt == 4 ? 1 : 0));
+__host__ __device__ constexpr int md_near(int kt, int nt, bool split) {
+  return nt == 1 ? (kt <= 6 ? 1 : 0) : (split ? (kt <= 2 ? 2 : (kt == 3 ? 1 : 0)) : (kt <= 3 ? 2 : (kt == 4 ? 1 : 0)));
 }
-__host__ __device__ constexpr uint32_t md_fixed_lds(int kt, int nt, int waves) {
-  // partial outputs, deltas, and per wave: the patch, the moments of w2, the bias moments
-  return pipe_lds(kt, 2, false) + (waves * SM_RC * MD_RS + SM_RC * MD_RS + waves * (16 * MD_RS + nt * 2 * 256 + (nt + 1) * 32)) * 4;
+__host__ __device__ constexpr uint32_t md_fixed_lds(int kt, int nt, int waves, bool split) {
+  // partial outputs, deltas, and per wave: the moments of w2, the bias moments
+  return pipe_lds(kt, 2, split) + (waves * SM_RC * MD_RS + SM_RC * MD_RS + waves * (nt * 2 * 256 + (nt + 1) * 32)) * 4;
 }
 __host__ inline void make_mlay(MLay& y, const int32_t* dims, int64_t n, const SmallCut& m) {
   const int d = dims[0];
@@ -99,8 +109,8 @@ __host__ inline void make_mlay(MLay& y, const int32_t* dims, int64_t n, const Sm
   y.cb[0] = d * y.h;
   y.cw[1] = y.cb[0] + y.h;
   y.cb[1] = y.cw[1] + y.h * y.c;
-  make_pipelay(y.p, d, y.cb[1] + y.c, n, md_fixed_lds(m.kt, m.nt, m.waves));
-  y.slot_floats = (uint32_t)(m.waves * (md_regs(m.kt, m.nt) + (m.nt - md_near(m.kt, m.nt)) * 8 * m.kt) * 64);
+  make_pipelay(y.p, d, y.cb[1] + y.c, n, md_fixed_lds(m.kt, m.nt, m.waves, m.co));
+  y.slot_floats = (uint32_t)(m.waves * (md_regs(m.kt, m.nt) + (m.nt - md_near(m.kt, m.nt, m.co)) * 8 * m.kt) * 64);
   y.lds_total = y.p.total;
 }
 // workgroups a CU holds: registers are budgeted for two waves per SIMD
@@ -110,9 +120,9 @@ __host__ inline int md_per_cu(const SmallCut& m, uint32_t lds_bytes) {
   return n < 1 ? 1 : n;
 }
 
-template <int KT, int NT, int W>
-struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
-  typedef RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> Base;
+template <int KT, int NT, int W, bool SPLIT>
+struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
+  typedef RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> Base;
   using Base::Base;
   using Base::f;
   using Base::init_value;
@@ -133,9 +143,11 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
   }
   __device__ __forceinline__ double total(double v) const { return block_sum(v, red); }
 
-  static constexpr int NEAR = md_near(KT, NT), NREGM = NEAR ? NEAR : 1;
+  static constexpr int NEAR = md_near(KT, NT, SPLIT), NREGM = NEAR ? NEAR : 1;
+  static constexpr int KB = sm_blocks(KT);
   struct State {
-    f32x4 w[NT][KT], m[NREGM][KT], v[NREGM][KT], g[NT][KT];  // hidden layer: lane (unit li, columns 16 kk + 4q + e)
+    HiddenWeights<KT, NT, SPLIT> w;
+    f32x4 m[NREGM][KT], v[NREGM][KT], g[NT][KT];       // hidden layer: lane (unit li, columns 16 kk + 4q + e)
     float bw[NT], bg[NT];                              // its bias
     f32x4 w2[NT], g2[NT];                              // output layer: lane (output li, units 4q + e of the tile)
     float ow, og;                                      // output bias: output li, alike in every q and wave
@@ -143,15 +155,15 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
   struct Acts {
     f32x4 a[NT][4];  // lane (unit li, rows 16 r + 4q..+3)
   };
-  static constexpr int O_ZP = Base::O_OWN, O_D3 = O_ZP + W * SM_RC * MD_RS, O_PATCH = O_D3 + SM_RC * MD_RS,
-                       O_M2 = O_PATCH + W * 16 * MD_RS, O_MOM = O_M2 + W * NT * 512, O_TOP = O_MOM + W * (NT + 1) * 32;
-  static_assert(O_TOP * 4 == md_fixed_lds(KT, NT, W), "LDS layout");
+  static constexpr int O_ZP = Base::O_OWN, O_D3 = O_ZP + W * SM_RC * MD_RS, O_M2 = O_D3 + SM_RC * MD_RS, O_MOM = O_M2 + W * NT * 512, O_TOP = O_MOM + W * (NT + 1) * 32;
+  static_assert(O_TOP * 4 == md_fixed_lds(KT, NT, W, SPLIT), "LDS layout");
   __device__ __forceinline__ bool has(int i, int w) const { return i + 1 < NT || w + i * W < nut; }
   // A 16 x 16 block of four values a lane (lane: column li, rows 4q..4q+3) turned over: lane li gets row li, columns
-  // 4q..4q+3.  The wave's LDS accesses stay in order, so that one patch serves every block.
-  __device__ __forceinline__ f32x4 turn(const f32x4& v) const {
+  // 4q..4q+3.  The patch is where the wave's partial outputs of row tile r go once it is done: the wave's LDS accesses
+  // stay in order, and nobody else reads them between the outputs of a chunk and the first barrier of the next.
+  __device__ __forceinline__ f32x4 turn(const f32x4& v, int r) const {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
-    float* p = f(O_PATCH) + wave() * (16 * MD_RS);
+    float* p = f(O_ZP) + (wave() * SM_RC + r * 16) * MD_RS;
 #pragma unroll
     for (int e = 0; e < 4; e++) p[(4 * q + e) * MD_RS + li] = v[e];
     __builtin_amdgcn_wave_barrier();
@@ -209,7 +221,23 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
     return (GlobalF32x4*)(slot + W * (NREG * 64) + (((wave() * (NT - NEAR) + i - NEAR) * 2 + which) * KT + kk) * 256) +
            (threadIdx.x & 63);
   }
-  // fn(index, reference) for the hidden weights
+  // fn(index, reference) for the hidden weights or one of their moments
+  template <class F>
+  __device__ __forceinline__ static void each_hidden(HiddenWeights<KT, NT, SPLIT>& w, F fn) {
+#pragma unroll
+    for (int i = 0; i < NT; i++)
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++) {
+        f32x4 x = w.get(i, kk);
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          float y_ = x[e];
+          fn(i * PER + 4 * kk + e, y_);
+          x[e] = y_;
+        }
+        w.put(i, kk, x);
+      }
+  }
   template <int N, class F>
   __device__ __forceinline__ static void each_hidden(f32x4 (&w)[N][KT], F fn) {
 #pragma unroll
@@ -298,29 +326,37 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
 
   // ---- forward ---------------------------------------------------------------
   template <bool ALL>
-  __device__ __forceinline__ void forward_tile(const State& R, const float* s, int r, f32x4 (&acc)[NT][4]) const {
+  __device__ __forceinline__ void forward_tile(const State& R, int b, int r, f32x4 (&acc)[NT][4]) const {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
-    const float* a_ = s + (r * 16 + li) * LDW + 4 * q;
-    f32x4 a[KT];
+    f32x4 c[NT];
 #pragma unroll
-    for (int kk = 0; kk < KT; kk++) a[kk] = *(const f32x4*)(a_ + kk * 16);
+    for (int i = 0; i < NT; i++) c[i] = f32x4{R.bw[i], R.bw[i], R.bw[i], R.bw[i]};
+    if constexpr (SPLIT) {
 #pragma unroll
-    for (int i = 0; i < NT; i++) acc[i][r] = f32x4{R.bw[i], R.bw[i], R.bw[i], R.bw[i]};
+      for (int kb = 0; kb < KB; kb++) sm_products<NT - (ALL ? 0 : 1)>(Base::by_row(Base::planes(b), r, kb), R.w.p[kb], c);
+    } else {
+      const float* a_ = xs(b) + (r * 16 + li) * LDW + 4 * q;
+      f32x4 a[KT];
 #pragma unroll
-    for (int kk = 0; kk < KT; kk++)
+      for (int kk = 0; kk < KT; kk++) a[kk] = *(const f32x4*)(a_ + kk * 16);
 #pragma unroll
-      for (int e = 0; e < 4; e++) {
+      for (int kk = 0; kk < KT; kk++)
 #pragma unroll
-        for (int i = 0; i < NT; i++)
-          if (i + 1 < NT || ALL) acc[i][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], R.w[i][kk][e], acc[i][r], 0, 0, 0);
-      }
+        for (int e = 0; e < 4; e++) {
+#pragma unroll
+          for (int i = 0; i < NT; i++)
+            if (i + 1 < NT || ALL) c[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], R.w.w[i][kk][e], c[i], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NT; i++) acc[i][r] = c[i];
     f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < NT; i++)
       if (i + 1 < NT || ALL) {
 #pragma unroll
-        for (int e = 0; e < 4; e++) acc[i][r][e] = sm_relu(acc[i][r][e]);
-        const f32x4 ar = turn(acc[i][r]);  // row li, units 4q..4q+3
+        for (int e = 0; e < 4; e++) acc[i][r][e] = SPLIT ? sm_relu_nan(acc[i][r][e]) : sm_relu(acc[i][r][e]);
+        const f32x4 ar = turn(acc[i][r], r);  // row li, units 4q..4q+3
 #pragma unroll
         for (int e = 0; e < 4; e++) z = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[e], R.w2[i][e], z, 0, 0, 0);
       }
@@ -329,19 +365,19 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
     for (int e = 0; e < 4; e++) zp[e * MD_RS] = z[e];
   }
   template <bool ALL>
-  __device__ __forceinline__ void forward_chunk(const State& R, const float* s, int nrt, f32x4 (&acc)[NT][4]) const {
+  __device__ __forceinline__ void forward_chunk(const State& R, int b, int nrt, f32x4 (&acc)[NT][4]) const {
     // (a ragged chunk leaves the loop early: every row tile has its own registers)
 #pragma unroll
     for (int r = 0; r < 4; r++) {
       if (r >= nrt) break;
-      forward_tile<ALL>(R, s, r, acc);
+      forward_tile<ALL>(R, b, r, acc);
     }
   }
   __device__ __forceinline__ void forward(const State& R, int b, int, int nrt, Acts& A) const {
     if (has(NT - 1, wave()))
-      forward_chunk<true>(R, xs(b), nrt, A.a);
+      forward_chunk<true>(R, b, nrt, A.a);
     else
-      forward_chunk<false>(R, xs(b), nrt, A.a);
+      forward_chunk<false>(R, b, nrt, A.a);
   }
 
   // ---- outputs: group g of four rows belongs to wave g mod W; lane (output li, row 4g + q) ----
@@ -401,20 +437,15 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
   }
 
   // ---- backward ----------------------------------------------------------------
+  // the hidden deltas of a row tile, and its share of the output layer's gradient
   template <bool ALL>
-  __device__ __forceinline__ void backward_tile(State& R, const float* s, int r, const f32x4 (&acc)[NT][4], const f32x4 (&wt)[NT]) const {
+  __device__ __forceinline__ void deltas(State& R, int r, const f32x4 (&acc)[NT][4], const f32x4 (&wt)[NT], f32x4 (&dh)[NT]) const {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
     const float* d3 = f(O_D3);
     const f32x4 da = *(const f32x4*)(d3 + (r * 16 + li) * MD_RS + 4 * q);  // A: row li, outputs 4q..4q+3
-    float db[4], a[KT][4];
+    float db[4];
 #pragma unroll
     for (int e = 0; e < 4; e++) db[e] = d3[(r * 16 + 4 * q + e) * MD_RS + li];  // B: row 4q + e, output li
-    const float* a_ = s + (r * 16 + 4 * q) * LDW + li;
-#pragma unroll
-    for (int kk = 0; kk < KT; kk++)
-#pragma unroll
-      for (int e = 0; e < 4; e++) a[kk][e] = a_[e * LDW + kk * 16];
-    f32x4 dh[NT];
 #pragma unroll
     for (int i = 0; i < NT; i++) dh[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -437,6 +468,19 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
           R.bg[i] += x;
         }
       }
+  }
+  // the hidden weights' gradient of a row tile ...
+  template <bool ALL>
+  __device__ __forceinline__ void backward_tile(State& R, const float* s, int r, const f32x4 (&acc)[NT][4], const f32x4 (&wt)[NT]) const {
+    const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
+    float a[KT][4];
+    const float* a_ = s + (r * 16 + 4 * q) * LDW + li;
+#pragma unroll
+    for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) a[kk][e] = a_[e * LDW + kk * 16];
+    f32x4 dh[NT];
+    deltas<ALL>(R, r, acc, wt, dh);
 #pragma unroll
     for (int kk = 0; kk < KT; kk++)
 #pragma unroll
@@ -446,22 +490,66 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
           if (i + 1 < NT || ALL) R.g[i][kk] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], dh[i][e], R.g[i][kk], 0, 0, 0);
       }
   }
+  // ... or of two, r and r + 1 (BOTH), which fill the 32 contracted rows of a split product
+  template <bool ALL, bool BOTH>
+  __device__ __forceinline__ void backward_pair(State& R, const char* x, int r, const f32x4 (&acc)[NT][4], const f32x4 (&wt)[NT]) const {
+    constexpr int TILES = NT - (ALL ? 0 : 1);
+    SmPlanes dp[NT];
+#pragma unroll
+    for (int t = 0; t < 2; t++) {
+      f32x4 dh[NT];
+      if (t == 0 || BOTH) deltas<ALL>(R, r + t, acc, wt, dh);
+#pragma unroll
+      for (int i = 0; i < TILES; i++)
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+          uint32_t h = 0u, m = 0u, l = 0u;
+          if (t == 0 || BOTH) sm_split2(dh[i][2 * e], dh[i][2 * e + 1], h, m, l);
+          dp[i].h[2 * t + e] = h;
+          dp[i].m[2 * t + e] = m;
+          dp[i].l[2 * t + e] = l;
+        }
+    }
+    if constexpr (TILES > 0) {
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++) {
+        f32x4 c[NT];
+#pragma unroll
+        for (int i = 0; i < TILES; i++) c[i] = R.g[i][kk];
+        sm_products<TILES>(Base::template by_column<BOTH>(x, r, kk), dp, c);
+#pragma unroll
+        for (int i = 0; i < TILES; i++) R.g[i][kk] = c[i];
+      }
+    }
+  }
   template <bool ALL>
-  __device__ __forceinline__ void backward_chunk(State& R, const float* s, int nrt, const f32x4 (&acc)[NT][4]) const {
+  __device__ __forceinline__ void backward_chunk(State& R, int b, int nrt, const f32x4 (&acc)[NT][4]) const {
     f32x4 wt[NT];  // unit li, outputs 4q..4q+3
 #pragma unroll
-    for (int i = 0; i < NT; i++) wt[i] = turn(R.w2[i]);
+    for (int i = 0; i < NT; i++) wt[i] = turn(R.w2[i], 0);
+    if constexpr (SPLIT) {
+      const char* x = Base::planes(b);
 #pragma unroll
-    for (int r = 0; r < 4; r++) {
-      if (r >= nrt) break;
-      backward_tile<ALL>(R, s, r, acc, wt);
+      for (int r = 0; r < 4; r += 2) {
+        if (r >= nrt) break;
+        if (r + 1 < nrt)
+          backward_pair<ALL, true>(R, x, r, acc, wt);
+        else
+          backward_pair<ALL, false>(R, x, r, acc, wt);
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        if (r >= nrt) break;
+        backward_tile<ALL>(R, xs(b), r, acc, wt);
+      }
     }
   }
   __device__ __forceinline__ void backward(State& R, int b, int nrt, const Acts& A) const {
     if (has(NT - 1, wave()))
-      backward_chunk<true>(R, xs(b), nrt, A.a);
+      backward_chunk<true>(R, b, nrt, A.a);
     else
-      backward_chunk<false>(R, xs(b), nrt, A.a);
+      backward_chunk<false>(R, b, nrt, A.a);
   }
 
   // ---- optimizer step (pads: see k_train_small) ----------------------------------
@@ -502,17 +590,20 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
     for (int i = 0; i < NT; i++)
       if (has(i, w_)) {
 #pragma unroll
-        for (int kk = 0; kk < KT; kk++)
+        for (int kk = 0; kk < KT; kk++) {
+          f32x4& mm = i < NEAR ? R.m[i < NEAR ? i : 0][kk] : mf[i < NEAR ? 0 : i - NEAR][kk];
+          f32x4& vv = i < NEAR ? R.v[i < NEAR ? i : 0][kk] : vf[i < NEAR ? 0 : i - NEAR][kk];
+          f32x4 x = R.w.get(i, kk);
 #pragma unroll
           for (int e = 0; e < 4; e++) {
-            f32x4& mm = i < NEAR ? R.m[i < NEAR ? i : 0][kk] : mf[i < NEAR ? 0 : i - NEAR][kk];
-            f32x4& vv = i < NEAR ? R.v[i < NEAR ? i : 0][kk] : vf[i < NEAR ? 0 : i - NEAR][kk];
-            float wr = R.w[i][kk][e], mr = mm[e], vr = vv[e];
+            float wr = x[e], mr = mm[e], vr = vv[e];
             opt_update(o, R.g[i][kk][e] + o.am * wr, wr, mr, vr);
-            R.w[i][kk][e] = wr;
+            x[e] = wr;
             mm[e] = mr;
             vv[e] = vr;
           }
+          R.w.put(i, kk, x);
+        }
         if (i >= NEAR) {
 #pragma unroll
           for (int kk = 0; kk < KT; kk++) {
@@ -546,16 +637,19 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
       const int t0 = (w_ + i * W) * 16;
       const bool unit = t0 + li < y.h;
 #pragma unroll
-      for (int kk = 0; kk < KT; kk++)
+      for (int kk = 0; kk < KT; kk++) {
+        f32x4 x = R.w.get(i, kk);
 #pragma unroll
         for (int e = 0; e < 4; e++)
           if (!unit || kk * 16 + 4 * q + e >= y.p.d) {
-            R.w[i][kk][e] = 0.f;
+            x[e] = 0.f;
             if (i < NEAR)
               R.m[i < NEAR ? i : 0][kk][e] = R.v[i < NEAR ? i : 0][kk][e] = 0.f;
             else
               (*far(i, 0, kk))[e] = (*far(i, 1, kk))[e] = 0.f;
           }
+        R.w.put(i, kk, x);
+      }
       if (!unit) {
         R.bw[i] = 0.f;
         *mom(i, 0) = *mom(i, 1) = 0.f;
@@ -581,12 +675,14 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
     for (int i = 0; i < NT; i++) {
       const int t0 = (w_ + i * W) * 16, j = t0 + li;
 #pragma unroll
-      for (int kk = 0; kk < KT; kk++)
+      for (int kk = 0; kk < KT; kk++) {
+        const f32x4 x = R.w.get(i, kk);
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           const int k = kk * 16 + 4 * q + e;
-          if (j < h && k < d) out[y.cw[0] + k * h + j] = GRAD ? R.g[i][kk][e] + am * R.w[i][kk][e] : R.w[i][kk][e];
+          if (j < h && k < d) out[y.cw[0] + k * h + j] = GRAD ? R.g[i][kk][e] + am * x[e] : x[e];
         }
+      }
       const float b = GRAD ? sm_rowsum(R.bg[i]) : R.bw[i];
       if (j < h && q == 0) out[y.cb[0] + j] = b;
 #pragma unroll
@@ -603,9 +699,11 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
 #pragma unroll
     for (int i = 0; i < NT; i++) {
 #pragma unroll
-      for (int kk = 0; kk < KT; kk++)
+      for (int kk = 0; kk < KT; kk++) {
+        const f32x4 x = R.w.get(i, kk);
 #pragma unroll
-        for (int e = 0; e < 4; e++) s += (double)R.w[i][kk][e] * (double)R.w[i][kk][e];
+        for (int e = 0; e < 4; e++) s += (double)x[e] * (double)x[e];
+      }
 #pragma unroll
       for (int e = 0; e < 4; e++) s += (double)R.w2[i][e] * (double)R.w2[i][e];
     }
@@ -613,9 +711,8 @@ struct Mid : RowPipe<Mid<KT, NT, W>, MLay, KT, W, 2, false> {
   }
 };
 
-template <int KT, int NT, int W>
-__global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_waves_per_eu(2, 2)))
-void k_train_mid(const TrainParams P) {
+template <int KT, int NT, int W, bool SPLIT>
+__device__ __forceinline__ void mid_models(const TrainParams& P) {
   extern __shared__ __align__(16) char smem[];
   __shared__ int s_item;
   __shared__ double red[W], trace_stash[2];
@@ -626,10 +723,22 @@ void k_train_mid(const TrainParams P) {
     const int item = __builtin_amdgcn_readfirstlane(s_item);
     if (item >= P.n_items) break;
     const __attribute__((address_space(4))) MItem* mi = (const __attribute__((address_space(4))) MItem*)P.items + item / P.n_folds;
-    Mid<KT, NT, W> T(P, mi->d, mi->y, smem, (float*)(P.slots + (uint64_t)blockIdx.x * P.slot_bytes), red, trace_stash,
-                       item % P.n_folds);
+    Mid<KT, NT, W, SPLIT> T(P, mi->d, mi->y, smem, (float*)(P.slots + (uint64_t)blockIdx.x * P.slot_bytes), red, trace_stash,
+                            item % P.n_folds);
     T.run();
   }
+}
+// the products as they are with one unit tile a wave, and up to 64 rows a step with two ...
+template <int KT, int NT, int W>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_waves_per_eu(2, 2)))
+void k_train_mid(const TrainParams P) {
+  mid_models<KT, NT, W, NT == 1 && md_splittable(KT, NT, W)>(P);
+}
+// ... and split with two
+template <int KT>
+__global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
+void k_train_mid2_split(const TrainParams P) {
+  mid_models<KT, 2, 8, true>(P);
 }
 
 }  // namespace

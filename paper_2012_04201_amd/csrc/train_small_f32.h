@@ -142,12 +142,13 @@ __host__ inline void make_pipelay(PipeLay& y, int d, int P, int64_t n, uint32_t 
   while ((1 << (2 * hb)) < n) hb++;
   const uint32_t ft = (uint32_t)((4 << hb) * 2), net = n <= SM_NET ? 2u << (2 * hb) : 0u;
   const uint32_t tab = (uint32_t)(2 * (n + SM_RC));  // (a chunk may read its row ids past the end: spare entries)
-  y.tabled = n >= 1 && n <= 0xffff && o + ft + net + 2 * tab <= SM_LDS_LIMIT;
-  y.netted = net > 0;  // (sized for n rows; the fold's own network is never wider)
+  const uint32_t need = o + ft + 2 * tab + 64;         // (rounded up to 16 bytes each)
+  y.tabled = n >= 1 && n <= 0xffff && need <= SM_LDS_LIMIT;
+  y.netted = net > 0 && need + net <= SM_LDS_LIMIT;  // (sized for n rows; the fold's own network is never wider)
   y.o_ft = y.o_net = y.o_sl = y.o_ep = o;
   if (y.tabled) {
     y.o_ft = take(ft);
-    y.o_net = take(net);
+    y.o_net = take(y.netted ? net : 0u);
     y.o_sl = take(tab);
     y.o_ep = take(tab);
   }
