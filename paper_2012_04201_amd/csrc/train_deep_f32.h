@@ -149,8 +149,8 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
     return Places{pin(wave() * per_wave * 64), pin(region - (W - wave()) * 64), pin(region), pin(region * (NEAR ? 1 : 3)),
                   pin(T[1]), pin(T[2])};
   }
-  // block n in the slot: set 0 the parameters, 1 and 2 the moments
-  __device__ __forceinline__ GlobalF32x4* kept(const Places& z, int set, int n) const {
+  // block n in a set of the slot, in 16-byte vectors
+  __device__ __forceinline__ static int place(const Places& z, int n) {
     int at = z.biases;
     if (n < B_BIAS) {
       const int l = n < KT ? 0 : 1 + (n - KT) / W;
@@ -158,7 +158,11 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
       if (n == B_OUT) at = KT + z.t1 + (H == 3 ? z.t2 : 0);
       at = z.own + at * 64;
     }
-    return (GlobalF32x4*)slot + set * z.region + at + (tid() & 63);
+    return at;
+  }
+  // block n: set 0 the parameters, 1 and 2 the moments
+  __device__ __forceinline__ GlobalF32x4* kept(const Places& z, int set, int n) const {
+    return (GlobalF32x4*)slot + set * z.region + place(z, n) + (tid() & 63);
   }
   // transposed weights of layer l (1..H-1): lane (unit li of in tile i, units 4q + e of out tile o)
   __device__ __forceinline__ GlobalF32x4* wt(const Places& z, int l, int i, int o) const {
@@ -551,12 +555,20 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
     o.adam = ADAM;
     const bool pads = ADAM && o.eps == 0.f;
     const Places z = places();
+    // Moments in the slot are fetched AHEAD blocks early.  A block that the wave does not have is sent out of the
+    // descriptor's range (zeros come back, nothing is written) instead of branched around: with the same memory operations
+    // on every path the waits are for the block that is needed, not for all that is in flight.
     f32x4 mf[NEAR ? 1 : NB], vf[NEAR ? 1 : NB];
+    const __amdgpu_buffer_rsrc_t mem = __builtin_amdgcn_make_buffer_rsrc(slot, 0, (uint32_t)z.region * 48u, 0x00020000);
+    const uint32_t lane16 = (tid() & 63) * 16;
+    auto where = [&](int n) __attribute__((always_inline)) { return used(n) ? lane16 : 0x80000000u; };
     auto fetch = [&](int n) __attribute__((always_inline)) {
       if constexpr (!NEAR)
-        if (n < NB && used(n)) {
-          mf[n] = *kept(z, 1, n);
-          if (ADAM) vf[n] = *kept(z, 2, n);
+        if (n < NB) {
+          const uint32_t vo = where(n);
+          const int at = place(z, n) * 16;
+          mf[n] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(mem, vo, at + z.region * 16, 0));
+          if (ADAM) vf[n] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(mem, vo, at + z.region * 32, 0));
         }
     };
     constexpr int AHEAD = 4;  // blocks of moments in flight
@@ -567,30 +579,34 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
 #pragma unroll
     for (int n = 0; n < NB; n++) {
       fetch(n + AHEAD);
-      if (!used(n)) continue;
-      const float am = n == B_BIAS ? 0.f : o.am;
       f32x4& mm = NEAR ? R.m[NEAR ? n : 0] : mf[NEAR ? 0 : n];
       f32x4& vv = NEAR ? R.v[NEAR ? n : 0] : vf[NEAR ? 0 : n];
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        if (n == B_BIAS && e > H) continue;
-        float wr = R.w[n][e], mr = mm[e], vr = vv[e];
-        opt_update(o, n == B_BIAS ? R.g[n][e] : R.g[n][e] + am * wr, wr, mr, vr);
-        R.w[n][e] = wr;
-        mm[e] = mr;
-        vv[e] = vr;
-      }
-      if (pads) {
+      if (used(n)) {
+        const float am = n == B_BIAS ? 0.f : o.am;
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-          int l, i;
-          bool isb;
-          if (packed(n, e, l, i, isb) < 0) R.w[n][e] = mm[e] = vv[e] = 0.f;
+          if (n == B_BIAS && e > H) continue;
+          float wr = R.w[n][e], mr = mm[e], vr = vv[e];
+          opt_update(o, n == B_BIAS ? R.g[n][e] : R.g[n][e] + am * wr, wr, mr, vr);
+          R.w[n][e] = wr;
+          mm[e] = mr;
+          vv[e] = vr;
+        }
+        if (pads) {
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            int l, i;
+            bool isb;
+            if (packed(n, e, l, i, isb) < 0) R.w[n][e] = mm[e] = vv[e] = 0.f;
+          }
         }
       }
       if constexpr (!NEAR) {
-        *kept(z, 1, n) = mm;
-        if (ADAM) *kept(z, 2, n) = vv;
+        const uint32_t vo = where(n);
+        const int at = place(z, n) * 16;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, mm), mem, vo, at + z.region * 16, 0);
+        if (ADAM) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, vv), mem, vo, at + z.region * 32, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     publish(R);
