@@ -1,23 +1,24 @@
 // Training / scoring kernel for fp32 models with two or three hidden layers (up to 64 inputs, hidden widths up to 128, up
 // to 16 outputs) on the row pipeline of train_small_f32.h.
 //
-// One workgroup trains one model.  Wave w owns unit tile w (16 units) of every level: its weights and their gradients
-// stay in registers for the whole run (as far as these reach: dp_near()), as blocks of four values a lane in the layout the MFMA (16x16x4 fp32) both takes
-// them in and leaves their gradient in (lane: unit li, columns 4q..4q+3 of a k tile).  The levels of a chunk of 64 rows
+// One workgroup trains one model.  Wave w owns unit tile w (16 units) of every level: its gradients, and its weights where
+// they fit (dp_stream()), stay in registers for the whole run, as blocks of four values a lane in the layout the MFMA
+// (16x16x4 fp32) both takes them in and leaves their gradient in (lane: unit li, columns 4q..4q+3 of a k tile).  The levels of a chunk of 64 rows
 // lie in LDS, row-major, because every wave needs all of them; a level's deltas are written over its activations.
 //
 //   forward   level l+1 [row][unit] = level l . W: operand rows from LDS, weights from registers, ReLU, back to LDS
 //   outputs   wave r takes row tile r: z = last level . W_out (its blocks gathered in LDS), softmax / loss / delta with
 //             reductions over the 16 lanes of a row
-//   backward  the data gradient contracts over a level's units, which are spread over the waves: the weights are kept a
-//             second time, transposed tile by tile, in global memory (they stay in L2), and fetched once per chunk; the
-//             weight gradient takes a level's activations from LDS and the wave's own deltas from registers
+//   backward  the data gradient contracts over a level's units, which are spread over the waves: their weights are in global
+//             memory too (they stay in L2), in an order that can be read along either side of a tile, and are fetched
+//             once per chunk; the weight gradient takes a level's activations from LDS and the wave's own deltas from registers
 //   update    Adam / SGD; the moments in registers where they fit, else in global memory, touched once per step
 //
 // Four waves up to 64 units (two models a CU), eight up to 128.  Barriers per chunk: 6 with two hidden layers, 9 with
 // three.  What bounds it: two waves per SIMD in step with each other, the waves past a narrow level's tiles idle, and the
 // chain of a chunk's phases; the kernel for any shape, which these models ran on before, kept every operand in global
-// memory.  256 suggestions x 5 folds on 569 x 30, one to three layers of 16..128 units, 10 epochs: 25.4 -> 9.4 ms a call.
+// memory.  256 suggestions x 5 folds on 569 x 30, one to three layers of 16..128 units, 10 epochs: 25.4 -> 9.4 ms a call, and
+// 8.2 with the moments' branches gone and the weights of the widest cuts in global memory alone.
 #pragma once
 #include <type_traits>
 
@@ -53,9 +54,14 @@ __host__ inline SmallCut deep_cut(const int32_t* dims, int L) {
 // Blocks of four values a lane holds: input layer, hidden layers, output layer, biases.
 __host__ __device__ constexpr int dp_blocks(int kt, int h, int waves) { return kt + (h - 1) * waves + 2; }
 // The moments live in registers up to here (with weights and gradients four times the blocks, of 256 registers).  Without
-// them the widest cuts still overflow: by the compiler's report three layers on eight waves spill 59, 117, 151 and 172
-// vector registers at one to four input tiles, every other variant 14 at most.
+// them three layers on eight waves still overflow: dp_stream().
 __host__ __device__ constexpr bool dp_near(int kt, int h, int waves) { return dp_blocks(kt, h, waves) <= 8; }
+// The weights of the hidden layers past the first are in global memory alone (one copy serves the forward products, the
+// data gradient and the update) where weights and gradients would take 152 registers and more: held, they made these cuts
+// spill 59, 117, 151 and 172 vector registers at one to four input tiles; now 4, 6, 25 and 8.  [128, 40, 100] on 50 inputs,
+// batch 24: 500 models a call 4.70 -> 3.29 ms, 20 models 1.73 -> 1.37.  The price is the bandwidth of a full chip, where
+// one wave spilled least: [128, 128, 128] on 20 inputs 5.37 -> 5.77 ms at batch 24 and 2.43 -> 2.31 at 160.
+__host__ __device__ constexpr bool dp_stream(int h, int waves) { return h == 3 && waves == 8; }
 __host__ __device__ constexpr uint32_t dp_fixed_lds(int kt, int h, int waves) {
   // levels, the output layer's blocks, output deltas
   return pipe_lds(kt, 1, false) + (h * SM_RC * (16 * waves + 4) + waves * 256 + SM_RC * MD_RS) * 4;
@@ -113,7 +119,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
   using Base::ys;
   static constexpr int LDW = Base::LDW, LDH = 16 * W + 4;
   static constexpr int NB = dp_blocks(KT, H, W), B_OUT = NB - 2, B_BIAS = NB - 1;
-  static constexpr bool NEAR = dp_near(KT, H, W);
+  static constexpr bool NEAR = dp_near(KT, H, W), STREAM = dp_stream(H, W);
   static constexpr int NM = NEAR ? NB : 1;
   static constexpr int O_LEV = Base::O_OWN, O_WO = O_LEV + H * SM_RC * LDH, O_D3 = O_WO + W * 256, O_TOP = O_D3 + SM_RC * MD_RS;
   static_assert(O_TOP * 4 == dp_fixed_lds(KT, H, W), "LDS layout");
@@ -133,8 +139,12 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
   // hidden layer (inputs: units of the level below), the output layer (lane: output li, units 4q + e of the wave's
   // tile), the biases (e < H: hidden layer e, unit li; e == H: output li; alike in the four q).
   struct State {
-    f32x4 w[NB], g[NB], m[NM], v[NM];
+    f32x4 w[STREAM ? KT + 2 : NB], g[NB], m[NM], v[NM];
   };
+  __device__ __forceinline__ static constexpr bool hidden(int n) { return n >= KT && n < B_OUT; }
+  // the register block of the weights of block n, which is not streamed
+  __device__ __forceinline__ static constexpr int reg(int n) { return STREAM && n >= KT ? n - B_OUT + KT : n; }
+  __device__ __forceinline__ static constexpr int layer(int n) { return n < KT ? 0 : (n >= B_OUT ? H : 1 + (n - KT) / W); }
   struct Acts {
     uint32_t bits[H];  // ReLU patterns of the wave's units: bit 4 r + e of row 16 r + 4q + e
   };
@@ -143,11 +153,11 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
   // What the addresses in the slot depend on, as values of each phase's own: kept for the whole run, the addresses of all
   // blocks would crowd the scalar registers out into vector registers.
   struct Places {
-    int own, biases, region, turned, t1, t2;
+    int own, biases, region, turned, t1, t2, t3;
   };
   __device__ __forceinline__ Places places() const {
     return Places{pin(wave() * per_wave * 64), pin(region - (W - wave()) * 64), pin(region), pin(region * (NEAR ? 1 : 3)),
-                  pin(T[1]), pin(T[2])};
+                  pin(T[1]), pin(T[2]), pin(T[H])};
   }
   // block n in a set of the slot, in 16-byte vectors
   __device__ __forceinline__ static int place(const Places& z, int n) {
@@ -164,9 +174,33 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
   __device__ __forceinline__ GlobalF32x4* kept(const Places& z, int set, int n) const {
     return (GlobalF32x4*)slot + set * z.region + place(z, n) + (tid() & 63);
   }
-  // transposed weights of layer l (1..H-1): lane (unit li of in tile i, units 4q + e of out tile o)
-  __device__ __forceinline__ GlobalF32x4* wt(const Places& z, int l, int i, int o) const {
-    return (GlobalF32x4*)slot + z.turned + ((l == 2 ? z.t1 * z.t2 : 0) + i * (l == 1 ? z.t2 : T[H]) + o) * 64 + (tid() & 63);
+  // Weights of layer l (1..H-1) from in tile i to out tile o, 256 floats: element e of lane n of the wave that owns them at
+  // 64 e + n, which is a row of 16 out units for each in unit, the rows in the order 0 4 8 12 1 5 ..
+  __device__ __forceinline__ static int turned(const Places& z, int l, int i, int o) {  // in 16-byte vectors
+    return z.turned + ((l == 2 ? z.t1 * z.t2 : 0) + i * (l == 1 ? z.t2 : z.t3) + o) * 64;
+  }
+  __device__ __forceinline__ GlobalF32* wt(const Places& z, int l, int i, int o) const {
+    return (GlobalF32*)((GlobalF32x4*)slot + turned(z, l, i, o)) + (tid() & 63);
+  }
+  // transposed: units 4q.. of the out tile for unit li of the in tile
+  __device__ __forceinline__ f32x4 across(const Places& z, int l, int i, int o) const {
+    const int li = tid() & 15, q = (tid() & 63) >> 4;
+    return ((GlobalF32x4*)slot + turned(z, l, i, o))[((li & 3) * 4 + (li >> 2)) * 4 + q];
+  }
+  __device__ __forceinline__ f32x4 along(const Places& z, int l, int i, int o) const {
+    const GlobalF32* p = wt(z, l, i, o);
+    return f32x4{p[0], p[64], p[128], p[192]};
+  }
+  __device__ __forceinline__ void put(const Places& z, int l, int i, int o, const f32x4& x) const {
+    GlobalF32* p = wt(z, l, i, o);
+#pragma unroll
+    for (int e = 0; e < 4; e++) p[e * 64] = x[e];
+  }
+  // the weights of block n, wherever they are
+  __device__ __forceinline__ f32x4 weights(const State& R, const Places& z, int n) const {
+    if constexpr (STREAM)
+      if (hidden(n)) return used(n) ? along(z, layer(n), (n - KT) % W, wave()) : f32x4{0.f, 0.f, 0.f, 0.f};
+    return R.w[reg(hidden(n) && STREAM ? 0 : n)];
   }
   __device__ __forceinline__ bool used(int n) const {  // block n holds parameters of this wave
     const int w_ = wave();
@@ -227,8 +261,12 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
     const Places z = places();
 #pragma unroll
     for (int n = 0; n < NB; n++) {
-      to[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (used(n)) to[n] = *kept(z, set, n);
+      if (STREAM && hidden(n)) {
+        if (used(n)) put(z, layer(n), (n - KT) % W, wave(), (f32x4)*kept(z, set, n));
+        continue;
+      }
+      to[reg(n)] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (used(n)) to[reg(n)] = *kept(z, set, n);
     }
   }
   __device__ __forceinline__ void load(State& R, const float* st) const {
@@ -255,7 +293,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
     const Places z = places();
 #pragma unroll
     for (int n = 0; n < NB; n++)
-      if (used(n)) *kept(z, 0, n) = R.w[n];
+      if (used(n)) *kept(z, 0, n) = weights(R, z, n);
   }
   __device__ __forceinline__ void restore_best(State& R) const {
     take(0, R.w);
@@ -266,28 +304,23 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
 #pragma unroll
     for (int n = 0; n < NB; n++) R.g[n] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  // The wave's output blocks into LDS and its hidden blocks, turned over, into global memory.  The turning patch is the
-  // wave's own output block (nobody reads it between the outputs of a chunk and the next chunk's first barrier), rotated
-  // so that the four q of an access hit different banks.
+  // The wave's output blocks into LDS and its hidden blocks into global memory: row by row of 16 units, so
+  // that no turning is needed on the way (through an LDS patch each block waited for the one before: [60, 60, 60] on 50 inputs
+  // 2.07 -> 1.95 ms, [128, 100] 1.29 -> 1.33 at batch 160).
   __device__ __forceinline__ void publish(const State& R) const {
-    const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
-    float* p = f(O_WO) + w_ * 256;
+    const int w_ = wave();
     const Places z = places();
 #pragma unroll
     for (int l = 1; l < H; l++)
       if (w_ < T[l + 1]) {
 #pragma unroll
         for (int kk = 0; kk < W; kk++)
-          if (kk < T[l]) {
-#pragma unroll
-            for (int e = 0; e < 4; e++) p[q * 64 + ((e * 16 + 16 * q + li) & 63)] = R.w[blk(l, kk)][e];
-            __builtin_amdgcn_wave_barrier();
-            const f32x4 t = *(const f32x4*)(p + (li >> 2) * 64 + (((li & 3) * 16 + 16 * (li >> 2) + 4 * q) & 63));
-            __builtin_amdgcn_wave_barrier();
-            *wt(z, l, kk, w_) = t;
-          }
+          if (kk < T[l]) put(z, l, kk, w_, weights(R, z, blk(l, kk)));
       }
-    *((f32x4*)p + lane) = R.w[B_OUT];
+    publish_outputs(R);
+  }
+  __device__ __forceinline__ void publish_outputs(const State& R) const {
+    *((f32x4*)(f(O_WO) + wave() * 256) + (tid() & 63)) = R.w[reg(B_OUT)];
   }
 
   // ---- products over the rows R0..R0+N-1 (16 rows each) ------------------------
@@ -343,13 +376,24 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
 
   // ---- forward ---------------------------------------------------------------
   __device__ __forceinline__ void forward(const State& R, int, int, int nrt, Acts& A) const {
-    __syncthreads();  // the chunk's inputs
     const int w_ = wave();
+    const Places z = places();
+    f32x4 ws[STREAM ? W : 1];  // a hidden layer's blocks, requested while the level below is computed
+    auto request = [&](int l) __attribute__((always_inline)) {
+      if constexpr (STREAM)
+        if (w_ < T[l + 1]) {
+#pragma unroll
+          for (int kk = 0; kk < W; kk++)
+            if (kk < T[l]) ws[STREAM ? kk : 0] = along(z, l, kk, w_);
+        }
+    };
+    request(1);
+    __syncthreads();  // the chunk's inputs
 #pragma unroll
     for (int l = 0; l < H; l++) {
       A.bits[l] = 0;
       if (w_ < T[l + 1]) {
-        const float bias = R.w[B_BIAS][l];
+        const float bias = R.w[reg(B_BIAS)][l];
         const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
         float* o = lev(l + 1) + 4 * q * LDH + w_ * 16 + li;
         uint32_t bits = 0;
@@ -361,7 +405,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
           if (l == 0)
             rows_times<R0, N, KT>(xs(0), LDW, &R.w[0], KT, acc);
           else
-            rows_times<R0, N, W>(lev(l ? l : 1), LDH, &R.w[blk(l ? l : 1, 0)], T[l], acc);
+            rows_times<R0, N, W>(lev(l ? l : 1), LDH, STREAM ? ws : &R.w[STREAM ? 0 : blk(l ? l : 1, 0)], T[l], acc);
 #pragma unroll
           for (int r = R0; r < R0 + N; r++)
 #pragma unroll
@@ -373,7 +417,10 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
         });
         A.bits[l] = bits;
       }
-      if (l + 1 < H) __syncthreads();
+      if (l + 1 < H) {
+        if (l > 0) request(l + 1);
+        __syncthreads();
+      }
     }
   }
 
@@ -397,7 +444,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
     float* d3 = f(O_D3) + (r * 16 + 4 * q) * MD_RS + li;
 #pragma unroll
     for (int e = 0; e < 4; e++) {
-      const float z = z0[e] + z1[e] + R.w[B_BIAS][H], yv = yv4[e];
+      const float z = z0[e] + z1[e] + R.w[reg(B_BIAS)][H], yv = yv4[e];
       const bool valid = r * 16 + 4 * q + e < rows;
       float dl = 0.f;
       if (n_classes >= 2) {
@@ -448,7 +495,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
       if (w_ < T[l]) {
 #pragma unroll
         for (int o = 0; o < 4; o++)
-          if (o0 + o < T[l + 1]) tr[o] = *wt(z, l, w_, o0 + o);
+          if (o0 + o < T[l + 1]) tr[o] = across(z, l, w_, o0 + o);
       }
     };
     fetch_tr(H - 1, 0);
@@ -558,8 +605,8 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
     // Moments in the slot are fetched AHEAD blocks early.  A block that the wave does not have is sent out of the
     // descriptor's range (zeros come back, nothing is written) instead of branched around: with the same memory operations
     // on every path the waits are for the block that is needed, not for all that is in flight.
-    f32x4 mf[NEAR ? 1 : NB], vf[NEAR ? 1 : NB];
-    const __amdgpu_buffer_rsrc_t mem = __builtin_amdgcn_make_buffer_rsrc(slot, 0, (uint32_t)z.region * 48u, 0x00020000);
+    f32x4 mf[NEAR ? 1 : NB], vf[NEAR ? 1 : NB], wf[STREAM ? NB : 1];
+    const __amdgpu_buffer_rsrc_t mem = __builtin_amdgcn_make_buffer_rsrc(slot, 0, y.slot_floats * 4u, 0x00020000);
     const uint32_t lane16 = (tid() & 63) * 16;
     auto where = [&](int n) __attribute__((always_inline)) { return used(n) ? lane16 : 0x80000000u; };
     auto fetch = [&](int n) __attribute__((always_inline)) {
@@ -569,7 +616,20 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
           const int at = place(z, n) * 16;
           mf[n] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(mem, vo, at + z.region * 16, 0));
           if (ADAM) vf[n] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(mem, vo, at + z.region * 32, 0));
+          if (STREAM && hidden(n)) {
+            const int block = turned(z, layer(n), (n - KT) % W, wave()) * 16;
+            const uint32_t from = used(n) ? lane16 / 4 : 0x80000000u;
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+              wf[STREAM ? n : 0][e] =
+                  __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mem, from + e * 256, block, 0));
+          }
         }
+    };
+    // The whole offset in the vector register: with a scalar register in the instruction the compiler leaves no wait state
+    // between a 16-byte store and an instruction that overwrites its data, and the last lanes then stored what came next.
+    auto store = [&](const f32x4& x, uint32_t at) __attribute__((always_inline)) {
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), mem, at, 0, 0);
     };
     constexpr int AHEAD = 4;  // blocks of moments in flight
 #pragma unroll
@@ -581,14 +641,15 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
       fetch(n + AHEAD);
       f32x4& mm = NEAR ? R.m[NEAR ? n : 0] : mf[NEAR ? 0 : n];
       f32x4& vv = NEAR ? R.v[NEAR ? n : 0] : vf[NEAR ? 0 : n];
+      f32x4& ww = STREAM && hidden(n) ? wf[STREAM ? n : 0] : R.w[reg(STREAM && hidden(n) ? 0 : n)];
       if (used(n)) {
         const float am = n == B_BIAS ? 0.f : o.am;
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           if (n == B_BIAS && e > H) continue;
-          float wr = R.w[n][e], mr = mm[e], vr = vv[e];
+          float wr = ww[e], mr = mm[e], vr = vv[e];
           opt_update(o, n == B_BIAS ? R.g[n][e] : R.g[n][e] + am * wr, wr, mr, vr);
-          R.w[n][e] = wr;
+          ww[e] = wr;
           mm[e] = mr;
           vv[e] = vr;
         }
@@ -597,42 +658,59 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
           for (int e = 0; e < 4; e++) {
             int l, i;
             bool isb;
-            if (packed(n, e, l, i, isb) < 0) R.w[n][e] = mm[e] = vv[e] = 0.f;
+            if (packed(n, e, l, i, isb) < 0) ww[e] = mm[e] = vv[e] = 0.f;
           }
         }
       }
       if constexpr (!NEAR) {
         const uint32_t vo = where(n);
         const int at = place(z, n) * 16;
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, mm), mem, vo, at + z.region * 16, 0);
-        if (ADAM) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, vv), mem, vo, at + z.region * 32, 0);
+        store(mm, vo + (uint32_t)(at + z.region * 16));
+        if (ADAM) store(vv, vo + (uint32_t)(at + z.region * 32));
+        if constexpr (STREAM)
+          if (hidden(n)) {
+            const int block = turned(z, layer(n), (n - KT) % W, wave()) * 16;
+            const uint32_t to = used(n) ? lane16 / 4 : 0x80000000u;
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+              __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, (float)ww[e]), mem, to + e * 256, block, 0);
+          }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    publish(R);
+    if constexpr (STREAM)
+      publish_outputs(R);
+    else
+      publish(R);
+    asm volatile("" ::: "memory");  // (what comes next reads through pointers what was written through the descriptor)
   }
   template <bool GRAD>
   __device__ __forceinline__ void record(const State& R, float am, float* out) const {
     const bool first = (threadIdx.x & 63) < 16;
+    const Places z = places();
 #pragma unroll
-    for (int n = 0; n < NB; n++)
+    for (int n = 0; n < NB; n++) {
+      const f32x4 ww = weights(R, z, n);
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         if (n == B_BIAS && e > H) continue;
         int l, i;
         bool isb;
         const int ci = packed(n, e, l, i, isb);
-        float x = R.w[n][e];
+        float x = ww[e];
         if (GRAD) x = n == B_BIAS ? sm_rowsum(R.g[n][e]) : R.g[n][e] + am * x;
         if (ci >= 0 && (n != B_BIAS || (first && (e < H || wave() == 0)))) out[ci] = x;
       }
+    }
   }
   __device__ __forceinline__ double penalty_sum(const State& R) const {
     double s = 0.0;
 #pragma unroll
-    for (int n = 0; n < B_BIAS; n++)
+    for (int n = 0; n < B_BIAS; n++) {
+      const f32x4 ww = weights(R, places(), n);
 #pragma unroll
-      for (int e = 0; e < 4; e++) s += (double)R.w[n][e] * (double)R.w[n][e];
+      for (int e = 0; e < 4; e++) s += (double)ww[e] * (double)ww[e];
+    }
     return block_sum(s, red);
   }
 };
