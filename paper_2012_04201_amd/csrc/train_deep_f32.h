@@ -324,21 +324,35 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
   }
 
   // ---- products over the rows R0..R0+N-1 (16 rows each) ------------------------
+  // Operand tiles requested before the products of the tile at hand (past the last: read, not used).  Up to two row tiles the
+  // products of a tile are too short to hide the next one's reads: [60, 60, 60] at batch 24 796 -> 764 us, [128, 128,
+  // 128] 1913 -> 1851.  Four row tiles need no look-ahead, and 14 blocks of weights and gradients leave no room for it
+  // (48 vector registers spilled: [128, 100] on 50 inputs 2.60 -> 3.35 ms).
+  __device__ __forceinline__ static constexpr int ahead(int n) { return n <= 2 && (STREAM || NB <= 13) ? 1 : 0; }
   // acc[r] += rows of s . b, over nk k tiles
   template <int R0, int N, int K>
   __device__ __forceinline__ static void rows_times(const float* s, int ld, const f32x4* b, int nk, f32x4* acc) {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
     const float* a_ = s + (R0 * 16 + li) * ld + 4 * q;
+    constexpr int AHEAD = ahead(N);
+    f32x4 a[2][N];
+    if (AHEAD) {
+#pragma unroll
+      for (int r = 0; r < N; r++) a[0][r] = *(const f32x4*)(a_ + r * 16 * ld);
+    }
 #pragma unroll
     for (int kk = 0; kk < K; kk++)
       if (kk < nk) {
-        f32x4 a[N];
+        if (kk + AHEAD < K) {
 #pragma unroll
-        for (int r = 0; r < N; r++) a[r] = *(const f32x4*)(a_ + r * 16 * ld + kk * 16);
+          for (int r = 0; r < N; r++) a[(kk + AHEAD) & 1][r] = *(const f32x4*)(a_ + r * 16 * ld + (kk + AHEAD) * 16);
+          if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int e = 0; e < 4; e++)
 #pragma unroll
-          for (int r = 0; r < N; r++) acc[R0 + r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r][e], b[kk][e], acc[R0 + r], 0, 0, 0);
+          for (int r = 0; r < N; r++)
+            acc[R0 + r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk & 1][r][e], b[kk][e], acc[R0 + r], 0, 0, 0);
       }
   }
   // g[kk] += columns of s^T . d
@@ -346,18 +360,27 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
   __device__ __forceinline__ static void gradient(const float* s, int ld, const f32x4* d, int nk, f32x4* g) {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
     const float* a_ = s + (R0 * 16 + 4 * q) * ld + li;
+    constexpr int AHEAD = ahead(N);
+    float a[2][N][4];
+    auto read = [&](int kk) __attribute__((always_inline)) {
+#pragma unroll
+      for (int r = 0; r < N; r++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) a[kk & 1][r][e] = a_[(r * 16 + e) * ld + kk * 16];
+    };
+    if (AHEAD) read(0);
 #pragma unroll
     for (int kk = 0; kk < K; kk++)
       if (kk < nk) {
-        float a[N][4];
+        if (kk + AHEAD < K) {
+          read(kk + AHEAD);
+          if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int r = 0; r < N; r++)
 #pragma unroll
-          for (int e = 0; e < 4; e++) a[r][e] = a_[(r * 16 + e) * ld + kk * 16];
-#pragma unroll
-        for (int r = 0; r < N; r++)
-#pragma unroll
-          for (int e = 0; e < 4; e++) g[kk] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r][e], d[R0 + r][e], g[kk], 0, 0, 0);
+          for (int e = 0; e < 4; e++)
+            g[kk] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk & 1][r][e], d[R0 + r][e], g[kk], 0, 0, 0);
       }
   }
   // fn(first row tile, number of them), compile-time, for the row tiles of a chunk
