@@ -18,7 +18,7 @@
 // three.  What bounds it: two waves per SIMD in step with each other, the waves past a narrow level's tiles idle, and the
 // chain of a chunk's phases; the kernel for any shape, which these models ran on before, kept every operand in global
 // memory.  256 suggestions x 5 folds on 569 x 30, one to three layers of 16..128 units, 10 epochs: 25.4 -> 9.4 ms a call, and
-// 8.2 with the moments' branches gone and the weights of the widest cuts in global memory alone.
+// 8.0 with the moments' branches gone, the weights of the widest cuts in global memory alone and operands read a tile ahead.
 #pragma once
 #include <type_traits>
 
@@ -454,10 +454,17 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
     const float* a_ = lev(H) + (r * 16 + li) * LDH + 4 * q;
     const f32x4* b_ = (const f32x4*)f(O_WO) + lane;
     f32x4 z0 = f32x4{0.f, 0.f, 0.f, 0.f}, z1 = z0;
+    // operands a tile ahead: few waves are at work here, so nothing else hides the reads
+    f32x4 as[2] = {*(const f32x4*)a_, f32x4{0.f, 0.f, 0.f, 0.f}}, bs[2] = {b_[0], f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int kk = 0; kk < W; kk++)
       if (kk < T[H]) {
-        const f32x4 a = *(const f32x4*)(a_ + kk * 16), b = b_[kk * 64];
+        if (kk + 1 < W) {
+          as[(kk + 1) & 1] = *(const f32x4*)(a_ + (kk + 1) * 16);
+          bs[(kk + 1) & 1] = b_[(kk + 1) * 64];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        const f32x4 a = as[kk & 1], b = bs[kk & 1];
         z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], z0, 0, 0, 0);
         z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], z1, 0, 0, 0);
         z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], z0, 0, 0, 0);
@@ -573,8 +580,8 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
           });
       };
       times_tr(0);
-      // in flight during the weight gradient: the second half, or the level below's first
-      if (W > 4)
+      // in flight during the weight gradient: the second half if there is one, else the level below's first
+      if (W > 4 && T[l + 1] > 4)
         fetch_tr(l, 4);
       else if (l > 1)
         fetch_tr(l - 1, 0);
@@ -582,7 +589,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
         each_rows(nrt, [&](auto r0, auto cnt) __attribute__((always_inline)) {
           gradient<decltype(r0)::value, decltype(cnt)::value, W>(lev(l), LDH, d, T[l], &R.g[blk(l, 0)]);
         });
-      if (W > 4) {
+      if (W > 4 && T[l + 1] > 4) {
         times_tr(4);
         if (l > 1) fetch_tr(l - 1, 0);
       }
