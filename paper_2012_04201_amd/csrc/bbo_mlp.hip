@@ -1497,10 +1497,21 @@ int bbo_mlp_workspace_bytes(int64_t n, int32_t d, int32_t n_classes, int32_t n_f
   Plan pl;
   rc = make_plan(pl, n, d, n_classes, n_folds, 0, hp, B, dtype);
   if (rc) return rc;
+  uint64_t total = pl.total;
+  // Models that take all rows in a step need less than the same models with smaller batches: a workspace made for a list of
+  // shapes holds them at any batch size.
+  if (std::any_of(pl.sub.begin(), pl.sub.end(), [](const SubPlan& sp) { return sp.kc == KC_FULL; })) {
+    std::vector<bbo_mlp_hparams> row_by_row(hp, hp + B);
+    for (bbo_mlp_hparams& h : row_by_row) h.batch_size = 1;
+    Plan other;
+    rc = make_plan(other, n, d, n_classes, n_folds, 0, row_by_row.data(), B, dtype);
+    if (rc) return rc;
+    total = std::max(total, other.total - other.items_bytes + pl.items_bytes);
+  }
   // (records at their largest, whatever kernel they are for: the size of a call's records does not decide whether a
   // workspace made for as many other models holds it)
   constexpr size_t record = std::max({sizeof(ItemDesc), sizeof(TItem), sizeof(SItem), sizeof(FItem), sizeof(MItem), sizeof(DItem)});
-  *out = (size_t)(pl.total + std::max<uint64_t>(record * (uint64_t)B + 256 * MAX_LAUNCHES, pl.items_bytes) - pl.items_bytes);
+  *out = (size_t)(total + std::max<uint64_t>(record * (uint64_t)B + 256 * MAX_LAUNCHES, pl.items_bytes) - pl.items_bytes);
   return BBO_OK;
 }
 
