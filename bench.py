@@ -28,6 +28,7 @@ KERNEL_SOURCES = {"k_train_tiled": ["common.h", "train_tiled_bf16.h"], "k_train_
                   "k_train_linear": ["common.h", "train_linear_f32.h"],
                   "k_train_linear_lds": ["common.h", "train_small_f32.h", "train_linear_lds_f32.h"],
                   "k_train": ["common.h", "bbo_mlp.hip"],
+                  "k_train_full": ["common.h", "train_small_f32.h", "train_full_f32.h"],
                   "k_train_mid": ["common.h", "train_small_f32.h", "train_mid_f32.h"]}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.txt")
 
@@ -152,7 +153,7 @@ def run_workload(idx, steps, warmup, suggestions=0, epochs=0, linear=False):
     if linear:  # up to two outputs on a data set that fits into LDS, as those of cfg2 and cfg3 do, have a kernel of their own
         kernel = "k_train_linear_lds" if c <= 2 else "k_train_linear"
     else:
-        kernel = "k_train_tiled" if dt else ("k_train_small" if idx in (0, 2, 3) else "k_train_mid")
+        kernel = "k_train_tiled" if dt else {0: "k_train_full", 1: "k_train_mid"}.get(idx, "k_train_small")
     tflops = flops / per_step / 1e12
     abytes = algorithmic_bytes(cfg)
     traffic = measured_traffic(cfg["name"], kernel)
