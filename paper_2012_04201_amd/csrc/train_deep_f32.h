@@ -661,7 +661,8 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
     auto store = [&](const f32x4& x, uint32_t at) __attribute__((always_inline)) {
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), mem, at, 0, 0);
     };
-    constexpr int AHEAD = 4;  // blocks of moments in flight
+    // blocks of moments in flight (256 suggestions of one to three layers: 7.98 ms a call, with three 8.01, with six 8.02)
+    constexpr int AHEAD = 4;
 #pragma unroll
     for (int n = 0; n < AHEAD; n++) fetch(n);
 #pragma unroll
