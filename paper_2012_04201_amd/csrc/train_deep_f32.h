@@ -15,8 +15,9 @@
 //   update    Adam / SGD; the moments in registers where they fit, else in global memory, touched once per step
 //
 // Four waves up to 64 units (two models a CU), eight up to 128.  Barriers per chunk: 6 with two hidden layers, 9 with
-// three.  What bounds it: two waves per SIMD in step with each other, the waves past a narrow level's tiles idle, and the
-// chain of a chunk's phases; the kernel for any shape, which these models ran on before, kept every operand in global
+// three; per step one more where the second hidden layer has more than 64 units.  What bounds it: two waves per SIMD in step
+// with each other, the waves past a narrow level's tiles idle, and the chain of a chunk's phases; the kernel for any shape,
+// which these models ran on before, kept every operand in global
 // memory.  256 suggestions x 5 folds on 569 x 30, one to three layers of 16..128 units, 10 epochs: 25.4 -> 9.4 ms a call, and
 // 8.0 with the moments' branches gone, the weights of the widest cuts in global memory alone and operands read a tile ahead.
 #pragma once
@@ -625,6 +626,20 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
       });
   }
 
+  // Ahead of the first store to layer 1's weights in global memory: behind the last barrier of the backward pass the waves of
+  // the first level still fetch the second half of that layer's out tiles, those of waves 4 and up.  (Every other fetch of
+  // another wave's weights lies ahead of that barrier.)  The condition is the fetch's own, the same in every wave.
+  __device__ __forceinline__ void before_weights() const {
+    if (W > 4 && T[2] > 4) __syncthreads();
+  }
+  // Blocks in the order of their update.  Where it stores the weights itself, layer 1's come last and the barrier in front of
+  // them finds the waves past most of their work: 256 suggestions of one to three layers 7.99 ms a call as without it, 8.09
+  // with the barrier ahead of all hidden blocks, 8.43 with one ahead of the whole update in place of the chunk's last.
+  __device__ __forceinline__ static constexpr int turn_of(int k) {
+    if (!STREAM || k < KT) return k;
+    return k < NB - W ? k + W : k - (NB - W) + KT;
+  }
+
   // ---- optimizer step (pads: see k_train_small) ----------------------------------
   template <bool ADAM>
   __device__ __forceinline__ void update(State& R, const OptC& oc) const {
@@ -664,12 +679,14 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
     // blocks of moments in flight (256 suggestions of one to three layers: 7.98 ms a call, with three 8.01, with six 8.02)
     constexpr int AHEAD = 4;
 #pragma unroll
-    for (int n = 0; n < AHEAD; n++) fetch(n);
+    for (int k = 0; k < AHEAD; k++) fetch(turn_of(k));
 #pragma unroll
     for (int e = 0; e <= H; e++) R.g[B_BIAS][e] = sm_rowsum(R.g[B_BIAS][e]);
 #pragma unroll
-    for (int n = 0; n < NB; n++) {
-      fetch(n + AHEAD);
+    for (int k = 0; k < NB; k++) {
+      const int n = turn_of(k);
+      if (STREAM && k == NB - W) before_weights();
+      if (k + AHEAD < NB) fetch(turn_of(k + AHEAD));
       f32x4& mm = NEAR ? R.m[NEAR ? n : 0] : mf[NEAR ? 0 : n];
       f32x4& vv = NEAR ? R.v[NEAR ? n : 0] : vf[NEAR ? 0 : n];
       f32x4& ww = STREAM && hidden(n) ? wf[STREAM ? n : 0] : R.w[reg(STREAM && hidden(n) ? 0 : n)];
@@ -709,10 +726,12 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if constexpr (STREAM)
+    if constexpr (STREAM) {
       publish_outputs(R);
-    else
+    } else {
+      before_weights();
       publish(R);
+    }
     asm volatile("" ::: "memory");  // (what comes next reads through pointers what was written through the descriptor)
   }
   template <bool GRAD>
