@@ -26,10 +26,8 @@ def weight_stores(listing):
             name = None
         elif name and line.split():
             op, streamed = line.split()[0], name[1:] == (3, 8)
-            if op == "s_barrier":
-                fetched = update = False
-            fetched |= op == "global_load_dwordx4"
-            update |= op == "buffer_store_dwordx4"
+            fetched = op == "global_load_dwordx4" or fetched and op != "s_barrier"
+            update = op == "buffer_store_dwordx4" or update and not op.startswith("v_mfma")
             if op == "buffer_store_dword" if streamed else update and op == "global_store_dword":
                 stores += 1
                 bad += fetched
