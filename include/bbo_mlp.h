@@ -113,7 +113,7 @@ int bbo_mlp_workspace_bytes(int64_t n, int32_t d, int32_t n_classes, int32_t n_f
  *             contents are scratch.  A workspace made for as many suggestions
  *             of wider layers will do too: where it has less than this call's
  *             bytes, the call's kernels share their part of it and follow each
- *             other, on half their workgroups or more (same results);
+ *             other, on fewer workgroups (same results);
  *             BBO_WORKSPACE_TOO_SMALL if it does not hold that either
  *   stream    hipStream_t (NULL = default stream)
  *
