@@ -1113,12 +1113,12 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
   pl.o_val = take(4ull * nn * n_folds);
   pl.o_counts = take(8ull * n_folds);
   // Side by side every launch has slots of its own.  Where that is more than the workspace holds the launches run in
-  // turn on shared slots, and the register-resident kernels on as few workgroups as fit, down to one for every fourth CU: a
-  // workspace sized for the widest models of a search holds any mix of narrower ones, though these come in more variants,
-  // and the variants of less than a CU's registers in more workgroups.  The line is drawn by CUs, and well below what a
-  // kernel would like, so that how many workgroups of a kernel a CU holds, and what a workgroup keeps in its slot, do not
-  // decide which calls a workspace of fixed size takes (a half of the workgroups refused 400 models of three layers of 64
-  // units once two of them shared a CU).
+  // turn on shared slots, and the register-resident kernels on as few workgroups as one for every second CU: a workspace
+  // sized for the widest models of a search holds any mix of narrower ones, though these come in more variants, and the
+  // variants of less than a CU's registers in more workgroups.  The line is drawn by CUs so that how many workgroups of a
+  // kernel a CU holds does not decide which calls a workspace of fixed size takes (half of the workgroups refused 400 models
+  // of three layers of 64 units once two of them shared a CU); one for every fourth CU where k_train_mid's products are
+  // split, which makes its slot up to 1.7 times as large as that of the same models with smaller batches.
   auto slots_of = [](const SubPlan& sp) {  // (slots are multiples of 256)
     return std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256);
   };
@@ -1131,7 +1131,8 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
       if ((sp.kc == KC_SMALL || sp.kc == KC_FULL || sp.kc == KC_MID || sp.kc == KC_DEEP) && sp.slot_bytes * sp.n_slots > left) {
         int cus = 0;
         if (int rc = device_cus(&cus)) return rc;
-        if (sp.slot_bytes * ((std::min(sp.n_slots, cus) + 3) / 4) <= left) sp.n_slots = (int)(left / sp.slot_bytes);
+        const int most_of = std::min(sp.n_slots, cus), least = sp.kc == KC_MID && sp.cut.co ? (most_of + 3) / 4 : (most_of + 1) / 2;
+        if (sp.slot_bytes * least <= left) sp.n_slots = (int)(left / sp.slot_bytes);
       }
       sp.o_slots = off;
       most = std::max(most, slots_of(sp));
