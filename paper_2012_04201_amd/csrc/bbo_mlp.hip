@@ -1504,13 +1504,24 @@ int bbo_mlp_workspace_bytes(int64_t n, int32_t d, int32_t n_classes, int32_t n_f
   rc = make_plan(pl, n, d, n_classes, n_folds, 0, hp, B, dtype);
   if (rc) return rc;
   uint64_t total = pl.total;
-  // Models that take all rows in a step need less than the same models with smaller batches: a workspace made for a list of
-  // shapes holds them at any batch size.
-  if (std::any_of(pl.sub.begin(), pl.sub.end(), [](const SubPlan& sp) { return sp.kc == KC_FULL; })) {
-    std::vector<bbo_mlp_hparams> row_by_row(hp, hp + B);
-    for (bbo_mlp_hparams& h : row_by_row) h.batch_size = 1;
+  // The batch size decides how some models are cut: k_train_full's need less than the same models with smaller batches,
+  // k_train_mid's more where a step has enough rows for split products.  A workspace made for a list of shapes holds them at
+  // any batch size.
+  auto may_grow = [](const SubPlan& sp) {
+    return sp.kc == KC_FULL || (sp.kc == KC_MID && !sp.cut.co && md_splittable(sp.cut.kt, sp.cut.nt, sp.cut.waves));
+  };
+  if (std::any_of(pl.sub.begin(), pl.sub.end(), may_grow)) {
+    std::vector<bbo_mlp_hparams> largest(hp, hp + B);
+    for (bbo_mlp_hparams& h : largest) {
+      int32_t dims[MAXL + 1];
+      int L;
+      fill_dims(h, d, n_classes, dims, &L);
+      const int k = kernel_class(dims, L, n, dtype);
+      if (k == KC_SMALL) h.batch_size = 1;
+      if (k == KC_MID) h.batch_size = 0;
+    }
     Plan other;
-    rc = make_plan(other, n, d, n_classes, n_folds, 0, row_by_row.data(), B, dtype);
+    rc = make_plan(other, n, d, n_classes, n_folds, 0, largest.data(), B, dtype);
     if (rc) return rc;
     total = std::max(total, other.total - other.items_bytes + pl.items_bytes);
   }

@@ -24,6 +24,29 @@ def test_the_static_workspace_holds_these_calls(child, n, d, c, K, shapes, batch
     assert rc == 0 and max(grids) >= 64
 
 
+# two unit tiles a wave, two to five input tiles: split products past 64 rows a step, and a larger slot with three and four
+@pytest.mark.parametrize("n,d,c,h", [(1797, 64, 10, 200), (40, 47, 10, 256), (453, 45, 10, 130), (273, 60, 7, 254), (300, 20, 5, 150),
+                                     (300, 80, 5, 150)])
+@pytest.mark.parametrize("count,folds", [(1, 1), (1, 3), (40, 5), (300, 5)])
+def test_a_workspace_holds_the_same_models_at_any_batch_size(child, n, d, c, h, count, folds):  # noqa: F811
+    sizes, grids = child("""
+        n, d, c, h, count, K = %r
+        shapes, batches = [[h - 30 * (i %% 2)] for i in range(count)], (0, 1, 32, 64, 65)
+        sizes, grids = [], []
+        for made in batches:
+            out = C.c_size_t(0)
+            assert L.bbo_mlp_workspace_bytes(C.c_int64(n), d, c, K, records(shapes, made), count, 0, C.byref(out)) == 0
+            sizes.append(out.value)
+            log()
+            rcs = [L.bbo_mlp_cv_eval(P(4096), P(4096), C.c_int64(n), d, c, P(4096), K, records(shapes, b), count, 0, P(4096),
+                                     P(4096), P(0), P(4096), out, P(900)) for b in batches]
+            assert rcs == [0] * 5, (made, rcs)
+            grids.append([int(l[2]) for l in log() if l[0] == "launch"])
+        print(json.dumps([sizes, grids]))
+    """ % ((n, d, c, h, count, folds),))
+    assert all(g == grids[0] for g in grids) and len(set(sizes)) == 1, sizes  # and on as many workgroups
+
+
 @pytest.mark.gpu
 def test_fewer_workgroups_give_the_same_bits(bb):  # noqa: F811
     n, d, c, K, shapes = DEEP[0]
