@@ -301,7 +301,7 @@ static void forward(const net_t* net, const data_t* D, const int32_t* rows, int6
         for (int k = 0; k < fi; k++) acc = accum(acc, s->a[l][r * fi + k] * W[(int64_t)k * fo + j], prec);
         double z = rnd(acc + b[j], prec);
         if (l + 1 < net->L) {
-          z = z > 0.0 ? z : 0.0;
+          z = z > 0.0 || isnan(z) ? z : 0.0;
           z = opnd(z, dt); /* BF: hidden activations */
         }
         s->a[l + 1][r * fo + j] = z;

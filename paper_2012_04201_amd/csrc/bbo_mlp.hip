@@ -398,7 +398,7 @@ struct Trainer {
                        typename O::vec4 pk;
 #pragma unroll
                        for (int r = 0; r < 4; r++) {
-                         pk[r] = O::cvt(fmaxf(acc[r] + bias, 0.f));
+                         pk[r] = O::cvt(relu(acc[r] + bias));
                          An[(i0 + r) * kpn + j] = pk[r];
                        }
                        *(typename O::vec4*)(ATn + (size_t)j * rows + i0) = pk;

@@ -287,6 +287,10 @@ struct OptC {
   float b1, b2, omb1, omb2, eps, lr_t, mu, lr, am;
 };
 
+// max(x, 0) in one instruction.  A NaN stays one, in every kernel: a model that blew up, or met a NaN in its data, has a score
+// that says so.  (fmaxf() and a median make it 0.)
+__device__ __forceinline__ float relu(float x) { return __builtin_elementwise_maximum(x, 0.f); }
+
 // (The multiply-adds are written out: of a sum of two products the compiler may contract either, and models that move
 // between the variants of a kernel keep their bits.)
 __device__ inline void opt_update(const OptC& c, float g, float& w, float& m, float& v) {

@@ -434,7 +434,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
           for (int r = R0; r < R0 + N; r++)
 #pragma unroll
             for (int e = 0; e < 4; e++) {
-              const float x = sm_relu(acc[r][e]);
+              const float x = relu(acc[r][e]);
               o[(r * 16 + e) * LDH] = x;
               bits |= (x > 0.f ? 1u : 0u) << (4 * r + e);
             }

@@ -202,7 +202,7 @@ struct Full {
 #pragma unroll
     for (int i = 0; i < NT; i++)
 #pragma unroll
-      for (int e = 0; e < 4; e++) acc[i][e] = sm_relu(acc[i][e]);
+      for (int e = 0; e < 4; e++) acc[i][e] = relu(acc[i][e]);
 #pragma unroll
     for (int cc = 0; cc < ZO; cc++) {
       float p[4];

@@ -356,7 +356,7 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
     for (int i = 0; i < NT; i++)
       if (i + 1 < NT || ALL) {
 #pragma unroll
-        for (int e = 0; e < 4; e++) acc[i][r][e] = SPLIT ? sm_relu_nan(acc[i][r][e]) : sm_relu(acc[i][r][e]);
+        for (int e = 0; e < 4; e++) acc[i][r][e] = relu(acc[i][r][e]);
         const f32x4 ar = turn(acc[i][r], r);  // row li, units 4q..4q+3
 #pragma unroll
         for (int e = 0; e < 4; e++) z = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[e], R.w2[i][e], z, 0, 0, 0);

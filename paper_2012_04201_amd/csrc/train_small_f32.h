@@ -234,10 +234,6 @@ __device__ __forceinline__ float sm_fold_row(const float (&v)[4], bool b2, bool 
   return (b2 ? B : A) + sm_dpp<0x1B>(x);           // and the reversal of the quad makes that i ^ 4
 }
 
-// max(x, 0), and 0 for a NaN, in one instruction: fmaxf() puts another in front that quiets NaNs where the compiler cannot
-// know that there are none, as in a matrix product's result.
-__device__ __forceinline__ float sm_relu(float x) { return __builtin_amdgcn_fmed3f(x, 0.f, INFINITY); }
-
 // Two classes by the difference of their logits, z = z[1] - z[0], of a row of class `one`.  The delta of class 1 (before
 // the division by the step's rows; class 0 has its negative): the probability of the other class, which does not cancel
 // as p - 1 does.  An infinite difference is a NaN in both, as it is with the logits apart.
@@ -315,7 +311,7 @@ __device__ __forceinline__ void sm_outputs(const float (&z)[sm_columns(CO)], flo
 // of 24).  A product of two such numbers is summed over six of the nine pairs, smallest first; the three left out are below
 // 2^-24 of it.  Per 32 contracted elements that is six matrix instructions of 16 cycles instead of eight of 32, and the
 // result is closer to the exact one: over 64 normal pairs 9.4e-8 relative rms against 1.45e-7 of the fp32 instructions.
-// (Infinities come out as NaN, hence sm_relu_nan().)
+// (Infinities come out as NaN.)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 struct SmPlanes {  // eight elements a lane, as operands
@@ -356,7 +352,6 @@ __device__ __forceinline__ void sm_products(const SmPlanes& a, const SmPlanes* b
   for (int i = 0; i < N; i++) c[i] = sm_product<S>(a, b[i], c[i]);
   if constexpr (S < 5) sm_products<N, S + 1>(a, b, c);
 }
-__device__ __forceinline__ float sm_relu_nan(float x) { return __builtin_elementwise_maximum(x, 0.f); }
 // Transposing LDS read of 16-bit elements: of the 16 x 4 elements that a row of 16 lanes addresses (lane t: four columns of
 // row t / 4 from column 4 (t mod 4) on) lane t gets column t of the four rows.
 __device__ __forceinline__ u32x2 sm_read_tr(const char* p) {
@@ -1199,7 +1194,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
     for (int e = 0; e < 4; e++) {
 #pragma unroll
       for (int i = 0; i < NT; i++) {
-        const float av = SPLIT ? sm_relu_nan(c[i][e]) : sm_relu(c[i][e]);
+        const float av = relu(c[i][e]);
         acc[i][r][e] = av;
 #pragma unroll
         for (int cc = 0; cc < ZO; cc++) p[cc][e] = i == 0 ? av * R.w2[0][cc] : p[cc][e] + av * R.w2[i][cc];

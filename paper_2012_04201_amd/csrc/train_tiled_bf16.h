@@ -455,7 +455,7 @@ struct Tiled {
                 uint32_t nib = 0;
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
-                  pk[r] = (__bf16)fmaxf(acc[ub][j][r] + bv[ub][r], 0.f);
+                  pk[r] = (__bf16)relu(acc[ub][j][r] + bv[ub][r]);
                   nib |= ((float)pk[r] > 0.f ? 1u : 0u) << r;
                 }
                 *(bf16x4*)(b + j * tile_bytes + ub * 32) = pk;
