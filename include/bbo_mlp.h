@@ -256,13 +256,14 @@ int64_t bbo_mlp_param_count(int32_t d, int32_t n_classes, const bbo_mlp_hparams*
  * Which training kernel suggestion hp[0] runs on for a data set of n rows (host
  * logic only, no device call): 0 the LDS-tiled bf16 kernel, 1 the
  * register-resident fp32 kernel (one hidden layer, up to 63 inputs and 4
- * outputs), 2 the kernels without a hidden layer (a wavefront per model; fp32
+ * outputs) or, for those of its models that take all their rows in every step
+ * and are small enough, its form for full batches, 2 the kernels without a hidden layer (a wavefront per model; fp32
  * data sets that fit into LDS have one of their own), 3 the generic kernel, 4
  * the wider register-resident fp32 kernel (one hidden layer, up to 127 inputs
  * and 16 outputs), 5 the fp32 kernel for two or three hidden layers (up to 64
- * inputs, 128 units and 16 outputs); negative on invalid input.  Every
- * suggestion of a call gets the kernel this returns for it, whatever else the
- * call holds (Algorithm 1's evaluate(params_list) treats the suggestions
+ * inputs, 128 units and 16 outputs); negative on invalid input.  The batch size
+ * does not change the value.  Every suggestion of a call gets the kernel this
+ * returns for it, whatever else the call holds (Algorithm 1's evaluate(params_list) treats the suggestions
  * independently).
  */
 int bbo_mlp_kernel_class(int64_t n, int32_t d, int32_t n_classes, const bbo_mlp_hparams* hp,

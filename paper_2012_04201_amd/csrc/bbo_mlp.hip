@@ -1020,7 +1020,8 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     }
     int k = kernel_class(dims, L, n, dtype);
     const SmallCut full = k == KC_SMALL ? full_cut(dims, L, n, h.batch_size) : SmallCut{0, 0, 0, 0};
-    if (full.waves) k = KC_FULL;  // (a form of the small kernel for models that take all rows at once)
+    if (full.waves) k = KC_FULL;  // (a form of the small kernel for models that take all rows at once, and named as that one by
+                                  // bbo_mlp_kernel_class())
     const SmallCut cut = k == KC_FULL ? full : k == KC_SMALL ? small_cut(dims) : (k == KC_MID ? mid_cut(dims, L, h.batch_size) : (k == KC_DEEP ? deep_cut(dims, L) : SmallCut{0, 0, 0, 0}));
     SubPlan& sp = launch_of(k, cut);
     uint64_t slot_bytes = 0;

@@ -76,8 +76,24 @@ int __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, intptr_t s) {
 int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, intptr_t* s) {
   return *grid = grid_, *block = block_, *lds = lds_, *s = stream_, OK;
 }
+/* the library's kernels, as its constructor registers them */
+static struct {
+  const void* f;
+  const char* name;
+} kernels[1024];
+static int n_kernels;
+void __hipRegisterFunction(void** modules, const void* f, char* device_function, const char* name, unsigned threads, void* tid,
+                           void* bid, void* block, void* grid, int* wave_size) {
+  (void)modules, (void)device_function, (void)threads, (void)tid, (void)bid, (void)block, (void)grid, (void)wave_size;
+  if (n_kernels < 1024) kernels[n_kernels].f = f, kernels[n_kernels++].name = name;
+}
+static const char* name_of(const void* f) {
+  for (int i = 0; i < n_kernels; i++)
+    if (kernels[i].f == f) return kernels[i].name;
+  return "?";
+}
 int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, intptr_t s) {
-  (void)f, (void)args;
+  (void)args;
   if (++launches == hr_fail_launch) return LOG("launch_failed %ld\n", (long)s), INVALID;
-  return LOG("launch %ld %u %u %zu\n", (long)s, grid.x, block.x, lds), OK;
+  return LOG("launch %ld %u %u %zu %s\n", (long)s, grid.x, block.x, lds, name_of(f)), OK;
 }
