@@ -21,7 +21,8 @@ const void* by_tiles(int nt, int co) {
     case 1: return by_outputs<KT, 1, W>(co);
     case 2: return by_outputs<KT, 2, W>(co);
     case 3: return by_outputs<KT, 3, W>(co);
-    case 4: return by_outputs<KT, 4, W>(co);
+    case 4:
+      if constexpr (W == 8) return by_outputs<KT, 4, W>(co);  // (from 100 rows on: full_cut())
   }
   return nullptr;
 }

@@ -87,6 +87,7 @@ void __hipRegisterFunction(void** modules, const void* f, char* device_function,
   (void)modules, (void)device_function, (void)threads, (void)tid, (void)bid, (void)block, (void)grid, (void)wave_size;
   if (n_kernels < 1024) kernels[n_kernels].f = f, kernels[n_kernels++].name = name;
 }
+const char* hr_kernel(int i) { return i < n_kernels ? kernels[i].name : 0; }
 static const char* name_of(const void* f) {
   for (int i = 0; i < n_kernels; i++)
     if (kernels[i].f == f) return kernels[i].name;

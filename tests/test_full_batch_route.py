@@ -38,3 +38,24 @@ def test_few_models_of_several_widths_share_a_launch(child):  # noqa: F811
     shapes = [[8], [16], [17], [32], [40], [48], [5]]
     assert kernels(child, 150, 6, 2, shapes, 0)[0] == [("k_train_full", (1, 3, 2, 8))]
     assert sorted(kernels(child, 150, 6, 2, shapes * 20, 0)[0]) == [("k_train_full", (1, t, 2, 8)) for t in (1, 2, 3)]
+
+
+def test_every_compiled_variant_is_reached(child):  # noqa: F811
+    compiled, launched = child("""
+        rt.hr_kernel.restype = C.c_char_p
+        compiled, i = [], 0
+        while rt.hr_kernel(i):
+            compiled.append(rt.hr_kernel(i).decode())
+            i += 1
+        launched = []
+        for n in (20, 120, 400):
+            for d in (3, 20):
+                for h in (9, 25, 41, 57):
+                    for c in (1, 2, 3, 4):
+                        rc = L.bbo_mlp_cv_eval(P(4096), P(4096), C.c_int64(n), d, c, P(4096), 5, records([[h]], 0), 1, 0, P(4096),
+                                               P(4096), P(0), P(4096), C.c_size_t(1 << 40), P(900))
+                        launched += [l[5] for l in log() if l[0] == "launch"]
+        print(json.dumps([compiled, launched]))
+        """)
+    full = {x for x in compiled if "k_train_full" in x}
+    assert len(full) == 44 and full == {x for x in launched if "k_train_full" in x}
