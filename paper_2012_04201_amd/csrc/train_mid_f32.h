@@ -17,8 +17,9 @@
 // pipes are busy a third of the time, the rest is the chain of a chunk (LDS reads in front of the products, the output
 // layer's reductions, the barriers) with two waves per SIMD to cover it.  Its predecessor kept the weights in LDS and the
 // moments in L2, one model of 8 waves per CU, four barriers per chunk: 1000 models of 64-128-10 on 1797 rows, 3 epochs,
-// took 5.5 ms and take 3.2 ms (64 units: 4.2 and 2.5 ms; 200 units: 8.7 and 5.1 ms).  With the row pipeline's leaner schedule and the input layer's products in split bfloat16
-// (md_splittable()) 512 suggestions of the digits shape took 14.0 ms instead of 15.5.
+// took 5.5 ms and take 3.2 ms (64 units: 4.2 and 2.5 ms; 200 units: 8.7 and 5.1 ms).  With the row pipeline's leaner schedule
+// and the input layer's products in split bfloat16 (md_splittable()) 512 suggestions of the digits shape took 14.0 ms instead
+// of 15.5.
 #pragma once
 #include "common.h"
 #include "train_small_f32.h"  // the row pipeline
@@ -68,9 +69,10 @@ struct MItem {
 
 // Input-layer products in split bfloat16 (see SmPlanes)?  With eight waves and two to five input tiles (six and more leave no
 // LDS for two buffers of planes); with two unit tiles a wave the weights' planes push the moments out of the registers and an
-// update takes 8000 cycles instead of 4500, which pays from 64 rows a step on.  us a call with fp32 products and split, 900
-// rows, 3 epochs: 64-100-10, 200 suggestions, 32 and 160 rows a step 1930 and 1750, 1458 and 1219; 64-200-10 3050 and 3586,
-// 2285 and 2101.  (Four waves: 64-64-10, 32 rows 1555 and 1566.)
+// update takes 8000 cycles instead of 4500, which pays from a chunk and a half a step on.  us a call with fp32 products and
+// split, 900 rows, 3 epochs, 200 suggestions: 64-100-10 at 32 and 160 rows a step 1930 and 1750, 1458 and 1219; 64-200-10 at 64,
+// 65, 80, 96 and 128 rows 2487 and 2569, 3085 and 3207, 2508 and 2581, 2408 and 2356, 2293 and 2148; 45-200-10 at 80 and 96 rows
+// 2160 and 2210, 2061 and 2032; 30-200-10 1820 and 1825, 1737 and 1678.  (Four waves: 64-64-10, 32 rows 1555 and 1566.)
 __host__ __device__ constexpr bool md_splittable(int kt, int nt, int waves) {
   return waves == 8 && kt >= 2 && kt <= 5 && kt * nt <= 8;
 }
@@ -88,7 +90,7 @@ __host__ inline SmallCut mid_cut(const int32_t* dims, int L, int32_t batch_size)
   m.nt = (nut + waves - 1) / waves;
   m.waves = m.kt * m.nt <= 12 ? waves : 0;
   // (co: split products)
-  m.co = md_splittable(m.kt, m.nt, waves) && (m.nt == 1 || batch_size <= 0 || batch_size > SM_RC) ? 1 : 0;
+  m.co = md_splittable(m.kt, m.nt, waves) && (m.nt == 1 || batch_size <= 0 || 2 * batch_size >= 3 * SM_RC) ? 1 : 0;
   return m;
 }
 __host__ __device__ constexpr int md_regs(int kt, int nt) { return nt * (4 * kt + 1 + 4) + 1; }
@@ -729,7 +731,7 @@ __device__ __forceinline__ void mid_models(const TrainParams& P) {
     T.run();
   }
 }
-// the products as they are with one unit tile a wave, and up to 64 rows a step with two ...
+// the products as they are with one unit tile a wave, and below 96 rows a step with two ...
 template <int KT, int NT, int W>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_waves_per_eu(2, 2)))
 void k_train_mid(const TrainParams P) {

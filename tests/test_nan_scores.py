@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 # them, the full-batch kernel, two and three hidden layers, no hidden layer, any shape, bfloat16
 SHAPES = [(10, 2, [20], 24, 0), (30, 2, [20], 24, 0), (30, 2, [100], 24, 0), (30, 1, [130], 64, 0), (40, 3, [50], 40, 0),
           (60, 2, [64], 64, 0), (60, 3, [64], 64, 0), (4, 3, [20], 0, 0), (30, 2, [40], 0, 0), (20, 0, [17], 0, 0),
-          (64, 10, [40], 32, 0), (64, 10, [100], 32, 0), (64, 10, [200], 64, 0), (64, 10, [200], 65, 0), (100, 5, [64], 32, 0),
+          (64, 10, [40], 32, 0), (64, 10, [100], 32, 0), (64, 10, [200], 64, 0), (64, 10, [200], 96, 0), (100, 5, [64], 32, 0),
           (30, 2, [40, 24], 24, 0), (30, 3, [100, 90], 24, 0), (20, 2, [70, 128, 30], 40, 0), (30, 2, [], 24, 0), (64, 10, [], 24, 0),
           (30, 2, [300], 24, 0), (70, 2, [40, 24], 0, 0), (64, 10, [128, 128], 64, 1), (64, 10, [256], 300, 1), (30, 2, [40, 24], 24, 1)]
 

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 # inputs, hidden, batch, scale of the inputs: two and four tiles of inputs, an odd number of row tiles, rows past a chunk
 @pytest.mark.parametrize("d,h,bs,c", [(17, 100, 64, 2), (30, 200, 80, 2), (32, 130, 49, 2), (30, 210, 17, 2), (50, 64, 33, 2),
-                                      (63, 128, 200, 2), (64, 100, 80, 10), (40, 200, 96, 7), (64, 256, 65, 16), (75, 100, 33, 5)])
+                                      (63, 128, 200, 2), (64, 100, 80, 10), (40, 200, 96, 7), (64, 256, 65, 16), (64, 256, 97, 16), (75, 100, 33, 5)])
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** -30, 2.0 ** 10])
 def test_gradients_are_as_close_to_exact_as_fp32_sums(bb, oracle, d, h, bs, c, scale):  # noqa: F811
     """The first step's gradients against pure fp64: no further off than the oracle's own with fp32 running sums, which
