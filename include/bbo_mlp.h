@@ -101,7 +101,10 @@ int bbo_mlp_workspace_bytes(int64_t n, int32_t d, int32_t n_classes, int32_t n_f
  *   X         device, row-major [n][d]; float32 (BBO_F32) or bfloat16 (BBO_BF16)
  *   y         device, [n]; int32 class ids 0..n_classes-1 if n_classes >= 2,
  *             int32 labels 0/1 if n_classes == 1 (one logit), float32 targets
- *             if n_classes == 0 (regression)
+ *             if n_classes == 0 (regression).  Labels are not checked: with
+ *             any other value the scores of the models that train on that row
+ *             or are scored on it mean nothing (the kernels count it as class
+ *             0 or as no class)
  *   fold_idx  device, int32 [n]; row i validates in fold fold_idx[i] and trains
  *             in every other fold; a negative value leaves the row unused
  *   hp        host, [B] suggestions

@@ -3,14 +3,14 @@
 //
 // An epoch is one step over the same rows, so nothing is fetched or permuted while it runs: a workgroup gathers the rows of
 // its model into LDS once (those it is fitted on, those set aside for early stopping and the held fold's, each part
-// padded to whole tiles of 16 rows) and its eight waves share the row tiles of a step.  Where train_small_f32.h gives the
+// padded to whole tiles of 16 rows) and its W waves (four up to 80 rows, eight beyond) share the row tiles of a step.  Where train_small_f32.h gives the
 // waves units, and walks the rows chunk by chunk, every wave here computes all of the model for its rows:
 //
 //   forward   D[row][unit] = xs[row][k] . w1[unit][k] on MFMA (16x16x4 fp32); the bias is column d of the inputs, a 1.
 //             ReLU; the outputs are sums over the 16 unit lanes, alike in the four quads: no exchange between waves.
 //   outputs   lane (row 4q + li % 4): softmax / logistic / squared loss, output delta (two classes: one column)
 //   backward  hidden deltas in the accumulators, products xs^T . delta in registers over the wave's row tiles
-//   reduce    the waves' gradients meet in LDS, a slot of 64 values per register; slot r belongs to wave r mod 8
+//   reduce    the waves' gradients meet in LDS, a slot of 64 values per register; slot r belongs to wave r mod W
 //   update    Adam / SGD of the wave's slots, a parameter a lane, moments in registers; the weights go back to LDS
 //
 // Two barriers a step.  What bounds it: the chain of a step, about 5500 cycles at 120 rows and 20 units, of which the
@@ -37,9 +37,14 @@ __host__ __device__ constexpr int fu_slots(int kt, int nt, int co) { return nt *
 __host__ __device__ constexpr uint32_t fu_lds(int kt, int nt, int co, int waves, int64_t n) {
   return (uint32_t)(fu_slots(kt, nt, co) * (1 + waves) * 64 + (n + 48) * (sm_ldw(kt) + 1)) * 4;
 }
-// Waves per SIMD the registers of a variant are budgeted for.
+// Waves per SIMD the registers of a variant are budgeted for.  27 of the 44 variants do not fit altogether: by the compiler's
+// report <2,2,3..4,4> spill 54 and 66 vector registers, <1,3,3..4,4> 53 and 52, <2,2,3..4,8> 20 and 34, <1,3,3..4,8> 18 and 30,
+// <1,4,1..2,8> 21 and 19, the others 19 at most.
 __host__ __device__ constexpr int fu_occupancy(int kt, int nt, int co) { return nt == 4 && co > 2 ? 2 : 4; }
-// By shape, rows and batch size alone; waves == 0: not a case of this kernel.
+// By shape, rows and batch size alone; waves == 0: not a case of this kernel.  Four unit tiles are the edge: us a call here over
+// train_small_f32.h as it was before this kernel, 14 inputs, 64 units, 15 epochs, 4, 200 and 1000 suggestions: two classes,
+// 100 rows 0.63, 0.84, 0.94; three classes, 256 rows 0.50, 0.84, 1.00, and 600 rows 0.43, 0.73, 0.82; four classes (4 inputs), 256
+// rows 0.54, 0.93, 1.11, and 300 rows 0.53, 0.87, 1.03.
 __host__ inline SmallCut full_cut(const int32_t* dims, int L, int64_t n, int32_t batch_size) {
   SmallCut m = {0, 0, 0, 0};
   if (L != 2 || dims[0] > 31 || dims[1] > 64 || dims[2] > 4 || n < 1 || (batch_size > 0 && batch_size < n)) return m;
