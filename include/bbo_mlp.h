@@ -125,7 +125,9 @@ int bbo_mlp_workspace_bytes(int64_t n, int32_t d, int32_t n_classes, int32_t n_f
  * a single output (n_classes == 1; the second score is the accuracy of the
  * rule z > 0), or half squared error (n_classes == 0); penalty
  * alpha/(2 m) * |W|^2 with m the rows of the step; Adam (bias corrections in
- * the step size, eps added to sqrt(v)) or SGD with (Nesterov) momentum;
+ * the step size, eps added to sqrt(v); an eps of less than 2^-120 counts as
+ * that, so that a parameter without a gradient stays where it is) or SGD with
+ * (Nesterov) momentum;
  * constant learning rate; exactly `epochs` passes in a seeded order; a short
  * last minibatch is kept.  BBO_BF16 rounds GEMM operands (inputs, weights,
  * hidden activations, deltas) to bfloat16 and keeps master weights, moments

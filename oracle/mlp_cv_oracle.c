@@ -433,7 +433,8 @@ typedef struct {
 
 static void adam_step(const oracle_hparams* hp, int64_t P, double* theta, const double* g,
                       opt_t* o, int prec) {
-  double b1 = hp->beta1, b2 = hp->beta2, lr = hp->lr, eps = hp->eps;
+  /* no 0 / 0: a parameter that has never had a gradient stays where it is */
+  double b1 = hp->beta1, b2 = hp->beta2, lr = hp->lr, eps = fabsf(hp->eps) < 0x1p-120f ? 0x1p-120 : hp->eps;
   o->t += 1;
   double lr_t = rnd(lr * sqrt(1.0 - pow(b2, (double)o->t)) / (1.0 - pow(b1, (double)o->t)), prec);
   double omb1 = rnd(1.0 - b1, prec), omb2 = rnd(1.0 - b2, prec);

@@ -409,7 +409,6 @@ struct Full {
       for (int s = 0; s < RS; s++) {
         if (rec && ci[s] >= 0) rec[1 + ci[s]] = g[s];
         opt_update(oc, g[s], p[s], m[s], v[s]);
-        if (ci[s] < 0) p[s] = m[s] = v[s] = 0.f;  // (with an eps of zero a pad's step is 0 / 0)
         if (rec && ci[s] >= 0) rec[1 + y.P + ci[s]] = p[s];
       }
       publish(p);

@@ -632,44 +632,6 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
       *mom(k, 0) = mb[k];
       if (ADAM) *mom(k, 1) = vb[k];
     }
-    if (ADAM && o.eps == 0.f) clear_pads(R);
-  }
-  __device__ __forceinline__ void clear_pads(State& R) const {
-    const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
-#pragma unroll
-    for (int i = 0; i < NT; i++) {
-      const int t0 = (w_ + i * W) * 16;
-      const bool unit = t0 + li < y.h;
-#pragma unroll
-      for (int kk = 0; kk < KT; kk++) {
-        f32x4 x = R.w.get(i, kk);
-#pragma unroll
-        for (int e = 0; e < 4; e++)
-          if (!unit || kk * 16 + 4 * q + e >= y.p.d) {
-            x[e] = 0.f;
-            if (i < NEAR)
-              R.m[i < NEAR ? i : 0][kk][e] = R.v[i < NEAR ? i : 0][kk][e] = 0.f;
-            else
-              (*far(i, 0, kk))[e] = (*far(i, 1, kk))[e] = 0.f;
-          }
-        R.w.put(i, kk, x);
-      }
-      if (!unit) {
-        R.bw[i] = 0.f;
-        *mom(i, 0) = *mom(i, 1) = 0.f;
-      }
-#pragma unroll
-      for (int e = 0; e < 4; e++)
-        if (li >= c || t0 + 4 * q + e >= y.h) {
-          R.w2[i][e] = 0.f;
-          (*mom2(i, 0))[e] = 0.f;
-          (*mom2(i, 1))[e] = 0.f;
-        }
-    }
-    if (li >= c) {
-      R.ow = 0.f;
-      *mom(NT, 0) = *mom(NT, 1) = 0.f;
-    }
   }
   template <bool GRAD>
   __device__ __forceinline__ void record(const State& R, float am, float* out) const {

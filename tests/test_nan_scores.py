@@ -35,3 +35,22 @@ def test_a_nan_in_a_row(bb, d, c, hidden, batch, dtype, row):  # noqa: F811
     without, _ = bb.bbo_mlp_cv_eval(X, y, c, ft, 5, hps, dtype)
     torch.cuda.synchronize()
     assert status.tolist() == [0, 0] and torch.equal(scores, without)
+
+
+@pytest.mark.parametrize("d,c,hidden,batch,dtype", SHAPES)
+def test_an_eps_of_zero_moves_no_parameter_without_a_gradient(bb, d, c, hidden, batch, dtype):  # noqa: F811
+    """A column of zeros and no penalty: its weights never have a gradient, and Adam's 0 / 0 is no step."""
+    cfg = small_problem(7 + d, 230, d, c, bf16=bool(dtype))
+    cfg["X"][:, 1] = 0
+    X, y, ft = bb.to_device(cfg)
+    hp = {"hidden": hidden, "batch_size": batch, "epochs": 3, "lr": 1e-3, "alpha": 0.0, "eps": 0.0, "seed": 3}
+    scores, status, _, tr = bb.bbo_mlp_cv_eval(X, y, c, ft, 5, [hp], dtype, want_per_fold=True, trace=(0, 1, 0, 3))
+    _, untraced = bb.bbo_mlp_cv_eval(X, y, c, ft, 5, [hp] * 3, dtype)
+    first = bb.bbo_mlp_init_params(d, c, hp, 1)
+    torch.cuda.synchronize()
+    assert status.tolist() == [0] and untraced.tolist() == [0] * 3 and bool(torch.isfinite(scores).all())
+    out = hidden[0] if hidden else max(c, 1)
+    after = tr["theta_after"]
+    assert bool(torch.isfinite(after).all())
+    assert torch.equal(after[:, out:2 * out], first[out:2 * out].expand(3, out))
+    assert not torch.equal(after[0, :out], first[:out])
