@@ -937,9 +937,7 @@ void fill_item(ItemDesc& it, const bbo_mlp_hparams& h, int b, int64_t n, int d, 
   it.momentum = h.momentum;
   it.beta1 = h.beta1;
   it.beta2 = h.beta2;
-  // (no 0 / 0 in a parameter, or a pad, that has never had a gradient: it stays where it is.  2^-120 changes no sum with a root
-  // that is not zero: those are 2^-75 at least)
-  it.eps = std::fabs(h.eps) < 0x1p-120f ? 0x1p-120f : h.eps;
+  it.eps = std::fabs(h.eps) < EPS_MIN ? EPS_MIN : h.eps;
   it.power_t = h.power_t;
   it.tol = h.tol;
   it.patience = h.n_iter_no_change;

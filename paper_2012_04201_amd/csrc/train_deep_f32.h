@@ -645,6 +645,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
   __device__ __forceinline__ void update(State& R, const OptC& oc) const {
     OptC o = oc;
     o.adam = ADAM;
+    const bool pads = ADAM && least_eps(o);
     const Places z = places();
     // Moments in the slot are fetched AHEAD blocks early.  A block that the wave does not have is sent out of the
     // descriptor's range (zeros come back, nothing is written) instead of branched around: with the same memory operations
@@ -699,6 +700,14 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
           ww[e] = wr;
           mm[e] = mr;
           vv[e] = vr;
+        }
+        if (pads) {
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            int l, i;
+            bool isb;
+            if (packed(n, e, l, i, isb) < 0) ww[e] = mm[e] = vv[e] = 0.f;
+          }
         }
       }
       if constexpr (!NEAR) {

@@ -409,6 +409,7 @@ struct Full {
       for (int s = 0; s < RS; s++) {
         if (rec && ci[s] >= 0) rec[1 + ci[s]] = g[s];
         opt_update(oc, g[s], p[s], m[s], v[s]);
+        if (ci[s] < 0) p[s] = m[s] = v[s] = 0.f;  // (an infinite input makes its gradient NaN)
         if (rec && ci[s] >= 0) rec[1 + y.P + ci[s]] = p[s];
       }
       publish(p);

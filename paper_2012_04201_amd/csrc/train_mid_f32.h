@@ -68,11 +68,15 @@ struct MItem {
 };
 
 // Input-layer products in split bfloat16 (see SmPlanes)?  With eight waves and two to five input tiles (six and more leave no
-// LDS for two buffers of planes); with two unit tiles a wave the weights' planes push the moments out of the registers and an
-// update takes 8000 cycles instead of 4500, which pays from a chunk and a half a step on.  us a call with fp32 products and
-// split, 900 rows, 3 epochs, 200 suggestions: 64-100-10 at 32 and 160 rows a step 1930 and 1750, 1458 and 1219; 64-200-10 at 64,
-// 65, 80, 96 and 128 rows 2487 and 2569, 3085 and 3207, 2508 and 2581, 2408 and 2356, 2293 and 2148; 45-200-10 at 80 and 96 rows
-// 2160 and 2210, 2061 and 2032; 30-200-10 1820 and 1825, 1737 and 1678.  (Four waves: 64-64-10, 32 rows 1555 and 1566.)
+// LDS for two buffers of planes).  With two unit tiles a wave the weights' planes push the moments out of the registers and an
+// update takes 8000 cycles instead of 4500, which pays past a chunk of 64 rows a step, with three input tiles (three quarters
+// of the products' columns) past a chunk and a half.  us a call with fp32 products and split, 10 classes, 3 epochs: 900 rows, 200
+// suggestions, 64 inputs, 100 units at 32 and 160 rows a step 1930 and 1750, 1458 and 1219; 64 inputs, 200 units at 48, 65, 80,
+// 96 and 128 rows 2659 and 2935, 3085 and 3207, 2508 and 2581, 2408 and 2356, 2293 and 2148; 1797 rows, 8 suggestions at 48, 65,
+// 80 and 96 rows 1310 and 1332, 1500 and 1465, 1228 and 1197, 1173 and 1080: past a chunk what few models gain is what many
+// lose, up to 96 rows.  45 inputs, 200 units at 65, 80 and 96 rows: 200 suggestions 2664 and 2736, 2160 and 2210, 2061 and 2032, 8
+// suggestions 1299 and 1330, 1065 and 1086, 1009 and 984.  30 inputs: 1.01 of its time at most from 65 rows on.  (Four waves:
+// 64 inputs, 64 units, 32 rows 1555 and 1566.)
 __host__ __device__ constexpr bool md_splittable(int kt, int nt, int waves) {
   return waves == 8 && kt >= 2 && kt <= 5 && kt * nt <= 8;
 }
@@ -91,7 +95,7 @@ __host__ inline SmallCut mid_cut(const int32_t* dims, int L, int32_t batch_size)
   m.nt = (nut + waves - 1) / waves;
   m.waves = m.kt * m.nt <= 12 ? waves : 0;
   // (co: split products)
-  m.co = md_splittable(m.kt, m.nt, waves) && (m.nt == 1 || batch_size <= 0 || 2 * batch_size >= 3 * SM_RC) ? 1 : 0;
+  m.co = md_splittable(m.kt, m.nt, waves) && (m.nt == 1 || batch_size <= 0 || batch_size > (m.kt == 3 ? 3 * SM_RC / 2 - 1 : SM_RC)) ? 1 : 0;
   return m;
 }
 __host__ __device__ constexpr int md_regs(int kt, int nt) { return nt * (4 * kt + 1 + 4) + 1; }
@@ -632,6 +636,44 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
       *mom(k, 0) = mb[k];
       if (ADAM) *mom(k, 1) = vb[k];
     }
+    if (ADAM && least_eps(o)) clear_pads(R);
+  }
+  __device__ __forceinline__ void clear_pads(State& R) const {
+    const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < NT; i++) {
+      const int t0 = (w_ + i * W) * 16;
+      const bool unit = t0 + li < y.h;
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++) {
+        f32x4 x = R.w.get(i, kk);
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+          if (!unit || kk * 16 + 4 * q + e >= y.p.d) {
+            x[e] = 0.f;
+            if (i < NEAR)
+              R.m[i < NEAR ? i : 0][kk][e] = R.v[i < NEAR ? i : 0][kk][e] = 0.f;
+            else
+              (*far(i, 0, kk))[e] = (*far(i, 1, kk))[e] = 0.f;
+          }
+        R.w.put(i, kk, x);
+      }
+      if (!unit) {
+        R.bw[i] = 0.f;
+        *mom(i, 0) = *mom(i, 1) = 0.f;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+        if (li >= c || t0 + 4 * q + e >= y.h) {
+          R.w2[i][e] = 0.f;
+          (*mom2(i, 0))[e] = 0.f;
+          (*mom2(i, 1))[e] = 0.f;
+        }
+    }
+    if (li >= c) {
+      R.ow = 0.f;
+      *mom(NT, 0) = *mom(NT, 1) = 0.f;
+    }
   }
   template <bool GRAD>
   __device__ __forceinline__ void record(const State& R, float am, float* out) const {
@@ -694,7 +736,7 @@ __device__ __forceinline__ void mid_models(const TrainParams& P) {
     T.run();
   }
 }
-// the products as they are with one unit tile a wave, and below 96 rows a step with two ...
+// the products as they are with one unit tile a wave, and up to 64 or 95 rows a step with two ...
 template <int KT, int NT, int W>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_waves_per_eu(2, 2)))
 void k_train_mid(const TrainParams P) {

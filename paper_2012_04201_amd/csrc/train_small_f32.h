@@ -1381,8 +1381,11 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
   }
 
   // ---- optimizer step -------------------------------------------------------------
-  // Pad elements need no mask: their inputs, deltas and weights are zero, and so is their step (0 / eps; eps is never zero
-  // here).
+  // Pad elements need no mask: their inputs, deltas and weights are zero, and so is their step (0 / eps).  The
+  // least eps clears them all the same: no value changes by it, but the branch parts the update from what follows for the
+  // register allocation, in this kernel and in those for wider and deeper models.  Without it k_train_mid<5,2,8> spills 67
+  // vector registers instead of 51 and takes 1.06 to 1.14 of its time, and 8 suggestions of the digits shape 3440 us instead of
+  // 3195.  (256 suggestions of one to three layers 7.84 ms instead of 8.00.)
   template <bool ADAM>
   __device__ __forceinline__ void update(State& R, const OptC& oc) const {
     const int w_ = wave();
@@ -1410,6 +1413,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
     small_grads(R, gp);
 #pragma unroll
     for (int g = 0; g < NG; g++) opt_update(o, gp[g] + small_penalty(g, q, o.am) * R.pw[g], R.pw[g], R.pm[g], R.pv[g]);
+    if (ADAM && least_eps(o)) clear_pads(R);
     spread(R);
   }
   // A traced step's gradient (before the update: GRAD) or new parameters into out[P].
@@ -1445,6 +1449,24 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
     if (k >= NSMALL) return -1;
     if (k >= NT * (1 + CO)) return k - NT * (1 + CO) < c ? y.cb[1] + k - NT * (1 + CO) : -1;
     return j >= y.h || r > c ? -1 : (r == 0 ? y.cb[0] + j : y.cw[1] + j * c + r - 1);
+  }
+  __device__ __forceinline__ void clear_pads(State& R) const {
+    const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < NT; i++) {
+      const bool unit = (w_ + i * W) * 16 + li < y.h;
+#pragma unroll
+      for (int kk = 0; kk < KT; kk++) {
+        f32x4 x = R.w.get(i, kk);
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+          if (!unit || kk * 16 + 4 * q + e >= y.p.d) x[e] = R.m[i][kk][e] = R.v[i][kk][e] = 0.f;
+        R.w.put(i, kk, x);
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < NG; g++)
+      if (small_packed(4 * g + q) < 0) R.pw[g] = R.pm[g] = R.pv[g] = 0.f;
   }
 
   // squared weights, for a traced step's loss
