@@ -1413,7 +1413,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
     small_grads(R, gp);
 #pragma unroll
     for (int g = 0; g < NG; g++) opt_update(o, gp[g] + small_penalty(g, q, o.am) * R.pw[g], R.pw[g], R.pm[g], R.pv[g]);
-    if (ADAM && least_eps(o)) clear_pads(R);
+    if (ADAM && o.eps == EPS_MIN) clear_pads(R);  // (by its value: see least_eps())
     spread(R);
   }
   // A traced step's gradient (before the update: GRAD) or new parameters into out[P].
