@@ -84,7 +84,7 @@ __host__ __device__ constexpr bool md_splittable(int kt, int nt, int waves) {
 // of this kernel.  One tile a wave while eight waves reach (more models a CU with four), else two: one tile leaves the
 // registers for everything, and eight waves of one tile beat four of two by a quarter even with the chip full (64-100-10,
 // 1000 models: 3.2 ms against 3.9).  Beyond kt * nt = 12 the weights and gradients alone overflow the registers; close to
-// it they crowd others out: by the compiler's report <3,2,8> spills 42 vector registers, <4,2,8> 21, <5,2,8> 51, <6,2,8> 204,
+// it they crowd others out: by the compiler's report <3,2,8> spills 26 vector registers, <4,2,8> 21, <5,2,8> 51, <6,2,8> 216,
 // the split form of <4,2,8> 19, the others 5 at most.  (<6,2,8> against its form before the leaner schedule, 90 inputs, 200 and
 // 250 units: 0.95 at 32 rows a step, 1.02 to 1.04 at 65 to 128.)
 __host__ inline SmallCut mid_cut(const int32_t* dims, int L, int32_t batch_size) {
