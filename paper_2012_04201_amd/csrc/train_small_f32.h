@@ -1384,8 +1384,8 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
   // Pad elements need no mask: their inputs, deltas and weights are zero, and so is their step (0 / eps).  The
   // least eps clears them all the same: no value changes by it, but the branch parts the update from what follows for the
   // register allocation, in this kernel and in those for wider and deeper models.  Without it k_train_mid<5,2,8> spills 67
-  // vector registers instead of 51 and takes 1.06 to 1.14 of its time, and 8 suggestions of the digits shape 3440 us instead of
-  // 3195.  (256 suggestions of one to three layers 7.84 ms instead of 8.00.)
+  // vector registers instead of 51 and takes 1.06 to 1.14 of its time.  (256 suggestions of one to three layers 7.84 ms instead
+  // of 8.00.)
   template <bool ADAM>
   __device__ __forceinline__ void update(State& R, const OptC& oc) const {
     const int w_ = wave();
