@@ -216,7 +216,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fold_lists(const int32_t* __restri
   const int f = blockIdx.x, fold = (int)blockIdx.x + fold_base, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (f == 0)
     for (int i = tid; i < n_words; i += NTHREADS) items[i] = records.words[i];
-  if (f == 0 && tid < n_queues) queue[tid] = 0;  // the work-queue counters of the launches that follow
+  if (f == 0)  // the work-queue counters of the launches that follow, and what their workgroups meet at
+    for (int i = tid; i < n_queues; i += NTHREADS) queue[i] = 0;
   if (tid == 0) base_tr = base_va = 0;
   __syncthreads();
   for (int64_t c0 = 0; c0 < n; c0 += NTHREADS) {
@@ -814,6 +815,7 @@ struct SubPlan {
   std::vector<int32_t> order;   // its suggestions, most expensive first
   uint64_t slot_bytes = 0;      // global memory per resident workgroup
   int n_slots = 0;              // workgroups to launch
+  int team = 1;                 // LDS-tiled kernel: workgroups per model, launched for each of the slots
   uint32_t lds_bytes = 0;       // dynamic LDS per workgroup
   int waves = 0;                // linear kernels: wavefronts per workgroup
   int dd = 0;                   // linear kernel with the data set in LDS: its padded columns; 0: the other one
@@ -828,6 +830,7 @@ constexpr int MAX_LAUNCHES = 64;  // queue counters in the workspace
 struct Plan {
   std::vector<SubPlan> sub;
   size_t n_items = 0;
+  int n_queues = MAX_LAUNCHES;  // words of the queue region: the launches' counters, and behind them the teams' control blocks
   bool in_turn = false;  // the launches share one slot region and run one after the other
   // workspace byte offsets; otherwise they run side by side, each with slots of its own
   uint64_t o_items = 0, items_bytes = 0, o_queue = 0, o_out = 0, o_train = 0, o_val = 0, o_counts = 0, total = 0;
@@ -977,6 +980,23 @@ void merge_full(Plan& pl, int n_folds) {
   pl.sub = std::move(kept);
 }
 
+constexpr int TEAM_XCDS = 8;  // a team's workgroups share an XCD: launched in eights, one for each
+
+// Workgroups that train one model together (Team in train_tiled_bf16.h) in a call of `models` models, of which each has
+// `sp`'s kernel; 1: each model has a workgroup of its own.  A team takes every step in one chunk and sets no rows aside.
+// It pays as soon as two workgroups a model have a CU each: us a step of one and of a team, 128-256-256-10, 64 rows, 8, 32, 64, 96 and
+// 128 models 57 and 37, 64 and 42, 66 and 49, 68 and 59, 95 and 82; 128-200-10, 256 rows 37 and 30 to 40 and 37.
+int team_size(const SubPlan& sp, size_t models, int64_t n, const bbo_mlp_hparams* hp, int cus) {
+  if (sp.kc != KC_TILED) return 1;
+  for (const int32_t b : sp.order) {
+    const bbo_mlp_hparams& h = hp[b];
+    if ((h.batch_size <= 0 || h.batch_size > TB_ROWS) && n > TB_ROWS) return 1;
+    if (h.n_iter_no_change > 0 && h.validation_fraction > 0.f) return 1;
+  }
+  const size_t teams = (models + TEAM_XCDS - 1) / TEAM_XCDS;  // of an XCD
+  return (int)std::max<size_t>(1, std::min<size_t>(TB_TEAM_MAX, (size_t)(cus / TEAM_XCDS) / teams));
+}
+
 // The launches of a call, their workgroups and where everything lies in a workspace of `room` bytes (pl.total may exceed
 // them: then the call does not fit).  one_stream: the launches may not run side by side.
 int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_base, const bbo_mlp_hparams* hp, int B,
@@ -1098,52 +1118,70 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
   }
   // the launch with the longest single model is enqueued first: nothing can make up for starting that one late
   std::stable_sort(pl.sub.begin(), pl.sub.end(), [](const SubPlan& a, const SubPlan& b2) { return a.longest > b2.longest; });
-  uint64_t off = 0;
-  auto take = [&](uint64_t bytes) {
-    uint64_t o = off;
-    off += (bytes + 255) & ~(uint64_t)255;
-    return o;
-  };
-  const uint64_t nn = (uint64_t)std::max<int64_t>(n, 1);
-  pl.o_items = off;
-  for (SubPlan& sp : pl.sub) sp.o_items = take(sp.item_bytes * sp.order.size());
-  pl.items_bytes = off - pl.o_items;
-  pl.o_queue = take(4 * MAX_LAUNCHES);
-  pl.o_out = take(8ull * std::max<size_t>(pl.n_items, 1));
-  pl.o_train = take(4ull * nn * n_folds);
-  pl.o_val = take(4ull * nn * n_folds);
-  pl.o_counts = take(8ull * n_folds);
-  // Side by side every launch has slots of its own.  Where that is more than the workspace holds the launches run in
-  // turn on shared slots, and the register-resident kernels on as few workgroups as one for every second CU: a workspace
-  // sized for the widest models of a search holds any mix of narrower ones, though these come in more variants, and the
-  // variants of less than a CU's registers in more workgroups.  The line is drawn by CUs so that how many workgroups of a
-  // kernel a CU holds does not decide which calls a workspace of fixed size takes (half of the workgroups refused 400 models
-  // of three layers of 64 units once two of them shared a CU); one for every fourth CU where k_train_mid's products are
-  // split, which makes its slot up to 1.7 times as large as that of the same models with smaller batches.
-  auto slots_of = [](const SubPlan& sp) {  // (slots are multiples of 256)
-    return std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256);
-  };
-  uint64_t sum = 0, most = 0;
-  for (const SubPlan& sp : pl.sub) sum += slots_of(sp);
-  pl.in_turn = one_stream || off + sum > room;
-  if (pl.in_turn) {
-    const uint64_t left = off < room ? room - off : 0;
-    for (SubPlan& sp : pl.sub) {
-      if ((sp.kc == KC_SMALL || sp.kc == KC_FULL || sp.kc == KC_MID || sp.kc == KC_DEEP) && sp.slot_bytes * sp.n_slots > left) {
-        int cus = 0;
-        if (int rc = device_cus(&cus)) return rc;
-        const int most_of = std::min(sp.n_slots, cus), least = sp.kc == KC_MID && sp.cut.co ? (most_of + 3) / 4 : (most_of + 1) / 2;
-        if (sp.slot_bytes * least <= left) sp.n_slots = (int)(left / sp.slot_bytes);
+  auto lay_out = [&]() -> int {
+    uint64_t off = 0;
+    auto take = [&](uint64_t bytes) {
+      uint64_t o = off;
+      off += (bytes + 255) & ~(uint64_t)255;
+      return o;
+    };
+    const uint64_t nn = (uint64_t)std::max<int64_t>(n, 1);
+    pl.o_items = off;
+    for (SubPlan& sp : pl.sub) sp.o_items = take(sp.item_bytes * sp.order.size());
+    pl.items_bytes = off - pl.o_items;
+    pl.o_queue = take(4ull * pl.n_queues);
+    pl.o_out = take(8ull * std::max<size_t>(pl.n_items, 1));
+    pl.o_train = take(4ull * nn * n_folds);
+    pl.o_val = take(4ull * nn * n_folds);
+    pl.o_counts = take(8ull * n_folds);
+    // Side by side every launch has slots of its own.  Where that is more than the workspace holds the launches run in
+    // turn on shared slots, and the register-resident kernels on as few workgroups as one for every second CU: a workspace
+    // sized for the widest models of a search holds any mix of narrower ones, though these come in more variants, and the
+    // variants of less than a CU's registers in more workgroups.  The line is drawn by CUs so that how many workgroups of a
+    // kernel a CU holds does not decide which calls a workspace of fixed size takes (half of the workgroups refused 400 models
+    // of three layers of 64 units once two of them shared a CU); one for every fourth CU where k_train_mid's products are
+    // split, which makes its slot up to 1.7 times as large as that of the same models with smaller batches.
+    auto slots_of = [](const SubPlan& sp) {  // (slots are multiples of 256)
+      return std::max<uint64_t>(sp.slot_bytes * (uint64_t)sp.n_slots, 256);
+    };
+    uint64_t sum = 0, most = 0;
+    for (const SubPlan& sp : pl.sub) sum += slots_of(sp);
+    pl.in_turn = one_stream || off + sum > room;
+    if (pl.in_turn) {
+      const uint64_t left = off < room ? room - off : 0;
+      for (SubPlan& sp : pl.sub) {
+        if ((sp.kc == KC_SMALL || sp.kc == KC_FULL || sp.kc == KC_MID || sp.kc == KC_DEEP) && sp.slot_bytes * sp.n_slots > left) {
+          int cus = 0;
+          if (int rc = device_cus(&cus)) return rc;
+          const int most_of = std::min(sp.n_slots, cus), least = sp.kc == KC_MID && sp.cut.co ? (most_of + 3) / 4 : (most_of + 1) / 2;
+          if (sp.slot_bytes * least <= left) sp.n_slots = (int)(left / sp.slot_bytes);
+        }
+        sp.o_slots = off;
+        most = std::max(most, slots_of(sp));
       }
-      sp.o_slots = off;
-      most = std::max(most, slots_of(sp));
+      take(most);
+    } else {
+      for (SubPlan& sp : pl.sub) sp.o_slots = take(slots_of(sp));
     }
-    take(most);
-  } else {
-    for (SubPlan& sp : pl.sub) sp.o_slots = take(slots_of(sp));
+    pl.total = off;
+    return BBO_OK;
+  };
+  // (one launch alone: beside others its workgroups would take the CUs of theirs)
+  pl.n_queues = MAX_LAUNCHES;
+  if (pl.sub.size() == 1 && pl.sub[0].kc == KC_TILED) {
+    SubPlan& sp = pl.sub[0];
+    int cus = 0;
+    if (int rc = device_cus(&cus)) return rc;
+    sp.team = team_size(sp, pl.n_items, n, hp, cus);
+    if (sp.team > 1) {
+      pl.n_queues += rup(sp.n_slots, TEAM_XCDS) * TB_TEAM_WORDS;
+      if (int rc = lay_out()) return rc;
+      if (pl.total <= room) return BBO_OK;
+      sp.team = 1;  // a workspace of fixed size holds what it held
+      pl.n_queues = MAX_LAUNCHES;
+    }
   }
-  pl.total = off;
-  return BBO_OK;
+  return lay_out();
 }
 
 
@@ -1346,6 +1384,8 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
   Plan pl;
   rc = make_plan(pl, n, d, n_classes, n_folds, fold_base, hp, B, dtype, workspace_bytes, static_ws);
   if (rc) return rc;
+  if (traced)
+    for (SubPlan& sp : pl.sub) sp.team = 1;  // the trace is one workgroup's
   if (static_ws && (pl.total > BBO_STATIC_SCRATCH_BYTES || pl.items_bytes > BBO_STATIC_MAX_ITEM_BYTES))
     return fail(BBO_WORKSPACE_TOO_SMALL,
                 "this problem needs " + std::to_string(pl.total) + " bytes of workspace (" +
@@ -1359,7 +1399,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
   PokeChunk chunk = {};
   auto fold_lists = [&](int n_words) {
     hipLaunchKernelGGL(k_fold_lists, dim3(n_folds), dim3(NTHREADS), 0, s, fold_idx, n, (int32_t*)(ws + pl.o_train),
-                       (int32_t*)(ws + pl.o_val), (int32_t*)(ws + pl.o_counts), queues, MAX_LAUNCHES, fold_base, chunk,
+                       (int32_t*)(ws + pl.o_val), (int32_t*)(ws + pl.o_counts), queues, pl.n_queues, fold_base, chunk,
                        (uint32_t*)(ws + pl.o_items), n_words);
     return hipGetLastError();
   };
@@ -1425,6 +1465,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
   P.trace_out = trace_out;
   P.state_in = traced ? state_in : nullptr;
   P.x_bf16 = dtype == BBO_BF16;
+  P.teams = (uint32_t*)(queues + MAX_LAUNCHES);
 
   // one launch per kernel variant that has items, side by side: the first on the caller's stream
   // (into a graph they are captured one after the other: no stream is created, or drawn into the capture, behind the
@@ -1453,7 +1494,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
     const void* fn;
     int threads = NTHREADS;
     if (k == KC_TILED) {
-      fn = tiled_kernel();
+      fn = tiled_kernel(sp.team > 1);
       threads = TB_THREADS;
     } else if (k == KC_SMALL) {
       const SmallCut& t = sp.cut;
@@ -1477,9 +1518,11 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
     }
     if (!fn) return fail(BBO_DEVICE_ERROR, "no kernel for this shape");  // ruled out by kernel_class()
     if (sp.lds_bytes && (rc = ensure_dynamic_lds(fn, sp.lds_bytes))) return rc;
+    P.team_size = sp.team;
+    const int workgroups = sp.team > 1 ? rup(sp.n_slots, TEAM_XCDS) * sp.team : sp.n_slots;
     void* args[] = {&P};
     const int lane = (int)(li % (size_t)(n_side + 1));
-    HIP_TRY(hipLaunchKernel(fn, dim3(sp.n_slots), dim3(threads), args, sp.lds_bytes, lane ? side.side->s[lane - 1] : s));
+    HIP_TRY(hipLaunchKernel(fn, dim3(workgroups), dim3(threads), args, sp.lds_bytes, lane ? side.side->s[lane - 1] : s));
     HIP_TRY(hipGetLastError());
   }
   HIP_TRY(side.join());

@@ -242,6 +242,8 @@ struct TrainParams {
   int64_t step_begin, step_end;
   float* trace_out;
   const float* state_in;  // optional [3P]: parameters, m, v of the traced item before step_begin
+  uint32_t* teams;        // LDS-tiled kernel with several workgroups per model: the teams' control blocks, zeroed
+  int32_t team_size;
   int32_t x_bf16;         // wavefront-per-model kernel: X holds bfloat16 and the products take bfloat16 operands
 };
 

@@ -4,7 +4,7 @@
 
 #define BBO_HIDDEN __attribute__((visibility("hidden")))
 
-BBO_HIDDEN const void* tiled_kernel();
+BBO_HIDDEN const void* tiled_kernel(bool team);  // a team of workgroups per model
 // unit tiles per wave, waves, output slots; one function per number of 16-wide k tiles of the input layer
 BBO_HIDDEN const void* small_kernel1(int nt, int waves, int co);
 BBO_HIDDEN const void* small_kernel2(int nt, int waves, int co);

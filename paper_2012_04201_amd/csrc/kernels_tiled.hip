@@ -5,6 +5,8 @@
 
 namespace {
 
+typedef const __attribute__((address_space(4))) TItem ConstTItem;
+
 __global__ __launch_bounds__(TB_THREADS) void k_train_tiled(const TrainParams P) {
   extern __shared__ __align__(16) char smem[];
   __shared__ int s_item;
@@ -16,12 +18,36 @@ __global__ __launch_bounds__(TB_THREADS) void k_train_tiled(const TrainParams P)
     __syncthreads();
     const int item = __builtin_amdgcn_readfirstlane(s_item);
     if (item >= P.n_items) break;
-    const __attribute__((address_space(4))) TItem* ti = (const __attribute__((address_space(4))) TItem*)P.items + item / P.n_folds;
-    Tiled T{P, ti->d, ti->y, slot, smem, red, item % P.n_folds};
-    T.run();
+    ConstTItem* ti = (ConstTItem*)P.items + item / P.n_folds;
+    Tiled<false> T{P, ti->d, ti->y, slot, smem, red, item % P.n_folds, Team{nullptr, 0, 1}, nullptr};
+    uint32_t meetings = 0;
+    T.run(meetings);
+  }
+}
+
+// A team of workgroups per model: workgroup (j * team_size + m) * 8 + x is member m of team 8 j + x, and the slot is the item's.
+__global__ __launch_bounds__(TB_THREADS) void k_train_tiled_team(const TrainParams P) {
+  extern __shared__ __align__(16) char smem[];
+  __shared__ int s_item, s_met;
+  __shared__ Team s_team;
+  __shared__ double red[TB_THREADS / 64];
+  const int x = blockIdx.x & 7, j = (int)(blockIdx.x >> 3) / P.team_size, m = (int)(blockIdx.x >> 3) % P.team_size;
+  if (threadIdx.x == 0) s_team.join(P.teams + (j * 8 + x) * TB_TEAM_WORDS, m, P.team_size);
+  __syncthreads();
+  const Team team{uniform(s_team.ctl), uniform(s_team.member), uniform(s_team.members)};
+  uint32_t meetings = 0;
+  for (int turn = 1;; turn++) {
+    __syncthreads();
+    if (threadIdx.x == 0) s_item = team.next_item(P.queue, P.n_items, turn);
+    __syncthreads();
+    const int item = __builtin_amdgcn_readfirstlane(s_item);
+    if (item >= P.n_items) break;
+    ConstTItem* ti = (ConstTItem*)P.items + item / P.n_folds;
+    Tiled<true> T{P, ti->d, ti->y, P.slots + (uint64_t)item * P.slot_bytes, smem, red, item % P.n_folds, team, &s_met};
+    T.run(meetings);
   }
 }
 
 }  // namespace
 
-const void* tiled_kernel() { return (const void*)k_train_tiled; }
+const void* tiled_kernel(bool team) { return team ? (const void*)k_train_tiled_team : (const void*)k_train_tiled; }

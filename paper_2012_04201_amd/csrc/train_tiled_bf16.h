@@ -181,6 +181,79 @@ __device__ inline bf16x8 lds_operand_tr(const char* base, int ld, int r0, int u0
   return u.v;
 }
 
+// Several workgroups that train one model together (calls with few models for the chip).  All of them run the forward pass
+// and the data gradients, on inputs of their own in LDS and the same weights, so they agree on every activation and delta
+// bit for bit; what they share out are the tiles of the weight gradients with the optimizer's state, which take most of a
+// step of few rows.  A member's new weights reach the others through the L2 of their XCD, with one meeting a step: the
+// operand copies and biases are double-buffered by step parity, so nobody writes what a slower member still reads.
+//
+// A team forms when the kernel starts: workgroups b, b + 8, b + 16, .. lie on one XCD as a rule, but it is the hardware's
+// own number that decides, and only workgroups that are running are counted in.  The leader waits for the others for a
+// bounded time (they may have no CU yet), closes the list and says who is in; a member that has waited as long for the
+// leader takes itself off the list.  Whoever is not in works alone, as a team of one.  So every later wait is for a
+// workgroup that runs.
+//
+// What bounds a team's step: what its members all do.  128-256-256-10, 64 rows a step, 64 models, k cycles with one workgroup
+// a model and with four: weight gradients 74 and 39 (the state of all models in flight comes from the memory-side cache),
+// forward pass 28 and 29, data gradients 19 and 20, rows 11 and 12, the meeting 1.
+constexpr int TB_TEAM_MAX = 8;
+constexpr int TB_TEAM_WORDS = 16;  // of a team's control block: [0..1] who came, [2] who is in, [3] item, [8..] members' meetings
+constexpr int TB_JOIN_POLLS = 200;      // about 100 us
+constexpr int TB_MEET_POLLS = 1 << 23;  // seconds: the members all run, so only a fault elsewhere lets a wait end here
+struct Team {
+  uint32_t* ctl;
+  int member, members;
+  // Called by one thread of a workgroup: its place among the `size` workgroups that share `ctl`.
+  __device__ void join(uint32_t* ctl_, int m, int size) {
+    unsigned long long* list = (unsigned long long*)ctl_;
+    constexpr unsigned long long CLOSED = 1ull << 63;
+    const unsigned long long me = 8 | (__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 7);  // XCC_ID
+    ctl = ctl_;
+    member = 0;
+    members = 1;
+    unsigned long long seen = atomicOr(list, me << (4 * m));
+    uint32_t in = 0;
+    if (m == 0) {
+      unsigned long long all = 0;
+      for (int k = 0; k < size; k++) all |= 8ull << (4 * k);
+      for (int i = 0; i < TB_JOIN_POLLS && (seen & all) != all; i++) {
+        __builtin_amdgcn_s_sleep(8);
+        seen = atomicOr(list, 0ull);
+      }
+      seen = atomicOr(list, CLOSED) | me;
+      for (int k = 0; k < size; k++) in |= ((seen >> (4 * k)) & 15) == me ? 1u << k : 0u;
+      atomicExch(&ctl[2], in | 0x100u);
+    } else {
+      if (seen & CLOSED) return;
+      for (int i = 0; i < 2 * TB_JOIN_POLLS && !in; i++) {
+        __builtin_amdgcn_s_sleep(8);
+        in = atomicOr(&ctl[2], 0u);
+      }
+      if (!in) {
+        if (!(atomicAnd(list, ~(15ull << (4 * m))) & CLOSED)) return;
+        while (!(in = atomicOr(&ctl[2], 0u))) {  // the leader has just closed the list
+        }
+      }
+    }
+    if (!((in >> m) & 1u)) return;
+    member = __popc(in & ((1u << m) - 1u));
+    members = __popc(in & 0xffu);
+  }
+  // Called by one thread: the team's turn-th item.
+  __device__ int next_item(int32_t* queue, int n_items, int turn) const {
+    if (members == 1) return atomicAdd(queue, 1);
+    if (member == 0) {
+      const int item = min(atomicAdd(queue, 1), n_items);
+      atomicExch(&ctl[3], (uint32_t)(turn << 16 | item));
+      return item;
+    }
+    uint32_t v;
+    while ((v = atomicOr(&ctl[3], 0u)) >> 16 != (uint32_t)turn) __builtin_amdgcn_s_sleep(4);
+    return (int)(v & 0xffffu);
+  }
+};
+
+template <bool TEAM>
 struct Tiled {
   const TrainParams& P;
   const ConstItemDesc& it;
@@ -189,6 +262,45 @@ struct Tiled {
   char* lds;
   double* red;
   int fl;  // which row list
+  Team team;
+  int* met;  // LDS: a meeting has come about
+
+  // The wave's number among all waves that share the tiles of a weight gradient, and how many those are.
+  __device__ __forceinline__ int team_wave() const { return uniform((int)(threadIdx.x >> 6)) + (TEAM ? team.member * TB_WAVES : 0); }
+  __device__ __forceinline__ int team_waves() const { return TEAM ? team.members * TB_WAVES : TB_WAVES; }
+  // What the members have stored is seen by all of them afterwards, where it is read with from_team(): a member's stores are in
+  // the L2 when its waves have waited for them.  n: the how many-th meeting.
+  __device__ __forceinline__ bool meet(uint32_t n) const {
+    if (!TEAM || team.members == 1) {
+      __syncthreads();
+      return true;
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      uint32_t* at = team.ctl + 8;
+      if (threadIdx.x == 0) __hip_atomic_store(at + team.member, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      const uint32_t* other = at + min((int)threadIdx.x, team.members - 1);
+      int i = 0;
+      while (__any((int)(__hip_atomic_load(other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n)) && i < TB_MEET_POLLS) i++;
+      if (threadIdx.x == 0) *met = i < TB_MEET_POLLS ? 1 : 0;
+    }
+    __syncthreads();
+    return *met != 0;
+  }
+  // A value of 8 or 16 bytes, `off` bytes (the lane's part, the wave's part) behind a pointer that is the same for all lanes.  What
+  // another member of a team may have written is read past the CU's vector cache (sc1), which may hold an older state of it:
+  // invalidating that cache at a meeting would take the agent-scope instruction, which drops lines of the L2 too and takes 7 us.
+  template <class V>
+  __device__ __forceinline__ static V from_team(const void* base, uint32_t lane_off, uint32_t wave_off) {
+    if constexpr (!TEAM) {
+      return *(const V*)((const char*)base + wave_off + lane_off);
+    } else {
+      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x40000000u, 0x00020000);
+      if constexpr (sizeof(V) == 16) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, wave_off, 16));
+      if constexpr (sizeof(V) == 8) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, lane_off, wave_off, 16));
+    }
+  }
 
   // The thread index as a value the compiler cannot see through: what a phase derives from it (lane
   // coordinates, LDS and global addresses) is then recomputed where it is used, in a few instructions, instead
@@ -200,6 +312,8 @@ struct Tiled {
   }
   __device__ __forceinline__ float* fp(uint64_t off) const { return (float*)(slot + off); }
   __device__ __forceinline__ __bf16* bp(uint64_t off) const { return (__bf16*)(slot + off); }
+  // the bias of layer l; a team's is double-buffered by step parity, like the operand copies (no partial gradients: one chunk a step)
+  __device__ __forceinline__ float* bias_of(int l, int par) const { return fp(TEAM && par ? y.bg[l] : y.bias[l]); }
   __device__ __forceinline__ char* buf() const { return lds + TB_LDS_BUF; }
   __device__ __forceinline__ char* dbuf() const { return lds + TB_LDS_DELTA; }
   __device__ __forceinline__ int32_t* rowlist() const { return (int32_t*)(lds + TB_LDS_ROWS); }
@@ -226,7 +340,7 @@ struct Tiled {
   // ---- parameters -------------------------------------------------------
   __device__ __forceinline__ void store_param(int l, int k, int j, bool isb, float val, int par) const {
     if (isb) {
-      fp(y.bias[l])[j] = val;
+      bias_of(l, par)[j] = val;
     } else {
       fp(y.w[l])[sidx(l, k, j)] = val;
       bp(y.oi[l][par])[oidx(l, j, k)] = (__bf16)val;
@@ -240,7 +354,7 @@ struct Tiled {
       const int fi = y.U[l], fo = y.U[l + 1];
       const uint64_t kw = key_fold(km, 16 + 2 * l), kb = key_fold(km, 16 + 2 * l + 1);
       const float bound = it.bound[l];
-      for (int i = threadIdx.x; i < fi * fo + fo; i += blockDim.x) {
+      for (int i = threadIdx.x + (TEAM ? team.member * TB_THREADS : 0); i < fi * fo + fo; i += team_waves() * 64) {
         const bool isb = i >= fi * fo;
         const int e = isb ? i - fi * fo : i;
         const uint32_t k24 = (uint32_t)(key_fold(isb ? kb : kw, (uint64_t)e) >> 40);
@@ -337,8 +451,13 @@ struct Tiled {
   __device__ __forceinline__ void spill_transposed(int l) const {
     const int t_ = tid(), lane = t_ & 63, w = t_ >> 6, li = lane & 15, q = lane >> 4;
     __bf16* T = bp(y.T[l]);
-    const int mta = (y.U[l] + 15) / 16;  // unit tiles that hold real units: the others are never read back
-    for (int mt = 0; mt < mta; mt++) {
+    int mt0 = 0, mta = (y.U[l] + 15) / 16;  // unit tiles that hold real units: the others are never read back
+    if (TEAM) {  // the in tiles of the member's share of wgrad_stream()'s tiles (a tile of two members' comes from both, alike)
+      const int Ne = (y.U[l + 1] + 15) / 16, TT = mta * Ne;
+      mt0 = team.member * TT / team.members / Ne;
+      mta = ((team.member + 1) * TT / team.members + Ne - 1) / Ne;
+    }
+    for (int mt = mt0; mt < mta; mt++) {
       const bf16x8 v = lds_operand_tr(buf(), TB_S, 32 * w, mt * 16, li, q);
       *(bf16x8*)(T + (((size_t)mt * 8 + w) * 16 + li) * 32 + q * 8) = v;
     }
@@ -354,16 +473,27 @@ struct Tiled {
   template <bool TR>
   __device__ __forceinline__ void gemm_operands(const __bf16* __restrict__ A, int kbn, int mt_a, i32x4 (&ar)[8][2]) const {
     const int t_ = tid(), lane = t_ & 63, w = t_ >> 6, li = lane & 15, q = lane >> 4;
-    const __bf16* A0 = TR ? A + ((size_t)(lane >> 5) * mt_a + 2 * w) * 256 + (lane & 31) * 8
-                          : A + (size_t)(2 * w) * kbn * 512 + opnd_lane(li, q);
-    const __bf16* A1 = A0 + (TR ? (size_t)256 : (size_t)kbn * 512);
-    const size_t kstep = TR ? (size_t)mt_a * 512 : (size_t)512;
+    if constexpr (TEAM) {
+      const uint32_t first = 2u * (TR ? ((lane >> 5) * mt_a + 2 * w) * 256 + (lane & 31) * 8 : 2 * w * kbn * 512 + opnd_lane(li, q));
+      const uint32_t second = TR ? 512u : (uint32_t)kbn * 1024u, kstep = TR ? (uint32_t)mt_a * 1024u : 1024u;
 #pragma unroll
-    for (int kb = 0; kb < 8; kb++)
-      if (kb < kbn) {
-        ar[kb][0] = *(const i32x4*)(A0 + (size_t)kb * kstep);
-        ar[kb][1] = *(const i32x4*)(A1 + (size_t)kb * kstep);
-      }
+      for (int kb = 0; kb < 8; kb++)
+        if (kb < kbn) {
+          ar[kb][0] = from_team<i32x4>(A, first, kb * kstep);
+          ar[kb][1] = from_team<i32x4>(A, first, kb * kstep + second);
+        }
+    } else {
+      const __bf16* A0 = TR ? A + ((size_t)(lane >> 5) * mt_a + 2 * w) * 256 + (lane & 31) * 8
+                            : A + (size_t)(2 * w) * kbn * 512 + opnd_lane(li, q);
+      const __bf16* A1 = A0 + (TR ? (size_t)256 : (size_t)kbn * 512);
+      const size_t kstep = TR ? (size_t)mt_a * 512 : (size_t)512;
+#pragma unroll
+      for (int kb = 0; kb < 8; kb++)
+        if (kb < kbn) {
+          ar[kb][0] = *(const i32x4*)(A0 + (size_t)kb * kstep);
+          ar[kb][1] = *(const i32x4*)(A1 + (size_t)kb * kstep);
+        }
+    }
     if (TR) {
       char* patch = lds + TB_LDS_STAGE + w * 2048;
 #pragma unroll
@@ -418,9 +548,9 @@ struct Tiled {
     const int t_ = tid(), lane = t_ & 63, w = t_ >> 6, q = lane >> 4;
     if (32 * w < y.UP[l + 1]) {
       gemm_operands<false>(bp(y.oi[l][par]), y.UP[l] / 32, 0, ar);
-      const float* bias = fp(y.bias[l]);
+      const float* bias = bias_of(l, par);
 #pragma unroll
-      for (int ub = 0; ub < 2; ub++) bv[ub] = *(const f32x4*)(bias + 32 * w + 16 * ub + 4 * q);
+      for (int ub = 0; ub < 2; ub++) bv[ub] = from_team<f32x4>(bias, (32 * w + 16 * ub + 4 * q) * 4, 0);
     }
   }
 
@@ -492,7 +622,7 @@ struct Tiled {
         const char* db = dbuf() + ((size_t)li * 16 + 4 * q) * 2;
 #pragma unroll
         for (int ub = 0; ub < 2; ub++) {
-          const bf16x4 a = *(const bf16x4*)(A + ((size_t)(2 * w + ub) * 16 + li) * 16 + 4 * q);
+          const bf16x4 a = from_team<bf16x4>(A, (((2 * w + ub) * 16 + li) * 16 + 4 * q) * 2, 0);
 #pragma unroll
           for (int jb = 0; jb < 16; jb++)
             if (jb < njb) {
@@ -539,17 +669,17 @@ struct Tiled {
   __device__ __forceinline__ void fetch_out(int par, i32x4 (&ar)[8][2]) const {
     const int l = y.L - 1, lane = tid() & 63, li = lane & 15, q = lane >> 4;
     const int kbn = y.UP[l] / 32;
-    const __bf16* Ap = bp(y.oi[l][par]) + opnd_lane(li, q);
+    const __bf16* A = bp(y.oi[l][par]);
 #pragma unroll
     for (int kb = 0; kb < 8; kb++)
-      if (kb < kbn) ar[kb][0] = *(const i32x4*)(Ap + kb * 512);
+      if (kb < kbn) ar[kb][0] = from_team<i32x4>(A, opnd_lane(li, q) * 2, kb * 1024);
   }
 
   template <bool TRAIN>
-  __device__ __forceinline__ void forward_out(const i32x4 (&ar)[8][2], int rows, float inv_mb, double& lsum, double& hits) const {
+  __device__ __forceinline__ void forward_out(const i32x4 (&ar)[8][2], int par, int rows, float inv_mb, double& lsum, double& hits) const {
     const int l = y.L - 1, c = y.U[y.L];
     const int t_ = tid(), lane = t_ & 63, w = t_ >> 6, li = lane & 15, q = lane >> 4;
-    const float* bias = fp(y.bias[l]);
+    const float* bias = bias_of(l, par);
     const int32_t* rl = rowlist();
     const int32_t* tg = targets();
     char* db = dbuf();
@@ -572,7 +702,7 @@ struct Tiled {
         const int r = 32 * w + jb * 16 + li;
         const int row = rl[r];
         const bool valid = r < rows && row >= 0;
-        const f32x4 b = *(const f32x4*)(bias + 4 * q);
+        const f32x4 b = from_team<f32x4>(bias, 16 * q, 0);
         float z[4];
 #pragma unroll
         for (int e = 0; e < 4; e++) z[e] = acc[e] + b[e];
@@ -887,11 +1017,12 @@ struct Tiled {
   template <bool ADAM, bool FROM_X, int LD, int KB>
   __device__ __forceinline__ void wgrad_stream(int l, const OptC& oc, int par_next, float* rec) const {
     const int t_ = tid(), lane = t_ & 63, li = lane & 15, q = lane >> 4;
-    const int w = uniform(t_ >> 6);
+    const int w = uniform(t_ >> 6), tw = team_wave(), tws = team_waves();
     float* W = uniform(fp(y.w[l]));
     float* Mo = uniform(fp(y.m[l]));
     float* Vo = uniform(fp(y.v[l]));
-    float* bias = uniform(fp(y.bias[l]));
+    const float* bias = uniform(bias_of(l, par_next ^ 1));
+    float* bias_next = uniform(bias_of(l, par_next));
     float* bm = uniform(fp(y.bm[l]));
     float* bv = uniform(fp(y.bv[l]));
     __bf16* oi = uniform(bp(y.oi[l][par_next]));
@@ -900,7 +1031,7 @@ struct Tiled {
     constexpr int S = TB_S;
     const int Mt = uniform(y.UP[l]) / 16, Nt = uniform(y.UP[l + 1]) / 16, Mr = (fi + 15) / 16, Ne = (fo + 15) / 16;
     const int cw = y.cw[l], cb = y.cb[l], Pn = y.P;
-    const int TT = Mr * Ne, t0 = w * TT / TB_WAVES, t1 = (w + 1) * TT / TB_WAVES;
+    const int TT = Mr * Ne, t0 = tw * TT / tws, t1 = (tw + 1) * TT / tws;
     constexpr int D = KB == 8 ? TB_STATE_AHEAD : TB_STATE_AHEAD_HALF;
     struct St {
       f32x4 w, m, v;
@@ -923,11 +1054,11 @@ struct Tiled {
         b[kb] = u.v;
       }
     };
-    // bias state of the wave's bias tiles (out tiles w and w + 8)
+    // bias state of the wave's bias tiles (out tiles w and w + 8; a team's waves have one at most)
     float bw_[2], bm_[2], bv_[2];
 #pragma unroll
     for (int i = 0; i < 2; i++) {
-      const int j = min(w + 8 * i, Ne - 1) * 16 + li;
+      const int j = min(tw + tws * i, Ne - 1) * 16 + li;
       bw_[i] = bias[j];
       bm_[i] = bm[j];
       bv_[i] = ADAM ? bv[j] : 0.f;
@@ -1093,7 +1224,7 @@ struct Tiled {
     const bf16x8 a1 = as_bf16x8(i32x4{ones, ones, ones, ones});
 #pragma unroll
     for (int i = 0; i < 2; i++) {
-      const int nt = w + 8 * i;
+      const int nt = tw + tws * i;
       if (nt < Ne) {
         bf16x8 b[KB];
         delta_operands(nt, b);
@@ -1108,7 +1239,7 @@ struct Tiled {
             rec[1 + cb + j] = g[0];
             rec[1 + Pn + cb + j] = wr;
           }
-          bias[j] = wr;
+          bias_next[j] = wr;
           bm[j] = mr;
           if (ADAM) bv[j] = vr;
         }
@@ -1124,11 +1255,12 @@ struct Tiled {
   __device__ __forceinline__ void wgrad_last(const OptC& oc, int par_next, float* rec) const {
     const int l = y.L - 1;
     const int t_ = tid(), lane = t_ & 63, li = lane & 15, q = lane >> 4;
-    const int w = uniform(t_ >> 6);
+    const int w = uniform(t_ >> 6), tw = team_wave(), tws = team_waves();
     float* W = uniform(fp(y.w[l]));
     float* Mo = uniform(fp(y.m[l]));
     float* Vo = uniform(fp(y.v[l]));
-    float* bias = uniform(fp(y.bias[l]));
+    float* bias = uniform(bias_of(l, par_next ^ 1));
+    float* bias_next = uniform(bias_of(l, par_next));
     float* bm = uniform(fp(y.bm[l]));
     float* bv = uniform(fp(y.bv[l]));
     __bf16* oi = uniform(bp(y.oi[l][par_next]));
@@ -1155,7 +1287,7 @@ struct Tiled {
     St st[2];
 #pragma unroll
     for (int k = 0; k < 2; k++) {
-      const int mt = w + 8 * k;
+      const int mt = tw + tws * k;
       // out of range: tiles past the layer, and the lanes whose elements are all pad (out unit or in units)
       const uint32_t vo = lane16 + (mt < Mr && li < fo && mt * 16 + 4 * q < fi ? 0u : OUT_OF_RANGE);
       st[k].w = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rW, vo, mt * 1024, LD));
@@ -1172,7 +1304,7 @@ struct Tiled {
     for (int kb = 0; kb < KB; kb++) b[kb] = lds_operand_tr(dbuf(), 16, kb * 32, 0, li, q);
 #pragma unroll
     for (int k = 0; k < 2; k++) {
-      const int mt = w + 8 * k;
+      const int mt = tw + tws * k;
       if (mt < Mr) {
         f32x4 g = zero4;
 #pragma unroll
@@ -1214,7 +1346,7 @@ struct Tiled {
         }
       }
     }
-    if (w == (Mr & 7)) {  // bias gradient: the column sums of the delta, through a row of ones
+    if (tw == Mr % tws) {  // bias gradient: the column sums of the delta, through a row of ones
       const int ones = li == 0 ? 0x3F803F80 : 0;  // two bf16 ones
       const bf16x8 a1 = as_bf16x8(i32x4{ones, ones, ones, ones});
       f32x4 g = zero4;
@@ -1227,7 +1359,7 @@ struct Tiled {
           rec[1 + cb + li] = g[0];
           rec[1 + Pn + cb + li] = wr;
         }
-        bias[li] = wr;
+        bias_next[li] = wr;
         bm[li] = mr;
         if (ADAM) bv[li] = vr;
       }
@@ -1246,7 +1378,7 @@ struct Tiled {
   // With ordinary stores as well: those 160 models 69 -> 59, 256 of 128-256-10 50 -> 42, 128 of 128-256-256-10 99 -> 95,
   // a full chip of wide models the same.
   __device__ __forceinline__ bool state_cached() const {
-    return gridDim.x <= 128 || gridDim.x * P.slot_bytes <= TB_CACHED_SLOTS || ((blockIdx.x >> 3) & 3) == 0;
+    return TEAM || gridDim.x <= 128 || gridDim.x * P.slot_bytes <= TB_CACHED_SLOTS || ((blockIdx.x >> 3) & 3) == 0;
   }
 
   __device__ __forceinline__ void wgrad(int l, int KB, bool first, bool last, const OptC& oc, int par_next,
@@ -1280,7 +1412,7 @@ struct Tiled {
         one_chunk(std::true_type{}, std::integral_constant<int, 8>{});
       else
         one_chunk(std::true_type{}, std::integral_constant<int, 4>{});
-    } else {
+    } else if (!TEAM) {  // (a team's models take every step in one chunk)
       wgrad_t(l, KB, first, last, oc, par_next, rec);
     }
     __syncthreads();
@@ -1331,12 +1463,13 @@ struct Tiled {
       }
     }
     if (w < KB)
-      forward_out<TRAIN>(ar, rows, inv_mb, lsum, hits);
+      forward_out<TRAIN>(ar, par, rows, inv_mb, lsum, hits);
     else if (TRAIN)  // no output delta for the rows of this wave: zeros (see backward_data)
       *(uint4*)(dbuf() + (32 * w) * 32 + (threadIdx.x & 63) * 16) = uint4{0, 0, 0, 0};
   }
 
-  __device__ __forceinline__ void run() const {
+  // meetings: of the team so far
+  __device__ __forceinline__ void run(uint32_t& meetings) const {
     const int L = y.L;
     const int n_tr = P.counts[2 * fl], n_va = P.counts[2 * fl + 1];
     const int32_t* tr = P.train_idx + (int64_t)fl * P.n;
@@ -1351,13 +1484,13 @@ struct Tiled {
     {
       uint4* z = (uint4*)slot;
       const uint64_t n16 = y.total / 16;
-      for (uint64_t i = threadIdx.x; i < n16; i += blockDim.x) z[i] = uint4{0, 0, 0, 0};
+      for (uint64_t i = threadIdx.x + (TEAM ? team.member * TB_THREADS : 0); i < n16; i += team_waves() * 64) z[i] = uint4{0, 0, 0, 0};
       // The activation buffer too: rows past a ragged chunk are never written, but the weight gradients read
       // them (against zero deltas), so they must hold finite numbers whatever ran on this CU before.
       uint4* zb = (uint4*)buf();
       for (uint32_t i = threadIdx.x; i < TB_ROWS * TB_S * 2 / 16; i += blockDim.x) zb[i] = uint4{0, 0, 0, 0};
     }
-    __syncthreads();
+    bool together = meet(++meetings);
     double b1t = 1.0, b2t = 1.0;
     int64_t gstep = 0;
     int e0 = 0, st0 = 0;
@@ -1373,7 +1506,7 @@ struct Tiled {
     } else {
       init_params();
     }
-    __syncthreads();
+    together &= meet(++meetings);
 
     OptC oc;
     oc.adam = it.solver == BBO_ADAM;
@@ -1438,10 +1571,12 @@ struct Tiled {
           const double data = block_sum(lsum, red) / (double)mb;
           if (threadIdx.x == 0) rec[0] = (float)(data + 0.5 * (double)it.alpha * pen / (double)mb);
         }
+        if (TEAM) together &= meet(++meetings);
       }
       }
       float watched = 0.f;
       if (watch && !final && !sp.n_hold) watched = (float)(block_sum(esum, red) / (double)n_fit);
+      if (TEAM && final && team.member > 0) break;  // the leader scores
       if (final && have_best) restore_best((int)(gstep & 1));
       if (final || (watch && sp.n_hold)) {
         // loss (and second score) of a list of rows under the current weights
@@ -1459,7 +1594,7 @@ struct Tiled {
         if (final) {
           if (threadIdx.x == 0) {
             float* out = P.item_out + 2 * ((int64_t)it.b * P.n_folds + fl);
-            out[0] = n_va > 0 ? (float)(lsum / (double)n_va) : __builtin_nanf("");
+            out[0] = n_va > 0 && together ? (float)(lsum / (double)n_va) : __builtin_nanf("");
             out[1] = n_va > 0 ? (float)(hits / (double)n_va) : __builtin_nanf("");  // accuracy | mean absolute error
           }
           break;
@@ -1468,7 +1603,7 @@ struct Tiled {
       }
       if (watch) {
         stop = plateau.stop_after(watched, it.tol, it.patience);
-        if (sp.n_hold && plateau.improved) {
+        if (!TEAM && sp.n_hold && plateau.improved) {  // (a team's models set no rows aside)
           keep_best();
           have_best = true;
         }
