@@ -338,7 +338,13 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
     f32x4 c[NT];
 #pragma unroll
-    for (int i = 0; i < NT; i++) c[i] = f32x4{R.bw[i], R.bw[i], R.bw[i], R.bw[i]};
+    for (int i = 0; i < NT; i++) {
+      float x = R.bw[i];
+      // (as in the small kernel: keeps the small parameters out of scratch memory; with four input tiles split the registers for
+      // them are not there, and 62 instead of 19 spill)
+      if (!(SPLIT && KT == 4)) asm("" : "+v"(x));
+      c[i] = f32x4{x, x, x, x};
+    }
     if constexpr (SPLIT) {
 #pragma unroll
       for (int kb = 0; kb < KB; kb++) sm_products<NT - (ALL ? 0 : 1)>(Base::by_row(Base::planes(b), r, kb), R.w.p[kb], c);
