@@ -121,8 +121,14 @@ __host__ __device__ constexpr int sm_columns(int co) { return co == 2 ? 1 : co; 
 __host__ __device__ constexpr bool sm_split(int kt, int nt, int co) { return (kt == 2 && nt >= 2) || (kt == 4 && nt == 1 && co <= 2); }
 // With four input tiles three buffers of planes would leave room for one workgroup a CU: two, and a second barrier.
 __host__ __device__ constexpr int sm_barriers(int kt, int nt, int co) { return kt == 4 && sm_split(kt, nt, co) ? 2 : 1; }
+// Hidden deltas without the output weight (see Small::FACTORED): the rows' deltas lie in LDS as planes too.
+__host__ __device__ constexpr bool sm_factored(int kt, int nt, int co) { return sm_columns(co) == 1 && (kt > 1 || sm_split(kt, nt, co)); }
+__host__ __device__ constexpr uint32_t sm_delta_planes(int kt, int nt, int co) {
+  return sm_factored(kt, nt, co) && sm_split(kt, nt, co) ? 3 * SM_RC * 2 : 0;
+}
 __host__ __device__ constexpr uint32_t sm_fixed_lds(int kt, int nt, int co, int waves) {
-  return pipe_lds(kt, 4 - sm_barriers(kt, nt, co), sm_split(kt, nt, co)) + (2 * waves + 1) * sm_columns(co) * SM_RC * 4;
+  return pipe_lds(kt, 4 - sm_barriers(kt, nt, co), sm_split(kt, nt, co)) + (2 * waves + 1) * sm_columns(co) * SM_RC * 4 +
+         sm_delta_planes(kt, nt, co);
 }
 
 // ... and the row tables behind `fixed` bytes of everything else
@@ -338,6 +344,9 @@ __device__ __forceinline__ void sm_split2(float a, float b, uint32_t& h, uint32_
 __device__ __forceinline__ f32x4 sm_mfma(const u32x4& a, const u32x4& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
+// An activation's derivative, 1 or 0 (0 for a NaN), and two of them as a mask of two bfloat16 values.
+__device__ __forceinline__ float sm_active(float a) { return __builtin_amdgcn_fmed3f(__builtin_ldexpf(a, 200), 0.f, 1.f); }
+__device__ __forceinline__ uint32_t sm_mask(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pknorm_u16(a, b)); }
 // The s-th of the six products, smallest first.
 template <int S>
 __device__ __forceinline__ f32x4 sm_product(const SmPlanes& a, const SmPlanes& b, const f32x4& c) {
@@ -965,19 +974,27 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
   static constexpr int NSMALL = NT * (1 + CO) + CO, NG = (NSMALL + 3) / 4;
   static constexpr bool SPLIT = sm_split(KT, NT, CO);
   static constexpr int KB = sm_blocks(KT);
+  // One output column: a unit's hidden deltas are its output weight times the rows' deltas where it is active, and the
+  // weight is the same for a whole step.  So the step's sums leave it out, and its gradients take it in at the end: with split
+  // products the deltas are then split once a row and not once a row and unit.  2000 models 569 x 30, us a call before and
+  // after: 128 units, 24 and 128 rows a step 2026 and 1959, 1057 and 1003; 190 units 3764 and 3145, 1656 and 1388.  fp32 products
+  // save a multiplication of each value for one of each parameter and step: 2 % at 45 inputs, a loss at 13.
+  static constexpr bool FACTORED = sm_factored(KT, NT, CO);
   struct State {
     HiddenWeights<KT, NT, SPLIT> w;
     f32x4 m[NT][KT], v[NT][KT], g[NT][KT];  // hidden layer: lane (unit li, columns 16 kk + 4q + e)
     float pw[NG], pm[NG], pv[NG];                      // the small parameters and their moments
     float bw[NT], w2[NT][ZO], ow[ZO];                  // the same as the products want them: alike in the four q
     float bg[NT], g2[NT][ZO], og[ZO];                  // the lane's share of their gradients
+    __device__ __forceinline__ float factor(int i) const { return FACTORED ? w2[i][0] : 1.f; }  // (of g and bg)
   };
 
   struct Acts {
     f32x4 a[NT][4];  // activations of the wave's tiles: lane (unit li, rows 16 r + 4q..+3)
   };
   // offsets in floats
-  static constexpr int O_ZP = Base::O_OWN, O_D2 = O_ZP + 2 * W * ZO * SM_RC, O_TOP = O_D2 + ZO * SM_RC;
+  static constexpr int O_ZP = Base::O_OWN, O_D2 = O_ZP + 2 * W * ZO * SM_RC, O_DP = O_D2 + ZO * SM_RC,
+                       O_TOP = O_DP + (int)sm_delta_planes(KT, NT, CO) / 4;
   static_assert(O_TOP * 4 == sm_fixed_lds(KT, NT, CO, W), "LDS layout");
   // does the wave's i-th tile exist?  Only the last one can be missing.
   __device__ __forceinline__ bool has(int i, int w) const { return i + 1 < NT || w + i * W < nut; }
@@ -1063,7 +1080,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
     float x[4 * NG];
 #pragma unroll
     for (int i = 0; i < NT; i++) {
-      x[i * (1 + CO)] = R.bg[i];
+      x[i * (1 + CO)] = R.bg[i] * R.factor(i);
 #pragma unroll
       for (int cc = 0; cc < ZO; cc++) {
         x[i * (1 + CO) + CO - ZO + 1 + cc] = R.g2[i][cc];
@@ -1186,7 +1203,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
       // them registers, and kept the small parameters and their gradients in scratch memory, where each wait is one for
       // the inputs in flight too.  2000 models 569 x 30, 128 units, 24 rows a step: 2372 us a call then, 1961 now.
       float x = R.bw[i];
-      if (NT > 1) asm("" : "+v"(x));
+      if (NT > 1 || KT > 1) asm("" : "+v"(x));
       c[i] = f32x4{x, x, x, x};
     }
     if constexpr (SPLIT) {
@@ -1281,6 +1298,14 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
         d2[cc * SM_RC] = dl[cc];
         R.og[cc] += dl[cc];
       }
+      if constexpr (FACTORED && SPLIT) {
+        uint16_t* dp = (uint16_t*)f(O_DP) + lane;
+        uint32_t h, m, l;
+        sm_split2(dl[0], 0.f, h, m, l);
+        dp[0] = (uint16_t)h;
+        dp[SM_RC] = (uint16_t)m;
+        dp[2 * SM_RC] = (uint16_t)l;
+      }
       __builtin_amdgcn_wave_barrier();
     }
   }
@@ -1299,7 +1324,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           const float av = acc[i][r][e];
-          float sum = dv[0][e] * R.w2[i][0];
+          float sum = FACTORED ? dv[0][e] : dv[0][e] * R.w2[i][0];
           R.g2[i][0] += av * dv[0][e];
 #pragma unroll
           for (int cc = 1; cc < ZO; cc++) {
@@ -1332,27 +1357,77 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
           if (i + 1 < NT || ALL) R.g[i][kk] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], dh[i][e], R.g[i][kk], 0, 0, 0);
       }
   }
+  // The hidden deltas of row tiles r and r + 1 (BOTH) as planes, and their shares of the small parameters' gradients.
+  template <bool ALL, int TILES, bool BOTH>
+  __device__ __forceinline__ void split_planes(State& R, int r, const f32x4 (&acc)[NT][4], SmPlanes (&dp)[TILES]) const {
+#pragma unroll
+    for (int t = 0; t < 2; t++) {
+      f32x4 dh[NT];
+      if (t == 0 || BOTH) deltas<ALL>(R, r + t, acc, dh);
+#pragma unroll
+      for (int i = 0; i < TILES; i++)
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+          uint32_t h = 0u, m = 0u, l = 0u;
+          if (t == 0 || BOTH) sm_split2(dh[i][2 * e], dh[i][2 * e + 1], h, m, l);
+          dp[i].h[2 * t + e] = h;
+          dp[i].m[2 * t + e] = m;
+          dp[i].l[2 * t + e] = l;
+        }
+    }
+  }
+  // The same without the unit's output weight: the rows' deltas, which outputs() has split once for all units, masked by
+  // the unit's activations.  Five vector instructions a value instead of eleven.
+  template <int TILES, bool BOTH>
+  __device__ __forceinline__ void masked_planes(State& R, int r, const f32x4 (&acc)[NT][4], SmPlanes (&dp)[TILES]) const {
+    const int o = ((tid() & 63) >> 4) * 16 + r * 4;
+    const uint16_t* s = (const uint16_t*)f(O_DP) + o;
+    u32x4 row[3];
+#pragma unroll
+    for (int j = 0; j < 3; j++) {
+      if (BOTH) {
+        row[j] = *(const u32x4*)(s + j * SM_RC);
+      } else {
+        const u32x2 x = *(const u32x2*)(s + j * SM_RC);
+        row[j] = u32x4{x[0], x[1], 0u, 0u};
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; t++) {
+      f32x4 dv;
+      if (t == 0 || BOTH) dv = *(const f32x4*)(f(O_D2) + o + 4 * t);
+#pragma unroll
+      for (int i = 0; i < TILES; i++)
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+          uint32_t on = 0u;
+          if (t == 0 || BOTH) {
+            float a[2];
+#pragma unroll
+            for (int j = 0; j < 2; j++) {
+              const float av = acc[i][r + t][2 * e + j], d = dv[2 * e + j];
+              a[j] = sm_active(av);
+              R.g2[i][0] = fmaf(av, d, R.g2[i][0]);
+              R.bg[i] = fmaf(a[j], d, R.bg[i]);
+            }
+            on = sm_mask(a[0], a[1]);
+          }
+          dp[i].h[2 * t + e] = row[0][2 * t + e] & on;
+          dp[i].m[2 * t + e] = row[1][2 * t + e] & on;
+          dp[i].l[2 * t + e] = row[2][2 * t + e] & on;
+        }
+    }
+  }
   // row tiles r and r + 1 (BOTH), which fill the 32 contracted rows of a product
   template <bool ALL, bool BOTH>
   __device__ __forceinline__ void backward_pair(State& R, const char* x, int r, const f32x4 (&acc)[NT][4]) const {
     constexpr int TILES = NT - (ALL ? 0 : 1);
     if constexpr (TILES > 0) {
       SmPlanes dp[TILES];
-#pragma unroll
-      for (int t = 0; t < 2; t++) {
-        f32x4 dh[NT];
-        if (t == 0 || BOTH) deltas<ALL>(R, r + t, acc, dh);
-#pragma unroll
-        for (int i = 0; i < TILES; i++)
-#pragma unroll
-          for (int e = 0; e < 2; e++) {
-            uint32_t h = 0u, m = 0u, l = 0u;
-            if (t == 0 || BOTH) sm_split2(dh[i][2 * e], dh[i][2 * e + 1], h, m, l);
-            dp[i].h[2 * t + e] = h;
-            dp[i].m[2 * t + e] = m;
-            dp[i].l[2 * t + e] = l;
-          }
-      }
+      if constexpr (FACTORED)
+        masked_planes<TILES, BOTH>(R, r, acc, dp);
+      else
+        split_planes<ALL, TILES, BOTH>(R, r, acc, dp);
 #pragma unroll
       for (int kk = 0; kk < KT; kk++) {
         f32x4 c[TILES];
@@ -1361,6 +1436,9 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
         sm_products<TILES>(Base::template by_column<BOTH>(x, r, kk), dp, c);
 #pragma unroll
         for (int i = 0; i < TILES; i++) R.g[i][kk] = c[i];
+      // (one column tile's operands at a time: 190 units, 24 and 128 rows a step, 3706 -> 3145 and 1480 -> 1388 us by what
+      // does not spill)
+      if constexpr (NT == 3) __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -1414,7 +1492,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
 #pragma unroll
           for (int e = 0; e < 4; e++) {
             float wr = x[e], mr = R.m[i][kk][e], vr = R.v[i][kk][e];
-            opt_update(o, R.g[i][kk][e] + o.am * wr, wr, mr, vr);
+            opt_update(o, fmaf(o.am, wr, R.g[i][kk][e] * R.factor(i)), wr, mr, vr);
             x[e] = wr;
             R.m[i][kk][e] = mr;
             R.v[i][kk][e] = vr;
@@ -1444,7 +1522,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           const int k = kk * 16 + 4 * q + e;
-          if (j < h && k < d) out[y.cw[0] + k * h + j] = GRAD ? R.g[i][kk][e] + am * x[e] : x[e];
+          if (j < h && k < d) out[y.cw[0] + k * h + j] = GRAD ? fmaf(am, x[e], R.g[i][kk][e] * R.factor(i)) : x[e];
         }
       }
     }
