@@ -153,6 +153,12 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
 
   static constexpr int NEAR = md_near(KT, NT, SPLIT), NREGM = NEAR ? NEAR : 1;
   static constexpr int KB = sm_blocks(KT);
+  // The forward pass takes the row tiles of a chunk together, except where their operands do not fit the registers: us a call one
+  // by one and together, 200 suggestions: 64 inputs, 10 classes, 150 units, 128 rows a step, split 2377 and 2493; 80 inputs, 190
+  // units, 24 rows 5809 and 6233; but fp32 products, 64 inputs, 150 units, 64 rows 2663 and 2576; 64 units, 128 rows 1473 and 1412;
+  // 80 inputs, 50 units, 128 rows 1256 and 1188.
+  static constexpr bool CROWDED = NT == 2 && KT >= (SPLIT ? 4 : 5);
+  static constexpr int GROUP = NT == 1 ? 2 : 1;  // row tiles whose hidden products take turns
   struct State {
     HiddenWeights<KT, NT, SPLIT> w;
     f32x4 m[NREGM][KT], v[NREGM][KT], g[NT][KT];       // hidden layer: lane (unit li, columns 16 kk + 4q + e)
@@ -169,13 +175,20 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
   // A 16 x 16 block of four values a lane (lane: column li, rows 4q..4q+3) turned over: lane li gets row li, columns
   // 4q..4q+3.  The patch is where the wave's partial outputs of row tile r go once it is done: the wave's LDS accesses
   // stay in order, and nobody else reads them between the outputs of a chunk and the first barrier of the next.
-  __device__ __forceinline__ f32x4 turn(const f32x4& v, int r) const {
+  __device__ __forceinline__ void turn_put(const f32x4& v, int r) const {
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
-    float* p = f(O_ZP) + (wave() * SM_RC + r * 16) * MD_RS;
+    float* p = f(O_ZP) + (wave() * SM_RC + r * 16 + 4 * q) * MD_RS + li;
 #pragma unroll
-    for (int e = 0; e < 4; e++) p[(4 * q + e) * MD_RS + li] = v[e];
+    for (int e = 0; e < 4; e++) p[e * MD_RS] = v[e];
+  }
+  __device__ __forceinline__ f32x4 turn_get(int r) const {
+    const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
+    return *(const f32x4*)(f(O_ZP) + (wave() * SM_RC + r * 16 + li) * MD_RS + 4 * q);
+  }
+  __device__ __forceinline__ f32x4 turn(const f32x4& v, int r) const {
+    turn_put(v, r);
     __builtin_amdgcn_wave_barrier();
-    const f32x4 t = *(const f32x4*)(p + li * MD_RS + 4 * q);
+    const f32x4 t = turn_get(r);
     __builtin_amdgcn_wave_barrier();
     return t;
   }
@@ -333,58 +346,104 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
   }
 
   // ---- forward ---------------------------------------------------------------
-  template <bool ALL>
-  __device__ __forceinline__ void forward_tile(const State& R, int b, int r, f32x4 (&acc)[NT][4]) const {
+  // The wave's hidden tiles of N row tiles from R0 on and then their shares of the outputs, each step of it for all of them
+  // before the next: they wait for LDS and for each other's products together.
+  template <bool ALL, int R0, int N>
+  __device__ __forceinline__ void forward_rows(const State& R, int b, f32x4 (&acc)[NT][4]) const {
+    constexpr int TILES = NT - (ALL ? 0 : 1);
     const int lane = tid() & 63, li = lane & 15, q = lane >> 4;
-    f32x4 c[NT];
 #pragma unroll
-    for (int i = 0; i < NT; i++) {
+    for (int i = 0; i < TILES; i++) {
       float x = R.bw[i];
-      // (as in the small kernel: keeps the small parameters out of scratch memory; with four input tiles split the registers for
-      // them are not there, and 62 instead of 19 spill)
+      // (as in the small kernel: keeps the small parameters out of scratch memory, where the registers have room for them)
       if (!(SPLIT && KT == 4)) asm("" : "+v"(x));
-      c[i] = f32x4{x, x, x, x};
+#pragma unroll
+      for (int r = R0; r < R0 + N; r++) acc[i][r] = f32x4{x, x, x, x};
     }
-    if constexpr (SPLIT) {
+    if constexpr (TILES > 0) {
 #pragma unroll
-      for (int kb = 0; kb < KB; kb++) sm_products<NT - (ALL ? 0 : 1)>(Base::by_row(Base::planes(b), r, kb), R.w.p[kb], c);
-    } else {
-      const float* a_ = xs(b) + (r * 16 + li) * LDW + 4 * q;
-      f32x4 a[KT];
+      for (int r = R0; r < R0 + N; r += GROUP) {
+        if constexpr (SPLIT) {
 #pragma unroll
-      for (int kk = 0; kk < KT; kk++) a[kk] = *(const f32x4*)(a_ + kk * 16);
+          for (int kb = 0; kb < KB; kb++) {
+            SmPlanes a[GROUP];
 #pragma unroll
-      for (int kk = 0; kk < KT; kk++)
+            for (int g = 0; g < GROUP; g++)
+              if (r + g < R0 + N) a[g] = Base::by_row(Base::planes(b), r + g, kb);
+            hidden_products<TILES, R0 + N>(a, R.w.p[kb], r, acc);
+          }
+        } else {
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
+          for (int g = 0; g < GROUP; g++) {
+            if (r + g >= R0 + N) continue;
+            const float* a_ = xs(b) + ((r + g) * 16 + li) * LDW + 4 * q;
+            f32x4 a[KT];
 #pragma unroll
-          for (int i = 0; i < NT; i++)
-            if (i + 1 < NT || ALL) c[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], R.w.w[i][kk][e], c[i], 0, 0, 0);
+            for (int kk = 0; kk < KT; kk++) a[kk] = *(const f32x4*)(a_ + kk * 16);
+#pragma unroll
+            for (int kk = 0; kk < KT; kk++)
+#pragma unroll
+              for (int e = 0; e < 4; e++)
+#pragma unroll
+                for (int i = 0; i < TILES; i++)
+                  acc[i][r + g] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk][e], R.w.w[i][kk][e], acc[i][r + g], 0, 0, 0);
+          }
         }
+      }
+    }
+    f32x4 z[N];
+#pragma unroll
+    for (int n = 0; n < N; n++) z[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < TILES; i++) {
+      f32x4 ar[N];  // row li, units 4q..4q+3
+#pragma unroll
+      for (int n = 0; n < N; n++) {
+#pragma unroll
+        for (int e = 0; e < 4; e++) acc[i][R0 + n][e] = relu(acc[i][R0 + n][e]);
+        turn_put(acc[i][R0 + n], R0 + n);
+      }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int n = 0; n < N; n++) ar[n] = turn_get(R0 + n);
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int n = 0; n < N; n++) z[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[n][e], R.w2[i][e], z[n], 0, 0, 0);
     }
 #pragma unroll
-    for (int i = 0; i < NT; i++) acc[i][r] = c[i];
-    f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < N; n++) {
+      float* zp = f(O_ZP) + (wave() * SM_RC + (R0 + n) * 16 + 4 * q) * MD_RS + li;
 #pragma unroll
-    for (int i = 0; i < NT; i++)
-      if (i + 1 < NT || ALL) {
+      for (int e = 0; e < 4; e++) zp[e * MD_RS] = z[n][e];
+    }
+  }
+  // one of the six split products of the group's row tiles from r on after the other
+  template <int TILES, int END, int S = 0>
+  __device__ __forceinline__ static void hidden_products(const SmPlanes (&a)[GROUP], const SmPlanes (&w)[NT], int r, f32x4 (&acc)[NT][4]) {
 #pragma unroll
-        for (int e = 0; e < 4; e++) acc[i][r][e] = relu(acc[i][r][e]);
-        const f32x4 ar = turn(acc[i][r], r);  // row li, units 4q..4q+3
+    for (int g = 0; g < GROUP; g++)
 #pragma unroll
-        for (int e = 0; e < 4; e++) z = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[e], R.w2[i][e], z, 0, 0, 0);
-      }
-    float* zp = f(O_ZP) + (wave() * SM_RC + r * 16 + 4 * q) * MD_RS + li;
-#pragma unroll
-    for (int e = 0; e < 4; e++) zp[e * MD_RS] = z[e];
+      for (int i = 0; i < TILES; i++)
+        if (r + g < END) acc[i][r + g] = sm_product<S>(a[g], w[i], acc[i][r + g]);
+    if constexpr (S < 5) hidden_products<TILES, END, S + 1>(a, w, r, acc);
   }
   template <bool ALL>
   __device__ __forceinline__ void forward_chunk(const State& R, int b, int nrt, f32x4 (&acc)[NT][4]) const {
-    // (a ragged chunk leaves the loop early: every row tile has its own registers)
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-      if (r >= nrt) break;
-      forward_tile<ALL>(R, b, r, acc);
+    if constexpr (CROWDED) {  // row tile by row tile
+      forward_rows<ALL, 0, 1>(R, b, acc);
+      if (nrt > 1) forward_rows<ALL, 1, 1>(R, b, acc);
+      if (nrt > 2) forward_rows<ALL, 2, 1>(R, b, acc);
+      if (nrt > 3) forward_rows<ALL, 3, 1>(R, b, acc);
+    } else if (nrt == 4) {
+      forward_rows<ALL, 0, 4>(R, b, acc);
+    } else if (nrt == 3) {
+      forward_rows<ALL, 0, 3>(R, b, acc);
+    } else if (nrt == 2) {
+      forward_rows<ALL, 0, 2>(R, b, acc);
+    } else {
+      forward_rows<ALL, 0, 1>(R, b, acc);
     }
   }
   __device__ __forceinline__ void forward(const State& R, int b, int, int nrt, Acts& A) const {
