@@ -293,9 +293,8 @@ struct OptC {
   float b1, b2, omb1, omb2, eps, lr_t, mu, lr, am;
 };
 
-// (By its exponent, which is an inline constant of an instruction: with the value itself k_train_mid<4,2,8> spills 36 vector
-// registers instead of 21.  In k_train_small<2,3,1,4> it is the other way round, 123 and 95.)
-__device__ __forceinline__ bool least_eps(const OptC& c) { return __float_as_uint(c.eps) >> 23 == __float_as_uint(EPS_MIN) >> 23; }
+// The least eps, in the units of opt_step(): larger by 2^12 at most.
+__device__ __forceinline__ bool least_eps(const OptC& c) { return __float_as_uint(c.eps) >> 23 <= (__float_as_uint(EPS_MIN) >> 23) + 12; }
 
 // max(x, 0) in one instruction.  A NaN stays one, in every kernel: a model that blew up, or met a NaN in its data, has a score
 // that says so.  (fmaxf() and a median make it 0.)
@@ -313,6 +312,31 @@ __device__ inline void opt_update(const OptC& c, float g, float& w, float& m, fl
     const float u = fmaf(c.mu, m, -(c.lr * g));
     m = u;
     w = w + (c.nest ? fmaf(c.mu, u, -(c.lr * g)) : u);
+  }
+}
+
+// The same with an Adam model's moments kept in units of what a gradient adds to them, m / (1 - b1) and v / (1 - b2): two
+// vector instructions and two roundings less.  eps is in units of sqrt(1 - b2) then, and the step size takes the rest.
+struct AdamUnits {
+  float m, v, eps;  // of the moments in units of their own; eps in its
+  double lr;
+  __device__ __forceinline__ AdamUnits(float b1, float b2, float e) {
+    const float omb1 = 1.f - b1, omb2 = 1.f - b2;
+    // (b2 = 1: a step size of zero, and moments that nobody sees)
+    const double root = omb2 != 0.f ? sqrt((double)omb2) : 1.0;
+    m = 1.f / omb1;
+    v = omb2 != 0.f ? 1.f / omb2 : 0.f;
+    eps = (float)((double)e / root);
+    lr = (double)omb1 / root;
+  }
+};
+__device__ inline void opt_step(const OptC& c, float g, float& w, float& m, float& v) {
+  if (c.adam) {
+    m = fmaf(c.b1, m, g);
+    v = fmaf(c.b2, v, g * g);
+    w = fmaf(-(c.lr_t * m), __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(v) + c.eps), w);
+  } else {
+    opt_update(c, g, w, m, v);
   }
 }
 

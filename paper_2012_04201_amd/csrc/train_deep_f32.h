@@ -237,7 +237,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
 
   // ---- parameters ----------------------------------------------------------
   // packed parameters (or moments), or the initial draw, -> the blocks of a set
-  __device__ __forceinline__ void unpack(const float* st, int set) const {
+  __device__ __forceinline__ void unpack(const float* st, int set, float unit = 1.f) const {
     const Places z = places();
 #pragma unroll 1
     for (int n = 0; n < NB; n++) {
@@ -252,7 +252,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
         int l, i;
         bool isb;
         const int ci = packed(n, e, l, i, isb);
-        x[e] = ci < 0 ? 0.f : (st ? st[ci] : init_value(l, i, isb));
+        x[e] = ci < 0 ? 0.f : (st ? st[ci] * unit : init_value(l, i, isb));
       }
       *kept(z, set, n) = x;
     }
@@ -270,12 +270,12 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
       if (used(n)) to[reg(n)] = *kept(z, set, n);
     }
   }
-  __device__ __forceinline__ void load(State& R, const float* st) const {
+  __device__ __forceinline__ void load(State& R, const float* st, float um, float uv) const {
     const Places z = places();
 #pragma unroll
     for (int which = 0; which < 2; which++) {
       if (st) {
-        unpack(st + (1 + which) * y.p.P, NEAR ? 0 : 1 + which);
+        unpack(st + (1 + which) * y.p.P, NEAR ? 0 : 1 + which, which ? uv : um);
         if constexpr (NEAR) take(0, which ? R.v : R.m);
       } else {
 #pragma unroll
@@ -645,7 +645,10 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
   __device__ __forceinline__ void update(State& R, const OptC& oc) const {
     OptC o = oc;
     o.adam = ADAM;
-    const bool pads = ADAM && least_eps(o);
+    // Pads need no mask (see k_train_small).  With three layers on four waves the least eps clears them all the same: no value
+    // changes, but the branch parts the blocks for the register allocation: 500 models of 569 x 50, 60-60-60, 24 rows a step, 3
+    // epochs 1957 us a call without it, 1755 with it; elsewhere it costs (128-40-100 3252 and 3491, 128-128-128 5245 and 6026).
+    const bool pads = ADAM && H == 3 && W == 4 && least_eps(o);
     const Places z = places();
     // Moments in the slot are fetched AHEAD blocks early.  A block that the wave does not have is sent out of the
     // descriptor's range (zeros come back, nothing is written) instead of branched around: with the same memory operations
@@ -696,7 +699,7 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
         for (int e = 0; e < 4; e++) {
           if (n == B_BIAS && e > H) continue;
           float wr = ww[e], mr = mm[e], vr = vv[e];
-          opt_update(o, n == B_BIAS ? R.g[n][e] : R.g[n][e] + am * wr, wr, mr, vr);
+          opt_step(o, n == B_BIAS ? R.g[n][e] : R.g[n][e] + am * wr, wr, mr, vr);
           ww[e] = wr;
           mm[e] = mr;
           vv[e] = vr;

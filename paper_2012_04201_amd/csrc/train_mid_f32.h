@@ -203,7 +203,7 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
   // ---- parameters ----------------------------------------------------------
   static constexpr int NREG = md_regs(KT, NT), PER = 4 * KT + 1 + 4;
   __device__ __forceinline__ float* park() const { return slot + wave() * (NREG * 64) + (threadIdx.x & 63); }
-  __device__ __forceinline__ void unpack(const float* st) const {
+  __device__ __forceinline__ void unpack(const float* st, float unit = 1.f) const {
     const int lane = threadIdx.x & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
     const int d = y.p.d, h = y.h;
     float* b = park();
@@ -232,7 +232,7 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
         if (u < h && li < c) ci = y.cw[1] + e;
       }
       float val = 0.f;
-      if (ci >= 0) val = st ? st[ci] : init_value(l, e, isb);
+      if (ci >= 0) val = st ? st[ci] * unit : init_value(l, e, isb);
       b[64 * n] = val;
     }
   }
@@ -272,13 +272,13 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
           w[i][kk][e] = x;
         }
   }
-  __device__ __forceinline__ void load(State& R, const float* st) const {
+  __device__ __forceinline__ void load(State& R, const float* st, float um, float uv) const {
     const float* b = park();
     auto take = [&](int n, float& x) { x = b[64 * n]; };
     auto zero = [&](int, float& x) { x = 0.f; };
 #pragma unroll
     for (int which = 0; which < 2; which++) {
-      if (st) unpack(st + (1 + which) * y.p.P);
+      if (st) unpack(st + (1 + which) * y.p.P, which ? uv : um);
       if constexpr (NEAR > 0) {
         if (st)
           each_hidden(which ? R.v : R.m, take);
@@ -670,7 +670,7 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
 #pragma unroll
           for (int e = 0; e < 4; e++) {
             float wr = x[e], mr = mm[e], vr = vv[e];
-            opt_update(o, R.g[i][kk][e] + o.am * wr, wr, mr, vr);
+            opt_step(o, R.g[i][kk][e] + o.am * wr, wr, mr, vr);
             x[e] = wr;
             mm[e] = mr;
             vv[e] = vr;
@@ -687,7 +687,7 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           float wr = R.w2[i][e], mr = m2[i][e], vr = v2[i][e];
-          opt_update(o, R.g2[i][e] + o.am * wr, wr, mr, vr);
+          opt_step(o, R.g2[i][e] + o.am * wr, wr, mr, vr);
           R.w2[i][e] = wr;
           m2[i][e] = mr;
           v2[i][e] = vr;
@@ -697,47 +697,9 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
       }
 #pragma unroll
     for (int k = 0; k <= NT; k++) {
-      opt_update(o, gb[k], k < NT ? R.bw[k < NT ? k : 0] : R.ow, mb[k], vb[k]);
+      opt_step(o, gb[k], k < NT ? R.bw[k < NT ? k : 0] : R.ow, mb[k], vb[k]);
       *mom(k, 0) = mb[k];
       if (ADAM) *mom(k, 1) = vb[k];
-    }
-    if (ADAM && least_eps(o)) clear_pads(R);
-  }
-  __device__ __forceinline__ void clear_pads(State& R) const {
-    const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
-#pragma unroll
-    for (int i = 0; i < NT; i++) {
-      const int t0 = (w_ + i * W) * 16;
-      const bool unit = t0 + li < y.h;
-#pragma unroll
-      for (int kk = 0; kk < KT; kk++) {
-        f32x4 x = R.w.get(i, kk);
-#pragma unroll
-        for (int e = 0; e < 4; e++)
-          if (!unit || kk * 16 + 4 * q + e >= y.p.d) {
-            x[e] = 0.f;
-            if (i < NEAR)
-              R.m[i < NEAR ? i : 0][kk][e] = R.v[i < NEAR ? i : 0][kk][e] = 0.f;
-            else
-              (*far(i, 0, kk))[e] = (*far(i, 1, kk))[e] = 0.f;
-          }
-        R.w.put(i, kk, x);
-      }
-      if (!unit) {
-        R.bw[i] = 0.f;
-        *mom(i, 0) = *mom(i, 1) = 0.f;
-      }
-#pragma unroll
-      for (int e = 0; e < 4; e++)
-        if (li >= c || t0 + 4 * q + e >= y.h) {
-          R.w2[i][e] = 0.f;
-          (*mom2(i, 0))[e] = 0.f;
-          (*mom2(i, 1))[e] = 0.f;
-        }
-    }
-    if (li >= c) {
-      R.ow = 0.f;
-      *mom(NT, 0) = *mom(NT, 1) = 0.f;
     }
   }
   template <bool GRAD>

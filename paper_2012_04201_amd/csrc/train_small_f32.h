@@ -739,17 +739,16 @@ struct RowPipe {
     }
     int e_lr = st0 > 0 ? e : e - 1;  // epoch of the step being worked on (set when one opens)
     int c2 = epoch_start(st0);       // the chunk at the position above
-    self.load(R, resume ? P.state_in : nullptr);
-
     OptC oc;
     const int solver = pin(it.solver);
     oc.adam = solver == BBO_ADAM;
+    self.load(R, resume ? P.state_in : nullptr, oc.adam ? AdamUnits(it.beta1, it.beta2, it.eps).m : 1.f,
+              oc.adam ? AdamUnits(it.beta1, it.beta2, it.eps).v : 1.f);
     oc.nest = it.nesterov != 0;
     oc.b1 = pin(it.beta1);
     oc.b2 = pin(it.beta2);
-    oc.omb1 = uniform(1.f - it.beta1);
-    oc.omb2 = uniform(1.f - it.beta2);
-    oc.eps = pin(it.eps);
+    oc.omb1 = oc.omb2 = 0.f;  // (not in these units)
+    oc.eps = uniform(AdamUnits(it.beta1, it.beta2, it.eps).eps);
     oc.mu = pin(it.momentum);
     oc.lr = it.lr;
     oc.lr_t = it.lr;
@@ -824,7 +823,8 @@ struct RowPipe {
                   q1 *= q1;
                   q2 *= q2;
                 }
-                lr_tab = (float)((double)item().lr * sqrt(1.0 - b2t) / (1.0 - b1t));
+                const double unit = AdamUnits(item().beta1, item().beta2, item().eps).lr;
+                lr_tab = (float)((double)item().lr * sqrt(1.0 - b2t) / (1.0 - b1t) * unit);
               }
               oc.lr_t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lr_tab), lr_at));
               lr_at++;
@@ -1106,7 +1106,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
   }
   // Packed parameters (or one of their moments) `st`, or the initial draw where st is null, into the wave's part of
   // the slot.  A rolled loop: the registers are filled from the slot afterwards.
-  __device__ __forceinline__ void unpack(const float* st) const {
+  __device__ __forceinline__ void unpack(const float* st, float unit = 1.f) const {
     const int lane = threadIdx.x & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
     const int d = y.p.d, h = y.h, c = y.c;
     float* b = park();
@@ -1135,21 +1135,21 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
         if (j < h && cc < c) ci = y.cw[1] + e;
       }
       float val = 0.f;
-      if (ci >= 0) val = st ? st[ci] : init_value(l, e, isb);
+      if (ci >= 0) val = st ? st[ci] * unit : init_value(l, e, isb);
       b[64 * n] = val;
     }
   }
-  __device__ __forceinline__ void load(State& R, const float* st) const {
+  __device__ __forceinline__ void load(State& R, const float* st, float um, float uv) const {
     const float* b = park();
     auto take = [&](int n, float& x) { x = b[64 * n]; };
     auto take_small = [](float& x, const float* at) { x = *at; };
     auto zero = [](int, float& x) { x = 0.f; };
     auto zero_small = [](float& x, const float*) { x = 0.f; };
     if (st) {
-      unpack(st + y.p.P);
+      unpack(st + y.p.P, um);
       each_hidden(R.m, take);
       each_small(R.pm, take_small);
-      unpack(st + 2 * y.p.P);
+      unpack(st + 2 * y.p.P, uv);
       each_hidden(R.v, take);
       each_small(R.pv, take_small);
     } else {
@@ -1436,9 +1436,6 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
         sm_products<TILES>(Base::template by_column<BOTH>(x, r, kk), dp, c);
 #pragma unroll
         for (int i = 0; i < TILES; i++) R.g[i][kk] = c[i];
-      // (one column tile's operands at a time: 190 units, 24 and 128 rows a step, 3706 -> 3145 and 1480 -> 1388 us by what
-      // does not spill)
-      if constexpr (NT == 3) __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -1473,11 +1470,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
   }
 
   // ---- optimizer step -------------------------------------------------------------
-  // Pad elements need no mask: their inputs, deltas and weights are zero, and so is their step (0 / eps).  The
-  // least eps clears them all the same: no value changes by it, but the branch parts the update from what follows for the
-  // register allocation, in this kernel and in those for wider and deeper models.  Without it k_train_mid<5,2,8> spills 67
-  // vector registers instead of 51 and takes 1.06 to 1.14 of its time.  (256 suggestions of one to three layers 7.84 ms instead
-  // of 8.00.)
+  // Pad elements need no mask: their inputs, deltas and weights are zero, and so is their step (0 / eps).
   template <bool ADAM>
   __device__ __forceinline__ void update(State& R, const OptC& oc) const {
     const int w_ = wave();
@@ -1492,7 +1485,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
 #pragma unroll
           for (int e = 0; e < 4; e++) {
             float wr = x[e], mr = R.m[i][kk][e], vr = R.v[i][kk][e];
-            opt_update(o, fmaf(o.am, wr, R.g[i][kk][e] * R.factor(i)), wr, mr, vr);
+            opt_step(o, fmaf(o.am, wr, R.g[i][kk][e] * R.factor(i)), wr, mr, vr);
             x[e] = wr;
             R.m[i][kk][e] = mr;
             R.v[i][kk][e] = vr;
@@ -1504,8 +1497,7 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
     float gp[NG];
     small_grads(R, gp);
 #pragma unroll
-    for (int g = 0; g < NG; g++) opt_update(o, gp[g] + small_penalty(g, q, o.am) * R.pw[g], R.pw[g], R.pm[g], R.pv[g]);
-    if (ADAM && o.eps == EPS_MIN) clear_pads(R);  // (by its value: see least_eps())
+    for (int g = 0; g < NG; g++) opt_step(o, gp[g] + small_penalty(g, q, o.am) * R.pw[g], R.pw[g], R.pm[g], R.pv[g]);
     spread(R);
   }
   // A traced step's gradient (before the update: GRAD) or new parameters into out[P].
@@ -1542,25 +1534,6 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
     if (k >= NT * (1 + CO)) return k - NT * (1 + CO) < c ? y.cb[1] + k - NT * (1 + CO) : -1;
     return j >= y.h || r > c ? -1 : (r == 0 ? y.cb[0] + j : y.cw[1] + j * c + r - 1);
   }
-  __device__ __forceinline__ void clear_pads(State& R) const {
-    const int lane = tid() & 63, w_ = wave(), li = lane & 15, q = lane >> 4;
-#pragma unroll
-    for (int i = 0; i < NT; i++) {
-      const bool unit = (w_ + i * W) * 16 + li < y.h;
-#pragma unroll
-      for (int kk = 0; kk < KT; kk++) {
-        f32x4 x = R.w.get(i, kk);
-#pragma unroll
-        for (int e = 0; e < 4; e++)
-          if (!unit || kk * 16 + 4 * q + e >= y.p.d) x[e] = R.m[i][kk][e] = R.v[i][kk][e] = 0.f;
-        R.w.put(i, kk, x);
-      }
-    }
-#pragma unroll
-    for (int g = 0; g < NG; g++)
-      if (small_packed(4 * g + q) < 0) R.pw[g] = R.pm[g] = R.pv[g] = 0.f;
-  }
-
   // squared weights, for a traced step's loss
   __device__ __forceinline__ double penalty_sum(const State& R) const {
     const int q = (threadIdx.x & 63) >> 4;
