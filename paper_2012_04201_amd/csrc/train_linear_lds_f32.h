@@ -18,10 +18,13 @@
 // weights, one sum per column serves both gradients, and the weights themselves, their moments and their updates stay two
 // (the classes of a column in lanes t and t + 32, or in one lane where there are more columns than 32).
 //
-// What bounds it: vector instructions, about 2 D per 64 rows for the products and 3 D per step for the folds, with the LDS
-// reads of the rows next.  10,240 models of 569 x 30, two classes, 20 epochs, took 1.67 ms a call with a column per class
-// and folds through the LDS crossbar, and take 1.11 ms.  (Gathering each chunk's rows from global memory, as
-// train_linear_f32.h does: 4.9 ms.)
+// What bounds it: vector instructions, about 2 D + 40 per 64 rows for products and deltas, 2.5 D per step for the folds, and
+// the row order's walk; four fifths of the time are theirs.  The order's lanes take positions from one counter: with fixed
+// positions a lane, the slowest went through the network 27 times an epoch of 455 rows, and goes 16 times.  The first chunk of a
+// step starts the sums, which nothing has to clear.  10,240 models of 569 x 30, two classes, 20 epochs, took 1.67 ms a call
+// with a column per class and folds through the LDS crossbar, 1.11 ms before the last three, and take 0.98 ms.  (Weights in
+// scalar registers instead of broadcast reads: 1.09 ms, by the 32 lane reads a step.  Gathering each chunk's rows from global
+// memory, as train_linear_f32.h does: 4.9 ms.)
 #pragma once
 #include "common.h"
 #include "train_small_f32.h"  // folding sums
@@ -60,7 +63,7 @@ __host__ inline LinLds ll_plan(int64_t n, int d, int c) {
 
 template <int D, int CO>
 struct LinearLds {
-  static constexpr int S = D + 4, NQ = D / 4, M = (D + 15) / 16;
+  static constexpr int S = D + 4, NQ = D / 4;
   static constexpr bool SPLIT = CO == 2 && D <= 32;  // the classes of a column in lanes t and t + 32
   static constexpr int NB = CO == 2 && !SPLIT ? 2 : 1;  // parameters of a lane
   const TrainParams& P;
@@ -113,24 +116,35 @@ struct LinearLds {
     }
     return valid ? dl : 0.f;  // (a row that is not there must not put an infinity of another row into the sums)
   }
-  // sum over the 64 lanes of g[t] for column t = lane, or lane mod 32 where there are no more than 32
+  // Sum over the 64 lanes of g[t] for column t = lane, or lane mod 32 where there are no more than 32.  The halvings over the
+  // 16-lane rows come first, while there are the most columns: two instructions each, where one within a row takes three.
   __device__ __forceinline__ float fold(const float (&g)[D]) const {
     const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
-    float r[4];
+    constexpr int H = D < 16 ? D : 16;
+    auto upper = [&](int t) { return sm_fold32(g[t], t + 32 < D ? g[t + 32 < D ? t + 32 : 0] : 0.f); };
+    float v[4];
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-      float v[4];
+    for (int t = 0; t < 4; t++) {
+      float p[4];
 #pragma unroll
-      for (int t = 0; t < 4; t++) {
-        float p[4];
-#pragma unroll
-        for (int e = 0; e < 4; e++) p[e] = 16 * i + 4 * t + e < D ? g[16 * i + 4 * t + e < D ? 16 * i + 4 * t + e : 0] : 0.f;
-        v[t] = 16 * i + 4 * t < D ? sm_fold_quad(p, b0, b1) : 0.f;
+      for (int e = 0; e < 4; e++) {
+        const int c = 4 * t + e;
+        p[e] = 0.f;
+        if (c < H) {
+          if constexpr (D > 32)
+            p[e] = sm_fold16(upper(c < H ? c : 0), upper(c < H ? c + 16 : 0));
+          else if constexpr (D > 16)
+            p[e] = sm_fold16(g[c < H ? c : 0], c + 16 < D ? g[c + 16 < D ? c + 16 : 0] : 0.f);
+          else
+            p[e] = g[c < H ? c : 0];
+        }
       }
-      r[i] = 16 * i < D ? sm_fold_row(v, b2, b3) : 0.f;
+      v[t] = 4 * t < H ? sm_fold_quad(p, b0, b1) : 0.f;
     }
-    const float lo = sm_fold16(r[0], r[1]);
-    return sm_fold32(lo, M > 2 ? sm_fold16(r[2], r[3]) : lo);
+    float r = sm_fold_row(v, b2, b3);
+    if constexpr (D <= 16) r = sm_fold16(r, r);
+    if constexpr (D <= 32) r = sm_fold32(r, r);
+    return r;
   }
   // the epoch's rows in visiting order (see train_linear_f32.h)
   __device__ __forceinline__ void epoch_order(uint64_t ke, int n_fit) const {
@@ -141,7 +155,9 @@ struct LinearLds {
       for (int i = lane; i < (4 << dm.hb); i += 64)
         ft[i] = (uint16_t)((uint32_t)key_fold(ke, ((uint64_t)(i >> dm.hb) << 32) | ((uint32_t)i & dm.mask)) & dm.mask);
       __builtin_amdgcn_wave_barrier();
-      int p = lane;
+      // a lane that has its position's row takes the next position that no lane has: positions differ in how often they
+      // go through the network
+      int p = lane, next = 64;
       uint32_t x = (uint32_t)p;
       while (p < n_fit) {
         uint32_t Lh = x >> dm.hb, Rh = x & dm.mask;
@@ -152,11 +168,14 @@ struct LinearLds {
           Rh = t;
         }
         x = (Lh << dm.hb) | Rh;
-        if (x < (uint32_t)n_fit) {
+        const bool found = x < (uint32_t)n_fit;
+        const uint64_t all = __ballot(found);
+        if (found) {
           ep[p] = sl[x];
-          p += 64;
+          p = next + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0));
           x = (uint32_t)p;
         }
+        next += __popcll(all);
       }
     }
     __builtin_amdgcn_wave_barrier();
@@ -194,6 +213,10 @@ struct LinearLds {
     const int bs = eff_batch(it.batch_size, n_fit);
     const int steps = n_fit > 0 ? (n_fit + bs - 1) / bs : 0;
     const float alpha = it.alpha;
+    // of a step of all `bs` rows and of an epoch's last (divisions take a dozen instructions each)
+    const float mb_full = (float)bs, mb_rest = (float)(n_fit - (steps - 1) * bs);
+    const float inv_full = uniform(1.f / mb_full), inv_rest = uniform(1.f / mb_rest);
+    const float am_full = uniform(alpha / mb_full), am_rest = uniform(alpha / mb_rest);
     const bool traced = P.trace_item == it.b * P.n_folds + fl;
     const bool resume = traced && P.state_in && steps > 0;
 
@@ -244,23 +267,23 @@ struct LinearLds {
       double esum = 0.0, unused = 0.0;  // the lane's share of the epoch's summed data loss
       for (int st = e == e0 ? st0 : 0; st < steps; st++, gstep++) {
         const int lo = st * bs, hi = min(lo + bs, n_fit);
-        const float mb = (float)(hi - lo), inv_mb = 1.f / mb;
+        const float mb = (float)(hi - lo), inv_mb = hi - lo == bs ? inv_full : inv_rest;
         float g[D];
-#pragma unroll
-        for (int i = 0; i < D; i++) g[i] = 0.f;
         double lstep = 0.0;
-        for (int at = lo; at < hi; at += 64) {
+        auto chunk = [&](int at, auto first) {
           asm volatile("" ::: "memory");  // the weights are read again for every chunk, not kept in registers
           const int row = ep[min(at + lane, hi - 1)];
           f32x4 x[NQ];
           load_row(row, x);
           const float dl = outputs<true>(forward(x), at + lane < hi, ys[row], inv_mb, loss, lstep, unused);
 #pragma unroll
-          for (int i = 0; i < D; i++) g[i] += x[i / 4][i % 4] * dl;
-        }
+          for (int i = 0; i < D; i++) g[i] = first ? x[i / 4][i % 4] * dl : fmaf(x[i / 4][i % 4], dl, g[i]);
+        };
+        chunk(lo, std::true_type{});
+        for (int at = lo + 64; at < hi; at += 64) chunk(at, std::false_type{});
         const float gs = fold(g);
         esum += lstep;
-        oc.am = alpha / mb;
+        oc.am = hi - lo == bs ? am_full : am_rest;
         if (oc.adam) {
           if (lr_at == 64) {
             // beta^t of the next 64 steps, a step per lane, by repeated squaring in double
