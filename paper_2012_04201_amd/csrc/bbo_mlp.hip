@@ -819,6 +819,7 @@ struct SubPlan {
   uint32_t lds_bytes = 0;       // dynamic LDS per workgroup
   int waves = 0;                // linear kernels: wavefronts per workgroup
   int dd = 0;                   // linear kernel with the data set in LDS: its padded columns; 0: the other one
+  int far = 0;                  // ... and the groups of four of them that stay in global memory
   size_t item_bytes = 0;        // size of a suggestion's record
   uint64_t o_items = 0;         // workspace byte offset of its records
   uint64_t o_slots = 0;         // ... and of its workgroups' slots
@@ -1096,10 +1097,11 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     if (k == KC_FULL) max_slots *= full_per_cu(sp.cut, sp.lds_bytes);
     if (k == KC_MID) max_slots *= md_per_cu(sp.cut, sp.lds_bytes);
     if (k == KC_DEEP) max_slots *= deep_per_cu(sp.cut, sp.lds_bytes);
-    const LinLds ll = k == KC_LINEAR && dtype == BBO_F32 ? ll_plan(n, d, n_classes >= 2 ? n_classes : 1) : LinLds{0, 0, 0, 0};
+    const LinLds ll = k == KC_LINEAR && dtype == BBO_F32 ? ll_plan(n, d, n_classes >= 2 ? n_classes : 1) : LinLds{0, 0, 0, 0, 0};
     if (ll.waves) {
       // one workgroup per CU; a call with few models spreads them over the CUs (four wavefronts to copy the data set)
       sp.dd = ll.dd;
+      sp.far = ll.far;
       sp.waves = (int)std::min<size_t>(ll.waves, std::max<size_t>(4, (n_items + max_slots - 1) / max_slots));
       sp.lds_bytes = ll.shared + sp.waves * ll.wave_bytes;
       units = n_items;
@@ -1511,7 +1513,7 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
       fn = sp.cut.nt == 2 ? deep_kernel2(sp.cut.kt, sp.cut.waves) : deep_kernel3(sp.cut.kt, sp.cut.waves);
       threads = 64 * sp.cut.waves;
     } else if (k == KC_LINEAR) {
-      fn = sp.dd ? linear_lds_kernel(sp.dd, c_out) : linear_kernel(ln_co(c_out), ln_ki(d));
+      fn = sp.dd ? linear_lds_kernel(sp.dd, c_out, sp.far > 0) : linear_kernel(ln_co(c_out), ln_ki(d));
       threads = 64 * sp.waves;
     } else {
       fn = dtype == BBO_F32 ? (const void*)k_train<float> : (const void*)k_train<__bf16>;

@@ -14,5 +14,5 @@ BBO_HIDDEN const void* full_kernel(int kt, int nt, int co, int waves);  // k til
 BBO_HIDDEN const void* mid_kernel(int kt, int nt, int waves, bool split);  // k tiles of the input layer, unit tiles per wave, waves, products
 BBO_HIDDEN const void* deep_kernel2(int kt, int waves);         // k tiles of the input layer, waves; two hidden layers
 BBO_HIDDEN const void* deep_kernel3(int kt, int waves);         // three
-BBO_HIDDEN const void* linear_lds_kernel(int dd, int co);      // padded inputs and bias, outputs
+BBO_HIDDEN const void* linear_lds_kernel(int dd, int co, bool far);  // padded inputs and bias, outputs, columns in global memory
 BBO_HIDDEN const void* linear_kernel(int co, int ki);          // padded outputs, rows of W per lane

@@ -38,6 +38,7 @@ constexpr uint32_t LL_LDS_LIMIT = 160 * 1024 - 64;
 __host__ __device__ constexpr int ll_occupancy(int dd) { return 2 * dd + 64 <= 128 ? 4 : (2 * dd + 64 <= 168 ? 3 : 2); }
 struct LinLds {
   int32_t dd, waves;           // columns (inputs and bias padded to a multiple of 8); wavefronts per workgroup, 0: not a case for it
+  int32_t far;                 // groups of four columns, from the first on, that stay in global memory
   uint32_t shared, wave_bytes; // LDS of the data set and of each wavefront
 };
 // LDS of a wavefront: weights, the training list in the order of the early-stopping cut, the epoch's row order, the round
@@ -47,35 +48,58 @@ __host__ __device__ inline uint32_t ll_wave_bytes(int dd, int64_t n) {
   while ((1 << (2 * hb)) < n) hb++;
   return (uint32_t)((dd * 4 + 2 * ((2 * n + 15) & ~15) + ((4 << hb) * 2)) + 15) & ~15u;
 }
-// By the size of the data set and the model alone: at least a wavefront per SIMD must fit beside the data set, or the
-// SIMDs idle and gathering rows from global memory is the better way.
-__host__ inline LinLds ll_plan(int64_t n, int d, int c) {
-  LinLds l = {0, 0, 0, 0};
+__host__ __device__ inline int ll_stride(int dd, int far) { return far > 0 ? dd - 4 * far : dd + 4; }
+// By the size of the data set and the model alone: at least a wavefront per SIMD must fit beside the data set.  Where it
+// does not, the first columns stay in global memory, as few as leave room for two wavefronts per SIMD (an odd number of
+// groups: the row stride of the others must be an odd number of 16 bytes), or for one.  A lane reads its row's first columns
+// itself, 16 bytes of a line of its own at a time, which the vector cache serves at a line per cycle and CU: 64 cycles a group and
+// chunk.  train_linear_f32.h, which took these sets before, brings a chunk into LDS element by element.  us a call of it and
+// of this: 735 x 52, 8715 models, 17 epochs 10253 and 2121; 5000 models, 10 epochs on 827 x 39 (one far group) 2893 and 904, on
+// 900 x 60 (9) 4970 and 1154, on 1500 x 60 (13) 8550 and 1958; 2000 models on 4096 x 60 (15) 13381 and 3953, 40 models 6888 and 2649.
+__host__ __device__ inline LinLds ll_plan(int64_t n, int d, int c) {
+  LinLds l = {0, 0, 0, 0, 0};
   if (c > 2 || d > 63 || n < 1 || n > 4096) return l;
   l.dd = rup(d + 1, 8);
-  l.shared = (uint32_t)((n * (l.dd + 4) * 4 + n * 4 + 15) & ~15);
   l.wave_bytes = ll_wave_bytes(l.dd, n);
-  if (l.shared + 4 * l.wave_bytes > LL_LDS_LIMIT) return l;
-  const int fit = (int)((LL_LDS_LIMIT - l.shared) / l.wave_bytes), most = 4 * ll_occupancy(l.dd);
-  l.waves = fit < most ? fit : most;
+  const int most = 4 * ll_occupancy(l.dd);
+  for (int least = 4; least <= 8; least += 4) {
+    LinLds t = l;
+    for (t.far = least == 4 ? 0 : 1; 4 * t.far <= d; t.far += t.far ? 2 : 1) {
+      t.shared = (uint32_t)((n * ll_stride(l.dd, t.far) * 4 + n * 4 + 15) & ~15);
+      const int fit = t.shared < LL_LDS_LIMIT ? (int)((LL_LDS_LIMIT - t.shared) / l.wave_bytes) : 0;
+      t.waves = fit < most ? fit : most;
+      if (t.waves >= least) break;
+      t.waves = 0;
+    }
+    if (t.waves) l = t;
+    if (l.waves && !l.far) break;
+  }
   return l;
 }
 
-template <int D, int CO>
+template <int D, int CO, bool FAR>
 struct LinearLds {
-  static constexpr int S = D + 4, NQ = D / 4;
+  static constexpr int NQ = D / 4;
   static constexpr bool SPLIT = CO == 2 && D <= 32;  // the classes of a column in lanes t and t + 32
   static constexpr int NB = CO == 2 && !SPLIT ? 2 : 1;  // parameters of a lane
   const TrainParams& P;
   const float *xs, *ys;
   float* ws;
   uint16_t *sl, *ep, *ft;
-  int lane, d, n_classes, Pn;
+  int lane, d, n_classes, Pn, far;
 
   __device__ __forceinline__ void load_row(int row, f32x4 (&x)[NQ]) const {
-    const float* p = xs + row * S;
+    if constexpr (FAR) {
+      typedef f32x4 __attribute__((aligned(4))) Unaligned;
+      const float* away = (const float*)P.X + row * d;
+      const int at = row * ll_stride(D, far) - 4 * far;
 #pragma unroll
-    for (int q = 0; q < NQ; q++) x[q] = *(const f32x4*)(p + 4 * q);
+      for (int q = 0; q < NQ; q++) x[q] = q < far ? *(const Unaligned*)(away + 4 * q) : *(const f32x4*)(xs + (at + 4 * q));
+    } else {
+      const float* p = xs + row * (D + 4);
+#pragma unroll
+      for (int q = 0; q < NQ; q++) x[q] = *(const f32x4*)(p + 4 * q);
+    }
   }
   // the output, or with two classes z[1] - z[0]
   __device__ __forceinline__ float forward(const f32x4 (&x)[NQ]) const {
@@ -357,26 +381,27 @@ struct LinearLds {
 };
 
 // The launch gives a workgroup the LDS of the data set and ll_wave_bytes() for each of its wavefronts.
-template <int D, int CO>
+template <int D, int CO, bool FAR>
 __global__ __attribute__((amdgpu_flat_work_group_size(64, 256 * ll_occupancy(D)),
                           amdgpu_waves_per_eu(ll_occupancy(D), ll_occupancy(D))))
 void k_train_linear_lds(const TrainParams P) {
   extern __shared__ __align__(16) char ll_lds[];
-  typedef LinearLds<D, CO> T;
+  typedef LinearLds<D, CO, FAR> T;
   const int n = (int)P.n, d = P.d;
-  float *xs = (float*)ll_lds, *ys = xs + n * T::S;
+  const int far = FAR ? uniform(ll_plan(n, d, CO).far) : 0, S = ll_stride(D, far);
+  float *xs = (float*)ll_lds, *ys = xs + n * S;
 #pragma unroll 8
-  for (int i = threadIdx.x; i < n * T::S; i += blockDim.x) {
-    const int r = i / T::S, k = i - r * T::S;
+  for (int i = threadIdx.x; i < n * S; i += blockDim.x) {
+    const int r = i / S, k = 4 * far + i - r * S;
     xs[i] = k < d ? ((const float*)P.X)[r * d + k] : (k == d ? 1.f : 0.f);
   }
   for (int i = threadIdx.x; i < n; i += blockDim.x) ys[i] = ((const float*)P.y)[i];  // (class ids as they are)
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  char* own = ll_lds + (((uint32_t)(n * T::S + n) * 4 + 15) & ~15u) + wave * ll_wave_bytes(D, n);
+  char* own = ll_lds + (((uint32_t)(n * S + n) * 4 + 15) & ~15u) + wave * ll_wave_bytes(D, n);
   const uint32_t list = (2 * n + 15) & ~15u;
   T t{P, xs, ys, (float*)own, (uint16_t*)(own + D * 4), (uint16_t*)(own + D * 4 + list),
-      (uint16_t*)(own + D * 4 + 2 * list), lane, d, P.n_classes, (d + 1) * CO};
+      (uint16_t*)(own + D * 4 + 2 * list), lane, d, P.n_classes, (d + 1) * CO, far};
   for (;;) {
     // every lane takes part in the pop (see k_train_linear)
     __builtin_amdgcn_wave_barrier();
