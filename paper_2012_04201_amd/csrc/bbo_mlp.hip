@@ -883,6 +883,13 @@ int device_cus(int* out) {
 
 // The dynamic-LDS limit of a kernel is a property of the kernel on a device: it is set when first needed and
 // raised when a later call needs more, not on every call.
+// More than half of a CU's LDS, which every workgroup of a call with several launches and few models is given, whatever it
+// uses: each hardware queue places its workgroups by itself, and two of them put theirs on the same CUs while others are
+// idle.  The line is at a workgroup for every second CU, so that two such calls on different streams still run side by side.
+// 40 models 506 x 13 in three launches 1435 -> 1254 us a call, 45 models 1302 x 18 2313 -> 2175, 347 x 22 612 -> 560; with
+// eight waves a model (1797 x 64) the registers keep workgroups apart already.
+constexpr uint32_t LDS_OF_A_CU = 82 * 1024;
+
 int ensure_dynamic_lds(const void* fn, uint32_t bytes) {
   struct Seen {
     int dev;
@@ -1484,6 +1491,14 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
     if ((rc = side_streams(n_side, &streams))) return rc;
     HIP_TRY(side.fork(streams, s, n_side));
   }
+  uint32_t least_lds = 0;
+  if (pl.sub.size() > 1) {
+    int cus = 0;
+    if ((rc = device_cus(&cus))) return rc;
+    size_t all = 0;
+    for (const SubPlan& sp : pl.sub) all += sp.n_slots;
+    if (2 * all <= (size_t)cus) least_lds = LDS_OF_A_CU;
+  }
   for (size_t li = 0; li < pl.sub.size(); li++) {
     const SubPlan& sp = pl.sub[li];
     const int k = sp.kc;
@@ -1519,12 +1534,13 @@ int run_eval(const void* X, const void* y, int64_t n, int32_t d, int32_t n_class
       fn = dtype == BBO_F32 ? (const void*)k_train<float> : (const void*)k_train<__bf16>;
     }
     if (!fn) return fail(BBO_DEVICE_ERROR, "no kernel for this shape");  // ruled out by kernel_class()
-    if (sp.lds_bytes && (rc = ensure_dynamic_lds(fn, sp.lds_bytes))) return rc;
+    const uint32_t lds_bytes = sp.lds_bytes ? std::max(sp.lds_bytes, least_lds) : 0;
+    if (lds_bytes && (rc = ensure_dynamic_lds(fn, lds_bytes))) return rc;
     P.team_size = sp.team;
     const int workgroups = sp.team > 1 ? rup(sp.n_slots, TEAM_XCDS) * sp.team : sp.n_slots;
     void* args[] = {&P};
     const int lane = (int)(li % (size_t)(n_side + 1));
-    HIP_TRY(hipLaunchKernel(fn, dim3(workgroups), dim3(threads), args, sp.lds_bytes, lane ? side.side->s[lane - 1] : s));
+    HIP_TRY(hipLaunchKernel(fn, dim3(workgroups), dim3(threads), args, lds_bytes, lane ? side.side->s[lane - 1] : s));
     HIP_TRY(hipGetLastError());
   }
   HIP_TRY(side.join());

@@ -56,6 +56,7 @@ __host__ __device__ inline int ll_stride(int dd, int far) { return far > 0 ? dd 
 // chunk.  train_linear_f32.h, which took these sets before, brings a chunk into LDS element by element.  us a call of it and
 // of this: 735 x 52, 8715 models, 17 epochs 10253 and 2121; 5000 models, 10 epochs on 827 x 39 (one far group) 2893 and 904, on
 // 900 x 60 (9) 4970 and 1154, on 1500 x 60 (13) 8550 and 1958; 2000 models on 4096 x 60 (15) 13381 and 3953, 40 models 6888 and 2649.
+// (Room for one wavefront per SIMD only, with fewer far columns: 1500 x 60 2694 instead of 1941, 5000 models 2000 x 30 1851 and 1496.)
 __host__ __device__ inline LinLds ll_plan(int64_t n, int d, int c) {
   LinLds l = {0, 0, 0, 0, 0};
   if (c > 2 || d > 63 || n < 1 || n > 4096) return l;

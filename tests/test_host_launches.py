@@ -156,3 +156,11 @@ def test_a_workspace_for_the_widest_models_holds_a_mix_of_narrower_ones(child, n
         assert (t0, l0) == (t1, l1) and g <= g1 <= 2 * g + 1
     assert len(grids(tight)) == len(grids(roomy))
     assert streams(tight) in (streams(roomy), {"900"}) and (ws < full or streams(tight) == streams(roomy))
+
+
+@pytest.mark.parametrize("models,apart", [(2, True), (6, True), (7, False), (60, False)])
+def test_workgroups_of_launches_side_by_side_get_a_cu_each(child, models, apart):
+    """40, 120, 140 and 1200 workgroups in four launches: up to one for every second of 256 CUs, no CU has the LDS for two."""
+    log = child("rc = evaluate(569, 30, 2, 5, [[50], [100], [150], [200]] * %d); assert rc == 0; print(json.dumps(log()))" % models)
+    lds = [int(l[4]) for l in log if l[0] == "launch" and "k_train" in l[5]]
+    assert len(lds) == 4 and (min(lds) * 2 > 160 * 1024) == apart
