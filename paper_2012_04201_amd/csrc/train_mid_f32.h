@@ -19,7 +19,7 @@
 // moments in L2, one model of 8 waves per CU, four barriers per chunk: 1000 models of 64-128-10 on 1797 rows, 3 epochs,
 // took 5.5 ms and take 3.2 ms (64 units: 4.2 and 2.5 ms; 200 units: 8.7 and 5.1 ms).  With the row pipeline's leaner schedule
 // and the input layer's products in split bfloat16 (md_splittable()) 512 suggestions of the digits shape took 14.0 ms instead
-// of 15.5.
+// of 15.5, and take 13.2 with the row tiles of a chunk together and moments in units of their own.
 #pragma once
 #include "common.h"
 #include "train_small_f32.h"  // the row pipeline
@@ -84,8 +84,8 @@ __host__ __device__ constexpr bool md_splittable(int kt, int nt, int waves) {
 // of this kernel.  One tile a wave while eight waves reach (more models a CU with four), else two: one tile leaves the
 // registers for everything, and eight waves of one tile beat four of two by a quarter even with the chip full (64-100-10,
 // 1000 models: 3.2 ms against 3.9).  Beyond kt * nt = 12 the weights and gradients alone overflow the registers; close to
-// it they crowd others out: by the compiler's report <3,2,8> spills 26 vector registers, <4,2,8> 21, <5,2,8> 51, <6,2,8> 216,
-// the split form of <4,2,8> 19, the others 5 at most.  (<6,2,8> against its form before the leaner schedule, 90 inputs, 200 and
+// it they crowd others out: by the compiler's report <3,2,8> spills 15 vector registers, <4,2,8> 7, <5,2,8> 50, <6,2,8> 134,
+// the split forms of <3,2,8> and <4,2,8> 48 and 40, the others 2 at most.  (<6,2,8> against its form before the leaner schedule, 90 inputs, 200 and
 // 250 units: 0.95 at 32 rows a step, 1.02 to 1.04 at 65 to 128.)
 __host__ inline SmallCut mid_cut(const int32_t* dims, int L, int32_t batch_size) {
   SmallCut m = {0, 0, 0, 0};

@@ -31,7 +31,8 @@
 // four lane groups q) is done four parameters at a time, one per q; the loss of a training chunk is computed only where the
 // stopping rule or a trace reads it.  With the output columns of two classes merged, these took 10,240 models 569 x 30 from
 // 30.7 to 27.4 ms and 40 models of 10,000 x 45 from 4.02 to 3.59; products in split bfloat16 (sm_split()) and the leaner
-// schedule then to 24.2 and 3.56.  The form before this one kept the weights in LDS and the moments in L2, at
+// schedule then to 24.2 and 3.56, hidden deltas without the output weight, small parameters in registers and moments in units of
+// their own to 19.0 and 3.46.  The form before this one kept the weights in LDS and the moments in L2, at
 // two workgroups per CU whatever the width and two barriers per chunk.  Before and after, per call: 10,240 models
 // 569 x 30, 50..200 units, 20 epochs 45.3 -> 32.4 ms; 40 models 506 x 13, SGD, 30 epochs 3.41 -> 1.74 ms; 40 models of
 // 10,000 x 45 rows, 3 epochs 10.9 -> 4.45 ms; 40 models 150 x 4, 20 epochs 0.39 -> 0.25 ms.
@@ -177,8 +178,8 @@ __host__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n, const Sm
 
 // Waves per SIMD the registers of a variant are budgeted for (512 registers per lane and SIMD).  The largest variants of a
 // budget do not fit it altogether: by the compiler's report <2,3,1,4> and <2,3,2,4> (129 to 192 units, 17 to 32 inputs)
-// spill 95 and 97 vector registers, <3,2,4,4> and <3,2,4,8> 92 and 78, <4,2,.,8> (129 units and more, 49 inputs and more)
-// 79, 157 and 209 at one, two and four output slots; the others 18 at most.  (<3,2,4,.> spilled 82 and 62 with the moments of the
+// spill 102 and 118 vector registers, <3,2,4,4> and <3,2,4,8> 103 and 80, <4,2,.,8> (129 units and more, 49 inputs and more)
+// 100, 135 and 223 at one, two and four output slots; the others 18 at most.  (<3,2,4,.> at first spilled 82 and 62 with the moments of the
 // small parameters in LDS.  45 inputs, four classes, 200 suggestions, us a call then and now: 100 units, 24, 64 and 128 rows a step
 // 1202 and 1185, 727 and 720, 649 and 669; 130 units 1165 and 1081 at 64 rows.  These moments in LDS again, four a lane: 60 and
 // 42 spilled, 100 units 671 at 128 rows, 130 units 1100 at 64.)  Four output slots need more than the 128
