@@ -645,10 +645,13 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
   __device__ __forceinline__ void update(State& R, const OptC& oc) const {
     OptC o = oc;
     o.adam = ADAM;
-    // Pads need no mask (see k_train_small).  With three layers on four waves the least eps clears them all the same: no value
-    // changes, but the branch parts the blocks for the register allocation: 500 models of 569 x 50, 60-60-60, 24 rows a step, 3
-    // epochs 1957 us a call without it, 1755 with it; elsewhere it costs (128-40-100 3252 and 3491, 128-128-128 5245 and 6026).
-    const bool pads = ADAM && H == 3 && W == 4 && least_eps(o);
+    // Pads need no mask (see k_train_small).  In two cuts the least eps clears them all the same: no value
+    // changes, but the branch parts the blocks for the register allocation.  Three layers on four waves: 500 models of 569 x 50,
+    // 60-60-60, 24 rows a step, 3 epochs 1957 us a call without it, 1755 with it; elsewhere it costs (128-40-100 3252 and 3491,
+    // 128-128-128 5245 and 6026).  Two layers on eight waves and three input tiles spill 28 registers without it and 8 with it: 500
+    // models of 569 x 40, 128-100, 5 epochs, 24, 64 and 128 rows a step 3946 and 3765, 2314 and 2146, 1953 and 1925, 100-70
+    // 3231 and 3269; with one, two and four tiles it costs 1 to 4 %.
+    const bool pads = ADAM && ((H == 3 && W == 4) || (H == 2 && W == 8 && KT == 3)) && least_eps(o);
     const Places z = places();
     // Moments in the slot are fetched AHEAD blocks early.  A block that the wave does not have is sent out of the
     // descriptor's range (zeros come back, nothing is written) instead of branched around: with the same memory operations
