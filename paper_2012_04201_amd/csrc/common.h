@@ -293,8 +293,8 @@ struct OptC {
   float b1, b2, omb1, omb2, eps, lr_t, mu, lr, am;
 };
 
-// The least eps, in the units of opt_step(): larger by 2^12 at most.
-__device__ __forceinline__ bool least_eps(const OptC& c) { return __float_as_uint(c.eps) >> 23 <= (__float_as_uint(EPS_MIN) >> 23) + 12; }
+// The least eps, in the units of opt_step(): smaller by less than a factor of 2.
+__device__ __forceinline__ bool least_eps(const OptC& c) { return __float_as_uint(c.eps) >> 23 <= __float_as_uint(EPS_MIN) >> 23; }
 
 // max(x, 0) in one instruction.  A NaN stays one, in every kernel: a model that blew up, or met a NaN in its data, has a score
 // that says so.  (fmaxf() and a median make it 0.)
@@ -315,18 +315,22 @@ __device__ inline void opt_update(const OptC& c, float g, float& w, float& m, fl
   }
 }
 
-// The same with an Adam model's moments kept in units of what a gradient adds to them, m / (1 - b1) and v / (1 - b2): two
-// vector instructions and two roundings less.  eps is in units of sqrt(1 - b2) then, and the step size takes the rest.
+// The same with an Adam model's gradients, moments and eps in units of their own, which take two vector instructions and
+// two roundings less: the output deltas, and with them every gradient, come scaled by a power of two (so no value is rounded
+// otherwise) just below sqrt(1 - b2), the moments are m * grad / (1 - b1) and v * grad^2 / (1 - b2), and the step size takes
+// the rest.  v is kept within a factor of 4 of its value, so that gradients may be as large as in opt_update(); in units of
+// 1 / (1 - b2), with the gradients as they are, it overflowed from gradients of 5.8e17 on with a b2 of 0.999.
 struct AdamUnits {
-  float m, v, eps;  // of the moments in units of their own; eps in its
+  float grad, m, v, eps;  // what each is multiplied by; eps in its unit
   double lr;
   __device__ __forceinline__ AdamUnits(float b1, float b2, float e) {
     const float omb1 = 1.f - b1, omb2 = 1.f - b2;
     // (b2 = 1: a step size of zero, and moments that nobody sees)
     const double root = omb2 != 0.f ? sqrt((double)omb2) : 1.0;
-    m = 1.f / omb1;
-    v = omb2 != 0.f ? 1.f / omb2 : 0.f;
-    eps = (float)((double)e / root);
+    grad = __uint_as_float(__float_as_uint((float)root) & 0x7f800000u);
+    m = grad / omb1;
+    v = omb2 != 0.f ? grad * grad / omb2 : 0.f;
+    eps = (float)((double)e * (double)grad / root);
     lr = (double)omb1 / root;
   }
 };

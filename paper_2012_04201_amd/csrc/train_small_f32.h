@@ -643,6 +643,14 @@ struct RowPipe {
     if (tabled && threadIdx.x < SM_RC) u16(o_sl)[n_tr + threadIdx.x] = 0;
   }
 
+  // A traced step's gradient as the caller wants it (see AdamUnits).  (With threadIdx.x every variant takes two registers more.)
+  __device__ __forceinline__ void out_of_unit(float* g) const {
+    __syncthreads();
+    const float unit = AdamUnits(item().beta1, item().beta2, item().eps).grad;
+#pragma unroll 1
+    for (int i = tid(); i < y.p.P; i += NTHR) g[i] /= unit;
+  }
+
   __device__ __forceinline__ void run() {
     Self& self = *static_cast<Self*>(this);
     const int n_tr = uniform(P.counts[2 * fl]), n_va = uniform(P.counts[2 * fl + 1]);
@@ -664,8 +672,9 @@ struct RowPipe {
     const bool watch = it.patience > 0 && steps > 0 && !resume;
     const int n_hold = pin(uniform(watch ? sp.n_hold : 0));
     const float mb_last = (float)(n_fit - (steps - 1) * bs);
-    const float inv_full = uniform(1.f / (float)bs), inv_last = uniform(1.f / mb_last);
-    const float am_full = uniform(it.alpha / (float)bs), am_last = uniform(it.alpha / mb_last);
+    const float unit = it.solver == BBO_ADAM ? AdamUnits(it.beta1, it.beta2, it.eps).grad : 1.f;  // of the gradients
+    const float inv_full = uniform(unit / (float)bs), inv_last = uniform(unit / mb_last);
+    const float am_full = uniform(unit * (it.alpha / (float)bs)), am_last = uniform(unit * (it.alpha / mb_last));
 
     // ---- the schedule: training chunks, after each epoch the rows set aside, at the end the held fold ----
     // Position of the chunk whose inputs are requested next: first row `at` in its order, step st of epoch e, `left`
@@ -824,8 +833,8 @@ struct RowPipe {
                   q1 *= q1;
                   q2 *= q2;
                 }
-                const double unit = AdamUnits(item().beta1, item().beta2, item().eps).lr;
-                lr_tab = (float)((double)item().lr * sqrt(1.0 - b2t) / (1.0 - b1t) * unit);
+                const double rest = AdamUnits(item().beta1, item().beta2, item().eps).lr;
+                lr_tab = (float)((double)item().lr * sqrt(1.0 - b2t) / (1.0 - b1t) * rest);
               }
               oc.lr_t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lr_tab), lr_at));
               lr_at++;
@@ -860,6 +869,7 @@ struct RowPipe {
               self.template update<false>(R, oc);
             if (recording) {
               self.template record<false>(R, oc.am, rec + 1 + y.p.P);
+              if (oc.adam) out_of_unit(rec + 1);
               const double after = self.total(lsum);
               const float mb = c0 & SC_RAGGED ? (float)last_rows : (float)bs;
               if (threadIdx.x == 0)
