@@ -24,7 +24,7 @@ PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}  # MI355X dense MFMA peaks
 PEAK_VALU_TFLOPS = 157.3  # fp32 vector: 256 CUs x 128 lanes x 2 flop (multiply-add) x 2.4 GHz
 PEAK_HBM_GBS = 8000.0
 # the sources each workload's training kernel is built from (the host code in bbo_mlp.hip does not count)
-KERNEL_SOURCES = {"k_train_tiled": ["common.h", "train_tiled_bf16.h"], "k_train_small": ["common.h", "train_small_f32.h"],
+KERNEL_SOURCES = {"k_train_tiled": ["common.h", "team.h", "train_tiled_bf16.h"], "k_train_small": ["common.h", "train_small_f32.h"],
                   "k_train_linear": ["common.h", "train_linear_f32.h"],
                   "k_train_linear_lds": ["common.h", "train_small_f32.h", "train_linear_lds_f32.h"],
                   "k_train": ["common.h", "bbo_mlp.hip"],

@@ -990,19 +990,19 @@ void merge_full(Plan& pl, int n_folds) {
 
 constexpr int TEAM_XCDS = 8;  // a team's workgroups share an XCD: launched in eights, one for each
 
-// Workgroups that train one model together (Team in train_tiled_bf16.h) in a call of `models` models, of which each has
+// Workgroups that train one model together (team.h) in a call of `models` models, of which each has
 // `sp`'s kernel; 1: each model has a workgroup of its own.  A team takes every step in one chunk and sets no rows aside.
 // It pays as soon as two workgroups a model have a CU each: us a step of one and of a team, 128-256-256-10, 64 rows, 8, 32, 64, 96 and
 // 128 models 57 and 37, 64 and 42, 66 and 49, 68 and 59, 95 and 82; 128-200-10, 256 rows 37 and 30 to 40 and 37.
 int team_size(const SubPlan& sp, size_t models, int64_t n, const bbo_mlp_hparams* hp, int cus) {
-  if (sp.kc != KC_TILED) return 1;
+  if (sp.kc != KC_TILED || (size_t)sp.n_slots < models) return 1;  // (a team has its model, and a slot, by number)
   for (const int32_t b : sp.order) {
     const bbo_mlp_hparams& h = hp[b];
     if ((h.batch_size <= 0 || h.batch_size > TB_ROWS) && n > TB_ROWS) return 1;
     if (h.n_iter_no_change > 0 && h.validation_fraction > 0.f) return 1;
   }
   const size_t teams = (models + TEAM_XCDS - 1) / TEAM_XCDS;  // of an XCD
-  return (int)std::max<size_t>(1, std::min<size_t>(TB_TEAM_MAX, (size_t)(cus / TEAM_XCDS) / teams));
+  return (int)std::max<size_t>(1, std::min<size_t>(TEAM_MOST, (size_t)(cus / TEAM_XCDS) / teams));
 }
 
 // The launches of a call, their workgroups and where everything lies in a workspace of `room` bytes (pl.total may exceed
@@ -1183,7 +1183,7 @@ int make_plan(Plan& pl, int64_t n, int d, int n_classes, int n_folds, int fold_b
     if (int rc = device_cus(&cus)) return rc;
     sp.team = team_size(sp, pl.n_items, n, hp, cus);
     if (sp.team > 1) {
-      pl.n_queues += rup(sp.n_slots, TEAM_XCDS) * TB_TEAM_WORDS;
+      pl.n_queues += rup(sp.n_slots, TEAM_XCDS) * TEAM_WORDS;
       if (int rc = lay_out()) return rc;
       if (pl.total <= room) return BBO_OK;
       sp.team = 1;  // a workspace of fixed size holds what it held

@@ -19,33 +19,29 @@ __global__ __launch_bounds__(TB_THREADS) void k_train_tiled(const TrainParams P)
     const int item = __builtin_amdgcn_readfirstlane(s_item);
     if (item >= P.n_items) break;
     ConstTItem* ti = (ConstTItem*)P.items + item / P.n_folds;
-    Tiled<false> T{P, ti->d, ti->y, slot, smem, red, item % P.n_folds, Team{nullptr, 0, 1}, nullptr};
-    uint32_t meetings = 0;
-    T.run(meetings);
+    Tiled<false> T{P, ti->d, ti->y, slot, smem, red, item % P.n_folds, Team{{nullptr}, {0, 1}}, nullptr};
+    T.run();
   }
 }
 
-// A team of workgroups per model: workgroup (j * team_size + m) * 8 + x is member m of team 8 j + x, and the slot is the item's.
+// A team of workgroups per model: workgroup (j * team_size + m) * 8 + x is member m of team 8 j + x, which has that item.  (A
+// queue would hand the longest model to whoever comes to it first, also to a workgroup that has been left alone.)
 __global__ __launch_bounds__(TB_THREADS) void k_train_tiled_team(const TrainParams P) {
   extern __shared__ __align__(16) char smem[];
-  __shared__ int s_item, s_met;
-  __shared__ Team s_team;
+  __shared__ int s_met;
+  __shared__ TeamPlace s_place;
   __shared__ double red[TB_THREADS / 64];
   const int x = blockIdx.x & 7, j = (int)(blockIdx.x >> 3) / P.team_size, m = (int)(blockIdx.x >> 3) % P.team_size;
-  if (threadIdx.x == 0) s_team.join(P.teams + (j * 8 + x) * TB_TEAM_WORDS, m, P.team_size);
+  const int item = 8 * j + x;
+  if (item >= P.n_items) return;
+  TeamBlock block{P.teams + item * TEAM_WORDS};
+  if (threadIdx.x == 0) s_place = team_join(block, m, P.team_size, __builtin_amdgcn_s_getreg(20 | (3 << 11)));  // XCC_ID
   __syncthreads();
-  const Team team{uniform(s_team.ctl), uniform(s_team.member), uniform(s_team.members)};
-  uint32_t meetings = 0;
-  for (int turn = 1;; turn++) {
-    __syncthreads();
-    if (threadIdx.x == 0) s_item = team.next_item(P.queue, P.n_items, turn);
-    __syncthreads();
-    const int item = __builtin_amdgcn_readfirstlane(s_item);
-    if (item >= P.n_items) break;
-    ConstTItem* ti = (ConstTItem*)P.items + item / P.n_folds;
-    Tiled<true> T{P, ti->d, ti->y, P.slots + (uint64_t)item * P.slot_bytes, smem, red, item % P.n_folds, team, &s_met};
-    T.run(meetings);
-  }
+  const Team team{block, {uniform(s_place.member), uniform(s_place.members)}};
+  if (team.place.members == 0) return;
+  ConstTItem* ti = (ConstTItem*)P.items + item / P.n_folds;
+  Tiled<true> T{P, ti->d, ti->y, P.slots + (uint64_t)item * P.slot_bytes, smem, red, item % P.n_folds, team, &s_met};
+  T.run();
 }
 
 }  // namespace

@@ -46,6 +46,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "team.h"
 
 namespace {
 
@@ -187,70 +188,21 @@ __device__ inline bf16x8 lds_operand_tr(const char* base, int ld, int r0, int u0
 // step of few rows.  A member's new weights reach the others through the L2 of their XCD, with one meeting a step: the
 // operand copies and biases are double-buffered by step parity, so nobody writes what a slower member still reads.
 //
-// A team forms when the kernel starts: workgroups b, b + 8, b + 16, .. lie on one XCD as a rule, but it is the hardware's
-// own number that decides, and only workgroups that are running are counted in.  The leader waits for the others for a
-// bounded time (they may have no CU yet), closes the list and says who is in; a member that has waited as long for the
-// leader takes itself off the list.  Whoever is not in works alone, as a team of one.  So every later wait is for a
-// workgroup that runs.
+// How a team forms and what its members wait for: team.h.
 //
 // What bounds a team's step: what its members all do.  128-256-256-10, 64 rows a step, 64 models, k cycles with one workgroup
 // a model and with four: weight gradients 74 and 39 (the state of all models in flight comes from the memory-side cache),
 // forward pass 28 and 29, data gradients 19 and 20, rows 11 and 12, the meeting 1.
-constexpr int TB_TEAM_MAX = 8;
-constexpr int TB_TEAM_WORDS = 16;  // of a team's control block: [0..1] who came, [2] who is in, [3] item, [8..] members' meetings
-constexpr int TB_JOIN_POLLS = 200;      // about 100 us
-constexpr int TB_MEET_POLLS = 1 << 23;  // seconds: the members all run, so only a fault elsewhere lets a wait end here
-struct Team {
+constexpr int TEAM_WORDS = 16;  // of a team's control block: [0..1] the list, [8..] members' meetings
+struct TeamBlock {
   uint32_t* ctl;
-  int member, members;
-  // Called by one thread of a workgroup: its place among the `size` workgroups that share `ctl`.
-  __device__ void join(uint32_t* ctl_, int m, int size) {
-    unsigned long long* list = (unsigned long long*)ctl_;
-    constexpr unsigned long long CLOSED = 1ull << 63;
-    const unsigned long long me = 8 | (__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 7);  // XCC_ID
-    ctl = ctl_;
-    member = 0;
-    members = 1;
-    unsigned long long seen = atomicOr(list, me << (4 * m));
-    uint32_t in = 0;
-    if (m == 0) {
-      unsigned long long all = 0;
-      for (int k = 0; k < size; k++) all |= 8ull << (4 * k);
-      for (int i = 0; i < TB_JOIN_POLLS && (seen & all) != all; i++) {
-        __builtin_amdgcn_s_sleep(8);
-        seen = atomicOr(list, 0ull);
-      }
-      seen = atomicOr(list, CLOSED) | me;
-      for (int k = 0; k < size; k++) in |= ((seen >> (4 * k)) & 15) == me ? 1u << k : 0u;
-      atomicExch(&ctl[2], in | 0x100u);
-    } else {
-      if (seen & CLOSED) return;
-      for (int i = 0; i < 2 * TB_JOIN_POLLS && !in; i++) {
-        __builtin_amdgcn_s_sleep(8);
-        in = atomicOr(&ctl[2], 0u);
-      }
-      if (!in) {
-        if (!(atomicAnd(list, ~(15ull << (4 * m))) & CLOSED)) return;
-        while (!(in = atomicOr(&ctl[2], 0u))) {  // the leader has just closed the list
-        }
-      }
-    }
-    if (!((in >> m) & 1u)) return;
-    member = __popc(in & ((1u << m) - 1u));
-    members = __popc(in & 0xffu);
-  }
-  // Called by one thread: the team's turn-th item.
-  __device__ int next_item(int32_t* queue, int n_items, int turn) const {
-    if (members == 1) return atomicAdd(queue, 1);
-    if (member == 0) {
-      const int item = min(atomicAdd(queue, 1), n_items);
-      atomicExch(&ctl[3], (uint32_t)(turn << 16 | item));
-      return item;
-    }
-    uint32_t v;
-    while ((v = atomicOr(&ctl[3], 0u)) >> 16 != (uint32_t)turn) __builtin_amdgcn_s_sleep(4);
-    return (int)(v & 0xffffu);
-  }
+  __device__ uint64_t list() const { return atomicOr((unsigned long long*)ctl, 0ull); }
+  __device__ uint64_t change(uint64_t from, uint64_t to) const { return atomicCAS((unsigned long long*)ctl, from, to); }
+  __device__ void pause() const { __builtin_amdgcn_s_sleep(8); }
+};
+struct Team {
+  TeamBlock block;
+  TeamPlace place;
 };
 
 template <bool TEAM>
@@ -266,24 +218,24 @@ struct Tiled {
   int* met;  // LDS: a meeting has come about
 
   // The wave's number among all waves that share the tiles of a weight gradient, and how many those are.
-  __device__ __forceinline__ int team_wave() const { return uniform((int)(threadIdx.x >> 6)) + (TEAM ? team.member * TB_WAVES : 0); }
-  __device__ __forceinline__ int team_waves() const { return TEAM ? team.members * TB_WAVES : TB_WAVES; }
+  __device__ __forceinline__ int team_wave() const { return uniform((int)(threadIdx.x >> 6)) + (TEAM ? team.place.member * TB_WAVES : 0); }
+  __device__ __forceinline__ int team_waves() const { return TEAM ? team.place.members * TB_WAVES : TB_WAVES; }
   // What the members have stored is seen by all of them afterwards, where it is read with from_team(): a member's stores are in
   // the L2 when its waves have waited for them.  n: the how many-th meeting.
   __device__ __forceinline__ bool meet(uint32_t n) const {
-    if (!TEAM || team.members == 1) {
+    if (!TEAM || team.place.members == 1) {
       __syncthreads();
       return true;
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x < 64) {
-      uint32_t* at = team.ctl + 8;
-      if (threadIdx.x == 0) __hip_atomic_store(at + team.member, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      const uint32_t* other = at + min((int)threadIdx.x, team.members - 1);
+      uint32_t* at = team.block.ctl + 8;
+      if (threadIdx.x == 0) __hip_atomic_store(at + team.place.member, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      const uint32_t* other = at + min((int)threadIdx.x, team.place.members - 1);
       int i = 0;
-      while (__any((int)(__hip_atomic_load(other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n)) && i < TB_MEET_POLLS) i++;
-      if (threadIdx.x == 0) *met = i < TB_MEET_POLLS ? 1 : 0;
+      while (__any((int)(__hip_atomic_load(other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n)) && i < TEAM_MEET_POLLS) i++;
+      if (threadIdx.x == 0) *met = i < TEAM_MEET_POLLS ? 1 : 0;
     }
     __syncthreads();
     return *met != 0;
@@ -354,7 +306,7 @@ struct Tiled {
       const int fi = y.U[l], fo = y.U[l + 1];
       const uint64_t kw = key_fold(km, 16 + 2 * l), kb = key_fold(km, 16 + 2 * l + 1);
       const float bound = it.bound[l];
-      for (int i = threadIdx.x + (TEAM ? team.member * TB_THREADS : 0); i < fi * fo + fo; i += team_waves() * 64) {
+      for (int i = threadIdx.x + (TEAM ? team.place.member * TB_THREADS : 0); i < fi * fo + fo; i += team_waves() * 64) {
         const bool isb = i >= fi * fo;
         const int e = isb ? i - fi * fo : i;
         const uint32_t k24 = (uint32_t)(key_fold(isb ? kb : kw, (uint64_t)e) >> 40);
@@ -454,8 +406,8 @@ struct Tiled {
     int mt0 = 0, mta = (y.U[l] + 15) / 16;  // unit tiles that hold real units: the others are never read back
     if (TEAM) {  // the in tiles of the member's share of wgrad_stream()'s tiles (a tile of two members' comes from both, alike)
       const int Ne = (y.U[l + 1] + 15) / 16, TT = mta * Ne;
-      mt0 = team.member * TT / team.members / Ne;
-      mta = ((team.member + 1) * TT / team.members + Ne - 1) / Ne;
+      mt0 = team.place.member * TT / team.place.members / Ne;
+      mta = ((team.place.member + 1) * TT / team.place.members + Ne - 1) / Ne;
     }
     for (int mt = mt0; mt < mta; mt++) {
       const bf16x8 v = lds_operand_tr(buf(), TB_S, 32 * w, mt * 16, li, q);
@@ -1468,8 +1420,8 @@ struct Tiled {
       *(uint4*)(dbuf() + (32 * w) * 32 + (threadIdx.x & 63) * 16) = uint4{0, 0, 0, 0};
   }
 
-  // meetings: of the team so far
-  __device__ __forceinline__ void run(uint32_t& meetings) const {
+  __device__ __forceinline__ void run() const {
+    uint32_t meetings = 0;
     const int L = y.L;
     const int n_tr = P.counts[2 * fl], n_va = P.counts[2 * fl + 1];
     const int32_t* tr = P.train_idx + (int64_t)fl * P.n;
@@ -1484,7 +1436,7 @@ struct Tiled {
     {
       uint4* z = (uint4*)slot;
       const uint64_t n16 = y.total / 16;
-      for (uint64_t i = threadIdx.x + (TEAM ? team.member * TB_THREADS : 0); i < n16; i += team_waves() * 64) z[i] = uint4{0, 0, 0, 0};
+      for (uint64_t i = threadIdx.x + (TEAM ? team.place.member * TB_THREADS : 0); i < n16; i += team_waves() * 64) z[i] = uint4{0, 0, 0, 0};
       // The activation buffer too: rows past a ragged chunk are never written, but the weight gradients read
       // them (against zero deltas), so they must hold finite numbers whatever ran on this CU before.
       uint4* zb = (uint4*)buf();
@@ -1576,7 +1528,7 @@ struct Tiled {
       }
       float watched = 0.f;
       if (watch && !final && !sp.n_hold) watched = (float)(block_sum(esum, red) / (double)n_fit);
-      if (TEAM && final && team.member > 0) break;  // the leader scores
+      if (TEAM && final && team.place.member > 0) break;  // the leader scores
       if (final && have_best) restore_best((int)(gstep & 1));
       if (final || (watch && sp.n_hold)) {
         // loss (and second score) of a list of rows under the current weights

@@ -69,3 +69,58 @@ def test_a_team_changes_no_bit(bb, n, d, c, K, models):  # noqa: F811
     for _ in range(3):
         together = bb.bbo_mlp_cv_eval(X, y, c, ft, K, hps, bb.BF16, want_per_fold=True)[2]
         assert torch.equal(together, apart)
+
+
+def teams_of(workspace, models):
+    """(members, meetings of each) per model, from the control blocks that a call leaves in its workspace: 16 words a team, the
+    list (four bits a member, 8 | its XCD, the leader's first; the highest bit says that it is closed) and from the ninth on how
+    many meetings each member has come to."""
+    w = workspace.cpu().numpy().view(np.uint32)
+    w = w[:w.size // 16 * 16].reshape(-1, 16)
+    closed = (w[:, 1] == 0x80000000) & (w[:, 0] & 8 > 0) & (w[:, 2] == 0)
+    first = next(i for i in range(len(w)) if closed[i:i + models].all() and closed[i:i + models].size == models)
+    out = []
+    for block in w[first:first + models]:
+        nibbles = [int(block[0]) >> 4 * k & 15 for k in range(8)]
+        members = sum(x == nibbles[0] for x in nibbles)
+        out.append((members, [int(x) for x in block[8:8 + members]]))
+    return out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("models", [1, 8, 30, 64])
+def test_teams_form_and_meet_after_every_step(bb, models):  # noqa: F811
+    """On a device without other work.  (Two meetings before the first step; one that is alone has none.)"""
+    n, d, c = 400, 64, 3
+    fold = np.where(np.arange(n) < 100, 0, 1).astype(np.int32)  # one fold of 300 training rows
+    X, y, ft = bb.to_device(dict(small_problem(5, n, d, c, bf16=True), n_folds=1, fold_idx=fold))
+    hps = [{"hidden": [100 + i % 50], "batch_size": 64, "epochs": 3, "seed": i} for i in range(models)]
+    need = bb.bbo_mlp_workspace_bytes(n, d, c, 1, hps, bb.BF16)
+    ws = torch.zeros(need, dtype=torch.uint8, device=X.device)
+    bb.bbo_mlp_cv_eval(X, y, c, ft, 1, hps, bb.BF16, workspace=ws)
+    torch.cuda.synchronize()
+    teams = teams_of(ws, models)
+    steps = 3 * -(-300 // 64)
+    print("members", sorted({m for m, _ in teams}))
+    assert all(m >= 2 for m, _ in teams)
+    assert all(met == [2 + steps] * m for m, met in teams), teams
+
+
+@pytest.mark.gpu
+def test_calls_at_once_change_no_bit(bb):  # noqa: F811
+    """Four calls on streams of their own, with more workgroups in all than there are CUs: teams come late or in part."""
+    n, d, c, K = 600, 64, 4, 4
+    X, y, ft = bb.to_device(dict(small_problem(9, n, d, c, bf16=True), n_folds=K, fold_idx=np.arange(n, dtype=np.int32) % K))
+    calls = [[{"hidden": [40 + 31 * i % 200] * (1 + i % 2), "batch_size": 64, "epochs": 4, "seed": 100 * j + i, "alpha": 0.1}
+              for i in range(10)] for j in range(4)]
+    alone = [bb.bbo_mlp_cv_eval(X, y, c, ft, K, hps, bb.BF16, want_per_fold=True)[2] for hps in calls]
+    rooms = [torch.empty(bb.bbo_mlp_workspace_bytes(n, d, c, K, hps, bb.BF16), dtype=torch.uint8, device=X.device) for hps in calls]
+    streams = [torch.cuda.Stream() for _ in calls]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        got = []
+        for hps, room, s in zip(calls, rooms, streams):
+            with torch.cuda.stream(s):
+                got.append(bb.bbo_mlp_cv_eval(X, y, c, ft, K, hps, bb.BF16, want_per_fold=True, workspace=room)[2])
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(alone, got))
