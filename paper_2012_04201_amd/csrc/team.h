@@ -1,10 +1,13 @@
-// How several workgroups come to train one model together.  Plain C++ over a control block `Ctl`, so that the same code runs on
-// the GPU (TeamBlock in train_tiled_bf16.h) and on threads of the host.
+// How several workgroups come to train one model together, and how they wait for each other.  Plain C++ over a control
+// block `Ctl`, so that the same code runs on the GPU (TeamBlock in train_tiled_bf16.h) and on threads of the host.
 //
 // A team forms when its kernel starts: whoever is running puts itself on a list, the leader waits for the others for a
 // bounded time (they may have no CU yet) and closes it.  A closed list is never changed again, so the word itself says who is
 // in, and nobody waits for an answer.  A member that has waited twice as long for the leader takes itself off.  Whoever is not
 // in has nothing to do: the leader trains the model with those who are, alone if need be.
+//
+// Every later wait is for a workgroup that runs, and bounded all the same.  Whoever gives one up says so in a word that is
+// never cleared, and all others of the team find it at the next meeting at the latest.
 #pragma once
 #include <stdint.h>
 
@@ -67,4 +70,19 @@ TEAM_FN TeamPlace team_join(Ctl& c, int m, int size, uint32_t xcd) {
   }
   if (put(me, 0)) return TeamPlace{0, 0};
   return team_place(seen, m);
+}
+
+// The n-th meeting: true once all members have come to it.  false: somebody has given up waiting, here or before.
+//   void arrive(int member, uint32_t n)
+//   int state(int members, uint32_t n)       1 all have arrived, 2 not and somebody has given up, 0 neither
+//   void give_up()
+template <class Ctl>
+TEAM_FN bool team_meet(Ctl& c, int member, int members, uint32_t n) {
+  c.arrive(member, n);
+  for (int i = 0; i < TEAM_MEET_POLLS; i++) {
+    const int s = c.state(members, n);
+    if (s) return s == 1;
+  }
+  c.give_up();
+  return false;
 }

@@ -193,12 +193,25 @@ __device__ inline bf16x8 lds_operand_tr(const char* base, int ld, int r0, int u0
 // What bounds a team's step: what its members all do.  128-256-256-10, 64 rows a step, 64 models, k cycles with one workgroup
 // a model and with four: weight gradients 74 and 39 (the state of all models in flight comes from the memory-side cache),
 // forward pass 28 and 29, data gradients 19 and 20, rows 11 and 12, the meeting 1.
-constexpr int TEAM_WORDS = 16;  // of a team's control block: [0..1] the list, [8..] members' meetings
+constexpr int TEAM_WORDS = 16;  // of a team's control block: [0..1] the list, [2] somebody has given up, [8..] members' meetings
 struct TeamBlock {
   uint32_t* ctl;
   __device__ uint64_t list() const { return atomicOr((unsigned long long*)ctl, 0ull); }
   __device__ uint64_t change(uint64_t from, uint64_t to) const { return atomicCAS((unsigned long long*)ctl, from, to); }
   __device__ void pause() const { __builtin_amdgcn_s_sleep(8); }
+  // Meetings: called by the first wave, all lanes.
+  __device__ void arrive(int member, uint32_t n) const {
+    if (threadIdx.x == 0) __hip_atomic_store(ctl + 8 + member, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __device__ int state(int members, uint32_t n) const {
+    const int lane = threadIdx.x;
+    const uint32_t v = __hip_atomic_load(lane < members ? ctl + 8 + lane : ctl + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!__any((int)(lane < members && v < n))) return 1;
+    return __any((int)(lane >= members && v != 0)) ? 2 : 0;
+  }
+  __device__ void give_up() const {
+    if (threadIdx.x == 0) __hip_atomic_store(ctl + 2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 };
 struct Team {
   TeamBlock block;
@@ -221,7 +234,7 @@ struct Tiled {
   __device__ __forceinline__ int team_wave() const { return uniform((int)(threadIdx.x >> 6)) + (TEAM ? team.place.member * TB_WAVES : 0); }
   __device__ __forceinline__ int team_waves() const { return TEAM ? team.place.members * TB_WAVES : TB_WAVES; }
   // What the members have stored is seen by all of them afterwards, where it is read with from_team(): a member's stores are in
-  // the L2 when its waves have waited for them.  n: the how many-th meeting.
+  // the L2 when its waves have waited for them.  n: the how many-th meeting.  false: the team has come apart.
   __device__ __forceinline__ bool meet(uint32_t n) const {
     if (!TEAM || team.place.members == 1) {
       __syncthreads();
@@ -230,15 +243,12 @@ struct Tiled {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x < 64) {
-      uint32_t* at = team.block.ctl + 8;
-      if (threadIdx.x == 0) __hip_atomic_store(at + team.place.member, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      const uint32_t* other = at + min((int)threadIdx.x, team.place.members - 1);
-      int i = 0;
-      while (__any((int)(__hip_atomic_load(other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n)) && i < TEAM_MEET_POLLS) i++;
-      if (threadIdx.x == 0) *met = i < TEAM_MEET_POLLS ? 1 : 0;
+      TeamBlock block = team.block;
+      const bool all = team_meet(block, team.place.member, team.place.members, n);
+      if (threadIdx.x == 0) *met = all ? 1 : 0;
     }
     __syncthreads();
-    return *met != 0;
+    return uniform(*met) != 0;
   }
   // A value of 8 or 16 bytes, `off` bytes (the lane's part, the wave's part) behind a pointer that is the same for all lanes.  What
   // another member of a team may have written is read past the CU's vector cache (sc1), which may hold an older state of it:
@@ -1458,7 +1468,7 @@ struct Tiled {
     } else {
       init_params();
     }
-    together &= meet(++meetings);
+    together = together && meet(++meetings);
 
     OptC oc;
     oc.adam = it.solver == BBO_ADAM;
@@ -1479,12 +1489,12 @@ struct Tiled {
     // set aside for early stopping after an epoch, the fold's held rows at the end) exists once in the code.
     bool stop = false, have_best = false;
     for (int e = e0;; e++) {
-      const bool final = stop || e >= it.epochs;
+      const bool final = stop || !together || e >= it.epochs;
       double esum = 0.0;  // the lane's share of the epoch's summed data loss
       if (!final) {
       const uint64_t ke = key_epoch(km, e);
       if (!oc.adam) oc.lr = epoch_lr(it.lr, it.power_t, e, n_fit);
-      for (int st = e == e0 ? st0 : 0; st < steps; st++, gstep++) {
+      for (int st = e == e0 ? st0 : 0; st < steps && together; st++, gstep++) {
         const int lo = st * bs, mb = min(bs, n_fit - lo);
         const int nch = (mb + TB_ROWS - 1) / TB_ROWS, par = (int)(gstep & 1);
         const float inv_mb = 1.f / (float)mb;
@@ -1523,12 +1533,18 @@ struct Tiled {
           const double data = block_sum(lsum, red) / (double)mb;
           if (threadIdx.x == 0) rec[0] = (float)(data + 0.5 * (double)it.alpha * pen / (double)mb);
         }
-        if (TEAM) together &= meet(++meetings);
+        if (TEAM) together = meet(++meetings);
       }
       }
       float watched = 0.f;
       if (watch && !final && !sp.n_hold) watched = (float)(block_sum(esum, red) / (double)n_fit);
-      if (TEAM && final && team.place.member > 0) break;  // the leader scores
+      if (TEAM && final && (team.place.member > 0 || !together)) {  // the leader scores
+        if (team.place.member == 0 && threadIdx.x == 0) {
+          float* out = P.item_out + 2 * ((int64_t)it.b * P.n_folds + fl);
+          out[0] = out[1] = __builtin_nanf("");
+        }
+        break;
+      }
       if (final && have_best) restore_best((int)(gstep & 1));
       if (final || (watch && sp.n_hold)) {
         // loss (and second score) of a list of rows under the current weights
@@ -1546,7 +1562,7 @@ struct Tiled {
         if (final) {
           if (threadIdx.x == 0) {
             float* out = P.item_out + 2 * ((int64_t)it.b * P.n_folds + fl);
-            out[0] = n_va > 0 && together ? (float)(lsum / (double)n_va) : __builtin_nanf("");
+            out[0] = n_va > 0 ? (float)(lsum / (double)n_va) : __builtin_nanf("");
             out[1] = n_va > 0 ? (float)(hits / (double)n_va) : __builtin_nanf("");  // accuracy | mean absolute error
           }
           break;

@@ -1,4 +1,4 @@
-"""CPU tests of how workgroups form a team (csrc/team.h), on threads of the host in place of workgroups."""
+"""CPU tests of how workgroups form a team and meet (csrc/team.h), on threads of the host in place of workgroups."""
 import os
 import shutil
 import subprocess
@@ -19,6 +19,7 @@ PRELUDE = r"""
 
 struct Block {
   std::atomic<uint64_t> word{0};
+  std::atomic<uint32_t> met[TEAM_MOST] = {}, gone{0};
 };
 struct Ctl {
   Block& b;
@@ -26,6 +27,13 @@ struct Ctl {
   uint64_t list() { return b.word.load(); }
   uint64_t change(uint64_t from, uint64_t to) { b.word.compare_exchange_strong(from, to); return from; }
   void pause() { if (us) std::this_thread::sleep_for(std::chrono::microseconds(us)); else std::this_thread::yield(); }
+  void arrive(int m, uint32_t n) { b.met[m].store(n); }
+  int state(int members, uint32_t n) {
+    int there = 0;
+    for (int k = 0; k < members; k++) there += b.met[k].load() >= n;
+    return there == members ? 1 : b.gone.load() ? 2 : 0;
+  }
+  void give_up() { b.gone.store(1); }
 };
 #define CHECK(x) do { if (!(x)) { printf("line %%d: %%s\n", __LINE__, #x); exit(1); } } while (0)
 static void nap(int ms) { std::this_thread::sleep_for(std::chrono::milliseconds(ms)); }
@@ -96,3 +104,40 @@ def test_leaving_while_the_list_is_closed(tmp_path):
       }
       for (int i = 0; i < 9; i++) printf("%d ", seen[i]);
     """)
+
+
+def test_meetings_wait_for_everybody(tmp_path):
+    run(tmp_path, r"""
+      Block b;
+      std::atomic<int> work{0};
+      std::vector<std::thread> t;
+      for (int m = 0; m < 4; m++) t.emplace_back([&, m] {
+        Ctl c{b, 0};
+        for (uint32_t n = 1; n <= 2000; n++) {
+          work++;
+          CHECK(team_meet(c, m, 4, n) && work.load() >= 4 * (int)n);
+        }
+      });
+      for (auto& x : t) x.join();
+      CHECK(b.gone.load() == 0);
+    """)
+
+
+@pytest.mark.parametrize("left", [0, 3])
+def test_a_lost_member_costs_one_wait_and_everybody_knows(tmp_path, left):
+    """A member stops coming after its tenth meeting: no other gets past the eleventh, and nobody waits a second time."""
+    run(tmp_path, r"""
+      Block b;
+      std::atomic<int> waits{0};
+      std::vector<std::thread> t;
+      for (int m = 0; m < 4; m++) t.emplace_back([&, m] {
+        struct Counting : Ctl { std::atomic<int>& w; Counting(Block& b, std::atomic<int>& w) : Ctl{b, 0}, w(w) {}
+                                void give_up() { w++; Ctl::give_up(); } } c(b, waits);
+        for (uint32_t n = 1; n <= 10; n++) CHECK(team_meet(c, m, 4, n));
+        if (m == %d) return;
+        CHECK(!team_meet(c, m, 4, 11));
+        CHECK(!team_meet(c, m, 4, 12) && !team_meet(c, m, 4, 13));
+      });
+      for (auto& x : t) x.join();
+      CHECK(b.gone.load() == 1 && waits.load() >= 1 && waits.load() <= 3);
+    """ % left)
