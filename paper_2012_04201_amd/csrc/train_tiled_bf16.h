@@ -251,8 +251,8 @@ struct Tiled {
     return uniform(*met) != 0;
   }
   // A value of 8 or 16 bytes, `off` bytes (the lane's part, the wave's part) behind a pointer that is the same for all lanes.  What
-  // another member of a team may have written is read past the CU's vector cache (sc1), which may hold an older state of it:
-  // invalidating that cache at a meeting would take the agent-scope instruction, which drops lines of the L2 too and takes 7 us.
+  // another member of a team may have written since the training began is read past the CU's vector cache (sc1), which may hold
+  // an older state of it.  (The agent-scope acquire at each meeting instead drops lines of the L2 too and takes 7 us.)
   template <class V>
   __device__ __forceinline__ static V from_team(const void* base, uint32_t lane_off, uint32_t wave_off) {
     if constexpr (!TEAM) {
@@ -1469,6 +1469,9 @@ struct Tiled {
       init_params();
     }
     together = together && meet(++meetings);
+    // Zeros and initial values come from whichever member an element's number falls to, and whoever owns its tile reads them with
+    // ordinary loads from here on: the CU's vector cache keeps nothing from before.
+    if (TEAM) asm volatile("buffer_inv sc0" ::: "memory");
 
     OptC oc;
     oc.adam = it.solver == BBO_ADAM;

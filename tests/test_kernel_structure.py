@@ -44,6 +44,24 @@ def test_linear_kernel_loop_nest_is_the_sources(tmp_path):
         assert "global_atomic_add" in body and "s_endpgm" in body
 
 
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
+def test_a_team_drops_the_lines_of_its_cache_before_the_first_step(tmp_path):
+    """Zeros and initial values are written by any member and read by a tile's owner with ordinary loads: its CU's vector cache is
+    invalidated in between, once, by the workgroup-scope instruction (the agent's drops lines of the L2 too)."""
+    out = tmp_path / "tiled.s"
+    cmd = ["hipcc", "-O3", "--offload-arch=gfx950", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "--cuda-device-only", "-S", os.path.join(CSRC, "kernels_tiled.hip"), "-o", str(out)]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    text = out.read_text()
+    found = {}
+    for name in re.findall(r"^(_Z\w*k_train_tiled\w*):", text, re.M):
+        body = text[text.index("\n" + name + ":"):]
+        body = body[:body.index(".Lfunc_end")]
+        found["team" in name] = re.findall(r"buffer_inv (.*)", body)
+    assert found == {False: [], True: ["sc0"]}
+
+
 @pytest.mark.skipif(shutil.which("nm") is None, reason="nm not on PATH")
 def test_the_library_holds_the_variants_that_the_cuts_can_ask_for():
     """The register-resident kernels are compiled for each way a model of their shapes is cut, and for no other."""
