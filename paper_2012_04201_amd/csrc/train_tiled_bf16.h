@@ -1441,7 +1441,7 @@ struct Tiled {
     const int n_fit = sp.n_fit;
     const int bs = eff_batch(it.batch_size, n_fit);
     const int steps = n_fit > 0 ? (n_fit + bs - 1) / bs : 0;
-    const bool traced = P.trace_item == it.b * P.n_folds + fl;
+    const bool traced = !TEAM && P.trace_item == it.b * P.n_folds + fl;  // (a traced call has no teams)
 
     {
       uint4* z = (uint4*)slot;
