@@ -20,6 +20,9 @@
  *     own device workspace, a static array inside the library).
  *   - Work is enqueued on the caller's stream and the call returns without
  *     waiting for it; outputs are valid once the stream has been synchronised.
+ *   - Calls on several streams, threads or processes share the device.  A call
+ *     of few models may use more compute units than it has models, but no more
+ *     than half of them for that; what else runs there changes no result.
  *   - Every function returns BBO_OK or an error code; bbo_mlp_last_error()
  *     gives the message of the calling thread's last failure.  Nothing throws
  *     or aborts across this boundary.  A training run that blows up

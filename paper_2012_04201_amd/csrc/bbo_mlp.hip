@@ -990,10 +990,13 @@ void merge_full(Plan& pl, int n_folds) {
 
 constexpr int TEAM_XCDS = 8;  // a team's workgroups share an XCD: launched in eights, one for each
 
-// Workgroups that train one model together (team.h) in a call of `models` models, of which each has
-// `sp`'s kernel; 1: each model has a workgroup of its own.  A team takes every step in one chunk and sets no rows aside.
-// It pays as soon as two workgroups a model have a CU each: us a step of one and of a team, 128-256-256-10, 64 rows, 8, 32, 64, 96 and
-// 128 models 57 and 37, 64 and 42, 66 and 49, 68 and 59, 95 and 82; 128-200-10, 256 rows 37 and 30 to 40 and 37.
+// Workgroups that train one model together (team.h) in a call of `models` models, of which each has `sp`'s kernel; 1: each model
+// has a workgroup of its own.  A team takes every step in one chunk and sets no rows aside.
+// Teams have half of the CUs between them: each of their workgroups holds one, which another caller's models would have had.  ms a
+// call of 64 hold-out models on 10,000 x 128 by 1, 2 and 4 processes at once: no teams 35.3, 36.4 and 40; half of the CUs (two a
+// model) 28.3, 29.7 and 32; all of them (four) 25.5, 27.4 and 53.  32 models: 35.0, 35.9 and 37, 23.9, 25.1 and 28, 22.7, 24.3
+// and 30.  Up to that line a team pays whenever two workgroups a model have a CU each: us a step of one and of a team,
+// 128-256-256-10, 64 rows, 8, 32 and 64 models 54 and 34, 62 and 41, 64 and 51; 128-200-10, 256 rows 33 and 25, 33 and 27, 35 and 30.
 int team_size(const SubPlan& sp, size_t models, int64_t n, const bbo_mlp_hparams* hp, int cus) {
   if (sp.kc != KC_TILED || (size_t)sp.n_slots < models) return 1;  // (a team has its model, and a slot, by number)
   for (const int32_t b : sp.order) {
@@ -1002,7 +1005,7 @@ int team_size(const SubPlan& sp, size_t models, int64_t n, const bbo_mlp_hparams
     if (h.n_iter_no_change > 0 && h.validation_fraction > 0.f) return 1;
   }
   const size_t teams = (models + TEAM_XCDS - 1) / TEAM_XCDS;  // of an XCD
-  return (int)std::max<size_t>(1, std::min<size_t>(TEAM_MOST, (size_t)(cus / TEAM_XCDS) / teams));
+  return (int)std::max<size_t>(1, std::min<size_t>(TEAM_MOST, (size_t)(cus / 2 / TEAM_XCDS) / teams));
 }
 
 // The launches of a call, their workgroups and where everything lies in a workspace of `room` bytes (pl.total may exceed

@@ -13,7 +13,7 @@ def expected(models, n, batch):
     """(workgroups, of which each model has)"""
     if batch == 0 and n > 256 or batch > 256 and n > 256:
         return min(models, CUS)
-    each = max(1, min(8, CUS // 8 // -(-models // 8)))
+    each = max(1, min(8, CUS // 2 // 8 // -(-models // 8)))  # half of the CUs: the others are other callers'
     return models if each == 1 else -(-models // 8) * 8 * each
 
 
@@ -26,11 +26,12 @@ def test_workgroups_of_a_call(child, models):  # noqa: F811
             log()
             rc = L.bbo_mlp_cv_eval(P(4096), P(4096), C.c_int64(n), 128, 10, P(4096), 1, records(shapes, batch), len(shapes), 1,
                                    P(4096), P(4096), P(0), P(4096), C.c_size_t(1 << 40), P(900))
-            got.append([rc] + [int(l[2]) for l in log() if l[0] == "launch"])
+            got.append([rc] + [int(l[2]) for l in log() if l[0] == "launch" and "k_train_tiled" in l[5]])
         print(json.dumps(got))
     """ % models)
     for (n, batch), got in zip(((1000, 64), (1000, 256), (1000, 257), (1000, 0), (256, 0), (256, 500)), grids):
-        assert got[0] == 0 and expected(models, n, batch) in got[1:], (n, batch, got)
+        assert got == [0, expected(models, n, batch)], (n, batch, got)
+        assert got[1] == models or got[1] <= CUS // 2
 
 
 def test_no_room_for_the_control_blocks_no_team(child):  # noqa: F811
@@ -48,11 +49,12 @@ def test_no_room_for_the_control_blocks_no_team(child):  # noqa: F811
             lo, hi = (lo, mid) if grid(mid) else (mid, hi)
         print(json.dumps([hi, grid(hi), [grid(hi + 64 * 40 - 1), grid(hi + 64 * 40), grid(need(1000, 128, 10, 2, shapes, 1))]]))
     """)
-    assert alone == 40 and grids == [40, 40 * 6, 40 * 6], (least, alone, grids)
+    assert alone == 40 and grids == [40, 40 * 3, 40 * 3], (least, alone, grids)
 
 
 # rows, inputs, classes, folds, models; a few small ones, whose weights a CU's vector cache holds from step to step
-CASES = [(300, 16, 0, 3, 1), (300, 8, 1, 2, 2), (700, 128, 10, 5, 3), (400, 200, 2, 5, 13), (1000, 256, 16, 4, 30)]
+CASES = [(300, 16, 0, 3, 1), (300, 8, 1, 2, 2), (700, 128, 10, 5, 3), (400, 200, 2, 5, 13), (1000, 256, 16, 4, 30),
+         (400, 200, 2, 4, 15), (1000, 256, 16, 4, 8), (700, 136, 7, 3, 7)]
 
 
 @pytest.mark.gpu
@@ -108,7 +110,7 @@ def test_teams_form_and_meet_after_every_step(bb, models):  # noqa: F811
 
 @pytest.mark.gpu
 def test_calls_at_once_change_no_bit(bb):  # noqa: F811
-    """Four calls on streams of their own, with more workgroups in all than there are CUs: teams come late or in part."""
+    """Four calls on streams of their own, whose teams together ask for more workgroups than there are CUs: some come late."""
     n, d, c, K = 600, 64, 4, 4
     X, y, ft = bb.to_device(dict(small_problem(9, n, d, c, bf16=True), n_folds=K, fold_idx=np.arange(n, dtype=np.int32) % K))
     calls = [[{"hidden": [40 + 31 * i % 200] * (1 + i % 2), "batch_size": 64, "epochs": 4, "seed": 100 * j + i, "alpha": 0.1}
