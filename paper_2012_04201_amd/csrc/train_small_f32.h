@@ -643,12 +643,16 @@ struct RowPipe {
     if (tabled && threadIdx.x < SM_RC) u16(o_sl)[n_tr + threadIdx.x] = 0;
   }
 
-  // A traced step's gradient as the caller wants it (see AdamUnits).  (With threadIdx.x every variant takes two registers more.)
-  __device__ __forceinline__ void out_of_unit(float* g) const {
-    __syncthreads();
+  // Traced gradients of `steps` steps as the caller wants them (see AdamUnits).
+  __device__ __forceinline__ void out_of_units(int64_t steps) const {
     const float unit = AdamUnits(item().beta1, item().beta2, item().eps).grad;
+    const int64_t row = 1 + 2 * (int64_t)y.p.P;
+    __syncthreads();
 #pragma unroll 1
-    for (int i = tid(); i < y.p.P; i += NTHR) g[i] /= unit;
+    for (int64_t i = tid(); i < steps * row; i += NTHR) {
+      const int64_t k = i % row;
+      if (k >= 1 && k <= y.p.P) params().trace_out[i] /= unit;
+    }
   }
 
   __device__ __forceinline__ void run() {
@@ -869,7 +873,6 @@ struct RowPipe {
               self.template update<false>(R, oc);
             if (recording) {
               self.template record<false>(R, oc.am, rec + 1 + y.p.P);
-              if (oc.adam) out_of_unit(rec + 1);
               const double after = self.total(lsum);
               const float mb = c0 & SC_RAGGED ? (float)last_rows : (float)bs;
               if (threadIdx.x == 0)
@@ -905,6 +908,7 @@ struct RowPipe {
         }
       }
     }
+    if (traced && oc.adam) out_of_units(min(gstep, params().step_end) - params().step_begin);
     lsum = self.total(lsum);
     hits = self.total(hits);
     if (threadIdx.x == 0) {
