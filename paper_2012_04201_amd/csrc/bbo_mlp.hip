@@ -993,9 +993,10 @@ constexpr int TEAM_XCDS = 8;  // a team's workgroups share an XCD: launched in e
 // Workgroups that train one model together (team.h) in a call of `models` models, of which each has `sp`'s kernel; 1: each model
 // has a workgroup of its own.  A team takes every step in one chunk and sets no rows aside.
 // Teams have half of the CUs between them: each of their workgroups holds one, which another caller's models would have had.  ms a
-// call of 64 hold-out models on 10,000 x 128 by 1, 2 and 4 processes at once: no teams 35.3, 36.4 and 40; half of the CUs (two a
-// model) 28.3, 29.7 and 32; all of them (four) 25.5, 27.4 and 53.  32 models: 35.0, 35.9 and 37, 23.9, 25.1 and 28, 22.7, 24.3
-// and 30.  Up to that line a team pays whenever two workgroups a model have a CU each: us a step of one and of a team,
+// call of 64 hold-out models on 10,000 x 128 by 1, 2, 4 and 8 processes at once: no teams 35.3, 36.4, 39.9 and 56; half of the CUs
+// (two a model) 28.2, 29.4, 34.4 and 57; all of them (four) 25.5, 29.1, 36.5 and 56.  32 models: 35.0, 36.0, 37.3 and 40.7; 23.7,
+// 25.2, 31.9 and 41.7; 22.7, 35.6, 39.2 and 47.  (With all of them, what other calls there are wait for the longest model too.)
+// Up to that line a team pays whenever two workgroups a model have a CU each: us a step of one and of a team,
 // 128-256-256-10, 64 rows, 8, 32 and 64 models 54 and 34, 62 and 41, 64 and 51; 128-200-10, 256 rows 33 and 25, 33 and 27, 35 and 30.
 int team_size(const SubPlan& sp, size_t models, int64_t n, const bbo_mlp_hparams* hp, int cus) {
   if (sp.kc != KC_TILED || (size_t)sp.n_slots < models) return 1;  // (a team has its model, and a slot, by number)

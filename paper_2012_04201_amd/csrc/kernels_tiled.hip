@@ -24,18 +24,18 @@ __global__ __launch_bounds__(TB_THREADS) void k_train_tiled(const TrainParams P)
   }
 }
 
-// A team of workgroups per model: workgroup (j * team_size + m) * 8 + x is member m of team 8 j + x, which has that item.  (A
-// queue would hand the longest model to whoever comes to it first, also to a workgroup that has been left alone.)
+// A team of workgroups per model; team k has item k.  (A queue would hand the longest model to whoever comes to it first, also to a
+// workgroup that has been left alone.)
 __global__ __launch_bounds__(TB_THREADS) void k_train_tiled_team(const TrainParams P) {
   extern __shared__ __align__(16) char smem[];
   __shared__ int s_met;
   __shared__ TeamPlace s_place;
   __shared__ double red[TB_THREADS / 64];
-  const int x = blockIdx.x & 7, j = (int)(blockIdx.x >> 3) / P.team_size, m = (int)(blockIdx.x >> 3) % P.team_size;
-  const int item = 8 * j + x;
+  const TeamSeat seat = team_seat(blockIdx.x, (int)(gridDim.x >> 3) / P.team_size);
+  const int item = seat.team;
   if (item >= P.n_items) return;
   TeamBlock block{P.teams + item * TEAM_WORDS};
-  if (threadIdx.x == 0) s_place = team_join(block, m, P.team_size, __builtin_amdgcn_s_getreg(20 | (3 << 11)));  // XCC_ID
+  if (threadIdx.x == 0) s_place = team_join(block, seat.member, P.team_size, __builtin_amdgcn_s_getreg(20 | (3 << 11)));  // XCC_ID
   __syncthreads();
   const Team team{block, {uniform(s_place.member), uniform(s_place.members)}};
   if (team.place.members == 0) return;

@@ -22,6 +22,17 @@ constexpr int TEAM_JOIN_POLLS = 200;      // about 100 us
 constexpr int TEAM_MEET_POLLS = 1 << 23;  // seconds: the members all run, so only a fault elsewhere lets a wait end here
 constexpr uint64_t TEAM_CLOSED = 1ull << 63;
 
+// Which team and which of its members a workgroup is, in a launch of rows * 8 teams: workgroups b, b + 8, .. lie on one XCD as a
+// rule, so a team's do.  All leaders come first: where CUs become free one by one, because other calls hold them, each is a model's
+// before any is a second one's, and who comes late finds the list closed.
+struct TeamSeat {
+  int team, member;
+};
+TEAM_FN TeamSeat team_seat(uint32_t block, int rows) {
+  const int at = (int)(block >> 3), m = at / rows;
+  return TeamSeat{(at - m * rows) * 8 + (int)(block & 7), m};
+}
+
 struct TeamPlace {
   int member, members;  // members == 0: not in the team
 };

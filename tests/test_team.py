@@ -70,6 +70,22 @@ def run(tmp_path, body):
     assert res.returncode == 0, res.stdout
 
 
+def test_all_leaders_are_launched_first_and_a_team_on_one_xcd(tmp_path):
+    run(tmp_path, r"""
+      for (int rows = 1; rows <= 16; rows++)
+        for (int size = 1; size <= 8; size++) {
+          std::vector<int> seen(rows * 8 * size, 0);
+          for (int b = 0; b < rows * 8 * size; b++) {
+            const TeamSeat s = team_seat(b, rows);
+            CHECK(s.team >= 0 && s.team < rows * 8 && s.member >= 0 && s.member < size && s.team % 8 == b % 8);
+            CHECK((s.member == 0) == (b < rows * 8));
+            seen[s.team * size + s.member]++;
+          }
+          for (int k : seen) CHECK(k == 1);
+        }
+    """)
+
+
 @pytest.mark.parametrize("size", [1, 2, 3, 8])
 def test_everybody_on_time(tmp_path, size):
     run(tmp_path, "for (int i = 0; i < 20; i++) CHECK(agreed(join(all(%d), %d, std::vector<int>(8, i %% 8), std::vector<int>(8, 0), 1000)) == %d);"
