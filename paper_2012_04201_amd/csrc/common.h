@@ -293,8 +293,9 @@ struct OptC {
   float b1, b2, omb1, omb2, eps, lr_t, mu, lr, am;
 };
 
-// The least eps, in the units of opt_step(): smaller by less than a factor of 2.
-__device__ __forceinline__ bool least_eps(const OptC& c) { return __float_as_uint(c.eps) >> 23 <= __float_as_uint(EPS_MIN) >> 23; }
+// The least eps, in the units of opt_step(): smaller by less than a factor of 2.  (By its value: where it was told by its exponent
+// k_train_deep<3, 2, 8> spilled 25 vector registers instead of 8.)
+__device__ __forceinline__ bool least_eps(const OptC& c) { return c.eps <= EPS_MIN; }
 
 // max(x, 0) in one instruction.  A NaN stays one, in every kernel: a model that blew up, or met a NaN in its data, has a score
 // that says so.  (fmaxf() and a median make it 0.)

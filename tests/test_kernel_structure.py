@@ -62,6 +62,21 @@ def test_a_team_drops_the_lines_of_its_cache_before_the_first_step(tmp_path):
     assert found == {False: [], True: ["sc0"]}
 
 
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
+def test_two_layers_on_eight_waves_and_three_input_tiles_keep_their_registers(tmp_path):
+    """The branch that parts the update's blocks is what keeps this variant's registers: with another form of its condition the
+    compiler spilled 25 vector registers instead of 8 (569 x 40, 100-70, 24 rows a step 3302 -> 3580 us a call)."""
+    src = tmp_path / "probe.hip"
+    src.write_text('#include "%s"\nnamespace {\ntemplate __global__ void k_train_deep<3, 2, 8>(const TrainParams);\n}\n'
+                   % os.path.join(CSRC, "train_deep_f32.h"))
+    cmd = ["hipcc", "-O3", "--offload-arch=gfx950", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "--cuda-device-only", "-c", "-Rpass-analysis=kernel-resource-usage", str(src), "-o", os.devnull]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    spilled = [int(x) for x in re.findall(r"VGPRs Spill: (\d+)", res.stderr)]
+    assert len(spilled) == 1 and spilled[0] <= 12, spilled
+
+
 @pytest.mark.skipif(shutil.which("nm") is None, reason="nm not on PATH")
 def test_the_library_holds_the_variants_that_the_cuts_can_ask_for():
     """The register-resident kernels are compiled for each way a model of their shapes is cut, and for no other."""
