@@ -120,6 +120,12 @@ struct Deep : RowPipe<Deep<KT, H, W>, DLay, KT, W, 3, false> {
   using Base::ys;
   static constexpr int LDW = Base::LDW, LDH = 16 * W + 4;
   static constexpr int NB = dp_blocks(KT, H, W), B_OUT = NB - 2, B_BIAS = NB - 1;
+  static constexpr bool LOAD_AHEAD = false;  // (see Small)
+  // us a call of 500 models without and with: 569 x 40, 120-60-60, 17 rows a step 7265 and 5960; 100-70, 24 rows 3284 and 3155; 569 x 30,
+  // 128-100-60 5880 and 5229; but 569 x 50, 60-60-60, 17 rows 3845 and 4572.
+  // (These kernels are larger than an instruction cache, and where one lies counts for as much: the same code of <3,3,4> and
+  // <2,3,8> took 1.00 to 1.14 and 1.01 to 1.17 of its time at twelve places that other kernels' sizes gave it.)
+  static constexpr bool RARE_APART = !(H == 3 && W == 4 && KT >= 3);
   static constexpr bool NEAR = dp_near(KT, H, W), STREAM = dp_stream(H, W);
   static constexpr int NM = NEAR ? NB : 1;
   static constexpr int O_LEV = Base::O_OWN, O_WO = O_LEV + H * SM_RC * LDH, O_D3 = O_WO + W * 256, O_TOP = O_D3 + SM_RC * MD_RS;

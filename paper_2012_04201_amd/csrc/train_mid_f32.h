@@ -153,6 +153,10 @@ struct Mid : RowPipe<Mid<KT, NT, W, SPLIT>, MLay, KT, W, 2, SPLIT> {
 
   static constexpr int NEAR = md_near(KT, NT, SPLIT), NREGM = NEAR ? NEAR : 1;
   static constexpr int KB = sm_blocks(KT);
+  static constexpr bool LOAD_AHEAD = false;  // (see Small)
+  // (us a call without and with, 24 rows a step: 40 models 900 x 48, ten classes, 150 units 2050 and 2028; 500 of 900 x 90, 250 units
+  // 4909 and 5258)
+  static constexpr bool RARE_APART = !(NT == 2 && KT >= 5);
   // The forward pass takes the row tiles of a chunk together, except where their operands do not fit the registers: us a call one
   // by one and together, 200 suggestions: 64 inputs, 10 classes, 150 units, 128 rows a step, split 2377 and 2493; 80 inputs, 190
   // units, 24 rows 5809 and 6233; but fp32 products, 64 inputs, 150 units, 64 rows 2663 and 2576; 64 units, 128 rows 1473 and 1412;

@@ -393,6 +393,11 @@ enum {
   SC_TABLE = 1 << 18,    // its epoch's rows are to be tabled
 };
 
+// A condition of RowPipe::run() that few steps meet: its code goes behind the step's, and what spills, spills there.  Not
+// the row lookups, which are every chunk's where rows are not tabled (70,000 x 13 1.01 to 1.02 of its time with them).  A macro: the
+// compiler takes the hint at a branch, before it inlines anything.
+#define SM_RARE(x) (Self::RARE_APART ? __builtin_expect(!!(x), 0) : !!(x))
+
 // The row pipeline of a training run, shared by the kernels that take their inputs through LDS in chunks of 64 rows:
 // the schedule, the rows of an epoch, the inputs two chunks ahead, the stopping rules, tracing and the scores.  `Self`
 // has the model: its state (State, what stays in registers for the run; Acts, what a chunk's forward pass leaves for
@@ -646,12 +651,12 @@ struct RowPipe {
   // Traced gradients of `steps` steps as the caller wants them (see AdamUnits).
   __device__ __forceinline__ void out_of_units(int64_t steps) const {
     const float unit = AdamUnits(item().beta1, item().beta2, item().eps).grad;
-    const int64_t row = 1 + 2 * (int64_t)y.p.P;
+    float* rec = params().trace_out + 1;
     __syncthreads();
 #pragma unroll 1
-    for (int64_t i = tid(); i < steps * row; i += NTHR) {
-      const int64_t k = i % row;
-      if (k >= 1 && k <= y.p.P) params().trace_out[i] /= unit;
+    for (; steps > 0; steps--, rec += 1 + 2 * (int64_t)y.p.P) {
+#pragma unroll 1
+      for (int k = tid(); k < y.p.P; k += NTHR) rec[k] /= unit;
     }
   }
 
@@ -753,11 +758,20 @@ struct RowPipe {
     }
     int e_lr = st0 > 0 ? e : e - 1;  // epoch of the step being worked on (set when one opens)
     int c2 = epoch_start(st0);       // the chunk at the position above
+    if constexpr (Self::LOAD_AHEAD) {
+      if (resume) {
+        const AdamUnits units(it.beta1, it.beta2, it.eps);
+        self.load(R, P.state_in, it.solver == BBO_ADAM ? units.m : 1.f, it.solver == BBO_ADAM ? units.v : 1.f);
+      } else {
+        self.load(R, nullptr, 1.f, 1.f);
+      }
+    }
     OptC oc;
     const int solver = pin(it.solver);
     oc.adam = solver == BBO_ADAM;
-    self.load(R, resume ? P.state_in : nullptr, oc.adam ? AdamUnits(it.beta1, it.beta2, it.eps).m : 1.f,
-              oc.adam ? AdamUnits(it.beta1, it.beta2, it.eps).v : 1.f);
+    if constexpr (!Self::LOAD_AHEAD)
+      self.load(R, resume ? P.state_in : nullptr, oc.adam ? AdamUnits(it.beta1, it.beta2, it.eps).m : 1.f,
+                oc.adam ? AdamUnits(it.beta1, it.beta2, it.eps).v : 1.f);
     oc.nest = it.nesterov != 0;
     oc.b1 = pin(it.beta1);
     oc.b2 = pin(it.beta2);
@@ -812,9 +826,9 @@ struct RowPipe {
                 lsum = 0.0;
                 if (!oc.adam) oc.lr = uniform(epoch_lr(item().lr, item().power_t, e_lr, n_fit));
               }
-              if (traced) {
+              if (SM_RARE(traced)) {
                 recording = gstep >= params().step_begin && gstep < params().step_end ? 1 : 0;
-                if (recording) {
+                if (SM_RARE(recording)) {
                   const double pen = self.penalty_sum(R);
                   // the step's loss is the difference this step makes to the epoch's sum; both wait in LDS
                   const double before = self.total(lsum);
@@ -826,7 +840,7 @@ struct RowPipe {
               }
             }
             if (oc.adam) {
-              if (lr_at == 64) {
+              if (SM_RARE(lr_at == 64)) {
                 // beta^t of the next 64 steps, a step per lane, by repeated squaring in double
                 lr_at = 0;
                 double q1 = (double)item().beta1, q2 = (double)item().beta2, b1t = 1.0, b2t = 1.0;
@@ -863,7 +877,7 @@ struct RowPipe {
           self.backward(R, b, nrt, acc);
           if (c0 & SC_LAST) {  // last chunk of the step
             float* rec = nullptr;
-            if (recording) {
+            if (SM_RARE(recording)) {
               rec = params().trace_out + (gstep - params().step_begin) * (1 + 2 * (int64_t)y.p.P);
               self.template record<true>(R, oc.am, rec + 1);
             }
@@ -871,7 +885,7 @@ struct RowPipe {
               self.template update<true>(R, oc);
             else
               self.template update<false>(R, oc);
-            if (recording) {
+            if (SM_RARE(recording)) {
               self.template record<false>(R, oc.am, rec + 1 + y.p.P);
               const double after = self.total(lsum);
               const float mb = c0 & SC_RAGGED ? (float)last_rows : (float)bs;
@@ -893,7 +907,7 @@ struct RowPipe {
         b = bn;
         par ^= 1;
         // the end of an epoch (with the rows set aside, if any): the stopping rule, decided alike in every wave
-        if (done & SC_DECIDE) {
+        if (SM_RARE(done & SC_DECIDE)) {
           const float watched = (float)(self.total(lsum) / (double)(n_hold ? n_hold : n_fit));
           const int stop = uniform(plateau.stop_after(watched, item().tol, item().patience) ? 1 : 0);
           if (n_hold && uniform(plateau.improved ? 1 : 0)) {
@@ -908,7 +922,7 @@ struct RowPipe {
         }
       }
     }
-    if (traced && oc.adam) out_of_units(min(gstep, params().step_end) - params().step_begin);
+    if (SM_RARE(traced && oc.adam)) out_of_units(min(gstep, params().step_end) - params().step_begin);
     lsum = self.total(lsum);
     hits = self.total(hits);
     if (threadIdx.x == 0) {
@@ -995,6 +1009,14 @@ struct Small : RowPipe<Small<KT, NT, CO, W>, SLay, KT, W, sm_barriers(KT, NT, CO
   // after: 128 units, 24 and 128 rows a step 2026 and 1959, 1057 and 1003; 190 units 3764 and 3145, 1656 and 1388.  fp32 products
   // save a multiplication of each value for one of each parameter and step: 2 % at 45 inputs, a loss at 13.
   static constexpr bool FACTORED = sm_factored(KT, NT, CO);
+  // With one input tile the model is loaded ahead of the optimizer's constants, and its moments' units are made only where there
+  // are moments.  40 models 506 x 13 of 50 units, 24 and 64 rows a step: SGD 1049 -> 1024 and 608 -> 593 us a call, Adam 1093 -> 1067
+  // and 627 -> 608; 1000 models at 64 rows 490 -> 481 and 496 -> 481.  Wider inputs keep their registers the other way round
+  // (<2,3,1,4> spills 102 against 128).
+  static constexpr bool LOAD_AHEAD = KT == 1;
+  // us a call without and with, 24 rows a step: 40 models 569 x 60, four classes, 180 units 5686 and 5477, 569 x 45, 100 units 3375 and 3197;
+  // but three unit tiles a wave, 569 x 30, two classes, 180 units 2538 and 2837, by five more registers spilled.
+  static constexpr bool RARE_APART = NT < 3;
   struct State {
     HiddenWeights<KT, NT, SPLIT> w;
     f32x4 m[NT][KT], v[NT][KT], g[NT][KT];  // hidden layer: lane (unit li, columns 16 kk + 4q + e)

@@ -63,18 +63,20 @@ def test_a_team_drops_the_lines_of_its_cache_before_the_first_step(tmp_path):
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
-def test_two_layers_on_eight_waves_and_three_input_tiles_keep_their_registers(tmp_path):
-    """The branch that parts the update's blocks is what keeps this variant's registers: with another form of its condition the
-    compiler spilled 25 vector registers instead of 8 (569 x 40, 100-70, 24 rows a step 3302 -> 3580 us a call)."""
+@pytest.mark.parametrize("cut,most", [("3, 2, 8", 12), ("2, 3, 8", 4)])
+def test_deep_kernels_on_eight_waves_keep_their_registers(tmp_path, cut, most):
+    """<3, 2, 8>: the branch that parts the update's blocks is what keeps its registers; with another form of its condition the
+    compiler spilled 25 vector registers instead of 8 (569 x 40, 100-70, 24 rows a step 3302 -> 3580 us a call).  <2, 3, 8>: what
+    few steps do is marked as rare and spills there; 8 registers where it is not (569 x 30, 128-100-60 5229 -> 5880)."""
     src = tmp_path / "probe.hip"
-    src.write_text('#include "%s"\nnamespace {\ntemplate __global__ void k_train_deep<3, 2, 8>(const TrainParams);\n}\n'
-                   % os.path.join(CSRC, "train_deep_f32.h"))
+    src.write_text('#include "%s"\nnamespace {\ntemplate __global__ void k_train_deep<%s>(const TrainParams);\n}\n'
+                   % (os.path.join(CSRC, "train_deep_f32.h"), cut))
     cmd = ["hipcc", "-O3", "--offload-arch=gfx950", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            "--cuda-device-only", "-c", "-Rpass-analysis=kernel-resource-usage", str(src), "-o", os.devnull]
     res = subprocess.run(cmd, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
     spilled = [int(x) for x in re.findall(r"VGPRs Spill: (\d+)", res.stderr)]
-    assert len(spilled) == 1 and spilled[0] <= 12, spilled
+    assert len(spilled) == 1 and spilled[0] <= most, spilled
 
 
 @pytest.mark.skipif(shutil.which("nm") is None, reason="nm not on PATH")
