@@ -881,15 +881,18 @@ int device_cus(int* out) {
   return BBO_OK;
 }
 
-// The dynamic-LDS limit of a kernel is a property of the kernel on a device: it is set when first needed and
-// raised when a later call needs more, not on every call.
 // More than half of a CU's LDS, which every workgroup of a call with several launches and few models is given, whatever it
 // uses: each hardware queue places its workgroups by itself, and two of them put theirs on the same CUs while others are
 // idle.  The line is at a workgroup for every second CU, so that two such calls on different streams still run side by side.
 // 40 models 506 x 13 in three launches 1435 -> 1254 us a call, 45 models 1302 x 18 2313 -> 2175, 347 x 22 612 -> 560; with
-// eight waves a model (1797 x 64) the registers keep workgroups apart already.
+// eight waves a model (1797 x 64) the registers keep workgroups apart already.  Beside other callers, us a call without and with
+// it by 1, 2, 3, 4 and 8 processes that all call at once: 40 models 506 x 13 1581 and 1309, 1465 and 1359, 1691 and 1476, 1766 and
+// 1613, 9417 and 8543; 125 of them 1927 and 1609, 1990 and 1680, 2177 and 1973, 2317 and 2438, 23.9 and 21.8 ms; 125 of 569 x 13 at
+// four 1944 and 1940.  (Only four calls of 125 models, nearly two a CU together, would have done better with shared CUs, by 5 %.)
 constexpr uint32_t LDS_OF_A_CU = 82 * 1024;
 
+// The dynamic-LDS limit of a kernel is a property of the kernel on a device: it is set when first needed and
+// raised when a later call needs more, not on every call.
 int ensure_dynamic_lds(const void* fn, uint32_t bytes) {
   struct Seen {
     int dev;
