@@ -59,7 +59,7 @@ __host__ __device__ constexpr int dp_blocks(int kt, int h, int waves) { return k
 __host__ __device__ constexpr bool dp_near(int kt, int h, int waves) { return dp_blocks(kt, h, waves) <= 8; }
 // The weights of the hidden layers past the first are in global memory alone (one copy serves the forward products, the
 // data gradient and the update) where weights and gradients would take 152 registers and more: held, they made these cuts
-// spill 59, 117, 151 and 172 vector registers at one to four input tiles; now 6, 8, 9 and 8.  [128, 40, 100] on 50 inputs,
+// spill 59, 117, 151 and 172 vector registers at one to four input tiles; now 0, 0, 2 and 4.  [128, 40, 100] on 50 inputs,
 // batch 24: 500 models a call 4.70 -> 3.29 ms, 20 models 1.73 -> 1.37.  The price is the bandwidth of a full chip where
 // little was spilled: [128, 128, 128] on 20 inputs 5.37 -> 5.77 ms at batch 24 and 2.43 -> 2.31 at 160.
 __host__ __device__ constexpr bool dp_stream(int h, int waves) { return h == 3 && waves == 8; }

@@ -84,8 +84,8 @@ __host__ __device__ constexpr bool md_splittable(int kt, int nt, int waves) {
 // of this kernel.  One tile a wave while eight waves reach (more models a CU with four), else two: one tile leaves the
 // registers for everything, and eight waves of one tile beat four of two by a quarter even with the chip full (64-100-10,
 // 1000 models: 3.2 ms against 3.9).  Beyond kt * nt = 12 the weights and gradients alone overflow the registers; close to
-// it they crowd others out: by the compiler's report <3,2,8> spills 15 vector registers, <4,2,8> 7, <5,2,8> 50, <6,2,8> 134,
-// the split forms of <3,2,8> and <4,2,8> 48 and 40, the others 2 at most.  (<6,2,8> against its form before the leaner schedule, 90 inputs, 200 and
+// it they crowd others out: by the compiler's report <3,2,8> and <4,2,8> spill 10 vector registers, <5,2,8> 50, <6,2,8> 110,
+// the split forms of <3,2,8> and <4,2,8> 24 and 45, the others 2 at most.  (<6,2,8> against its form before the leaner schedule, 90 inputs, 200 and
 // 250 units: 0.95 at 32 rows a step, 1.02 to 1.04 at 65 to 128.)
 __host__ inline SmallCut mid_cut(const int32_t* dims, int L, int32_t batch_size) {
   SmallCut m = {0, 0, 0, 0};

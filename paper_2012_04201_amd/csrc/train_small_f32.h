@@ -178,8 +178,8 @@ __host__ inline void make_slay(SLay& y, const int32_t* dims, int64_t n, const Sm
 
 // Waves per SIMD the registers of a variant are budgeted for (512 registers per lane and SIMD).  The largest variants of a
 // budget do not fit it altogether: by the compiler's report <2,3,1,4> and <2,3,2,4> (129 to 192 units, 17 to 32 inputs)
-// spill 102 and 118 vector registers, <3,2,4,4> and <3,2,4,8> 103 and 80, <4,2,.,8> (129 units and more, 49 inputs and more)
-// 100, 135 and 223 at one, two and four output slots; the others 18 at most.  (<3,2,4,.> at first spilled 82 and 62 with the moments of the
+// spill 102 and 118 vector registers, <3,2,4,4> and <3,2,4,8> 103 and 75, <4,2,.,8> (129 units and more, 49 inputs and more)
+// 109, 105 and 222 at one, two and four output slots; the others 21 at most.  (<3,2,4,.> at first spilled 82 and 62 with the moments of the
 // small parameters in LDS.  45 inputs, four classes, 200 suggestions, us a call then and now: 100 units, 24, 64 and 128 rows a step
 // 1202 and 1185, 727 and 720, 649 and 669; 130 units 1165 and 1081 at 64 rows.  These moments in LDS again, four a lane: 60 and
 // 42 spilled, 100 units 671 at 128 rows, 130 units 1100 at 64.)  Four output slots need more than the 128
