@@ -19,7 +19,7 @@
 // moments in L2, one model of 8 waves per CU, four barriers per chunk: 1000 models of 64-128-10 on 1797 rows, 3 epochs,
 // took 5.5 ms and take 3.2 ms (64 units: 4.2 and 2.5 ms; 200 units: 8.7 and 5.1 ms).  With the row pipeline's leaner schedule
 // and the input layer's products in split bfloat16 (md_splittable()) 512 suggestions of the digits shape took 14.0 ms instead
-// of 15.5, and take 13.2 with the row tiles of a chunk together and moments in units of their own.
+// of 15.5, 13.2 with the row tiles of a chunk together and moments in units of their own, and take 12.9 with rare code apart.
 #pragma once
 #include "common.h"
 #include "train_small_f32.h"  // the row pipeline

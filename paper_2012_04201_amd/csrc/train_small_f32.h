@@ -32,7 +32,7 @@
 // stopping rule or a trace reads it.  With the output columns of two classes merged, these took 10,240 models 569 x 30 from
 // 30.7 to 27.4 ms and 40 models of 10,000 x 45 from 4.02 to 3.59; products in split bfloat16 (sm_split()) and the leaner
 // schedule then to 24.2 and 3.56, hidden deltas without the output weight, small parameters in registers and moments in units of
-// their own to 19.0 and 3.46.  The form before this one kept the weights in LDS and the moments in L2, at
+// their own to 19.0 and 3.46, rare code apart to 18.9 and 3.42.  The form before this one kept the weights in LDS and the moments in L2, at
 // two workgroups per CU whatever the width and two barriers per chunk.  Before and after, per call: 10,240 models
 // 569 x 30, 50..200 units, 20 epochs 45.3 -> 32.4 ms; 40 models 506 x 13, SGD, 30 epochs 3.41 -> 1.74 ms; 40 models of
 // 10,000 x 45 rows, 3 epochs 10.9 -> 4.45 ms; 40 models 150 x 4, 20 epochs 0.39 -> 0.25 ms.
